@@ -120,27 +120,30 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
     tile_n = in_group / gsz;
 }
 
-// Epilogue shared by both GEMM kernels: register r of accumulator tile (tn, tm) holds feature
+// Epilogue shared by the GEMM kernels.  Register r of accumulator tile (tn, tm) holds feature
 // 32 tn + 8 (r / 4) + 4 g + r % 4 of the wave's feature range and token 32 tm + l32 of its token range.
 // TMX of the wave's BM / (32 WGM) rows of accumulator tiles are held in acc, starting at row tm_base (the GEMM kernels
 // hold all of them; the tail finish kernel one per workgroup, which lets several workgroups share a CU).
 // SC: the sums are products of 8-bit codes and take the factor a_scale * w_scale[feature] as they are read.
+//
+// One accumulator row (32 tokens x the wave's features, fp32) at a time goes through a region of LDS that belongs to the
+// wave alone (epi_wave_bytes, no barrier) and comes back with the lanes along the features: every store then writes whole
+// 128-byte lines (128 - 512 consecutive bytes per token), and the residual and the rotary table are read the same way, one
+// accumulator row ahead.  Straight from the accumulator layout a store instruction wrote 32 pieces of 16 bytes, and an L2
+// that serves 32 CUs took each piece as a request of its own; the loads were one serial round trip per quad, the
+// accumulators leaving no registers for more (they spilled; now nothing does with four waves).
+// 13B layer, T = 7963: q/k/v 1056 -> 967 us, W_o 384 -> 353, W_down 894 -> 861, gate/up 1680 -> 1650; on 8-bit operands at
+// T = 3875 q/k/v 317 -> 279 us, W_down with its tail 278 -> 253.
+template <int BN, int WGN>
+constexpr int epi_wave_bytes() { return 32 * (BN / WGN) * 4; }
+
 template <int BM, int BN, int EPI, int D, int WGM = 2, int WGN = 2, int TMX = BM / (32 * WGM), bool SC = false>
 __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * WGN)][TMX], const GemmArgs& p,
-                                              int tile_m, int tile_n, int wm, int wn, int l32, int g, int tm_base = 0,
-                                              int split = 0) {
+                                              int tile_m, int tile_n, int wm, int wn, int l32, int g, int tm_base,
+                                              int split, unsigned char* lds) {
     constexpr int TM = TMX, TN = BN / (32 * WGN);
-    const int t0 = tile_m * BM + 32 * tm_base;
-    // factors of the 4 consecutive features n .. n + 3 (n a multiple of 4 below the feature count)
-    auto scale4 = [&](int n) -> float4 {
-        if constexpr (SC) {
-            const float4 w = *reinterpret_cast<const float4*>(p.w_scale + n);
-            return make_float4(w.x * p.a_scale, w.y * p.a_scale, w.z * p.a_scale, w.w * p.a_scale);
-        } else {
-            return make_float4(1.f, 1.f, 1.f, 1.f);
-        }
-    };
-    if (EPI == EPI_SLAB) {
+    const int t0 = tile_m * BM + 32 * tm_base + wm * (BM / WGM);
+    if constexpr (EPI == EPI_SLAB) {
         // Split-K partial sums -> this split's slab.  These tiles were accumulated with the operands
         // swapped: register r holds token 8 (r / 4) + 4 g + r % 4 and feature l32, so one store
         // instruction writes two runs of 32 consecutive floats.  Plain stores: nothing is read back in
@@ -153,153 +156,163 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * W
                 const int n = tile_n * BN + wn * (BN / WGN) + 32 * tn + l32;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int t = t0 + wm * (BM / WGM) + 32 * tm + 8 * (r >> 2) + 4 * g + (r & 3);
+                    const int t = t0 + 32 * tm + 8 * (r >> 2) + 4 * g + (r & 3);
                     if (t < p.T && n < p.N) slab[(int64_t)t * p.N + n] = acc[tn][tm][r];
                 }
             }
         return;
-    }
+    } else {
+        // A lane's unit of work: chunk c_lo (4 consecutive features) of a token, or, where features are combined in pairs
+        // (gate and up, the two halves of a rotated head), chunks c_lo and c_hi.
+        constexpr int FEAT = BN / WGN, CPR = FEAT / 4, ROWB = FEAT * 4;
+        constexpr bool PAIRED = EPI == EPI_SWIGLU || EPI == EPI_QKV_ROPE;
+        constexpr int UPR = PAIRED ? CPR / 2 : CPR;      // units per token
+        constexpr int RPI = 64 / UPR, IT = 32 / RPI;     // tokens per wave access, accesses per accumulator row
+        static_assert(CPR >= 16, "the row swizzle permutes 16 chunks");
+        const int lane = l32 + 32 * g, u = lane % UPR, row0 = lane / UPR;
+        constexpr int DH = D > 0 ? D : 64;
+        int c_lo, c_hi, n_lo, n_hi;                      // chunks and first features (rows of the weight matrix)
+        int head = 0;
+        bool ok;
+        if (EPI == EPI_QKV_ROPE) {
+            const int hh = u / (DH / 8), ii = u % (DH / 8);
+            c_lo = hh * (DH / 4) + ii, c_hi = c_lo + DH / 8;
+            head = (tile_n * BN + wn * FEAT) / DH + hh;
+            n_lo = head * DH + 4 * ii, n_hi = n_lo + DH / 2;
+            ok = head < p.n_q + 2 * p.n_kv;
+        } else if (EPI == EPI_SWIGLU) {
+            c_lo = u, c_hi = u + CPR / 2;
+            n_lo = tile_n * (BN / 2) + wn * (FEAT / 2) + 4 * u, n_hi = p.n_half + n_lo;
+            ok = n_lo < p.n_half;   // n_half is a multiple of 8: whole units in or out
+        } else {
+            c_lo = c_hi = u;
+            n_lo = n_hi = tile_n * BN + wn * FEAT + 4 * u;
+            ok = n_lo < p.N;        // N is a multiple of 4 on every path that reaches here
+        }
+        float4 s_lo = make_float4(1.f, 1.f, 1.f, 1.f), s_hi = s_lo;
+        if constexpr (SC) {
+            if (ok) {
+                s_lo = *reinterpret_cast<const float4*>(p.w_scale + n_lo);
+                s_lo.x *= p.a_scale; s_lo.y *= p.a_scale; s_lo.z *= p.a_scale; s_lo.w *= p.a_scale;
+                if constexpr (PAIRED) {
+                    s_hi = *reinterpret_cast<const float4*>(p.w_scale + n_hi);
+                    s_hi.x *= p.a_scale; s_hi.y *= p.a_scale; s_hi.z *= p.a_scale; s_hi.w *= p.a_scale;
+                }
+            }
+        }
+        // what a unit reads besides the sums, fetched one accumulator row ahead (with eight waves, which have half the
+        // registers each, half a row ahead)
+        constexpr int PER = WGM * WGN > 4 ? 2 : 1, NOP = IT / PER;
+        struct Operands { float4 a[NOP], b[NOP]; int slot[NOP]; };
+        Operands ops[2];
+        auto fetch = [&](int step, Operands& o) __attribute__((always_inline)) {   // step = PER tm + part of the row
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm) {
-        const int t = t0 + wm * (BM / WGM) + 32 * tm + l32;
-        if (t >= p.T) continue;
-        if (EPI == EPI_SLAB) {
-            // handled before this loop (transposed accumulator layout)
-        } else if (EPI == EPI_QKV_ROPE) {
-            // The wave owns features [nb, nb + 128): one head (d = 128) or two (d = 64).  The rotation
-            // partner of feature i is i + d/2: same lane, same register, D/64 tiles further on.
-            constexpr int TPH = (D > 0 ? D : 64) / 32;   // tiles per head
-            constexpr int HPW = 4 / TPH;                 // heads per wave
-            const int nb = tile_n * BN + wn * 128;
-            const int64_t slot = p.tok_slot[t];
-            const float2* cs = p.rope_cs + (int64_t)t * (D / 2);
-            const int kv_dim = p.n_kv * D;
-#pragma unroll
-            for (int hh = 0; hh < HPW; ++hh) {
-                const int head = nb / D + hh;
-                if (head >= p.n_q + 2 * p.n_kv) continue;
+            for (int j = 0; j < NOP; ++j) {
+                const int64_t t = min(t0 + 32 * (step / PER) + RPI * (step % PER * NOP + j) + row0, p.T - 1);   // rows past T: the last token again, never stored
+                if constexpr (EPI == EPI_QKV_ROPE) {
+                    o.slot[j] = p.tok_slot[t];
+                    const float4* cs = reinterpret_cast<const float4*>(p.rope_cs + t * (DH / 2) + 4 * (u % (DH / 8)));
+                    o.a[j] = cs[0];
+                    o.b[j] = cs[1];
+                } else if constexpr (EPI == EPI_RES_BF16_OUT_F32) {
+                    uint2 r = make_uint2(0, 0);   // no residual given: plain fp32 output
+                    if (p.residual && ok) r = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p.residual) + t * p.N + n_lo);
+                    o.a[j].x = __uint_as_float(r.x);
+                    o.a[j].y = __uint_as_float(r.y);
+                } else if constexpr (EPI == EPI_RES_F32_OUT_BF16) {
+                    if (ok) o.a[j] = *reinterpret_cast<const float4*>(static_cast<const float*>(p.residual) + t * p.N + n_lo);
+                }
+            }
+        };
+        auto unit = [&](int t, const float4& lo, const float4& hi, const float4& oa, const float4& ob, int slot_) __attribute__((always_inline)) {
+            if constexpr (EPI == EPI_QKV_ROPE) {
+                const int64_t slot = slot_;
+                const int kv_dim = p.n_kv * DH, i = n_lo - head * DH;
                 if (head < p.n_q + p.n_kv) {
-                    uint16_t* dst = head < p.n_q
-                                        ? static_cast<uint16_t*>(p.out) + (int64_t)t * (p.n_q * D) + head * D
-                                        : p.k_pages + slot * kv_dim + (head - p.n_q) * D;
+                    const float co[4] = {oa.x, oa.z, ob.x, ob.z}, si[4] = {oa.y, oa.w, ob.y, ob.w};
+                    const float av[4] = {lo.x, lo.y, lo.z, lo.w}, bv[4] = {hi.x, hi.y, hi.z, hi.w};
+                    float l4[4], h4[4];
 #pragma unroll
-                    for (int tl = 0; tl < TPH / 2; ++tl) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int i = 32 * tl + 8 * q + 4 * g;
-                            const float4 c01 = *reinterpret_cast<const float4*>(cs + i);
-                            const float4 c23 = *reinterpret_cast<const float4*>(cs + i + 2);
-                            const float co[4] = {c01.x, c01.z, c23.x, c23.z}, si[4] = {c01.y, c01.w, c23.y, c23.w};
-                            const float4 sa4 = scale4(head * D + i), sb4 = scale4(head * D + i + D / 2);
-                            const float sa[4] = {sa4.x, sa4.y, sa4.z, sa4.w}, sb[4] = {sb4.x, sb4.y, sb4.z, sb4.w};
-                            float lo[4], hi[4];
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) {
-                                float a = acc[hh * TPH + tl][tm][4 * q + j];
-                                float b = acc[hh * TPH + tl + TPH / 2][tm][4 * q + j];
-                                if constexpr (SC) a *= sa[j], b *= sb[j];
-                                lo[j] = a * co[j] - b * si[j];
-                                hi[j] = a * si[j] + b * co[j];
-                            }
-                            if (p.kv_fp8 && head >= p.n_q) {   // quantised cache: one byte per element, quantised from fp32
-                                uint8_t* dst8 = reinterpret_cast<uint8_t*>(p.k_pages) + slot * kv_dim + (head - p.n_q) * D + i;
-                                const float s = p.k_inv;
-                                *reinterpret_cast<uint32_t*>(dst8) = pack_fp8x4(lo[0] * s, lo[1] * s, lo[2] * s, lo[3] * s);
-                                *reinterpret_cast<uint32_t*>(dst8 + D / 2) = pack_fp8x4(hi[0] * s, hi[1] * s, hi[2] * s, hi[3] * s);
-                            } else {
-                                *reinterpret_cast<uint2*>(dst + i) = make_uint2(pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]));
-                                *reinterpret_cast<uint2*>(dst + i + D / 2) =
-                                    make_uint2(pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3]));
-                            }
-                            // every register is taken by the accumulators: keep the scheduler from starting the
-                            // next quads' table loads early (they would spill)
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
+                    for (int e = 0; e < 4; ++e) {
+                        l4[e] = av[e] * co[e] - bv[e] * si[e];
+                        h4[e] = av[e] * si[e] + bv[e] * co[e];
+                    }
+                    if (p.kv_fp8 && head >= p.n_q) {   // quantised cache: one byte per element, quantised from fp32
+                        uint8_t* dst8 = reinterpret_cast<uint8_t*>(p.k_pages) + slot * kv_dim + (head - p.n_q) * DH + i;
+                        const float s = p.k_inv;
+                        *reinterpret_cast<uint32_t*>(dst8) = pack_fp8x4(l4[0] * s, l4[1] * s, l4[2] * s, l4[3] * s);
+                        *reinterpret_cast<uint32_t*>(dst8 + DH / 2) = pack_fp8x4(h4[0] * s, h4[1] * s, h4[2] * s, h4[3] * s);
+                    } else {
+                        uint16_t* dst = (head < p.n_q ? static_cast<uint16_t*>(p.out) + (int64_t)t * (p.n_q * DH) + head * DH
+                                                      : p.k_pages + slot * kv_dim + (head - p.n_q) * DH) + i;
+                        *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(l4[0], l4[1]), pack_bf16x2(l4[2], l4[3]));
+                        *reinterpret_cast<uint2*>(dst + DH / 2) = make_uint2(pack_bf16x2(h4[0], h4[1]), pack_bf16x2(h4[2], h4[3]));
                     }
                 } else {
-                    uint16_t* dst = p.v_pages + slot * kv_dim + (head - p.n_q - p.n_kv) * D;
-#pragma unroll
-                    for (int tl = 0; tl < TPH; ++tl) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int i = 32 * tl + 8 * q + 4 * g;
-                            f32x16_t a = acc[hh * TPH + tl][tm];
-                            if constexpr (SC) {
-                                const float4 sv = scale4(head * D + i);
-                                a[4 * q] *= sv.x; a[4 * q + 1] *= sv.y; a[4 * q + 2] *= sv.z; a[4 * q + 3] *= sv.w;
-                            }
-                            if (p.kv_fp8) {
-                                const float s = p.v_inv;
-                                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(p.v_pages) + slot * kv_dim +
-                                                             (head - p.n_q - p.n_kv) * D + i) =
-                                    pack_fp8x4(a[4 * q] * s, a[4 * q + 1] * s, a[4 * q + 2] * s, a[4 * q + 3] * s);
-                            } else {
-                                *reinterpret_cast<uint2*>(dst + i) = make_uint2(pack_bf16x2(a[4 * q], a[4 * q + 1]),
-                                                                                pack_bf16x2(a[4 * q + 2], a[4 * q + 3]));
-                            }
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                    }
-                }
-            }
-        } else if (EPI == EPI_SWIGLU) {
-#pragma unroll
-            for (int tn = 0; tn < TN / 2; ++tn) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = tile_n * (BN / 2) + wn * (BN / (2 * WGN)) + 32 * tn + 8 * q + 4 * g;
-                    if (i >= p.n_half) continue;  // n_half is a multiple of 8, i of 4: whole quad in or out
-                    float o[4];
-                    const float4 sg4 = scale4(i), su4 = scale4(p.n_half + i);
-                    const float sg[4] = {sg4.x, sg4.y, sg4.z, sg4.w}, su[4] = {su4.x, su4.y, su4.z, su4.w};
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        float gate = acc[tn][tm][4 * q + j], up = acc[tn + TN / 2][tm][4 * q + j];
-                        if constexpr (SC) gate *= sg[j], up *= su[j];
-                        o[j] = silu_mul(gate, up);
-                    }
-                    if (SC && p.out_f8) {   // the down projection reads codes
-                        const float s = p.out_inv;
-                        *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(p.out) + (int64_t)t * p.n_half + i) =
-                            pack_fp8x4(o[0] * s, o[1] * s, o[2] * s, o[3] * s);
-                        continue;
-                    }
-                    uint2 st = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
-                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + (int64_t)t * p.n_half + i) = st;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int n = tile_n * BN + wn * (BN / WGN) + 32 * tn + 8 * q + 4 * g;
-                    if (n >= p.N) continue;  // N is a multiple of 4 on every path that reaches here
-                    const int64_t o = (int64_t)t * p.N + n;
-                    float v[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) v[j] = acc[tn][tm][4 * q + j];
-                    if constexpr (SC) {
-                        const float4 sc = scale4(n);
-                        v[0] *= sc.x; v[1] *= sc.y; v[2] *= sc.z; v[3] *= sc.w;
-                    }
-                    if (EPI == EPI_RES_BF16_OUT_F32) {
-                        uint2 r = make_uint2(0, 0);  // no residual given: plain fp32 output
-                        if (p.residual) r = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p.residual) + o);
-                        float4 st = make_float4(v[0] + bf16_lo(r.x), v[1] + bf16_hi(r.x), v[2] + bf16_lo(r.y),
-                                                v[3] + bf16_hi(r.y));
-                        *reinterpret_cast<float4*>(static_cast<float*>(p.out) + o) = st;
+                    const int64_t o = slot * kv_dim + (head - p.n_q - p.n_kv) * DH + i;
+                    if (p.kv_fp8) {
+                        uint8_t* dst8 = reinterpret_cast<uint8_t*>(p.v_pages) + o;
+                        const float s = p.v_inv;
+                        *reinterpret_cast<uint32_t*>(dst8) = pack_fp8x4(lo.x * s, lo.y * s, lo.z * s, lo.w * s);
+                        *reinterpret_cast<uint32_t*>(dst8 + DH / 2) = pack_fp8x4(hi.x * s, hi.y * s, hi.z * s, hi.w * s);
                     } else {
-                        if (EPI == EPI_RES_F32_OUT_BF16) {
-                            const float4 r = *reinterpret_cast<const float4*>(static_cast<const float*>(p.residual) + o);
-                            v[0] += r.x; v[1] += r.y; v[2] += r.z; v[3] += r.w;
-                        }
-                        uint2 st = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-                        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + o) = st;
+                        *reinterpret_cast<uint2*>(p.v_pages + o) = make_uint2(pack_bf16x2(lo.x, lo.y), pack_bf16x2(lo.z, lo.w));
+                        *reinterpret_cast<uint2*>(p.v_pages + o + DH / 2) = make_uint2(pack_bf16x2(hi.x, hi.y), pack_bf16x2(hi.z, hi.w));
                     }
-                    __builtin_amdgcn_sched_barrier(0);   // see the q/k/v epilogue
+                }
+            } else if constexpr (EPI == EPI_SWIGLU) {
+                const float o0 = silu_mul(lo.x, hi.x), o1 = silu_mul(lo.y, hi.y), o2 = silu_mul(lo.z, hi.z), o3 = silu_mul(lo.w, hi.w);
+                const int64_t o = (int64_t)t * p.n_half + n_lo;
+                if (SC && p.out_f8) {   // the down projection reads codes
+                    const float s = p.out_inv;
+                    *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(p.out) + o) = pack_fp8x4(o0 * s, o1 * s, o2 * s, o3 * s);
+                } else {
+                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + o) = make_uint2(pack_bf16x2(o0, o1), pack_bf16x2(o2, o3));
+                }
+            } else {
+                const int64_t o = (int64_t)t * p.N + n_lo;
+                if constexpr (EPI == EPI_RES_BF16_OUT_F32) {
+                    const uint32_t r0 = __float_as_uint(oa.x), r1 = __float_as_uint(oa.y);
+                    *reinterpret_cast<float4*>(static_cast<float*>(p.out) + o) =
+                        make_float4(lo.x + bf16_lo(r0), lo.y + bf16_hi(r0), lo.z + bf16_lo(r1), lo.w + bf16_hi(r1));
+                } else {
+                    float4 v = lo;
+                    if constexpr (EPI == EPI_RES_F32_OUT_BF16) v.x += oa.x, v.y += oa.y, v.z += oa.z, v.w += oa.w;
+                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + o) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
                 }
             }
+        };
+        fetch(0, ops[0]);
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            unsigned char* wr = lds + l32 * ROWB;
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4*>(wr + (((8 * tn + 2 * q + g) ^ (l32 & 15)) << 4)) =
+                        make_float4(acc[tn][tm][4 * q], acc[tn][tm][4 * q + 1], acc[tn][tm][4 * q + 2], acc[tn][tm][4 * q + 3]);
+            // the wave's LDS accesses stay in program order: writes, reads, the next row's writes
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < IT; ++j) {
+                const int step = PER * tm + j / NOP, jo = j % NOP;
+                if (jo == 0 && step + 1 < PER * TM) fetch(step + 1, ops[(step + 1) & 1]);
+                const Operands& cur = ops[step & 1];
+                const int row = RPI * j + row0, t = t0 + 32 * tm + row;
+                const unsigned char* rd = lds + row * ROWB;
+                float4 lo = *reinterpret_cast<const float4*>(rd + ((c_lo ^ (row & 15)) << 4));
+                float4 hi = lo;
+                if constexpr (PAIRED) hi = *reinterpret_cast<const float4*>(rd + ((c_hi ^ (row & 15)) << 4));
+                if constexpr (SC) {
+                    lo.x *= s_lo.x; lo.y *= s_lo.y; lo.z *= s_lo.z; lo.w *= s_lo.w;
+                    if constexpr (PAIRED) hi.x *= s_hi.x, hi.y *= s_hi.y, hi.z *= s_hi.z, hi.w *= s_hi.w;
+                }
+                if (ok && t < p.T) unit(t, lo, hi, cur.a[jo], cur.b[jo], cur.slot[jo]);
+            }
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
 }
@@ -418,7 +431,8 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs p) {
         if (more) store_lds((kt + 1) & 1);
         __syncthreads();
     }
-    gemm_epilogue<BM, BN, EPI, D>(acc, p, tile_m, tile_n, wm, wn, l32, g);
+    static_assert(4 * epi_wave_bytes<BN, 2>() <= 2 * STAGE, "the epilogue's rows fit the stages");
+    gemm_epilogue<BM, BN, EPI, D>(acc, p, tile_m, tile_n, wm, wn, l32, g, 0, 0, smem + wave * epi_wave_bytes<BN, 2>());
 }
 
 // ------------------------------------------------------------------------------------------
@@ -758,7 +772,13 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
                 }
         return;
     }
-    gemm_epilogue<BM, BN, EPI, D, WGM, WGN, BM / (32 * WGM), F8>(acc, p, tile_m, tile_n, wm, wn, l32, g, 0, split);
+    if constexpr (EPI != EPI_SLAB) {   // the epilogue takes over the ring: every wave is done with it
+        static_assert(NW * epi_wave_bytes<BN, WGN>() <= NS * STAGE, "the epilogue's rows fit the ring");
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+    gemm_epilogue<BM, BN, EPI, D, WGM, WGN, TM, F8>(acc, p, tile_m, tile_n, wm, wn, l32, g, 0, split,
+                                                    smem + wave * epi_wave_bytes<BN, WGN>());
 }
 
 // Second half of a tail split: workgroup (tail tile, row tm of accumulator tiles) has the thread layout of
@@ -794,7 +814,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_tail_finish_kernel(GemmAr
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[tn][0][4 * c + e] += v[tn][c][e];
     }
-    gemm_epilogue<BM, BN, EPI, D, WGM, WGN, 1, SC>(acc, p, tile_m, tile_n, wm, wn, l32, g, tm_sel);
+    __shared__ __align__(16) unsigned char rows[NW * epi_wave_bytes<BN, WGN>()];
+    gemm_epilogue<BM, BN, EPI, D, WGM, WGN, 1, SC>(acc, p, tile_m, tile_n, wm, wn, l32, g, tm_sel, 0,
+                                                   rows + wave * epi_wave_bytes<BN, WGN>());
 }
 
 // ------------------------------------------------------------------------------------------
