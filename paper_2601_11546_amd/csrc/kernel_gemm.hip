@@ -1024,6 +1024,23 @@ hipError_t launch_skinny(const GemmArgs& p, hipStream_t s) {
     return launch_split<128, EPI, D, 256, true>(p, splits, s);
 }
 
+// The output layer of a decode batch: at most 256 rows against a weight matrix far larger than the activations, with no
+// scratch to split k into.  Wide enough that 128-feature tiles fill the CUs, it runs as ONE token tile on a deep ring, so
+// that the weights are read once; the general plan takes 64 x 128 tiles with one stage in flight and, beyond 64 rows, reads
+// the weights once per 64 rows.  32000 x 5120: 24 rows 85 -> 52 us, 129 rows 115 -> 84 us.
+bool wide_whole_applies(const GemmArgs& p) {
+    const int tiles = (p.N + 127) / 128, rounds = (tiles + 255) / 256;
+    return !p.accum && p.T <= SKINNY_MAX_T && p.K % 64 == 0 && tiles >= 0.8 * 256 * rounds && forced_cand() < 0;
+}
+
+template <int EPI>
+hipError_t launch_wide_whole(const GemmArgs& p, hipStream_t s) {
+    if (p.T <= 64) return launch_skinny_whole<64, EPI>(p, s);
+    if (p.T <= 128) return launch_skinny_whole<128, EPI>(p, s);
+    if (p.T <= 192) return launch_skinny_whole<192, EPI>(p, s);
+    return launch_skinny_whole<256, EPI>(p, s);
+}
+
 bool skinny_applies(int T, int N, int K, const float* accum) {
     return accum != nullptr && T <= SKINNY_MAX_T && K % 64 == 0 && N % 4 == 0;
 }
@@ -1260,6 +1277,7 @@ hipError_t launch_linear(const void* a, const void* w, int32_t T, int32_t N, int
             default: return hipErrorInvalidValue;
         }
     }
+    if (epilogue == EPI_RES_BF16_OUT_F32 && wide_whole_applies(p)) return launch_wide_whole<EPI_RES_BF16_OUT_F32>(p, s);
     switch (epilogue) {
         case EPI_BF16: return launch_epi<EPI_BF16>(p, s);
         case EPI_RES_BF16_OUT_F32: return launch_epi<EPI_RES_BF16_OUT_F32>(p, s);
