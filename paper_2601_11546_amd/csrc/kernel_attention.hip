@@ -88,13 +88,14 @@ __device__ __forceinline__ void state_init(RowState<D>& st, const AttnArgs& p, c
     }
 }
 
+// part_row: the row of the partial-state buffers a WRITE_PARTIAL item stores to
 template <int D>
 __device__ __forceinline__ void state_store(const RowState<D>& st, const AttnArgs& p, const AttnItem& it,
-                                            int64_t row_id, int g) {
+                                            int64_t row_id, int64_t part_row, int g) {
     const float l_tot = st.l + __shfl_xor(st.l, 32, 64);
     if (it.flags & ITEM_WRITE_PARTIAL) {
-        if (g == 0) *reinterpret_cast<float2*>(p.part_ml + row_id * 2) = make_float2(st.m, l_tot);
-        float* po = p.part_o + row_id * D + 4 * g;
+        if (g == 0) *reinterpret_cast<float2*>(p.part_ml + part_row * 2) = make_float2(st.m, l_tot);
+        float* po = p.part_o + part_row * D + 4 * g;
 #pragma unroll
         for (int td = 0; td < D / 32; ++td)
 #pragma unroll
@@ -412,7 +413,11 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
         // the other buffer is free since the barrier above: every wave had finished the previous block before it
         if (FP8 && b + 1 < n_blocks) store_raw((b + 1) & 1);
     }
-    if (valid) state_store<D>(st, p, it, row_id, g);
+    if (valid) {
+        int64_t part_row = row_id;
+        if (it.flags & ITEM_SLOTS) part_row = (int64_t)(p.T + p.attn_tok[it.pad0 + ti] + it.pad1) * p.n_q + hq;
+        state_store<D>(st, p, it, row_id, part_row, g);
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -823,12 +828,18 @@ hipError_t launch_attention(const BatchDev& b, const relserve_layer& L, const vo
     };
     p.T = b.T;
     p.merge_items = b.merge_items;
-    launch(3, b.items_prefix, b.n_items_prefix, nullptr, 0, false);
-    if (b.n_items_tile > 0 && b.n_items_split > 0) {   // both kinds of rows: one launch for their own keys
-        launch(2, b.items_tile, b.n_items_tile, b.items_split, b.n_items_split, false);
+    const bool slots = b.n_scratch_slots > 0;
+    if (slots) p.T = 0;   // the buffers hold slots alone
+    if (slots && b.n_items_prefix > 0) {   // prefix chunks and own keys are independent of each other: one launch
+        launch(2, b.items_prefix, b.n_items_prefix, b.items_split, b.n_items_split, false);
     } else {
-        launch(4, b.items_tile, b.n_items_tile, nullptr, 0, false);
-        launch(5, b.items_split, b.n_items_split, nullptr, 0, true);
+        launch(3, b.items_prefix, b.n_items_prefix, nullptr, 0, false);
+        if (b.n_items_tile > 0 && b.n_items_split > 0) {   // both kinds of rows: one launch for their own keys
+            launch(2, b.items_tile, b.n_items_tile, b.items_split, b.n_items_split, false);
+        } else {
+            launch(4, b.items_tile, b.n_items_tile, nullptr, 0, false);
+            launch(5, b.items_split, b.n_items_split, nullptr, 0, true);
+        }
     }
     if (e == hipSuccess && b.n_merge > 0) {
         profile_mark(prof, 10, s, true);

@@ -1200,7 +1200,7 @@ void gemm_force_plan(int cand, int splits) {
 
 int64_t gemm_scratch_floats(int64_t T, int64_t n_max) {
     // skinny: one slab per split, at most 256 units of 128 x 256 floats, or a single slab of T x N
-    return T <= SKINNY_MAX_T ? std::max<int64_t>(T * n_max, 256 * 128 * 256) : kTailFloats;
+    return T <= SKINNY_MAX_T ? std::max<int64_t>(T * n_max, GEMM_SKINNY_FLOATS) : kTailFloats;
 }
 
 

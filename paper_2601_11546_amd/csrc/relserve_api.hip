@@ -56,6 +56,73 @@ Workspace carve(const relserve_layer& L, int64_t T, void* base) {
     return w;
 }
 
+// Cut of a batch of decode rows (see expand_batch): per shared prefix the number and length of its chunks, and the length
+// of the chunks of own keys (0 = uncut).
+struct SlotPlan {
+    bool use = false;
+    std::vector<int32_t> prefix_chunks, prefix_len;
+    int32_t chunk_len = 0;
+};
+
+template <typename OwnKeys, typename ChunksOf>
+SlotPlan plan_slots(const relserve_layer_config& cfg, const relserve_batch_desc& d, const std::vector<uint8_t>& joint,
+                    OwnKeys own_keys, ChunksOf chunks_of) {
+    SlotPlan plan;
+    const int32_t B = d.num_reqs;
+    int64_t own_total = 0;
+    for (int32_t r = 0; r < B; ++r) own_total += own_keys(r);
+    // A prefix chunk should not outlast the own keys: these stream at about 6 TB/s behind 8 us of latency, a block of 64
+    // prefix keys takes a workgroup about 2.5 us.
+    const double own_us = 8.0 + (double)own_total * cfg.n_kv_heads * cfg.head_dim * 4.0 / 6.0e6;
+    const int32_t blocks_max = std::max(2, (int32_t)(own_us / 2.5));
+    plan.prefix_chunks.assign(d.num_prefixes, 0);
+    plan.prefix_len.assign(d.num_prefixes, 0);
+    bool any = false;
+    for (int32_t p = 0; p < d.num_prefixes; ++p) {
+        if (!joint[p]) continue;
+        any = true;
+        const int32_t blocks = (d.prefix_len[p] + 63) / 64, n = (blocks + blocks_max - 1) / blocks_max;
+        plan.prefix_len[p] = (blocks + n - 1) / n * 64;
+        plan.prefix_chunks[p] = (d.prefix_len[p] + plan.prefix_len[p] - 1) / plan.prefix_len[p];
+    }
+    // Own keys: the smallest chunk whose waves stay within two rounds (256 CUs x 8 resident waves each) and whose states
+    // fit the slots; a batch with more waves than that balances by itself.
+    const int64_t cap = scratch_slot_cap(cfg.n_q_heads, cfg.head_dim);
+    auto slots_at = [&](int32_t len, int64_t& items, bool& cut) {
+        int64_t slots = 0;
+        items = 0, cut = false;
+        for (int32_t r = 0; r < B; ++r) {
+            const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
+            const int32_t n = chunks_of(own_keys(r), len);
+            const int32_t parts = n + (pid >= 0 && joint[pid] ? plan.prefix_chunks[pid] : 0);
+            if (parts > 1) slots += parts;
+            items += n;
+            cut |= n > 1;
+        }
+        return slots;
+    };
+    int64_t items = 0;
+    bool cut = false;
+    for (int32_t len = 64; len <= 1024; len *= 2) {
+        const int64_t slots = slots_at(len, items, cut);
+        if (!cut) break;
+        if (slots <= cap && items * cfg.n_kv_heads <= 2 * 2048) {
+            plan.chunk_len = len;
+            break;
+        }
+    }
+    const int64_t slots = slots_at(plan.chunk_len, items, cut);
+    plan.use = slots <= cap && (any || cut);
+    return plan;
+}
+
+// Where the attention passes of a batch keep partial state: the workspace's own rows, or (slot plans) the GEMM scratch.
+struct PartialState { float* o; float* ml; };
+PartialState partial_state(const relserve_layer& L, const BatchDev& b, const Workspace& w) {
+    if (b.n_scratch_slots == 0) return {w.part_o, w.part_ml};
+    return {w.accum, w.accum + (int64_t)b.n_scratch_slots * L.q_dim};
+}
+
 bool is_pow2(int32_t v) { return v > 0 && (v & (v - 1)) == 0; }
 
 // Workspace of relserve_layer_step_static: a fixed array in device memory, one copy per GPU the library runs on,
@@ -194,6 +261,32 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         std::vector<uint8_t> joint(d.num_prefixes, 0);
         for (int32_t p = 0; p < d.num_prefixes; ++p)
             joint[p] = (members[p] >= 2 && d.prefix_len[p] > 0);
+        auto own_keys = [&](int32_t r) {
+            const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
+            return d.ctx_len[r] - ((pid >= 0 && joint[pid]) ? d.prefix_len[pid] : 0);
+        };
+        auto chunks_of = [](int32_t own, int32_t len) { return len > 0 ? std::max(1, (own + len / 2) / len) : 1; };
+
+        // Batches of decode rows alone (at most SKINNY_MAX_T): every part of a row's keys is an item of its own -- chunks of
+        // the shared prefix for the tiled kernel, chunks of its own keys for the wave kernel -- in ONE launch, each leaving
+        // its running state in a slot of the GEMM scratch, and one merge finishes the rows.  The prefix pass of few rows is
+        // few workgroups that walk the whole template one block after the other, with the own keys waiting behind it.
+        // Attention of a 13B layer, template of 512: 4 rows 13.5 + 11.8 us (prefix pass, own keys) -> 8.7 + 4.5 (launch,
+        // merge), 24 rows 14.4 + 14.2 -> 13.9 + 4.7; 70B shape, 256 rows, templates of 768: 26.4 + 76.2 + 5.1 -> 82.0 + 6.5.
+        // With prefill rows in the batch the partial states are the larger part of the traffic and the passes stay apart.
+        SlotPlan plan;
+        if (hb.n_prefill == 0 && T > 0 && T <= SKINNY_MAX_T) plan = plan_slots(cfg, d, joint, own_keys, chunks_of);
+
+        std::vector<int32_t> row_slot;      // per request: its first slot (slot plan only)
+        if (plan.use) {
+            row_slot.resize(B);
+            for (int32_t r = 0; r < B; ++r) {
+                const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
+                const int32_t n = (pid >= 0 && joint[pid] ? plan.prefix_chunks[pid] : 0) + chunks_of(own_keys(r), plan.chunk_len);
+                row_slot[r] = hb.n_scratch_slots;
+                if (n > 1) hb.n_scratch_slots += n;
+            }
+        }
         for (int32_t p = 0; p < d.num_prefixes; ++p) {
             if (!joint[p]) continue;
             ++hb.n_groups;
@@ -202,29 +295,36 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
                 if (d.prefix_id[r] == p)
                     for (int32_t t = d.q_start[r]; t < d.q_start[r + 1]; ++t) hb.attn_tok.push_back(t);
             const int32_t n = (int32_t)hb.attn_tok.size() - start;
-            for (int32_t o = 0; o < n; o += tile_tok) {
-                AttnItem it{};
-                it.tok_off = start + o;
-                it.n_tok = std::min(tile_tok, n - o);
-                it.bt_req = first_member[p];
-                it.key_begin = 0;
-                it.key_end = d.prefix_len[p];
-                it.flags = ITEM_WRITE_PARTIAL;
-                hb.items_prefix.push_back(it);
-            }
+            const int32_t slots = (int32_t)hb.attn_tok.size();
+            if (plan.use)
+                for (int32_t r = 0; r < B; ++r)
+                    if (d.prefix_id[r] == p) hb.attn_tok.push_back(row_slot[r]);
+            const int32_t n_chunks = plan.use ? plan.prefix_chunks[p] : 1;
+            const int32_t per = plan.use ? plan.prefix_len[p] : d.prefix_len[p];
+            for (int32_t c = 0; c < n_chunks; ++c)
+                for (int32_t o = 0; o < n; o += tile_tok) {
+                    AttnItem it{};
+                    it.tok_off = start + o;
+                    it.n_tok = std::min(tile_tok, n - o);
+                    it.bt_req = first_member[p];
+                    it.key_begin = c * per;
+                    it.key_end = std::min((c + 1) * per, d.prefix_len[p]);
+                    it.flags = ITEM_WRITE_PARTIAL;
+                    if (plan.use) {
+                        it.flags |= ITEM_SLOTS;
+                        it.pad0 = slots + o;
+                        it.pad1 = c;
+                    }
+                    hb.items_prefix.push_back(it);
+                }
         }
         // Decode rows with many own keys are cut into chunks (one wave item each, merged afterwards), so that one long
         // context does not set the kernel's duration and the waves come in several even rounds.  The chunk length is
         // the smallest of 128 .. 1024 keys whose chunks fit the partial-state slots of the workspace.
-        auto own_keys = [&](int32_t r) {
-            const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
-            return d.ctx_len[r] - ((pid >= 0 && joint[pid]) ? d.prefix_len[pid] : 0);
-        };
-        auto chunks_of = [](int32_t own, int32_t len) { return len > 0 ? std::max(1, (own + len / 2) / len) : 1; };
-        int32_t chunk_len = 0;   // 0 = no row is cut
+        int32_t chunk_len = plan.use ? plan.chunk_len : 0;   // 0 = no row is cut
         // (with two rounds of waves or more -- 256 CUs x 8 resident waves each -- the rows balance by themselves: cutting
         // the 128 rows x 40 heads of 1024 keys of a 13B decode batch in two left its kernel at 6.5 TB/s and added the merge)
-        if ((int64_t)hb.n_decode * cfg.n_kv_heads < 2 * 2048) {
+        if (!plan.use && (int64_t)hb.n_decode * cfg.n_kv_heads < 2 * 2048) {
             const int64_t cap = split_slot_cap(T);
             for (int32_t len = 128; len <= 1024 && chunk_len == 0; len *= 2) {
                 int64_t slots = 0;
@@ -244,14 +344,17 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
             const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
             const bool grouped = pid >= 0 && joint[pid];
             const int32_t kb = grouped ? d.prefix_len[pid] : 0;
-            const int32_t flags = ITEM_CAUSAL | (grouped ? ITEM_INIT_PARTIAL : 0);
+            const int32_t flags = ITEM_CAUSAL | (grouped && !plan.use ? ITEM_INIT_PARTIAL : 0);
             const int32_t past = d.ctx_len[r] - q_len;
             if (q_len == 1) {
                 const int32_t own = d.ctx_len[r] - kb;
                 const int32_t n_chunks = chunks_of(own, chunk_len);
+                const int32_t n_prefix = plan.use && grouped ? plan.prefix_chunks[pid] : 0;   // parts of the row another item computes
                 // chunk boundaries on multiples of 32 keys (the wave kernel's block) counted from the first own key
                 const int32_t per = n_chunks > 1 ? ((own + n_chunks - 1) / n_chunks + 31) / 32 * 32 : own;
-                if (n_chunks > 1) hb.merge_items.push_back(MergeItem{d.q_start[r], next_slot, 0, 0});
+                const bool parts = n_chunks + n_prefix > 1;
+                if (plan.use) next_slot = row_slot[r] + n_prefix;
+                if (parts) hb.merge_items.push_back(MergeItem{d.q_start[r], plan.use ? row_slot[r] : next_slot, n_prefix, 0});
                 for (int32_t c = 0; c < n_chunks; ++c) {
                     const int32_t b0 = kb + c * per, b1 = std::min(kb + (c + 1) * per, d.ctx_len[r]);
                     if (b0 >= b1) break;
@@ -264,7 +367,7 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
                     it.key_begin = b0;
                     it.key_end = b1;
                     it.flags = c == 0 ? flags : ITEM_CAUSAL;      // only the first chunk continues from the prefix pass's state
-                    if (n_chunks > 1) {
+                    if (parts) {
                         it.flags |= ITEM_WRITE_PARTIAL;
                         it.pad1 = next_slot++;
                         ++hb.merge_items.back().n_chunks;
@@ -469,6 +572,7 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
     dv.n_items_prefix = (int32_t)hb.items_prefix.size();
     dv.n_items_tile = (int32_t)hb.items_tile.size();
     dv.n_items_split = (int32_t)hb.items_split.size();
+    dv.n_scratch_slots = hb.n_scratch_slots;
     b->info = relserve_batch_info{T, B, hb.n_decode, hb.n_prefill, hb.n_groups,
                                   dv.n_items_prefix + dv.n_items_tile + dv.n_items_split};
 
@@ -607,8 +711,9 @@ int32_t relserve_attention(const relserve_layer* L, const relserve_batch* b, con
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kAlign)) return RELSERVE_ERR_WORKSPACE;
     Workspace w = carve(*L, b->dev.T, workspace);
     if (w.total > workspace_bytes) return RELSERVE_ERR_WORKSPACE;
-    hipError_t e = launch_attention(b->dev, *L, q, q_pitch, cache.k_pages, cache.v_pages, out, w.part_o,
-                                    w.part_ml, static_cast<hipStream_t>(stream), nullptr, kv_format(cache));
+    const PartialState part = partial_state(*L, b->dev, w);
+    hipError_t e = launch_attention(b->dev, *L, q, q_pitch, cache.k_pages, cache.v_pages, out, part.o,
+                                    part.ml, static_cast<hipStream_t>(stream), nullptr, kv_format(cache));
     return e == hipSuccess ? RELSERVE_OK : RELSERVE_ERR_HIP;
 }
 
@@ -642,14 +747,15 @@ int32_t relserve_layer_step(const relserve_layer* L, const relserve_batch* b, co
     // the GEMMs split K across workgroups (whole skinny problems, narrow outputs at mid-size T, or the
     // incomplete last round of tiles) through an fp32 scratch that they write before they read
     float* accum = w.accum;
+    const PartialState part = partial_state(*L, b->dev, w);
     run(S_NORM1, [&] { return launch_rmsnorm(x, false, wt->w_in_norm, c.rms_eps, T, c.hidden, w.h, s); });
     run(S_QKV, [&] {
         return launch_qkv_rope_append(b->dev, *L, w.h, wt->w_qkv, w.q, cache.k_pages, cache.v_pages, s, accum, packed,
                                       kv_format(cache));
     });
     if (e == hipSuccess)
-        e = launch_attention(b->dev, *L, w.q, L->q_dim, cache.k_pages, cache.v_pages, w.attn, w.part_o,
-                             w.part_ml, s, prof, kv_format(cache));
+        e = launch_attention(b->dev, *L, w.q, L->q_dim, cache.k_pages, cache.v_pages, w.attn, part.o,
+                             part.ml, s, prof, kv_format(cache));
     run(S_O, [&] { return launch_linear(w.attn, wt->w_o, T, c.hidden, L->q_dim, 1, x, w.x1, s, accum, packed); });
     run(S_NORM2, [&] { return launch_rmsnorm(w.x1, true, wt->w_post_norm, c.rms_eps, T, c.hidden, w.h, s); });
     run(S_GU, [&] {
@@ -690,6 +796,7 @@ int32_t relserve_layer_step_w8a8(const relserve_layer* L, const relserve_batch* 
         profile_mark(prof, slot, s, false);
     };
     float* accum = w.accum;
+    const PartialState part = partial_state(*L, b->dev, w);
     const CodeScales qkv{wt->s_qkv, wt->a_qkv, 0.0f}, o{wt->s_o, wt->a_o, 0.0f}, gu{wt->s_gate_up, wt->a_gate_up, wt->a_down},
         down{wt->s_down, wt->a_down, 0.0f};
     run(S_NORM1, [&] { return launch_rmsnorm(x, false, wt->w_in_norm, c.rms_eps, T, c.hidden, w.h, s, nullptr, wt->a_qkv); });
@@ -698,8 +805,8 @@ int32_t relserve_layer_step_w8a8(const relserve_layer* L, const relserve_batch* 
                                       kv_format(cache), &qkv);
     });
     if (e == hipSuccess)
-        e = launch_attention(b->dev, *L, w.q, L->q_dim, cache.k_pages, cache.v_pages, w.attn, w.part_o,
-                             w.part_ml, s, prof, kv_format(cache));
+        e = launch_attention(b->dev, *L, w.q, L->q_dim, cache.k_pages, cache.v_pages, w.attn, part.o,
+                             part.ml, s, prof, kv_format(cache));
     // the attention output exists as bf16; its codes go where the rotated queries were (read by now)
     run(S_QUANT, [&] { return launch_quantise_bf16(w.attn, (int64_t)T * L->q_dim, wt->a_o, w.q, s); });
     run(S_O, [&] { return launch_linear(w.q, wt->w_o, T, c.hidden, L->q_dim, 1, x, w.x1, s, accum, packed, &o); });

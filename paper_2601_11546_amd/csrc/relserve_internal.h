@@ -17,7 +17,8 @@ namespace relserve {
 enum : int32_t {
     ITEM_CAUSAL = 1,        // a row at position p sees keys <= p
     ITEM_INIT_PARTIAL = 2,  // running softmax state starts from the stored prefix partial
-    ITEM_WRITE_PARTIAL = 4  // store the running state instead of the normalised output
+    ITEM_WRITE_PARTIAL = 4, // store the running state instead of the normalised output
+    ITEM_SLOTS = 8          // prefix items that do so in the slots of their rows: slot attn_tok[pad0 + i] + pad1 for query token i
 };
 
 struct AttnItem {
@@ -27,8 +28,8 @@ struct AttnItem {
     int32_t key_begin;  // first key position (page aligned)
     int32_t key_end;    // one past the last key position any row may see
     int32_t flags;
-    int32_t pad0;       // decode items: the query token
-    int32_t pad1;       // decode items that write partial state: the slot
+    int32_t pad0;       // decode items: the query token; prefix items with slots: where their rows' first slots are listed
+    int32_t pad1;       // decode items that write partial state: the slot; prefix items with slots: the chunk's number
 };
 
 // A decode row whose own keys were cut into several wave items (chunks): each chunk stores its running softmax state
@@ -43,6 +44,12 @@ struct MergeItem {
 // Slots of partial state the chunked decode rows of a batch of T tokens may use (rows T .. T + cap of the partial-state
 // buffers, behind the T rows that hold the shared-prefix pass's state).
 inline int64_t split_slot_cap(int64_t T) { return 2 * (T < 2048 ? T : 2048); }
+
+// Slots in the GEMM scratch, which is idle while the attention passes run (batches that use it have at most SKINNY_MAX_T
+// tokens): n_q (d + 2) floats each, and never more than GEMM_SKINNY_FLOATS hold.
+constexpr int SKINNY_MAX_T = 256;      // batches up to this many tokens take the split-K GEMM path
+constexpr int64_t GEMM_SKINNY_FLOATS = 256 * 128 * 256;                // least GEMM scratch at T <= SKINNY_MAX_T
+inline int64_t scratch_slot_cap(int32_t n_q, int32_t d) { return GEMM_SKINNY_FLOATS / ((int64_t)n_q * (d + 2)); }
 
 // Device-side view of a prepared batch (all pointers into one device allocation).
 struct BatchDev {
@@ -59,6 +66,7 @@ struct BatchDev {
     const AttnItem* items_split;   // wave items (decode rows, or chunks of their keys)
     const MergeItem* merge_items;  // decode rows cut into chunks
     int32_t n_items_prefix, n_items_tile, n_items_split, n_merge;
+    int32_t n_scratch_slots;     // > 0: the partial state lives in that many slots of the GEMM scratch, not in rows of part_o
 };
 
 }  // namespace relserve
@@ -95,13 +103,13 @@ struct HostBatch {
     std::vector<AttnItem> items_prefix, items_tile, items_split;
     std::vector<MergeItem> merge_items;
     int32_t n_decode = 0, n_prefill = 0, n_groups = 0;
+    int32_t n_scratch_slots = 0;
 };
 int32_t expand_batch(const relserve_layer_config& cfg, const relserve_batch_desc& d, bool build_items,
                      HostBatch* out);
 
 // Rows of queries one attention workgroup covers (4 waves x 32 MFMA columns).
 constexpr int ATTN_BLOCK_M = 128;
-constexpr int SKINNY_MAX_T = 256;      // batches up to this many tokens take the split-K GEMM path
 constexpr int64_t GEMM_TAIL_FLOATS = 256 * 65536;      // GEMM scratch at T > 256: partial tiles of one round of split 256 x 256 tiles
 constexpr int ATTN_SPLIT_ROWS = 16;   // query heads per kv head the decode kernel's 16-column MFMA holds
 
@@ -147,7 +155,8 @@ hipError_t launch_qkv_rope_append(const BatchDev& b, const relserve_layer& L, co
 // bf16 [n] -> 8-bit codes of value / scale (n % 8 == 0)
 hipError_t launch_quantise_bf16(const void* in, int64_t n, float scale, void* codes, hipStream_t s);
 // Attention passes; part_o [T + split_slot_cap(T), n_q, d] fp32 and part_ml [.., n_q, 2] fp32 hold the prefix partials
-// (rows of the tokens) and the chunk partials of split decode rows (rows T + slot).
+// (rows of the tokens) and the chunk partials of split decode rows (rows T + slot); of a
+// batch with n_scratch_slots they hold that many slots alone.
 hipError_t launch_attention(const BatchDev& b, const relserve_layer& L, const void* q, int32_t q_pitch,
                             const void* k_pages, const void* v_pages, void* out, float* part_o,
                             float* part_ml, hipStream_t s, relserve_layer* prof, KvFormat kv = KvFormat{});
