@@ -688,8 +688,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     };
     // Small tiles (two or three workgroups per CU, a handful of MFMAs per k step) do better when the
     // compiler orders the steps between hand-overs and the other resident workgroups fill the gaps;
-    // only their hand-over step keeps the fixed order, with the whole refill in it.
-    constexpr bool FIXED = NM >= 12;
+    // only their hand-over step keeps the fixed order, with the whole refill in it.  Tiles of 6 and 8 products per wave run
+    // alone on their CU and take the fixed order too: 13B layer, four projections, 250 -> 239 us at T = 256, 347 -> 329 at 400
+    // (q/k/v on 128 x 256 tiles 88 -> 77), but the SwiGLU kernel on that tile loses (122 -> 129) and keeps the compiler's.
+    constexpr bool FIXED = NM >= 12 || (NM >= 6 && !(EPI == EPI_SWIGLU && BM == 128));
     int cur = 0;  // stage being computed
     // One k iteration (one LDS stage).  refill_open: the refill begun at the previous hand-over is still being
     // issued; refill_next: this iteration's hand-over starts another one.
@@ -1012,16 +1014,21 @@ hipError_t launch_skinny(const GemmArgs& p, hipStream_t s) {
         if (p.T <= 64) return launch_split<64, EPI, D, 128, true>(p, choose_splits(p.T, p.N, p.K, 64, 128), s);
         return launch_split<128, EPI, D, 128, true>(p, choose_splits(p.T, p.N, p.K, 128, 128), s);
     }
-    // two token tiles: 256-feature tiles; a projection wide enough to need no k split runs the fused kernel
-    const int splits = choose_splits(p.T, p.N, p.K, 128);
+    // 129 .. 256 tokens: one token tile of 192 or 256 rows x 128 features, so that every weight is read once (two tiles of
+    // 128 rows read them twice; what the CUs draw from the L2 is the bound here, weights and activations together).
+    // A projection that fills the CUs without a k split runs whole.  13B layer, its four projections, before -> now:
+    // 248 -> 208 us at T = 160, 253 -> 232 at 200, 265 -> 239 at 256 (with an event pair per launch).
+    const int splits = choose_splits(p.T, p.N, p.K, p.T <= 192 ? 192 : 256, 128);
     if (splits == 1) {
-        // wide enough that one 256 x 256 tile per CU is (nearly) a full round: one token tile instead of two
-        // halves the weight fragments read from LDS per flop
+        // wide enough that one 256 x 256 tile per CU is (nearly) a full round: half the activation reads again
         const int tiles256 = EPI == EPI_SWIGLU ? (p.n_half + 127) / 128 : (p.N + 255) / 256;
         if (p.T > 192 && tiles256 >= 200 && tiles256 <= 256) return launch_skinny_whole<256, EPI, D, 256>(p, s);
-        return launch_skinny_whole<128, EPI, D, 256>(p, s);
+        if constexpr (EPI == EPI_QKV_ROPE)   // the fused rotation needs 128 features per wave
+            return launch_skinny_whole<128, EPI, D, 256>(p, s);
+        else
+            return p.T <= 192 ? launch_skinny_whole<192, EPI>(p, s) : launch_skinny_whole<256, EPI>(p, s);
     }
-    return launch_split<128, EPI, D, 256, true>(p, splits, s);
+    return p.T <= 192 ? launch_split<192, EPI, D, 128, true>(p, splits, s) : launch_split<256, EPI, D, 128, true>(p, splits, s);
 }
 
 // The output layer of a decode batch: at most 256 rows against a weight matrix far larger than the activations, with no

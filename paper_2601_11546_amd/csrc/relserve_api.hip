@@ -254,7 +254,8 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
 
     for (int32_t r = 0; r < B; ++r) (d.q_start[r + 1] - d.q_start[r] == 1 ? hb.n_decode : hb.n_prefill)++;
 
-    if (build_items) {
+    auto build = [&](bool slots_allowed, ItemLists& il) {
+        hb.n_groups = 0;
         const int32_t group = cfg.n_q_heads / cfg.n_kv_heads;
         const int32_t tile_tok = ATTN_BLOCK_M / group;    // tokens per row-tiled item (rows past tile_tok * group stay idle)
         // a prefix is handled jointly when at least two requests of the batch carry it
@@ -275,7 +276,7 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         // merge), 24 rows 14.4 + 14.2 -> 13.9 + 4.7; 70B shape, 256 rows, templates of 768: 26.4 + 76.2 + 5.1 -> 82.0 + 6.5.
         // With prefill rows in the batch the partial states are the larger part of the traffic and the passes stay apart.
         SlotPlan plan;
-        if (hb.n_prefill == 0 && T > 0 && T <= SKINNY_MAX_T) plan = plan_slots(cfg, d, joint, own_keys, chunks_of);
+        if (slots_allowed && hb.n_prefill == 0 && T > 0 && T <= SKINNY_MAX_T) plan = plan_slots(cfg, d, joint, own_keys, chunks_of);
 
         std::vector<int32_t> row_slot;      // per request: its first slot (slot plan only)
         if (plan.use) {
@@ -283,22 +284,22 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
             for (int32_t r = 0; r < B; ++r) {
                 const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
                 const int32_t n = (pid >= 0 && joint[pid] ? plan.prefix_chunks[pid] : 0) + chunks_of(own_keys(r), plan.chunk_len);
-                row_slot[r] = hb.n_scratch_slots;
-                if (n > 1) hb.n_scratch_slots += n;
+                row_slot[r] = il.n_scratch_slots;
+                if (n > 1) il.n_scratch_slots += n;
             }
         }
         for (int32_t p = 0; p < d.num_prefixes; ++p) {
             if (!joint[p]) continue;
             ++hb.n_groups;
-            const int32_t start = (int32_t)hb.attn_tok.size();
+            const int32_t start = (int32_t)il.attn_tok.size();
             for (int32_t r = 0; r < B; ++r)
                 if (d.prefix_id[r] == p)
-                    for (int32_t t = d.q_start[r]; t < d.q_start[r + 1]; ++t) hb.attn_tok.push_back(t);
-            const int32_t n = (int32_t)hb.attn_tok.size() - start;
-            const int32_t slots = (int32_t)hb.attn_tok.size();
+                    for (int32_t t = d.q_start[r]; t < d.q_start[r + 1]; ++t) il.attn_tok.push_back(t);
+            const int32_t n = (int32_t)il.attn_tok.size() - start;
+            const int32_t slots = (int32_t)il.attn_tok.size();
             if (plan.use)
                 for (int32_t r = 0; r < B; ++r)
-                    if (d.prefix_id[r] == p) hb.attn_tok.push_back(row_slot[r]);
+                    if (d.prefix_id[r] == p) il.attn_tok.push_back(row_slot[r]);
             const int32_t n_chunks = plan.use ? plan.prefix_chunks[p] : 1;
             const int32_t per = plan.use ? plan.prefix_len[p] : d.prefix_len[p];
             for (int32_t c = 0; c < n_chunks; ++c)
@@ -315,7 +316,7 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
                         it.pad0 = slots + o;
                         it.pad1 = c;
                     }
-                    hb.items_prefix.push_back(it);
+                    il.items_prefix.push_back(it);
                 }
         }
         // Decode rows with many own keys are cut into chunks (one wave item each, merged afterwards), so that one long
@@ -354,13 +355,13 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
                 const int32_t per = n_chunks > 1 ? ((own + n_chunks - 1) / n_chunks + 31) / 32 * 32 : own;
                 const bool parts = n_chunks + n_prefix > 1;
                 if (plan.use) next_slot = row_slot[r] + n_prefix;
-                if (parts) hb.merge_items.push_back(MergeItem{d.q_start[r], plan.use ? row_slot[r] : next_slot, n_prefix, 0});
+                if (parts) il.merge_items.push_back(MergeItem{d.q_start[r], plan.use ? row_slot[r] : next_slot, n_prefix, 0});
                 for (int32_t c = 0; c < n_chunks; ++c) {
                     const int32_t b0 = kb + c * per, b1 = std::min(kb + (c + 1) * per, d.ctx_len[r]);
                     if (b0 >= b1) break;
                     AttnItem it{};
-                    it.tok_off = (int32_t)hb.attn_tok.size();
-                    hb.attn_tok.push_back(d.q_start[r]);
+                    it.tok_off = (int32_t)il.attn_tok.size();
+                    il.attn_tok.push_back(d.q_start[r]);
                     it.n_tok = 1;
                     it.pad0 = d.q_start[r];  // the decode kernel takes its single token from here
                     it.bt_req = r;
@@ -370,21 +371,21 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
                     if (parts) {
                         it.flags |= ITEM_WRITE_PARTIAL;
                         it.pad1 = next_slot++;
-                        ++hb.merge_items.back().n_chunks;
+                        ++il.merge_items.back().n_chunks;
                     }
-                    hb.items_split.push_back(it);
+                    il.items_split.push_back(it);
                 }
             } else {
                 for (int32_t o = 0; o < q_len; o += tile_tok) {
                     AttnItem it{};
-                    it.tok_off = (int32_t)hb.attn_tok.size();
+                    it.tok_off = (int32_t)il.attn_tok.size();
                     it.n_tok = std::min(tile_tok, q_len - o);
-                    for (int32_t j = 0; j < it.n_tok; ++j) hb.attn_tok.push_back(d.q_start[r] + o + j);
+                    for (int32_t j = 0; j < it.n_tok; ++j) il.attn_tok.push_back(d.q_start[r] + o + j);
                     it.bt_req = r;
                     it.key_begin = kb;
                     it.key_end = past + o + it.n_tok;  // the item's last row sees keys up to itself
                     it.flags = flags;
-                    hb.items_tile.push_back(it);
+                    il.items_tile.push_back(it);
                 }
             }
         }
@@ -392,8 +393,12 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         auto longer = [](const AttnItem& a, const AttnItem& b) {
             return (a.key_end - a.key_begin) > (b.key_end - b.key_begin);
         };
-        std::stable_sort(hb.items_tile.begin(), hb.items_tile.end(), longer);
-        std::stable_sort(hb.items_split.begin(), hb.items_split.end(), longer);
+        std::stable_sort(il.items_tile.begin(), il.items_tile.end(), longer);
+        std::stable_sort(il.items_split.begin(), il.items_split.end(), longer);
+    };
+    if (build_items) {
+        build(true, hb.items);
+        if (hb.items.n_scratch_slots > 0) build(false, hb.in_sequence);
     }
     *out = std::move(hb);
     return RELSERVE_OK;
@@ -516,11 +521,17 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
     const size_t o_slot = reserve(sizeof(int32_t) * T);
     const size_t o_last = reserve(sizeof(int32_t) * B);
     const size_t o_bt = reserve(sizeof(int32_t) * (size_t)B * desc->max_blocks);
-    const size_t o_tok = reserve(sizeof(int32_t) * hb.attn_tok.size());
-    const size_t o_ip = reserve(sizeof(AttnItem) * hb.items_prefix.size());
-    const size_t o_it = reserve(sizeof(AttnItem) * hb.items_tile.size());
-    const size_t o_is = reserve(sizeof(AttnItem) * hb.items_split.size());
-    const size_t o_mi = reserve(sizeof(MergeItem) * hb.merge_items.size());
+    struct ListOffsets { size_t tok, prefix, tile, split, merge; };
+    auto reserve_lists = [&](const ItemLists& il) {
+        ListOffsets o;
+        o.tok = reserve(sizeof(int32_t) * il.attn_tok.size());
+        o.prefix = reserve(sizeof(AttnItem) * il.items_prefix.size());
+        o.tile = reserve(sizeof(AttnItem) * il.items_tile.size());
+        o.split = reserve(sizeof(AttnItem) * il.items_split.size());
+        o.merge = reserve(sizeof(MergeItem) * il.merge_items.size());
+        return o;
+    };
+    const ListOffsets o_items = reserve_lists(hb.items), o_seq = reserve_lists(hb.in_sequence);
     const size_t o_freq = reserve(sizeof(float) * half);
     const size_t host_bytes = off;
     const size_t o_cs = reserve(sizeof(float2) * (size_t)T * half);
@@ -537,11 +548,15 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
         put(o_last, last.data(), sizeof(int32_t) * B);
     }
     put(o_bt, desc->block_table, sizeof(int32_t) * (size_t)B * desc->max_blocks);
-    put(o_tok, hb.attn_tok.data(), sizeof(int32_t) * hb.attn_tok.size());
-    put(o_ip, hb.items_prefix.data(), sizeof(AttnItem) * hb.items_prefix.size());
-    put(o_it, hb.items_tile.data(), sizeof(AttnItem) * hb.items_tile.size());
-    put(o_is, hb.items_split.data(), sizeof(AttnItem) * hb.items_split.size());
-    put(o_mi, hb.merge_items.data(), sizeof(MergeItem) * hb.merge_items.size());
+    auto put_lists = [&](const ListOffsets& o, const ItemLists& il) {
+        put(o.tok, il.attn_tok.data(), sizeof(int32_t) * il.attn_tok.size());
+        put(o.prefix, il.items_prefix.data(), sizeof(AttnItem) * il.items_prefix.size());
+        put(o.tile, il.items_tile.data(), sizeof(AttnItem) * il.items_tile.size());
+        put(o.split, il.items_split.data(), sizeof(AttnItem) * il.items_split.size());
+        put(o.merge, il.merge_items.data(), sizeof(MergeItem) * il.merge_items.size());
+    };
+    put_lists(o_items, hb.items);
+    put_lists(o_seq, hb.in_sequence);
     put(o_freq, L->inv_freq.data(), sizeof(float) * half);
 
     relserve_batch* b = new (std::nothrow) relserve_batch();
@@ -562,17 +577,22 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
     dv.tok_slot = reinterpret_cast<int32_t*>(base + o_slot);
     dv.last_tok = reinterpret_cast<int32_t*>(base + o_last);
     dv.block_table = reinterpret_cast<int32_t*>(base + o_bt);
-    dv.attn_tok = reinterpret_cast<int32_t*>(base + o_tok);
-    dv.items_prefix = reinterpret_cast<AttnItem*>(base + o_ip);
-    dv.items_tile = reinterpret_cast<AttnItem*>(base + o_it);
-    dv.items_split = reinterpret_cast<AttnItem*>(base + o_is);
-    dv.merge_items = reinterpret_cast<MergeItem*>(base + o_mi);
-    dv.n_merge = (int32_t)hb.merge_items.size();
     dv.rope_cs = reinterpret_cast<float2*>(base + o_cs);
-    dv.n_items_prefix = (int32_t)hb.items_prefix.size();
-    dv.n_items_tile = (int32_t)hb.items_tile.size();
-    dv.n_items_split = (int32_t)hb.items_split.size();
-    dv.n_scratch_slots = hb.n_scratch_slots;
+    auto view_lists = [&](BatchDev& v, const ListOffsets& o, const ItemLists& il) {
+        v.attn_tok = reinterpret_cast<int32_t*>(base + o.tok);
+        v.items_prefix = reinterpret_cast<AttnItem*>(base + o.prefix);
+        v.items_tile = reinterpret_cast<AttnItem*>(base + o.tile);
+        v.items_split = reinterpret_cast<AttnItem*>(base + o.split);
+        v.merge_items = reinterpret_cast<MergeItem*>(base + o.merge);
+        v.n_items_prefix = (int32_t)il.items_prefix.size();
+        v.n_items_tile = (int32_t)il.items_tile.size();
+        v.n_items_split = (int32_t)il.items_split.size();
+        v.n_merge = (int32_t)il.merge_items.size();
+        v.n_scratch_slots = il.n_scratch_slots;
+    };
+    view_lists(dv, o_items, hb.items);
+    b->dev_in_sequence = dv;
+    if (dv.n_scratch_slots > 0) view_lists(b->dev_in_sequence, o_seq, hb.in_sequence);
     b->info = relserve_batch_info{T, B, hb.n_decode, hb.n_prefill, hb.n_groups,
                                   dv.n_items_prefix + dv.n_items_tile + dv.n_items_split};
 
@@ -796,7 +816,10 @@ int32_t relserve_layer_step_w8a8(const relserve_layer* L, const relserve_batch* 
         profile_mark(prof, slot, s, false);
     };
     float* accum = w.accum;
-    const PartialState part = partial_state(*L, b->dev, w);
+    // Codes amplify: an attention output that rounds differently by 1e-3 moves about 2 % of W_o's inputs to the neighbouring
+    // code, and a wide layer's output by up to 7e-3.  The rows' keys are therefore taken in one running sequence here.
+    const BatchDev& batch = b->dev_in_sequence;
+    const PartialState part = partial_state(*L, batch, w);
     const CodeScales qkv{wt->s_qkv, wt->a_qkv, 0.0f}, o{wt->s_o, wt->a_o, 0.0f}, gu{wt->s_gate_up, wt->a_gate_up, wt->a_down},
         down{wt->s_down, wt->a_down, 0.0f};
     run(S_NORM1, [&] { return launch_rmsnorm(x, false, wt->w_in_norm, c.rms_eps, T, c.hidden, w.h, s, nullptr, wt->a_qkv); });
@@ -805,7 +828,7 @@ int32_t relserve_layer_step_w8a8(const relserve_layer* L, const relserve_batch* 
                                       kv_format(cache), &qkv);
     });
     if (e == hipSuccess)
-        e = launch_attention(b->dev, *L, w.q, L->q_dim, cache.k_pages, cache.v_pages, w.attn, part.o,
+        e = launch_attention(batch, *L, w.q, L->q_dim, cache.k_pages, cache.v_pages, w.attn, part.o,
                              part.ml, s, prof, kv_format(cache));
     // the attention output exists as bf16; its codes go where the rotated queries were (read by now)
     run(S_QUANT, [&] { return launch_quantise_bf16(w.attn, (int64_t)T * L->q_dim, wt->a_o, w.q, s); });

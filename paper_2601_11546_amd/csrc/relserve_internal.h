@@ -89,21 +89,28 @@ struct relserve_layer {
 struct relserve_batch {
     relserve_layer_config cfg;  // shape it was prepared for
     relserve::BatchDev dev;
+    relserve::BatchDev dev_in_sequence;   // the same batch without slots (see HostBatch); equals dev where dev has none
     void* blob = nullptr;  // the one device allocation
     relserve_batch_info info;
 };
 
 namespace relserve {
 
+// The attention work of a batch.
+struct ItemLists {
+    std::vector<int32_t> attn_tok;
+    std::vector<AttnItem> items_prefix, items_tile, items_split;
+    std::vector<MergeItem> merge_items;
+    int32_t n_scratch_slots = 0;
+};
+
 // Host-side expansion of a descriptor (no device calls); shared by validate / slots / prepare.
 struct HostBatch {
     int32_t T = 0;
     std::vector<int32_t> tok_req, tok_pos, tok_slot;
-    std::vector<int32_t> attn_tok;
-    std::vector<AttnItem> items_prefix, items_tile, items_split;
-    std::vector<MergeItem> merge_items;
+    ItemLists items;         // what a step runs
+    ItemLists in_sequence;   // only where `items` uses slots: the same work with every row's keys in one running sequence
     int32_t n_decode = 0, n_prefill = 0, n_groups = 0;
-    int32_t n_scratch_slots = 0;
 };
 int32_t expand_batch(const relserve_layer_config& cfg, const relserve_batch_desc& d, bool build_items,
                      HostBatch* out);

@@ -35,3 +35,26 @@ def test_wide_output_of_few_rows(rs, oracle, T):
     resb = W.f32_to_bf16_bits(rng.standard_normal((T, N), dtype=np.float32))
     rs.relserve_linear(a, w, 1, dev_bf16(resb), out)
     assert_close(host_f32(out)[rows], want + W.bf16_bits_to_f32(resb[rows]), "wide + residual", max_abs=1e-3 * scale, rel_l2=1e-4)
+
+
+@pytest.mark.parametrize("T", [129, 160, 192, 193, 255, 256])
+@pytest.mark.parametrize("packed", [False, True])
+def test_one_token_tile_of_192_or_256_rows(rs, oracle, T, packed):
+    """Projections of 129 .. 256 tokens inside a layer step (the entry that has split scratch): k split over workgroups for
+    every projection, and a gate/up projection that is wide enough to run whole."""
+    for shape in (W.LayerShape(512, 4, 2, 128, 704, 16, 1e-5, 10000.0), W.LayerShape(256, 4, 4, 64, 8256, 16, 1e-5, 10000.0)):
+        b = W.build_batch(shape, [T - 7] + [1] * 7, [T - 7] + [5] * 7, seed=T)
+        wl = W.Workload("one_tile", shape, b, T)
+        weights, x = wl.weights(), W.make_activations(b.T, shape.hidden, T)
+        kp, vp = W.make_cache(shape, b.num_pages, T)
+        wd = {k: dev_bf16(v) for k, v in weights.items()}
+        if packed:
+            wd = rs.pack_layer_weights(wd)
+        layer = rs.relserve_layer_create(shape)
+        pb = rs.relserve_batch_prepare(layer, b)
+        ws = torch.full((rs.relserve_workspace_bytes(layer, b.T),), 0xff, dtype=torch.uint8, device="cuda")
+        xd = dev_bf16(x)
+        y = torch.empty_like(xd)
+        rs.relserve_layer_step(layer, pb, wd, xd, y, dev_bf16(kp), dev_bf16(vp), ws)
+        want = oracle.layer_step(shape, b, weights, x, kp, vp).y_f32
+        assert_close(host_f32(y), want, f"step T={T}")     # the whole step's bar
