@@ -69,6 +69,7 @@ struct GemmArgs {
     float a_scale;
     int32_t out_f8;
     float out_inv;
+    int32_t keep_order;      // 16-bit operands whose k ranges are cut as those of 8-bit ones (see plan_for)
 };
 
 // Test hook (relserve_debug_force_gemm_plan): tile candidate (index into kTiles) and tail splits every launch
@@ -234,8 +235,9 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * W
                     float l4[4], h4[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        l4[e] = av[e] * co[e] - bv[e] * si[e];
-                        h4[e] = av[e] * si[e] + bv[e] * co[e];
+                        // which product is rounded is fixed here, not left to the compiler: the same bits whatever the tile
+                        l4[e] = __builtin_fmaf(av[e], co[e], -(bv[e] * si[e]));
+                        h4[e] = __builtin_fmaf(av[e], si[e], bv[e] * co[e]);
                     }
                     if (p.kv_fp8 && head >= p.n_q) {   // quantised cache: one byte per element, quantised from fp32
                         uint8_t* dst8 = reinterpret_cast<uint8_t*>(p.k_pages) + slot * kv_dim + (head - p.n_q) * DH + i;
@@ -1128,24 +1130,37 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
     return p.f8 ? go(std::true_type{}) : go(std::false_type{});
 }
 
-// Tile choice.  A launch runs ceil(tiles / resident workgroups) rounds; the cost of a round is the
-// tile's MFMA work divided by the tile shape's measured in-tile efficiency (relative to 256 x 256).
-// The candidate with the lowest estimated cost wins: this trades tile quantisation in T (padding
-// to BM), the tail round, and the per-tile efficiency against each other.
-struct TileCand { int bm, bn, wg_per_cu; float eff; bool qkv; };   // qkv: usable by the fused q/k/v epilogue (128 features per wave)
+// Tile choice.  A launch runs ceil(tiles / CUs) rounds; the cost of a round is the tile's MFMA work divided by the tile
+// shape's in-tile efficiency (relative to 256 x 256), plus what a round costs whatever the tile.  The candidate with the
+// lowest estimated cost wins: this trades tile quantisation in T (padding to BM), the tail round, and the per-tile
+// efficiency against each other.
+struct TileCand { int bm, bn, wg_per_cu; float eff, eff_swiglu, eff_order; bool qkv; };   // qkv: usable by the fused q/k/v epilogue (128 features per wave)
 constexpr TileCand kTiles[] = {
-    // efficiencies from per-round times of forced plans at T = 288 ... 1282 on the 13B layer's projections
-    {256, 256, 1, 1.00f, true}, {192, 256, 1, 0.92f, true}, {128, 256, 1, 0.68f, true}, {128, 128, 2, 0.76f, false},
-    {64, 128, 3, 0.60f, false}};
+    // Fitted to the times of every forced plan (tile x 1 .. 8 tail splits) of the four projections of five layer shapes at
+    // T = 264 ... 4200, 16-bit and 8-bit: over those the chosen plan is 0.4 % slower than the best one on average, where the
+    // efficiencies read off an earlier epilogue and issue order (0.92 / 0.68 / 0.76 / 0.60 throughout) left 4.5 %: W_o on
+    // 128 x 256 tiles at T = 1152 93 -> 75 us, 70B W_o at T = 1000 149 -> 122, gate/up at T = 640 213 -> 188.
+    {256, 256, 1, 1.00f, 1.00f, 1.00f, true}, {192, 256, 1, 0.88f, 0.88f, 0.92f, true}, {128, 256, 1, 0.90f, 0.75f, 0.68f, true},
+    {128, 128, 2, 0.50f, 0.80f, 0.76f, false}, {64, 128, 3, 0.40f, 0.50f, 0.60f, false}};
 
 // A tail (the tiles of the incomplete last round) may split its k range over workgroups, so that the
 // round takes 1 / splits of a tile time; the price is that every partial tile is written to memory
 // and read back by the workgroup that finishes the tile.  Costs in seconds.
 constexpr double kCuFlops = 5.2e12;          // sustained MFMA rate of one CU inside a 256 x 256 tile
-constexpr double kSlabBytesPerSec = 3.0e12;  // partial tiles through memory (written by the GEMM, read by the finish kernel)
-constexpr double kTailFinishSec = 6e-6;      // the finish kernel's launch and ramp
+// Which tiles split their k range, and how often, also fixes the order of every sum.  A stack of quantised layers amplifies
+// a last-bit difference of a sum to 2e-2 of its logits after four layers (a code on the other side of its rounding boundary
+// in one layer moves many in the next; the layers of a 16-bit stack write different codes into quantised pools), so for 8-bit
+// operands, and for stacks over quantised pools, that choice stays with the older fit (eff_order and the
+// constants beside it): where it splits a tail, that very plan runs; where it does not, whole tiles of any shape give the
+// same bits and the newer fit picks the shape.
+struct PlanCosts { double round_sec, slab_bytes_per_sec, tail_finish_sec; int boost_bm; };
+constexpr PlanCosts kCosts{5e-6, 3.7e12, 4e-6, 256};        // first loads and last stores of a round; partial tiles through memory
+constexpr PlanCosts kOrderCosts{0.0, 3.0e12, 6e-6, 192};    // (written by the GEMM, read by the finish kernel); its launch and ramp
 
-Plan choose_plan(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail) {
+enum class PlanFit { Time16, TimeSwiglu, Order };
+
+Plan choose_plan(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, PlanFit fit) {
+    const PlanCosts& cost_of = fit == PlanFit::Order ? kOrderCosts : kCosts;
     const int n_cand = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
     const int f_cand = forced_cand(), f_splits = forced_splits();
     const bool force = f_cand >= 0 && f_cand < n_cand;
@@ -1159,16 +1174,19 @@ Plan choose_plan(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail) 
             if (f_cand != i && !(need_bn256 && !kTiles[f_cand].qkv)) continue;
             if (f_cand == i) forced_splits = f_splits;
         }
-        const double eff = c.eff;
-        const int64_t tiles = ((T + c.bm - 1) / c.bm) * ((n_eff + c.bn - 1) / c.bn);
+        const double eff = fit == PlanFit::Order ? c.eff_order : fit == PlanFit::TimeSwiglu ? c.eff_swiglu : c.eff;
+        const int64_t tiles = (int64_t)((T + c.bm - 1) / c.bm) * ((n_eff + c.bn - 1) / c.bn);
+        const double t_tile = 2.0 * c.bm * c.bn * (double)K / (eff * kCuFlops);
         const int64_t slots = 256 * c.wg_per_cu;
-        // resident workgroups of a CU share its MFMA pipes: a round of wg_per_cu tiles costs wg_per_cu tile times
-        double t_round = c.wg_per_cu * 2.0 * c.bm * c.bn * (double)K / (eff * kCuFlops);
-        // a launch that leaves CUs idle runs its big tiles faster (the chip is power-limited: up to 2.2 GHz
-        // instead of ~1.9); the small tiles are bound by L2 traffic and gain nothing
-        if (tiles < slots && c.bm >= 192) t_round /= 1.0 + 0.25 * (1.0 - (double)tiles / (double)slots);
+        // resident workgroups of a CU share its MFMA pipes: wg_per_cu tiles on a CU take wg_per_cu tile times
+        double t_round = c.wg_per_cu * t_tile + cost_of.round_sec;
+        // a launch that leaves CUs idle runs its largest tiles faster (the chip is power-limited: up to 2.2 GHz instead of
+        // ~1.9); the smaller ones are bound by L2 traffic and gain nothing
+        if (tiles < slots && c.bm >= cost_of.boost_bm) t_round /= 1.0 + 0.25 * (1.0 - (double)tiles / (double)slots);
         const int64_t full = tiles / slots, rem = tiles % slots;
-        const double whole = (double)(full + (rem ? 1 : 0)) * t_round;
+        const double whole = c.wg_per_cu == 1 || fit == PlanFit::Order
+                                 ? (double)(full + (rem ? 1 : 0)) * t_round
+                                 : (double)((tiles + 255) / 256) * t_tile + (double)(full + (rem ? 1 : 0)) * cost_of.round_sec;
         if (whole < best_cost && forced_splits <= 1) best_cost = whole, best = Plan{i, 0, 1};
         const int nk = K / 64;
         // tiles that share a CU (two or three workgroups) gained nothing from split tails in any measured case
@@ -1178,18 +1196,27 @@ Plan choose_plan(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail) 
             const int64_t units = rem * sp;
             if (units * c.bm * c.bn > kTailFloats) break;
             const double rounds = (double)((units + slots - 1) / slots);
-            const double slabs = (double)units * c.bm * c.bn * 4.0 * 2.0 / kSlabBytesPerSec;
-            const double cost = full * t_round + rounds * t_round / sp + slabs + kTailFinishSec;
+            const double slabs = (double)units * c.bm * c.bn * 4.0 * 2.0 / cost_of.slab_bytes_per_sec;
+            const double cost = full * t_round + rounds * t_round / sp + slabs + cost_of.tail_finish_sec;
             if (cost < best_cost || forced_splits > 1) best_cost = cost, best = Plan{i, (int)rem, sp};
         }
     }
     return best;
 }
 
+Plan plan_for(const GemmArgs& p, int64_t n_eff, bool need_bn256, bool swiglu) {
+    const PlanFit fit = swiglu ? PlanFit::TimeSwiglu : PlanFit::Time16;
+    if (p.f8 || p.keep_order) {
+        const Plan order = choose_plan(p.T, n_eff, p.K, need_bn256, p.accum != nullptr, PlanFit::Order);
+        return order.tail_tiles > 0 || forced_cand() >= 0 ? order : choose_plan(p.T, n_eff, p.K, need_bn256, false, fit);
+    }
+    return choose_plan(p.T, n_eff, p.K, need_bn256, p.accum != nullptr, fit);
+}
+
 template <int EPI>
 hipError_t launch_epi(const GemmArgs& p, hipStream_t s) {
     const int64_t n_eff = EPI == EPI_SWIGLU ? 2 * (int64_t)p.n_half : p.N;
-    const Plan plan = choose_plan(p.T, n_eff, p.K, false, p.accum != nullptr);
+    const Plan plan = plan_for(p, n_eff, false, EPI == EPI_SWIGLU);
     switch (plan.cand) {
         case 0: return launch_cfg<256, 256, EPI>(p, s, plan);
         case 1: return launch_cfg<192, 256, EPI>(p, s, plan);
@@ -1236,6 +1263,10 @@ hipError_t launch_pack_weight(const void* w, int32_t N, int32_t K, void* out, hi
 // 8-bit operands: the kernels see rows of K / 2 two-byte units (same bytes, same layouts) and the scales
 static hipError_t set_codes(GemmArgs& p, const CodeScales* codes) {
     if (!codes) return hipSuccess;
+    if (codes->order_only) {
+        p.keep_order = 1;
+        return hipSuccess;
+    }
     if (p.K % 128 || !codes->w_scale || !(codes->a_scale > 0.0f)) return hipErrorInvalidValue;
     p.f8 = 1;
     p.K /= 2;
@@ -1298,7 +1329,7 @@ namespace {
 template <int D>
 hipError_t launch_qkv_d(const GemmArgs& p, hipStream_t s) {
     if (p.T <= 64) return launch_cfg<64, 256, EPI_QKV_ROPE, D>(p, s);
-    const Plan plan = choose_plan(p.T, p.N, p.K, true, p.accum != nullptr);   // the rotation needs 128 features per wave
+    const Plan plan = plan_for(p, p.N, true, false);   // the rotation needs 128 features per wave
     switch (plan.cand) {
         case 0: return launch_cfg<256, 256, EPI_QKV_ROPE, D>(p, s, plan);
         case 1: return launch_cfg<192, 256, EPI_QKV_ROPE, D>(p, s, plan);
@@ -1334,6 +1365,7 @@ hipError_t launch_qkv_rope_append(const BatchDev& b, const relserve_layer& L, co
     p.v_inv = (float)(1.0 / (double)kv.v_scale);
     p.accum = accum;
     if (hipError_t e = set_codes(p, codes)) return e;
+    p.keep_order |= kv.keep_order ? 1 : 0;
     if (skinny_applies(p.T, p.N, p.K, accum))
         return L.cfg.head_dim == 128 ? launch_skinny<EPI_QKV_ROPE, 128>(p, s) : launch_skinny<EPI_QKV_ROPE, 64>(p, s);
     return L.cfg.head_dim == 128 ? launch_qkv_d<128>(p, s) : launch_qkv_d<64>(p, s);

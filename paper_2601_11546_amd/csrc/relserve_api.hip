@@ -737,9 +737,11 @@ int32_t relserve_attention(const relserve_layer* L, const relserve_batch* b, con
     return e == hipSuccess ? RELSERVE_OK : RELSERVE_ERR_HIP;
 }
 
-int32_t relserve_layer_step(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt,
-                            const void* x, void* y, relserve_kv_cache cache, void* workspace,
-                            size_t workspace_bytes, void* stream) {
+// keep_order: this is a layer of a stack over quantised pools.  A 16-bit activation that rounds the other way in one layer
+// moves codes of the next layer's keys and values, so the sums and each row's softmax keep their reference order there.
+static int32_t layer_step(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt, const void* x,
+                          void* y, relserve_kv_cache cache, void* workspace, size_t workspace_bytes, void* stream,
+                          bool keep_order) {
     drop_stale_hip_error();
     if (int32_t rc = check_pair(L, b)) return rc;
     if (!wt) return RELSERVE_ERR_NULL_POINTER;
@@ -767,22 +769,32 @@ int32_t relserve_layer_step(const relserve_layer* L, const relserve_batch* b, co
     // the GEMMs split K across workgroups (whole skinny problems, narrow outputs at mid-size T, or the
     // incomplete last round of tiles) through an fp32 scratch that they write before they read
     float* accum = w.accum;
-    const PartialState part = partial_state(*L, b->dev, w);
+    const BatchDev& batch = keep_order ? b->dev_in_sequence : b->dev;
+    const PartialState part = partial_state(*L, batch, w);
+    KvFormat kv = kv_format(cache);
+    kv.keep_order = keep_order;
+    CodeScales order;
+    order.order_only = true;
+    const CodeScales* codes = keep_order ? &order : nullptr;
     run(S_NORM1, [&] { return launch_rmsnorm(x, false, wt->w_in_norm, c.rms_eps, T, c.hidden, w.h, s); });
     run(S_QKV, [&] {
-        return launch_qkv_rope_append(b->dev, *L, w.h, wt->w_qkv, w.q, cache.k_pages, cache.v_pages, s, accum, packed,
-                                      kv_format(cache));
+        return launch_qkv_rope_append(b->dev, *L, w.h, wt->w_qkv, w.q, cache.k_pages, cache.v_pages, s, accum, packed, kv);
     });
     if (e == hipSuccess)
-        e = launch_attention(b->dev, *L, w.q, L->q_dim, cache.k_pages, cache.v_pages, w.attn, part.o,
-                             part.ml, s, prof, kv_format(cache));
-    run(S_O, [&] { return launch_linear(w.attn, wt->w_o, T, c.hidden, L->q_dim, 1, x, w.x1, s, accum, packed); });
+        e = launch_attention(batch, *L, w.q, L->q_dim, cache.k_pages, cache.v_pages, w.attn, part.o, part.ml, s, prof, kv);
+    run(S_O, [&] { return launch_linear(w.attn, wt->w_o, T, c.hidden, L->q_dim, 1, x, w.x1, s, accum, packed, codes); });
     run(S_NORM2, [&] { return launch_rmsnorm(w.x1, true, wt->w_post_norm, c.rms_eps, T, c.hidden, w.h, s); });
     run(S_GU, [&] {
-        return launch_linear(w.h, wt->w_gate_up, T, 2 * c.mlp_dim, c.hidden, 3, nullptr, w.act, s, accum, packed);
+        return launch_linear(w.h, wt->w_gate_up, T, 2 * c.mlp_dim, c.hidden, 3, nullptr, w.act, s, accum, packed, codes);
     });
-    run(S_DOWN, [&] { return launch_linear(w.act, wt->w_down, T, c.hidden, c.mlp_dim, 2, w.x1, y, s, accum, packed); });
+    run(S_DOWN, [&] { return launch_linear(w.act, wt->w_down, T, c.hidden, c.mlp_dim, 2, w.x1, y, s, accum, packed, codes); });
     return e == hipSuccess ? RELSERVE_OK : RELSERVE_ERR_HIP;
+}
+
+int32_t relserve_layer_step(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt,
+                            const void* x, void* y, relserve_kv_cache cache, void* workspace,
+                            size_t workspace_bytes, void* stream) {
+    return layer_step(L, b, wt, x, y, cache, workspace, workspace_bytes, stream, false);
 }
 
 int32_t relserve_layer_step_w8a8(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights_w8a8* wt,
@@ -932,7 +944,8 @@ int32_t model_step(const relserve_layer* L, const relserve_batch* b, const relse
     if (launch_embedding(token_ids, m->embedding, m->vocab, H, T, x, s) != hipSuccess) return RELSERVE_ERR_HIP;
     for (int32_t l = 0; l < m->n_layers; ++l) {   // the residual stream stays in x, rounded to bf16 between layers
         const int32_t rc = q8 ? relserve_layer_step_w8a8(L, b, &q8[l], x, x, m->caches[l], workspace, layer_ws, stream)
-                              : relserve_layer_step(L, b, &m->layers[l], x, x, m->caches[l], workspace, layer_ws, stream);
+                              : layer_step(L, b, &m->layers[l], x, x, m->caches[l], workspace, layer_ws, stream,
+                                           m->n_layers > 1 && m->caches[l].dtype == RELSERVE_KV_FP8);
         if (rc) return rc;
     }
     if (launch_rmsnorm(x, false, m->w_final_norm, L->cfg.rms_eps, B, H, h_last, s, b->dev.last_tok) != hipSuccess)

@@ -144,6 +144,7 @@ struct CodeScales {
     const float* w_scale = nullptr;   // [N] device
     float a_scale = 1.0f;
     float out_scale = 0.0f;
+    bool order_only = false;          // 16-bit operands, no scales: the launch plan keeps the order of the sums (see plan_for)
 };
 hipError_t launch_linear(const void* a, const void* w, int32_t T, int32_t N, int32_t K, int32_t epilogue,
                          const void* residual, void* out, hipStream_t s, float* accum = nullptr, bool w_packed = false,
@@ -155,6 +156,7 @@ hipError_t launch_pack_weight(const void* w, int32_t N, int32_t K, void* out, hi
 struct KvFormat {
     bool fp8 = false;
     float k_scale = 1.0f, v_scale = 1.0f;
+    bool keep_order = false;   // a layer of a stack over quantised pools: sums and softmax in their reference order
 };
 hipError_t launch_qkv_rope_append(const BatchDev& b, const relserve_layer& L, const void* h, const void* w_qkv,
                                   void* q_out, void* k_pages, void* v_pages, hipStream_t s, float* accum = nullptr,
