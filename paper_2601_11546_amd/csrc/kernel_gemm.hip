@@ -69,7 +69,6 @@ struct GemmArgs {
     float a_scale;
     int32_t out_f8;
     float out_inv;
-    int32_t keep_order;      // 16-bit operands whose k ranges are cut as those of 8-bit ones (see plan_for)
 };
 
 // Test hook (relserve_debug_force_gemm_plan): tile candidate (index into kTiles) and tail splits every launch
@@ -1020,7 +1019,9 @@ hipError_t launch_skinny(const GemmArgs& p, hipStream_t s) {
     // 128 rows read them twice; what the CUs draw from the L2 is the bound here, weights and activations together).
     // A projection that fills the CUs without a k split runs whole.  13B layer, its four projections, before -> now:
     // 248 -> 208 us at T = 160, 253 -> 232 at 200, 265 -> 239 at 256 (with an event pair per launch).
-    const int splits = choose_splits(p.T, p.N, p.K, p.T <= 192 ? 192 : 256, 128);
+    // The k ranges are those of 128 x 256 tiles (never fewer tiles than these): how often a sum is cut does not depend on
+    // the tile that computes it.
+    const int splits = choose_splits(p.T, p.N, p.K, 128);
     if (splits == 1) {
         // wide enough that one 256 x 256 tile per CU is (nearly) a full round: half the activation reads again
         const int tiles256 = EPI == EPI_SWIGLU ? (p.n_half + 127) / 128 : (p.N + 255) / 256;
@@ -1130,93 +1131,111 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
     return p.f8 ? go(std::true_type{}) : go(std::false_type{});
 }
 
-// Tile choice.  A launch runs ceil(tiles / CUs) rounds; the cost of a round is the tile's MFMA work divided by the tile
-// shape's in-tile efficiency (relative to 256 x 256), plus what a round costs whatever the tile.  The candidate with the
-// lowest estimated cost wins: this trades tile quantisation in T (padding to BM), the tail round, and the per-tile
-// efficiency against each other.
-struct TileCand { int bm, bn, wg_per_cu; float eff, eff_swiglu, eff_order; bool qkv; };   // qkv: usable by the fused q/k/v epilogue (128 features per wave)
+// Tile choice, in two steps.
+//
+// 1. The cut: which tiles split their k range, and how often.  Of a launch of ceil(tiles / resident workgroups) rounds the
+// tiles of the incomplete last one (the tail) may split it, so that the round takes 1 / splits of a tile time; the price is
+// that every partial tile is written to memory and read back by the kernel that finishes the tile.  The cut fixes the order
+// of every sum, and a last-bit difference does not stay small: a few layers on it decides between near-equal next tokens,
+// and a code on the other side of its rounding boundary moves many in the next layer (2e-2 of the logits of four quantised
+// layers).  So the cut depends on the sizes alone, for every kind of operand, and these constants are kept as they are: a
+// refit of them for 16-bit operands changed a next token in 129 (four 13B layers, 128 decode rows and a 512-token chunk).
+//
+// 2. The shape of whole tiles: any gives the same bits, so where nothing is split the fastest one runs (whole_tile).
+struct TileCand { int bm, bn, wg_per_cu; float eff_cut, eff, eff_swiglu; bool qkv; };   // qkv: usable by the fused q/k/v epilogue (128 features per wave)
 constexpr TileCand kTiles[] = {
-    // Fitted to the times of every forced plan (tile x 1 .. 8 tail splits) of the four projections of five layer shapes at
-    // T = 264 ... 4200, 16-bit and 8-bit: over those the chosen plan is 0.4 % slower than the best one on average, where the
-    // efficiencies read off an earlier epilogue and issue order (0.92 / 0.68 / 0.76 / 0.60 throughout) left 4.5 %: W_o on
-    // 128 x 256 tiles at T = 1152 93 -> 75 us, 70B W_o at T = 1000 149 -> 122, gate/up at T = 640 213 -> 188.
-    {256, 256, 1, 1.00f, 1.00f, 1.00f, true}, {192, 256, 1, 0.88f, 0.88f, 0.92f, true}, {128, 256, 1, 0.90f, 0.75f, 0.68f, true},
-    {128, 128, 2, 0.50f, 0.80f, 0.76f, false}, {64, 128, 3, 0.40f, 0.50f, 0.60f, false}};
+    {256, 256, 1, 1.00f, 1.00f, 1.00f, true}, {192, 256, 1, 0.92f, 0.88f, 0.88f, true}, {128, 256, 1, 0.68f, 0.90f, 0.75f, true},
+    {128, 128, 2, 0.76f, 0.50f, 0.80f, false}, {64, 128, 3, 0.60f, 0.40f, 0.50f, false}};
+constexpr int kTileCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
-// A tail (the tiles of the incomplete last round) may split its k range over workgroups, so that the
-// round takes 1 / splits of a tile time; the price is that every partial tile is written to memory
-// and read back by the workgroup that finishes the tile.  Costs in seconds.
 constexpr double kCuFlops = 5.2e12;          // sustained MFMA rate of one CU inside a 256 x 256 tile
-// Which tiles split their k range, and how often, also fixes the order of every sum.  A stack of quantised layers amplifies
-// a last-bit difference of a sum to 2e-2 of its logits after four layers (a code on the other side of its rounding boundary
-// in one layer moves many in the next; the layers of a 16-bit stack write different codes into quantised pools), so for 8-bit
-// operands, and for stacks over quantised pools, that choice stays with the older fit (eff_order and the
-// constants beside it): where it splits a tail, that very plan runs; where it does not, whole tiles of any shape give the
-// same bits and the newer fit picks the shape.
-struct PlanCosts { double round_sec, slab_bytes_per_sec, tail_finish_sec; int boost_bm; };
-constexpr PlanCosts kCosts{5e-6, 3.7e12, 4e-6, 256};        // first loads and last stores of a round; partial tiles through memory
-constexpr PlanCosts kOrderCosts{0.0, 3.0e12, 6e-6, 192};    // (written by the GEMM, read by the finish kernel); its launch and ramp
+constexpr double kSlabBytesPerSec = 3.0e12;  // partial tiles through memory (written by the GEMM, read by the finish kernel)
+constexpr double kTailFinishSec = 6e-6;      // the finish kernel's launch and ramp
+constexpr double kRoundSec = 5e-6;           // what a round of whole tiles costs whatever the tile: first loads and last stores
 
-enum class PlanFit { Time16, TimeSwiglu, Order };
+int64_t tile_count(const TileCand& c, int T, int64_t n_eff) { return (int64_t)((T + c.bm - 1) / c.bm) * ((n_eff + c.bn - 1) / c.bn); }
+double tile_sec(const TileCand& c, int K, double eff) { return 2.0 * c.bm * c.bn * (double)K / (eff * kCuFlops); }
+// a launch that leaves CUs idle runs its big tiles faster (the chip is power-limited: up to 2.2 GHz instead of ~1.9);
+// the small ones are bound by L2 traffic and gain nothing
+double idle_boost(int64_t tiles, int64_t slots) { return tiles < slots ? 1.0 + 0.25 * (1.0 - (double)tiles / (double)slots) : 1.0; }
 
-Plan choose_plan(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, PlanFit fit) {
-    const PlanCosts& cost_of = fit == PlanFit::Order ? kOrderCosts : kCosts;
-    const int n_cand = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
-    const int f_cand = forced_cand(), f_splits = forced_splits();
-    const bool force = f_cand >= 0 && f_cand < n_cand;
+// need_bn256: the fused q/k/v epilogue's tiles only
+Plan choose_cut(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail) {
     Plan best{0, 0, 1};
     double best_cost = 1e300;
-    for (int i = 0; i < n_cand; ++i) {
+    for (int i = 0; i < kTileCount; ++i) {
         const TileCand& c = kTiles[i];
-        int forced_splits = 0;
         if (need_bn256 && !c.qkv) continue;
-        if (force) {
-            if (f_cand != i && !(need_bn256 && !kTiles[f_cand].qkv)) continue;
-            if (f_cand == i) forced_splits = f_splits;
-        }
-        const double eff = fit == PlanFit::Order ? c.eff_order : fit == PlanFit::TimeSwiglu ? c.eff_swiglu : c.eff;
-        const int64_t tiles = (int64_t)((T + c.bm - 1) / c.bm) * ((n_eff + c.bn - 1) / c.bn);
-        const double t_tile = 2.0 * c.bm * c.bn * (double)K / (eff * kCuFlops);
-        const int64_t slots = 256 * c.wg_per_cu;
-        // resident workgroups of a CU share its MFMA pipes: wg_per_cu tiles on a CU take wg_per_cu tile times
-        double t_round = c.wg_per_cu * t_tile + cost_of.round_sec;
-        // a launch that leaves CUs idle runs its largest tiles faster (the chip is power-limited: up to 2.2 GHz instead of
-        // ~1.9); the smaller ones are bound by L2 traffic and gain nothing
-        if (tiles < slots && c.bm >= cost_of.boost_bm) t_round /= 1.0 + 0.25 * (1.0 - (double)tiles / (double)slots);
+        const int64_t tiles = tile_count(c, T, n_eff), slots = 256 * c.wg_per_cu;
+        // resident workgroups of a CU share its MFMA pipes: a round of wg_per_cu tiles costs wg_per_cu tile times
+        double t_round = c.wg_per_cu * tile_sec(c, K, c.eff_cut);
+        if (c.bm >= 192) t_round /= idle_boost(tiles, slots);
         const int64_t full = tiles / slots, rem = tiles % slots;
-        const double whole = c.wg_per_cu == 1 || fit == PlanFit::Order
-                                 ? (double)(full + (rem ? 1 : 0)) * t_round
-                                 : (double)((tiles + 255) / 256) * t_tile + (double)(full + (rem ? 1 : 0)) * cost_of.round_sec;
-        if (whole < best_cost && forced_splits <= 1) best_cost = whole, best = Plan{i, 0, 1};
+        const double whole = (double)(full + (rem ? 1 : 0)) * t_round;
+        if (whole < best_cost) best_cost = whole, best = Plan{i, 0, 1};
         const int nk = K / 64;
         // tiles that share a CU (two or three workgroups) gained nothing from split tails in any measured case
-        const bool can_tail = allow_tail && rem > 0 && K % 64 == 0 && (c.wg_per_cu == 1 || forced_splits > 1);
+        const bool can_tail = allow_tail && rem > 0 && K % 64 == 0 && c.wg_per_cu == 1;
         for (int sp = 2; can_tail && sp <= 8 && nk / sp >= 8; ++sp) {
-            if (forced_splits > 1 && sp != forced_splits) continue;
             const int64_t units = rem * sp;
             if (units * c.bm * c.bn > kTailFloats) break;
             const double rounds = (double)((units + slots - 1) / slots);
-            const double slabs = (double)units * c.bm * c.bn * 4.0 * 2.0 / cost_of.slab_bytes_per_sec;
-            const double cost = full * t_round + rounds * t_round / sp + slabs + cost_of.tail_finish_sec;
-            if (cost < best_cost || forced_splits > 1) best_cost = cost, best = Plan{i, (int)rem, sp};
+            const double slabs = (double)units * c.bm * c.bn * 4.0 * 2.0 / kSlabBytesPerSec;
+            const double cost = full * t_round + rounds * t_round / sp + slabs + kTailFinishSec;
+            if (cost < best_cost) best_cost = cost, best = Plan{i, (int)rem, sp};
         }
     }
     return best;
 }
 
-Plan plan_for(const GemmArgs& p, int64_t n_eff, bool need_bn256, bool swiglu) {
-    const PlanFit fit = swiglu ? PlanFit::TimeSwiglu : PlanFit::Time16;
-    if (p.f8 || p.keep_order) {
-        const Plan order = choose_plan(p.T, n_eff, p.K, need_bn256, p.accum != nullptr, PlanFit::Order);
-        return order.tail_tiles > 0 || forced_cand() >= 0 ? order : choose_plan(p.T, n_eff, p.K, need_bn256, false, fit);
+// The cost of a round is the tile's MFMA work over the shape's in-tile efficiency (relative to 256 x 256) plus kRoundSec;
+// this trades tile quantisation in T (padding to BM), the incomplete round, and the efficiency against each other.
+int whole_tile(int T, int64_t n_eff, int K, bool need_bn256, bool swiglu) {
+    int best = 0;
+    double best_cost = 1e300;
+    for (int i = 0; i < kTileCount; ++i) {
+        const TileCand& c = kTiles[i];
+        if (need_bn256 && !c.qkv) continue;
+        const int64_t tiles = tile_count(c, T, n_eff), slots = 256 * c.wg_per_cu, rounds = (tiles + slots - 1) / slots;
+        const double t_tile = tile_sec(c, K, swiglu ? c.eff_swiglu : c.eff);
+        double cost;
+        if (c.wg_per_cu > 1)   // tiles of an incomplete round share fewer CUs' pipes
+            cost = (double)((tiles + 255) / 256) * t_tile + (double)rounds * kRoundSec;
+        else
+            cost = (double)rounds * (t_tile + kRoundSec) / (c.bm >= 256 ? idle_boost(tiles, slots) : 1.0);
+        if (cost < best_cost) best_cost = cost, best = i;
     }
-    return choose_plan(p.T, n_eff, p.K, need_bn256, p.accum != nullptr, fit);
+    return best;
+}
+
+// Test hook: the forced tile, or the nearest one the epilogue can run on; its whole incomplete round split if asked for.
+bool forced_plan(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, Plan* out) {
+    const int cand = forced_cand(), splits = forced_splits();
+    if (cand < 0 || cand >= kTileCount) return false;
+    if (need_bn256 && !kTiles[cand].qkv) {   // whole tiles of the best shape that can
+        *out = Plan{whole_tile(T, n_eff, K, true, false), 0, 1};
+        return true;
+    }
+    const TileCand& c = kTiles[cand];
+    const int64_t rem = tile_count(c, T, n_eff) % (256 * c.wg_per_cu);
+    const bool tail = allow_tail && splits > 1 && splits <= 8 && rem > 0 && K % 64 == 0 && K / 64 / splits >= 8 &&
+                      rem * splits * c.bm * c.bn <= kTailFloats;
+    *out = tail ? Plan{cand, (int)rem, splits} : Plan{cand, 0, 1};
+    return true;
+}
+
+Plan plan_for(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, bool swiglu) {
+    Plan plan;
+    if (forced_plan(T, n_eff, K, need_bn256, allow_tail, &plan)) return plan;
+    plan = choose_cut(T, n_eff, K, need_bn256, allow_tail);
+    if (plan.tail_tiles == 0) plan.cand = whole_tile(T, n_eff, K, need_bn256, swiglu);
+    return plan;
 }
 
 template <int EPI>
 hipError_t launch_epi(const GemmArgs& p, hipStream_t s) {
     const int64_t n_eff = EPI == EPI_SWIGLU ? 2 * (int64_t)p.n_half : p.N;
-    const Plan plan = plan_for(p, n_eff, false, EPI == EPI_SWIGLU);
+    const Plan plan = plan_for(p.T, n_eff, p.K, false, p.accum != nullptr, EPI == EPI_SWIGLU);
     switch (plan.cand) {
         case 0: return launch_cfg<256, 256, EPI>(p, s, plan);
         case 1: return launch_cfg<192, 256, EPI>(p, s, plan);
@@ -1230,6 +1249,11 @@ hipError_t launch_epi(const GemmArgs& p, hipStream_t s) {
 
 void gemm_force_plan(int cand, int splits) {
     g_forced_plan.store(cand < 0 ? -1 : (cand | (splits << 8)), std::memory_order_relaxed);
+}
+
+GemmPlan gemm_plan(int32_t T, int64_t features, int32_t K, bool qkv, bool swiglu, bool scratch) {
+    const Plan p = plan_for(T, features, K, qkv, scratch, swiglu);
+    return GemmPlan{kTiles[p.cand].bm, kTiles[p.cand].bn, p.tail_tiles, p.splits};
 }
 
 int64_t gemm_scratch_floats(int64_t T, int64_t n_max) {
@@ -1263,10 +1287,6 @@ hipError_t launch_pack_weight(const void* w, int32_t N, int32_t K, void* out, hi
 // 8-bit operands: the kernels see rows of K / 2 two-byte units (same bytes, same layouts) and the scales
 static hipError_t set_codes(GemmArgs& p, const CodeScales* codes) {
     if (!codes) return hipSuccess;
-    if (codes->order_only) {
-        p.keep_order = 1;
-        return hipSuccess;
-    }
     if (p.K % 128 || !codes->w_scale || !(codes->a_scale > 0.0f)) return hipErrorInvalidValue;
     p.f8 = 1;
     p.K /= 2;
@@ -1329,7 +1349,7 @@ namespace {
 template <int D>
 hipError_t launch_qkv_d(const GemmArgs& p, hipStream_t s) {
     if (p.T <= 64) return launch_cfg<64, 256, EPI_QKV_ROPE, D>(p, s);
-    const Plan plan = plan_for(p, p.N, true, false);   // the rotation needs 128 features per wave
+    const Plan plan = plan_for(p.T, p.N, p.K, true, p.accum != nullptr, false);   // the rotation needs 128 features per wave
     switch (plan.cand) {
         case 0: return launch_cfg<256, 256, EPI_QKV_ROPE, D>(p, s, plan);
         case 1: return launch_cfg<192, 256, EPI_QKV_ROPE, D>(p, s, plan);
@@ -1365,7 +1385,6 @@ hipError_t launch_qkv_rope_append(const BatchDev& b, const relserve_layer& L, co
     p.v_inv = (float)(1.0 / (double)kv.v_scale);
     p.accum = accum;
     if (hipError_t e = set_codes(p, codes)) return e;
-    p.keep_order |= kv.keep_order ? 1 : 0;
     if (skinny_applies(p.T, p.N, p.K, accum))
         return L.cfg.head_dim == 128 ? launch_skinny<EPI_QKV_ROPE, 128>(p, s) : launch_skinny<EPI_QKV_ROPE, 64>(p, s);
     return L.cfg.head_dim == 128 ? launch_qkv_d<128>(p, s) : launch_qkv_d<64>(p, s);

@@ -738,7 +738,7 @@ int32_t relserve_attention(const relserve_layer* L, const relserve_batch* b, con
 }
 
 // keep_order: this is a layer of a stack over quantised pools.  A 16-bit activation that rounds the other way in one layer
-// moves codes of the next layer's keys and values, so the sums and each row's softmax keep their reference order there.
+// moves codes of the next layer's keys and values, so each row's softmax keeps its order there.
 static int32_t layer_step(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt, const void* x,
                           void* y, relserve_kv_cache cache, void* workspace, size_t workspace_bytes, void* stream,
                           bool keep_order) {
@@ -771,23 +771,19 @@ static int32_t layer_step(const relserve_layer* L, const relserve_batch* b, cons
     float* accum = w.accum;
     const BatchDev& batch = keep_order ? b->dev_in_sequence : b->dev;
     const PartialState part = partial_state(*L, batch, w);
-    KvFormat kv = kv_format(cache);
-    kv.keep_order = keep_order;
-    CodeScales order;
-    order.order_only = true;
-    const CodeScales* codes = keep_order ? &order : nullptr;
+    const KvFormat kv = kv_format(cache);
     run(S_NORM1, [&] { return launch_rmsnorm(x, false, wt->w_in_norm, c.rms_eps, T, c.hidden, w.h, s); });
     run(S_QKV, [&] {
         return launch_qkv_rope_append(b->dev, *L, w.h, wt->w_qkv, w.q, cache.k_pages, cache.v_pages, s, accum, packed, kv);
     });
     if (e == hipSuccess)
         e = launch_attention(batch, *L, w.q, L->q_dim, cache.k_pages, cache.v_pages, w.attn, part.o, part.ml, s, prof, kv);
-    run(S_O, [&] { return launch_linear(w.attn, wt->w_o, T, c.hidden, L->q_dim, 1, x, w.x1, s, accum, packed, codes); });
+    run(S_O, [&] { return launch_linear(w.attn, wt->w_o, T, c.hidden, L->q_dim, 1, x, w.x1, s, accum, packed); });
     run(S_NORM2, [&] { return launch_rmsnorm(w.x1, true, wt->w_post_norm, c.rms_eps, T, c.hidden, w.h, s); });
     run(S_GU, [&] {
-        return launch_linear(w.h, wt->w_gate_up, T, 2 * c.mlp_dim, c.hidden, 3, nullptr, w.act, s, accum, packed, codes);
+        return launch_linear(w.h, wt->w_gate_up, T, 2 * c.mlp_dim, c.hidden, 3, nullptr, w.act, s, accum, packed);
     });
-    run(S_DOWN, [&] { return launch_linear(w.act, wt->w_down, T, c.hidden, c.mlp_dim, 2, w.x1, y, s, accum, packed, codes); });
+    run(S_DOWN, [&] { return launch_linear(w.act, wt->w_down, T, c.hidden, c.mlp_dim, 2, w.x1, y, s, accum, packed); });
     return e == hipSuccess ? RELSERVE_OK : RELSERVE_ERR_HIP;
 }
 

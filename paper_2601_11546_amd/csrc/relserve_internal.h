@@ -138,13 +138,16 @@ hipError_t launch_rope_append(const BatchDev& b, const relserve_layer& L, void* 
 // ones split K over workgroups (partial tiles written there, summed by a second kernel).
 int64_t gemm_scratch_floats(int64_t T, int64_t n_max);
 void gemm_force_plan(int cand, int splits);   // test hook, see relserve_debug_force_gemm_plan
+// How a projection of more tokens than SKINNY_MAX_T is tiled (host arithmetic alone): tiles of rows tokens x cols features,
+// of which the last tail_tiles split their k range `splits` ways.  K counts 2-byte units, so half of it for 8-bit codes.
+struct GemmPlan { int32_t rows, cols, tail_tiles, splits; };
+GemmPlan gemm_plan(int32_t T, int64_t features, int32_t K, bool qkv, bool swiglu, bool scratch);
 // Quantised projection: a [T, K] and w [N, K] hold 8-bit codes (K % 128 == 0); the sums take the factor
 // a_scale * w_scale[n]; out_scale > 0 makes a SwiGLU epilogue store codes of value / out_scale.
 struct CodeScales {
     const float* w_scale = nullptr;   // [N] device
     float a_scale = 1.0f;
     float out_scale = 0.0f;
-    bool order_only = false;          // 16-bit operands, no scales: the launch plan keeps the order of the sums (see plan_for)
 };
 hipError_t launch_linear(const void* a, const void* w, int32_t T, int32_t N, int32_t K, int32_t epilogue,
                          const void* residual, void* out, hipStream_t s, float* accum = nullptr, bool w_packed = false,
@@ -156,7 +159,6 @@ hipError_t launch_pack_weight(const void* w, int32_t N, int32_t K, void* out, hi
 struct KvFormat {
     bool fp8 = false;
     float k_scale = 1.0f, v_scale = 1.0f;
-    bool keep_order = false;   // a layer of a stack over quantised pools: sums and softmax in their reference order
 };
 hipError_t launch_qkv_rope_append(const BatchDev& b, const relserve_layer& L, const void* h, const void* w_qkv,
                                   void* q_out, void* k_pages, void* v_pages, hipStream_t s, float* accum = nullptr,

@@ -1,0 +1,60 @@
+"""The k ranges a projection's sums are cut into (CPU: host arithmetic of the built library).
+
+Which tiles split their k range fixes the order of every sum.  It depends on the sizes alone -- not on the operands' width,
+not on the tile shape that happens to be fastest -- and the sizes below pin it: a row that changes reorders sums that
+serving results were recorded with."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+WHOLE = None
+
+# (tokens, features, K in 2-byte units, fused q/k/v epilogue, SwiGLU): (tile rows, tile features, split tiles, ways), or WHOLE
+CUTS = {
+    (257, 2560, 4096, 1, 0): (192, 256, 20, 5), (257, 3584, 5120, 1, 0): (192, 256, 28, 5),
+    (300, 7168, 2560, 1, 0): (192, 256, 56, 2), (300, 7168, 5120, 1, 0): (192, 256, 56, 3),
+    (300, 8192, 3584, 0, 0): (192, 256, 64, 3), (300, 8192, 4096, 0, 0): (192, 256, 64, 3),
+    (384, 5120, 2560, 0, 0): (192, 256, 40, 3), (385, 3584, 5120, 1, 0): (128, 256, 56, 4),
+    (512, 5120, 6912, 0, 0): (192, 256, 60, 4), (512, 8192, 14336, 0, 0): (256, 256, 64, 4),
+    (640, 10240, 8192, 1, 0): (256, 256, 120, 2), (769, 3584, 5120, 1, 0): (192, 256, 70, 3),
+    (769, 5120, 27648, 0, 0): (256, 256, 80, 3), (1000, 57344, 4096, 0, 1): (256, 256, 128, 2),
+    (1152, 2560, 4096, 1, 0): (192, 256, 60, 3), (3001, 2560, 8192, 1, 0): (256, 256, 120, 2),
+    # the projections of a 13B layer at 640 tokens (128 decode rows and a 512-token chunk), 16-bit and 8-bit
+    (640, 15360, 5120, 1, 0): WHOLE, (640, 15360, 2560, 1, 0): WHOLE, (640, 27648, 5120, 0, 1): WHOLE, (640, 27648, 2560, 0, 1): WHOLE,
+    (384, 15360, 2560, 1, 0): WHOLE, (384, 55296, 5120, 0, 1): WHOLE, (512, 15360, 5120, 1, 0): WHOLE,
+    (769, 5120, 2560, 0, 0): WHOLE, (1152, 8192, 4096, 0, 0): WHOLE, (2048, 8192, 8192, 0, 0): WHOLE,
+    (2048, 57344, 8192, 0, 1): WHOLE, (2304, 7168, 2560, 1, 0): WHOLE, (3001, 3584, 2560, 1, 0): WHOLE,
+}
+
+
+def host_program(tmp_path, name):
+    """A program under tests/host, linked with the built library."""
+    from paper_2601_11546_amd import binding
+    exe, lib_dir = str(tmp_path / name), os.path.dirname(binding.LIB_PATH)
+    cmd = ["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+           "-I", os.path.join(ROOT, "paper_2601_11546_amd", "csrc"), os.path.join(ROOT, "tests", "host", f"{name}.cpp"),
+           "-o", exe, "-L", lib_dir, "-lrelserve", f"-Wl,-rpath,{lib_dir}", "-L", "/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return exe
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    exe = host_program(tmp_path_factory.mktemp("plans"), "gemm_plans")
+
+    def ask(rows):
+        text = "".join("%d %d %d %d %d\n" % row for row in rows)
+        r = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stderr
+        return [tuple(map(int, line.split())) for line in r.stdout.splitlines()]
+    return ask
+
+
+def test_cuts_are_pinned(plans):
+    rows = list(CUTS)
+    for row, got in zip(rows, plans(rows)):
+        want = CUTS[row]
+        assert (got[2:] == (0, 1)) if want is WHOLE else (got == want), (row, got, want)

@@ -58,3 +58,64 @@ def test_one_token_tile_of_192_or_256_rows(rs, oracle, T, packed):
         rs.relserve_layer_step(layer, pb, wd, xd, y, dev_bf16(kp), dev_bf16(vp), ws)
         want = oracle.layer_step(shape, b, weights, x, kp, vp).y_f32
         assert_close(host_f32(y), want, f"step T={T}")     # the whole step's bar
+
+
+@pytest.mark.parametrize("w8a8", [False, True], ids=["bf16", "codes"])
+@pytest.mark.parametrize("T", [1, 300])
+def test_whole_tiles_of_any_shape_give_the_same_bits(rs, T, w8a8):
+    """The tile shape of a projection that splits nothing is a matter of time alone: one running sum over k each."""
+    N, K = 1168, 640
+    g = torch.Generator(device="cuda").manual_seed(T)
+    if w8a8:
+        def codes(*s):
+            return torch.randint(0, 120, s, generator=g, device="cuda", dtype=torch.uint8) | (torch.randint(0, 2, s, generator=g, device="cuda", dtype=torch.uint8) << 7)
+        a, w, sw = codes(T, K), codes(N, K), torch.rand(N, generator=g, device="cuda") * 1e-3
+        run = lambda epi, res, out: rs.relserve_linear_w8a8(a, w, sw, 0.03, epi, res, out)
+    else:
+        a = torch.randn(T, K, generator=g, device="cuda").bfloat16()
+        w = (torch.randn(N, K, generator=g, device="cuda") * 0.05).bfloat16()
+        run = lambda epi, res, out: rs.relserve_linear(a, w, epi, res, out)
+    rb, rf = torch.randn(T, N, generator=g, device="cuda").bfloat16(), torch.randn(T, N, generator=g, device="cuda")
+    for epi, res, cols, dtype in ((0, None, N, torch.bfloat16), (1, rb, N, torch.float32), (2, rf, N, torch.bfloat16), (3, None, N // 2, torch.bfloat16)):
+        outs = []
+        for tile in (-1, 0, 1, 2, 3, 4):
+            out = torch.empty(T, cols, dtype=dtype, device="cuda")
+            rs.relserve_debug_force_gemm_plan(tile, 0)
+            try:
+                run(epi, res, out)
+                torch.cuda.synchronize()
+            finally:
+                rs.relserve_debug_force_gemm_plan(-1, 0)
+            outs.append(out)
+        for tile, out in enumerate(outs[1:]):
+            assert torch.equal(out, outs[0]), (epi, tile)
+
+
+def test_iteration_of_640_tokens_keeps_its_sums_whole(rs):
+    """The q/k/v projection of a 13B layer at T = 640 (128 decode rows and a 512-token chunk) fills its rounds well enough to
+    split nothing: the appended keys and values carry the bits of whole tiles, as its gate/up projection's sums do."""
+    shape = W.LLAMA_13B
+    b = W.build_batch(shape, [512] + [1] * 128, [512] + [40] * 128, seed=1)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    randn = lambda *s, std=0.02: torch.empty(*s, dtype=torch.float32, device="cuda").normal_(0, std, generator=g).bfloat16()
+    H, I = shape.hidden, shape.mlp_dim
+    wd = {"w_in_norm": randn(H, std=1.0), "w_qkv": randn(shape.qkv_dim, H), "w_o": randn(H, shape.q_dim), "w_post_norm": randn(H, std=1.0),
+          "w_gate_up": randn(2 * I, H), "w_down": randn(H, I)}
+    x = randn(b.T, H, std=1.0)
+    pool = (b.num_pages, shape.page_size, shape.n_kv_heads, shape.head_dim)
+    cached = randn(*pool, std=1.0), randn(*pool, std=1.0)
+    layer = rs.relserve_layer_create(shape)
+    pb = rs.relserve_batch_prepare(layer, b)
+    ws = torch.empty(rs.relserve_workspace_bytes(layer, b.T), dtype=torch.uint8, device="cuda")
+    pools = []
+    for tile in (-1, 0, 1, 2):
+        k, v, y = cached[0].clone(), cached[1].clone(), torch.empty_like(x)
+        rs.relserve_debug_force_gemm_plan(tile, 0)
+        try:
+            rs.relserve_layer_step(layer, pb, wd, x, y, k, v, ws)
+            torch.cuda.synchronize()
+        finally:
+            rs.relserve_debug_force_gemm_plan(-1, 0)
+        pools.append((k, v))
+    for tile, (k, v) in enumerate(pools[1:]):
+        assert torch.equal(k, pools[0][0]) and torch.equal(v, pools[0][1]), tile
