@@ -57,24 +57,25 @@ Workspace carve(const relserve_layer& L, int64_t T, void* base) {
 }
 
 // Cut of a batch of decode rows (see expand_batch): per shared prefix the number and length of its chunks, and the length
-// of the chunks of own keys (0 = uncut).
+// of the chunks of own keys.
 struct SlotPlan {
     bool use = false;
     std::vector<int32_t> prefix_chunks, prefix_len;
     int32_t chunk_len = 0;
 };
 
+// rows_len: the chunk length of the same rows without slots (0 = uncut, -1 = no row is long enough to cut).
 template <typename OwnKeys, typename ChunksOf>
 SlotPlan plan_slots(const relserve_layer_config& cfg, const relserve_batch_desc& d, const std::vector<uint8_t>& joint,
-                    OwnKeys own_keys, ChunksOf chunks_of) {
+                    OwnKeys own_keys, ChunksOf chunks_of, int32_t rows_len) {
     SlotPlan plan;
     const int32_t B = d.num_reqs;
     int64_t own_total = 0;
     for (int32_t r = 0; r < B; ++r) own_total += own_keys(r);
-    // A prefix chunk should not outlast the own keys: these stream at about 6 TB/s behind 8 us of latency, a block of 64
-    // prefix keys takes a workgroup about 2.5 us.
-    const double own_us = 8.0 + (double)own_total * cfg.n_kv_heads * cfg.head_dim * 4.0 / 6.0e6;
-    const int32_t blocks_max = std::max(2, (int32_t)(own_us / 2.5));
+    const double stream_us = (double)own_total * cfg.n_kv_heads * cfg.head_dim * 4.0 / 6.0e6;   // the own keys at about 6 TB/s
+    // A prefix chunk should not outlast the own keys (these start behind 8 us of latency): a block of 64 prefix keys takes a
+    // workgroup about 2.5 us.
+    const int32_t blocks_max = (int32_t)std::min(1e6, std::max(2.0, (8.0 + stream_us) / 2.5));
     plan.prefix_chunks.assign(d.num_prefixes, 0);
     plan.prefix_len.assign(d.num_prefixes, 0);
     bool any = false;
@@ -85,34 +86,35 @@ SlotPlan plan_slots(const relserve_layer_config& cfg, const relserve_batch_desc&
         plan.prefix_len[p] = (blocks + n - 1) / n * 64;
         plan.prefix_chunks[p] = (d.prefix_len[p] + plan.prefix_len[p] - 1) / plan.prefix_len[p];
     }
-    // Own keys: the smallest chunk whose waves stay within two rounds (256 CUs x 8 resident waves each) and whose states
-    // fit the slots; a batch with more waves than that balances by itself.
+    // Nor should an item of own keys: beside other rows a wave walks one in about 0.055 us, and an item is up to a chunk and a
+    // half.  So the longest chunk of 64 .. 512 keys that takes no longer than the stream, whatever the batch: one long row
+    // among short ones is cut as well.  13B layer behind a template of 512 (without slots / now): 100 rows of 60 keys and one
+    // of 3000 53 / 37 us, of 8000 73 / 55; 60 rows, ten of them of 8000 285 / 268; 60 rows of 1000 206 / 195; 4 of 1000 47 / 22.
+    const double ideal = std::min(512.0, stream_us / 0.08);
+    int32_t len = 64;
+    while (2 * len <= ideal) len *= 2;
+    // Two rounds of waves (256 CUs x 8 resident waves) with much to read: the rows balance by themselves, and a kernel with the
+    // tiled items in it holds fewer waves of them than one without (200 rows of 1000: 626 us without slots, 647 with).
+    if ((int64_t)B * cfg.n_kv_heads >= 2 * 2048 && stream_us > 200.0) return plan;
+    // Without a template slots are only for rows that the workspace's own (2 T) cannot cut about as finely: 4 rows of 1000
+    // 33 / 19 us, 2 of 8000 437 / 65; but 24 rows with two of 1500 17 / 21.
+    if (!any && (rows_len < 0 || (rows_len > 0 && rows_len < 2 * ideal))) return plan;
     const int64_t cap = scratch_slot_cap(cfg.n_q_heads, cfg.head_dim);
-    auto slots_at = [&](int32_t len, int64_t& items, bool& cut) {
+    for (; len <= 1024; len *= 2) {
         int64_t slots = 0;
-        items = 0, cut = false;
+        bool cut = false;
         for (int32_t r = 0; r < B; ++r) {
             const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
             const int32_t n = chunks_of(own_keys(r), len);
             const int32_t parts = n + (pid >= 0 && joint[pid] ? plan.prefix_chunks[pid] : 0);
             if (parts > 1) slots += parts;
-            items += n;
             cut |= n > 1;
         }
-        return slots;
-    };
-    int64_t items = 0;
-    bool cut = false;
-    for (int32_t len = 64; len <= 1024; len *= 2) {
-        const int64_t slots = slots_at(len, items, cut);
-        if (!cut) break;
-        if (slots <= cap && items * cfg.n_kv_heads <= 2 * 2048) {
-            plan.chunk_len = len;
-            break;
-        }
+        if (slots > cap) continue;
+        plan.chunk_len = len;
+        plan.use = any || cut;
+        break;
     }
-    const int64_t slots = slots_at(plan.chunk_len, items, cut);
-    plan.use = slots <= cap && (any || cut);
     return plan;
 }
 
@@ -275,8 +277,29 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         // Attention of a 13B layer, template of 512: 4 rows 13.5 + 11.8 us (prefix pass, own keys) -> 8.7 + 4.5 (launch,
         // merge), 24 rows 14.4 + 14.2 -> 13.9 + 4.7; 70B shape, 256 rows, templates of 768: 26.4 + 76.2 + 5.1 -> 82.0 + 6.5.
         // With prefill rows in the batch the partial states are the larger part of the traffic and the passes stay apart.
+        // Without slots, decode rows with many own keys are cut into chunks too (one wave item each, merged afterwards), so that
+        // one long context does not set the kernel's duration and the waves come in several even rounds.  The chunk length is
+        // the smallest of 128 .. 1024 keys whose chunks fit the partial-state slots of the workspace.
+        // (with two rounds of waves or more -- 256 CUs x 8 resident waves each -- the rows balance by themselves: cutting
+        // the 128 rows x 40 heads of 1024 keys of a 13B decode batch in two left its kernel at 6.5 TB/s and added the merge)
+        auto rows_chunk_len = [&]() -> int32_t {   // 0 = uncut, -1 = uncut because no row is longer than a chunk and a half
+            if ((int64_t)hb.n_decode * cfg.n_kv_heads >= 2 * 2048) return 0;
+            for (int32_t len = 128; len <= 1024; len *= 2) {
+                int64_t slots = 0;
+                bool any = false;
+                for (int32_t r = 0; r < B; ++r)
+                    if (d.q_start[r + 1] - d.q_start[r] == 1) {
+                        const int32_t n = chunks_of(own_keys(r), len);
+                        if (n > 1) slots += n, any = true;
+                    }
+                if (!any) return len == 128 ? -1 : 0;   // nothing to cut at any larger length
+                if (slots <= split_slot_cap(T)) return len;
+            }
+            return 0;
+        };
+        const int32_t rows_len = rows_chunk_len();
         SlotPlan plan;
-        if (slots_allowed && hb.n_prefill == 0 && T > 0 && T <= SKINNY_MAX_T) plan = plan_slots(cfg, d, joint, own_keys, chunks_of);
+        if (slots_allowed && hb.n_prefill == 0 && T > 0 && T <= SKINNY_MAX_T) plan = plan_slots(cfg, d, joint, own_keys, chunks_of, rows_len);
 
         std::vector<int32_t> row_slot;      // per request: its first slot (slot plan only)
         if (plan.use) {
@@ -319,26 +342,7 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
                     il.items_prefix.push_back(it);
                 }
         }
-        // Decode rows with many own keys are cut into chunks (one wave item each, merged afterwards), so that one long
-        // context does not set the kernel's duration and the waves come in several even rounds.  The chunk length is
-        // the smallest of 128 .. 1024 keys whose chunks fit the partial-state slots of the workspace.
-        int32_t chunk_len = plan.use ? plan.chunk_len : 0;   // 0 = no row is cut
-        // (with two rounds of waves or more -- 256 CUs x 8 resident waves each -- the rows balance by themselves: cutting
-        // the 128 rows x 40 heads of 1024 keys of a 13B decode batch in two left its kernel at 6.5 TB/s and added the merge)
-        if (!plan.use && (int64_t)hb.n_decode * cfg.n_kv_heads < 2 * 2048) {
-            const int64_t cap = split_slot_cap(T);
-            for (int32_t len = 128; len <= 1024 && chunk_len == 0; len *= 2) {
-                int64_t slots = 0;
-                bool any = false;
-                for (int32_t r = 0; r < B; ++r)
-                    if (d.q_start[r + 1] - d.q_start[r] == 1) {
-                        const int32_t n = chunks_of(own_keys(r), len);
-                        if (n > 1) slots += n, any = true;
-                    }
-                if (!any) break;               // no row is longer than a chunk and a half: nothing to cut at any larger length
-                if (slots <= cap) chunk_len = len;
-            }
-        }
+        const int32_t chunk_len = plan.use ? plan.chunk_len : std::max(0, rows_len);   // 0 = no row is cut
         int32_t next_slot = 0;
         for (int32_t r = 0; r < B; ++r) {
             const int32_t q_len = d.q_start[r + 1] - d.q_start[r];

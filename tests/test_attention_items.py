@@ -1,0 +1,53 @@
+"""How the attention of a decode batch is cut into items (CPU: host arithmetic of the built library).  The program checks for
+every batch that the items cover each row's keys exactly once and that every slot is written once, in range and merged."""
+import numpy as np
+import pytest
+
+from paper_2601_11546_amd import workloads as W
+from tests import host_program
+
+
+@pytest.fixture(scope="module")
+def cut(tmp_path_factory):
+    exe = host_program.build(tmp_path_factory.mktemp("items"), "attention_items")
+
+    def ask(shape, own, prefix=0, members=None, page=16):
+        head = (shape.n_q_heads, shape.n_kv_heads, shape.head_dim, page, len(own), prefix, len(own) if members is None else members)
+        return host_program.run(exe, " ".join(map(str, (*head, *own))) + "\n")[0]
+    return ask
+
+
+# rows of 60 own keys among which `n_long` have `long` of them, behind a template
+@pytest.mark.parametrize("shape,rows,n_long,long,prefix", [
+    (W.LLAMA_13B, 60, 10, 8000, 512), (W.LLAMA_13B, 100, 1, 8000, 512), (W.LLAMA_13B, 100, 1, 1500, 512), (W.LLAMA_13B, 200, 2, 8000, 512),
+    (W.LLAMA_13B, 60, 60, 1000, 512), (W.LLAMA_13B, 2, 2, 8000, 512), (W.LLAMA_70B, 250, 3, 8000, 768), (W.LLAMA_70B, 250, 100, 3000, 768),
+    (W.QWEN_32B_TP2, 200, 5, 4000, 256), (W.LLAMA_70B_TP4, 128, 128, 3000, 256), (W.LLAMA_13B, 200, 2, 8000, 0), (W.LLAMA_13B, 100, 1, 3000, 0),
+])
+def test_long_rows_are_cut(cut, shape, rows, n_long, long, prefix):
+    """No wave walks more than a chunk and a half of the longest chunk length (512 keys), whatever the rest of the batch."""
+    own = np.full(rows, 60)
+    own[np.random.default_rng(1).permutation(rows)[:n_long]] = long
+    slots, longest, *_ = cut(shape, own, prefix)
+    assert longest < 768, (slots, longest)
+
+
+def test_small_batches_behind_a_template_are_cut_finely(cut):
+    assert cut(W.LLAMA_13B, [136, 100, 64, 31], 512)[1] <= 96             # chunks of 64 keys
+    slots, longest, prefix_item, *_ = cut(W.LLAMA_13B, [83] * 24, 512)
+    assert slots > 0 and longest < 96 and prefix_item < 512
+
+
+def test_batches_that_keep_their_rows_in_sequence(cut):
+    """Many waves with much to read balance by themselves; without a template slots are for rows nothing else cuts as finely."""
+    for own, prefix in (([1024] * 128, 0), ([1000] * 200, 512), ([400] * 256, 512), ([1500, 1500] + [60] * 22, 0), ([100] * 4, 0)):
+        assert cut(W.LLAMA_13B, own, prefix)[0] == 0, (len(own), own[0], prefix)
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_random_batches_are_covered(cut, seed):
+    rng = np.random.default_rng(seed)
+    shape = [W.TINY, W.TINY_GQA, W.TINY_G5, W.LLAMA_13B, W.LLAMA_70B, W.QWEN_32B_TP2][seed % 6]
+    rows = int(rng.integers(1, 257))
+    own = np.exp(rng.uniform(0, np.log(9000 if seed % 3 else 300), rows)).astype(int) + 1
+    page = int(rng.choice([8, 16, 64, 256]))
+    cut(shape, own, int(rng.integers(0, 4000)) // page * page, int(rng.integers(1, rows + 1)), page)

@@ -3,12 +3,10 @@
 Which tiles split their k range fixes the order of every sum.  It depends on the sizes alone -- not on the operands' width,
 not on the tile shape that happens to be fastest -- and the sizes below pin it: a row that changes reorders sums that
 serving results were recorded with."""
-import os
-import subprocess
-
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+from tests import host_program
+
 WHOLE = None
 
 # (tokens, features, K in 2-byte units, fused q/k/v epilogue, SwiGLU): (tile rows, tile features, split tiles, ways), or WHOLE
@@ -29,28 +27,10 @@ CUTS = {
 }
 
 
-def host_program(tmp_path, name):
-    """A program under tests/host, linked with the built library."""
-    from paper_2601_11546_amd import binding
-    exe, lib_dir = str(tmp_path / name), os.path.dirname(binding.LIB_PATH)
-    cmd = ["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
-           "-I", os.path.join(ROOT, "paper_2601_11546_amd", "csrc"), os.path.join(ROOT, "tests", "host", f"{name}.cpp"),
-           "-o", exe, "-L", lib_dir, "-lrelserve", f"-Wl,-rpath,{lib_dir}", "-L", "/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr[-3000:]
-    return exe
-
-
 @pytest.fixture(scope="module")
 def plans(tmp_path_factory):
-    exe = host_program(tmp_path_factory.mktemp("plans"), "gemm_plans")
-
-    def ask(rows):
-        text = "".join("%d %d %d %d %d\n" % row for row in rows)
-        r = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60)
-        assert r.returncode == 0, r.stderr
-        return [tuple(map(int, line.split())) for line in r.stdout.splitlines()]
-    return ask
+    exe = host_program.build(tmp_path_factory.mktemp("plans"), "gemm_plans")
+    return lambda rows: host_program.run(exe, "".join("%d %d %d %d %d\n" % row for row in rows))
 
 
 def test_cuts_are_pinned(plans):
