@@ -716,7 +716,8 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(AttnArgs p) {
         const float2 ml = *reinterpret_cast<const float2*>(p.part_ml + prow * 2);
         const float4 v = *reinterpret_cast<const float4*>(p.part_o + prow * D + d0);
         const float m_new = fmaxf(M, ml.x);
-        const float a = __builtin_amdgcn_exp2f(M - m_new), w = __builtin_amdgcn_exp2f(ml.x - m_new);   // a = 0 at the first chunk
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;   // no key with a finite score so far
+        const float a = __builtin_amdgcn_exp2f(M - m_use), w = __builtin_amdgcn_exp2f(ml.x - m_use);   // a = 0 at the first chunk
         M = m_new;
         L = L * a + w * ml.y;
         o.x = o.x * a + w * v.x; o.y = o.y * a + w * v.y; o.z = o.z * a + w * v.z; o.w = o.w * a + w * v.w;

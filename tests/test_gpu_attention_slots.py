@@ -65,3 +65,26 @@ def test_batch_sizes(rs, oracle, n):
     own[0] = 900
     b = W.build_batch(shape, [1] * n, 272 + own, [0] * n, [272], seed=6)
     _check(rs, oracle, shape, b, np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 12)])))
+
+
+@pytest.mark.parametrize("members", [6, 1], ids=["template", "own"])
+def test_parts_without_a_finite_score(rs, oracle, members):
+    """Keys whose scores are -inf have no weight: a row whose first part holds nothing else takes its value from the rest."""
+    shape = W.TINY_GQA
+    b = W.build_batch(shape, [1] * members, [1040 + 100] * members, [0] * members, [1040], seed=9)
+    rng = np.random.default_rng(3)
+    q = np.abs(rng.standard_normal((b.T, shape.n_q_heads, shape.head_dim), dtype=np.float32))
+    q_bits = W.f32_to_bf16_bits(q.reshape(b.T, -1))
+    kp, vp = W.make_cache(shape, b.num_pages, 11)
+    for page in np.asarray(b.block_table).reshape(members, -1)[0, :192 // shape.page_size]:   # the first 192 keys, shared by all rows
+        kp[page, :, :, 0] = 0xff80                                                            # -inf
+    layer = rs.relserve_layer_create(shape)
+    pb = rs.relserve_batch_prepare(layer, b)
+    ws = torch.full((rs.relserve_workspace_bytes(layer, b.T),), 0xff, dtype=torch.uint8, device="cuda")
+    out = torch.zeros(b.T, shape.q_dim, dtype=torch.bfloat16, device="cuda")
+    rs.relserve_attention(layer, pb, dev_bf16(q_bits), shape.q_dim, dev_bf16(kp), dev_bf16(vp), out, ws)
+    got, qf = host_f32(out), W.bf16_bits_to_f32(q_bits)
+    for t in range(members):
+        want = oracle.attention_token(shape, b, t, int(b.past[t]), qf[t].reshape(shape.n_q_heads, -1), kp, vp)
+        assert np.isfinite(want).all()
+        assert_close(got[t], want.reshape(-1), f"row {t}", max_abs=2e-2, rel_l2=1e-2)   # the attention stage's bar
