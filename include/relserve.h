@@ -260,7 +260,8 @@ int32_t relserve_model_workspace_bytes(const relserve_layer* layer, int32_t max_
 
 /* One model step over a prepared batch: x = embedding[token_ids] (ids outside
  * [0, vocab) are clamped, never dereferenced out of range), n_layers layer
- * steps with the stream rounded to bf16 between layers, final RMSNorm and the
+ * steps with the stream rounded to bf16 between layers (bit for bit those of
+ * relserve_layer_step on the same pools, whatever the depth), final RMSNorm and the
  * output layer on the last query token of every request.  token_ids: device
  * int32 [T]; logits: device fp32 [num_reqs, vocab]. */
 int32_t relserve_model_step(const relserve_layer* layer, const relserve_batch* batch,

@@ -125,6 +125,14 @@ PartialState partial_state(const relserve_layer& L, const BatchDev& b, const Wor
     return {w.accum, w.accum + (int64_t)b.n_scratch_slots * L.q_dim};
 }
 
+// The cut of the attention a step over these pools runs.  A 16-bit output that rounds the other way moves codes of the keys and
+// values the next layer appends to its quantised pool, and those move the rest of the stack (3 % of the codes of a third 13B
+// layer, 2e-2 of the logits after four), so over quantised pools every entry point takes the cut without slots, whose results
+// stacks were recorded with.
+const BatchDev& attention_batch(const relserve_batch& b, const relserve_kv_cache& cache) {
+    return cache.dtype == RELSERVE_KV_FP8 ? b.dev_no_slots : b.dev;
+}
+
 bool is_pow2(int32_t v) { return v > 0 && (v & (v - 1)) == 0; }
 
 // Workspace of relserve_layer_step_static: a fixed array in device memory, one copy per GPU the library runs on,
@@ -402,7 +410,7 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
     };
     if (build_items) {
         build(true, hb.items);
-        if (hb.items.n_scratch_slots > 0) build(false, hb.in_sequence);
+        if (hb.items.n_scratch_slots > 0) build(false, hb.no_slots);
     }
     *out = std::move(hb);
     return RELSERVE_OK;
@@ -535,7 +543,7 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
         o.merge = reserve(sizeof(MergeItem) * il.merge_items.size());
         return o;
     };
-    const ListOffsets o_items = reserve_lists(hb.items), o_seq = reserve_lists(hb.in_sequence);
+    const ListOffsets o_items = reserve_lists(hb.items), o_seq = reserve_lists(hb.no_slots);
     const size_t o_freq = reserve(sizeof(float) * half);
     const size_t host_bytes = off;
     const size_t o_cs = reserve(sizeof(float2) * (size_t)T * half);
@@ -560,7 +568,7 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
         put(o.merge, il.merge_items.data(), sizeof(MergeItem) * il.merge_items.size());
     };
     put_lists(o_items, hb.items);
-    put_lists(o_seq, hb.in_sequence);
+    put_lists(o_seq, hb.no_slots);
     put(o_freq, L->inv_freq.data(), sizeof(float) * half);
 
     relserve_batch* b = new (std::nothrow) relserve_batch();
@@ -595,8 +603,8 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
         v.n_scratch_slots = il.n_scratch_slots;
     };
     view_lists(dv, o_items, hb.items);
-    b->dev_in_sequence = dv;
-    if (dv.n_scratch_slots > 0) view_lists(b->dev_in_sequence, o_seq, hb.in_sequence);
+    b->dev_no_slots = dv;
+    if (dv.n_scratch_slots > 0) view_lists(b->dev_no_slots, o_seq, hb.no_slots);
     b->info = relserve_batch_info{T, B, hb.n_decode, hb.n_prefill, hb.n_groups,
                                   dv.n_items_prefix + dv.n_items_tile + dv.n_items_split};
 
@@ -735,17 +743,16 @@ int32_t relserve_attention(const relserve_layer* L, const relserve_batch* b, con
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kAlign)) return RELSERVE_ERR_WORKSPACE;
     Workspace w = carve(*L, b->dev.T, workspace);
     if (w.total > workspace_bytes) return RELSERVE_ERR_WORKSPACE;
-    const PartialState part = partial_state(*L, b->dev, w);
-    hipError_t e = launch_attention(b->dev, *L, q, q_pitch, cache.k_pages, cache.v_pages, out, part.o,
+    const BatchDev& batch = attention_batch(*b, cache);
+    const PartialState part = partial_state(*L, batch, w);
+    hipError_t e = launch_attention(batch, *L, q, q_pitch, cache.k_pages, cache.v_pages, out, part.o,
                                     part.ml, static_cast<hipStream_t>(stream), nullptr, kv_format(cache));
     return e == hipSuccess ? RELSERVE_OK : RELSERVE_ERR_HIP;
 }
 
-// keep_order: this is a layer of a stack over quantised pools.  A 16-bit activation that rounds the other way in one layer
-// moves codes of the next layer's keys and values, so each row's softmax keeps its order there.
-static int32_t layer_step(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt, const void* x,
-                          void* y, relserve_kv_cache cache, void* workspace, size_t workspace_bytes, void* stream,
-                          bool keep_order) {
+int32_t relserve_layer_step(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt,
+                            const void* x, void* y, relserve_kv_cache cache, void* workspace,
+                            size_t workspace_bytes, void* stream) {
     drop_stale_hip_error();
     if (int32_t rc = check_pair(L, b)) return rc;
     if (!wt) return RELSERVE_ERR_NULL_POINTER;
@@ -773,7 +780,7 @@ static int32_t layer_step(const relserve_layer* L, const relserve_batch* b, cons
     // the GEMMs split K across workgroups (whole skinny problems, narrow outputs at mid-size T, or the
     // incomplete last round of tiles) through an fp32 scratch that they write before they read
     float* accum = w.accum;
-    const BatchDev& batch = keep_order ? b->dev_in_sequence : b->dev;
+    const BatchDev& batch = attention_batch(*b, cache);
     const PartialState part = partial_state(*L, batch, w);
     const KvFormat kv = kv_format(cache);
     run(S_NORM1, [&] { return launch_rmsnorm(x, false, wt->w_in_norm, c.rms_eps, T, c.hidden, w.h, s); });
@@ -789,12 +796,6 @@ static int32_t layer_step(const relserve_layer* L, const relserve_batch* b, cons
     });
     run(S_DOWN, [&] { return launch_linear(w.act, wt->w_down, T, c.hidden, c.mlp_dim, 2, w.x1, y, s, accum, packed); });
     return e == hipSuccess ? RELSERVE_OK : RELSERVE_ERR_HIP;
-}
-
-int32_t relserve_layer_step(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt,
-                            const void* x, void* y, relserve_kv_cache cache, void* workspace,
-                            size_t workspace_bytes, void* stream) {
-    return layer_step(L, b, wt, x, y, cache, workspace, workspace_bytes, stream, false);
 }
 
 int32_t relserve_layer_step_w8a8(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights_w8a8* wt,
@@ -829,8 +830,8 @@ int32_t relserve_layer_step_w8a8(const relserve_layer* L, const relserve_batch* 
     };
     float* accum = w.accum;
     // Codes amplify: an attention output that rounds differently by 1e-3 moves about 2 % of W_o's inputs to the neighbouring
-    // code, and a wide layer's output by up to 7e-3.  The rows' keys are therefore taken in one running sequence here.
-    const BatchDev& batch = b->dev_in_sequence;
+    // code, and a wide layer's output by up to 7e-3.  The attention is therefore cut as it is over quantised pools.
+    const BatchDev& batch = b->dev_no_slots;
     const PartialState part = partial_state(*L, batch, w);
     const CodeScales qkv{wt->s_qkv, wt->a_qkv, 0.0f}, o{wt->s_o, wt->a_o, 0.0f}, gu{wt->s_gate_up, wt->a_gate_up, wt->a_down},
         down{wt->s_down, wt->a_down, 0.0f};
@@ -944,8 +945,7 @@ int32_t model_step(const relserve_layer* L, const relserve_batch* b, const relse
     if (launch_embedding(token_ids, m->embedding, m->vocab, H, T, x, s) != hipSuccess) return RELSERVE_ERR_HIP;
     for (int32_t l = 0; l < m->n_layers; ++l) {   // the residual stream stays in x, rounded to bf16 between layers
         const int32_t rc = q8 ? relserve_layer_step_w8a8(L, b, &q8[l], x, x, m->caches[l], workspace, layer_ws, stream)
-                              : layer_step(L, b, &m->layers[l], x, x, m->caches[l], workspace, layer_ws, stream,
-                                           m->n_layers > 1 && m->caches[l].dtype == RELSERVE_KV_FP8);
+                              : relserve_layer_step(L, b, &m->layers[l], x, x, m->caches[l], workspace, layer_ws, stream);
         if (rc) return rc;
     }
     if (launch_rmsnorm(x, false, m->w_final_norm, L->cfg.rms_eps, B, H, h_last, s, b->dev.last_tok) != hipSuccess)

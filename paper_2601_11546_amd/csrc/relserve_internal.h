@@ -89,7 +89,7 @@ struct relserve_layer {
 struct relserve_batch {
     relserve_layer_config cfg;  // shape it was prepared for
     relserve::BatchDev dev;
-    relserve::BatchDev dev_in_sequence;   // the same batch without slots (see HostBatch); equals dev where dev has none
+    relserve::BatchDev dev_no_slots;      // the same batch without slots (see HostBatch); equals dev where dev has none
     void* blob = nullptr;  // the one device allocation
     relserve_batch_info info;
 };
@@ -108,8 +108,9 @@ struct ItemLists {
 struct HostBatch {
     int32_t T = 0;
     std::vector<int32_t> tok_req, tok_pos, tok_slot;
-    ItemLists items;         // what a step runs
-    ItemLists in_sequence;   // only where `items` uses slots: the same work with every row's keys in one running sequence
+    ItemLists items;         // what a step on 16-bit operands and pools runs
+    ItemLists no_slots;      // only where `items` uses slots: the same work cut without them (prefix pass, then own keys; long
+                             // rows in chunks that the workspace's own slots hold)
     int32_t n_decode = 0, n_prefill = 0, n_groups = 0;
 };
 int32_t expand_batch(const relserve_layer_config& cfg, const relserve_batch_desc& d, bool build_items,

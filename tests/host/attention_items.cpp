@@ -93,7 +93,7 @@ int main() {
         }
         int own, pre, own2 = 0, pre2 = 0;
         if (!check(hb.items, cfg, ctx, own, pre)) return 1;
-        if (hb.items.n_scratch_slots > 0 && !check(hb.in_sequence, cfg, ctx, own2, pre2)) return 1;
+        if (hb.items.n_scratch_slots > 0 && !check(hb.no_slots, cfg, ctx, own2, pre2)) return 1;
         std::printf("%d %d %d %d %d\n", hb.items.n_scratch_slots, own, pre, own2, pre2);
     }
     return 0;
