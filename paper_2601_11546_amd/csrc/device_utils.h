@@ -51,6 +51,16 @@ __device__ __forceinline__ float silu_mul(float gate, float up) {
     return gate * up * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(gate * -1.4426950408889634f));
 }
 
+// Rotary embedding of four pairs (lo, hi) by the angles of c01, c23 = (cos, sin) twice each, from fp32 sums.  Which product is
+// rounded is fixed here, not left to the compiler (which chose differently from kernel to kernel, and within one): the same
+// sums give the same bits on every path.
+__device__ __forceinline__ void rotate4(const float4& lo, const float4& hi, const float4& c01, const float4& c23, float4& l, float4& h) {
+    l.x = __builtin_fmaf(lo.x, c01.x, -(hi.x * c01.y)); h.x = __builtin_fmaf(lo.x, c01.y, hi.x * c01.x);
+    l.y = __builtin_fmaf(lo.y, c01.z, -(hi.y * c01.w)); h.y = __builtin_fmaf(lo.y, c01.w, hi.y * c01.z);
+    l.z = __builtin_fmaf(lo.z, c23.x, -(hi.z * c23.y)); h.z = __builtin_fmaf(lo.z, c23.y, hi.z * c23.x);
+    l.w = __builtin_fmaf(lo.w, c23.z, -(hi.w * c23.w)); h.w = __builtin_fmaf(lo.w, c23.w, hi.w * c23.z);
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

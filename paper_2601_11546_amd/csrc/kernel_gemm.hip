@@ -229,25 +229,18 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * W
                 const int64_t slot = slot_;
                 const int kv_dim = p.n_kv * DH, i = n_lo - head * DH;
                 if (head < p.n_q + p.n_kv) {
-                    const float co[4] = {oa.x, oa.z, ob.x, ob.z}, si[4] = {oa.y, oa.w, ob.y, ob.w};
-                    const float av[4] = {lo.x, lo.y, lo.z, lo.w}, bv[4] = {hi.x, hi.y, hi.z, hi.w};
-                    float l4[4], h4[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        // which product is rounded is fixed here, not left to the compiler: the same bits whatever the tile
-                        l4[e] = __builtin_fmaf(av[e], co[e], -(bv[e] * si[e]));
-                        h4[e] = __builtin_fmaf(av[e], si[e], bv[e] * co[e]);
-                    }
+                    float4 rl, rh;
+                    rotate4(lo, hi, oa, ob, rl, rh);
                     if (p.kv_fp8 && head >= p.n_q) {   // quantised cache: one byte per element, quantised from fp32
                         uint8_t* dst8 = reinterpret_cast<uint8_t*>(p.k_pages) + slot * kv_dim + (head - p.n_q) * DH + i;
                         const float s = p.k_inv;
-                        *reinterpret_cast<uint32_t*>(dst8) = pack_fp8x4(l4[0] * s, l4[1] * s, l4[2] * s, l4[3] * s);
-                        *reinterpret_cast<uint32_t*>(dst8 + DH / 2) = pack_fp8x4(h4[0] * s, h4[1] * s, h4[2] * s, h4[3] * s);
+                        *reinterpret_cast<uint32_t*>(dst8) = pack_fp8x4(rl.x * s, rl.y * s, rl.z * s, rl.w * s);
+                        *reinterpret_cast<uint32_t*>(dst8 + DH / 2) = pack_fp8x4(rh.x * s, rh.y * s, rh.z * s, rh.w * s);
                     } else {
                         uint16_t* dst = (head < p.n_q ? static_cast<uint16_t*>(p.out) + (int64_t)t * (p.n_q * DH) + head * DH
                                                       : p.k_pages + slot * kv_dim + (head - p.n_q) * DH) + i;
-                        *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(l4[0], l4[1]), pack_bf16x2(l4[2], l4[3]));
-                        *reinterpret_cast<uint2*>(dst + DH / 2) = make_uint2(pack_bf16x2(h4[0], h4[1]), pack_bf16x2(h4[2], h4[3]));
+                        *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(rl.x, rl.y), pack_bf16x2(rl.z, rl.w));
+                        *reinterpret_cast<uint2*>(dst + DH / 2) = make_uint2(pack_bf16x2(rh.x, rh.y), pack_bf16x2(rh.z, rh.w));
                     }
                 } else {
                     const int64_t o = slot * kv_dim + (head - p.n_q - p.n_kv) * DH + i;
@@ -878,25 +871,19 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p) {
             const float4 hi = code_scale(slab_sum(row + head * 2 * HALF + HALF + i0, stride, p.n_splits), p, head * 2 * HALF + HALF + i0);
             const float2* cs = p.rope_cs + (int64_t)t * HALF + i0;
             const float4 c01 = *reinterpret_cast<const float4*>(cs), c23 = *reinterpret_cast<const float4*>(cs + 2);
-            const float a[4] = {lo.x, lo.y, lo.z, lo.w}, b[4] = {hi.x, hi.y, hi.z, hi.w};
-            const float co[4] = {c01.x, c01.z, c23.x, c23.z}, si[4] = {c01.y, c01.w, c23.y, c23.w};
-            float l2[4], h2[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                l2[j] = a[j] * co[j] - b[j] * si[j];
-                h2[j] = a[j] * si[j] + b[j] * co[j];
-            }
+            float4 rl, rh;
+            rotate4(lo, hi, c01, c23, rl, rh);
             if (p.kv_fp8 && head >= p.n_q) {
                 uint8_t* dst8 = reinterpret_cast<uint8_t*>(p.k_pages) + slot * kv_dim + (head - p.n_q) * 2 * HALF + i0;
                 const float s = p.k_inv;
-                *reinterpret_cast<uint32_t*>(dst8) = pack_fp8x4(l2[0] * s, l2[1] * s, l2[2] * s, l2[3] * s);
-                *reinterpret_cast<uint32_t*>(dst8 + HALF) = pack_fp8x4(h2[0] * s, h2[1] * s, h2[2] * s, h2[3] * s);
+                *reinterpret_cast<uint32_t*>(dst8) = pack_fp8x4(rl.x * s, rl.y * s, rl.z * s, rl.w * s);
+                *reinterpret_cast<uint32_t*>(dst8 + HALF) = pack_fp8x4(rh.x * s, rh.y * s, rh.z * s, rh.w * s);
                 return;
             }
             uint16_t* dst = head < p.n_q ? static_cast<uint16_t*>(p.out) + (int64_t)t * (p.n_q * 2 * HALF) + head * 2 * HALF
                                          : p.k_pages + slot * kv_dim + (head - p.n_q) * 2 * HALF;
-            *reinterpret_cast<uint2*>(dst + i0) = make_uint2(pack_bf16x2(l2[0], l2[1]), pack_bf16x2(l2[2], l2[3]));
-            *reinterpret_cast<uint2*>(dst + HALF + i0) = make_uint2(pack_bf16x2(h2[0], h2[1]), pack_bf16x2(h2[2], h2[3]));
+            *reinterpret_cast<uint2*>(dst + i0) = make_uint2(pack_bf16x2(rl.x, rl.y), pack_bf16x2(rl.z, rl.w));
+            *reinterpret_cast<uint2*>(dst + HALF + i0) = make_uint2(pack_bf16x2(rh.x, rh.y), pack_bf16x2(rh.z, rh.w));
         } else {
             const int c = (u - rot_units) * 4;
             const float4 v = code_scale(slab_sum(row + (p.n_q + p.n_kv) * 2 * HALF + c, stride, p.n_splits), p, (p.n_q + p.n_kv) * 2 * HALF + c);

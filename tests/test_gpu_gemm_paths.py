@@ -119,3 +119,36 @@ def test_iteration_of_640_tokens_keeps_its_sums_whole(rs):
         pools.append((k, v))
     for tile, (k, v) in enumerate(pools[1:]):
         assert torch.equal(k, pools[0][0]) and torch.equal(v, pools[0][1]), tile
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+def test_rotation_rounds_the_same_on_every_path(rs, d, fp8):
+    """Activations of +-1 and weights that are multiples of 1/64: every order of a sum is exact, so the appended keys and values of
+    a token differ between the paths (k split over workgroups, split tail, whole tiles) only if the rotation rounds differently."""
+    shape = W.LayerShape(4096, 2048 // d, 1024 // d, d, 512, 16, 1e-5, 10000.0)    # q/k/v at 300 tokens: 32 tiles split 4 ways
+    g = torch.Generator(device="cuda").manual_seed(d)
+    H, I = shape.hidden, shape.mlp_dim
+    ones = torch.ones(H, device="cuda", dtype=torch.bfloat16)
+    ints = lambda *s: (torch.randint(-4, 5, s, generator=g, device="cuda").float() / 64).bfloat16()
+    wd = {"w_in_norm": ones, "w_qkv": ints(shape.qkv_dim, H), "w_o": ints(H, shape.q_dim), "w_post_norm": ones, "w_gate_up": ints(2 * I, H),
+          "w_down": ints(H, I)}
+    x = (torch.randint(0, 2, (300, H), generator=g, device="cuda") * 2 - 1).to(torch.bfloat16)
+    layer = rs.relserve_layer_create(shape)
+    want = None
+    for T, tile in ((60, -1), (100, -1), (200, -1), (300, -1), (300, 0), (300, 1), (300, 2)):
+        b = W.build_batch(shape, [T], [T], seed=0)
+        b.block_table[:] = np.arange(b.block_table.size).reshape(b.block_table.shape)        # token t in slot t
+        pb = rs.relserve_batch_prepare(layer, b)
+        pool = lambda: torch.zeros(b.num_pages, 16, shape.n_kv_heads, d, device="cuda", dtype=torch.uint8 if fp8 else torch.bfloat16)
+        k, v = pool(), pool()
+        ws = torch.empty(rs.relserve_workspace_bytes(layer, T), dtype=torch.uint8, device="cuda")
+        rs.relserve_debug_force_gemm_plan(tile, 0)
+        try:
+            rs.relserve_layer_step(layer, pb, wd, x[:T], torch.empty_like(x[:T]), *((rs.QuantPool(k, 0.05), rs.QuantPool(v, 0.05)) if fp8 else (k, v)), ws)
+            torch.cuda.synchronize()
+        finally:
+            rs.relserve_debug_force_gemm_plan(-1, 0)
+        got = [p.view(torch.uint8).reshape(-1, shape.kv_dim * (1 if fp8 else 2))[:60] for p in (k, v)]
+        want = want or got
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (T, tile)
