@@ -684,8 +684,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // compiler orders the steps between hand-overs and the other resident workgroups fill the gaps;
     // only their hand-over step keeps the fixed order, with the whole refill in it.  Tiles of 6 and 8 products per wave run
     // alone on their CU and take the fixed order too: 13B layer, four projections, 250 -> 239 us at T = 256, 347 -> 329 at 400
-    // (q/k/v on 128 x 256 tiles 88 -> 77), but the SwiGLU kernel on that tile loses (122 -> 129) and keeps the compiler's.
-    constexpr bool FIXED = NM >= 12 || (NM >= 6 && !(EPI == EPI_SWIGLU && BM == 128));
+    // (q/k/v on 128 x 256 tiles 88 -> 77; on 8-bit operands W_down of the 32B shape at T = 1100 180 -> 173), but the SwiGLU
+    // kernel on that tile loses (122 -> 129) and keeps the compiler's, and so does the eight-wave 8-bit 256 x 256 tile, whose
+    // second wave per SIMD fills the gaps (13B at T = 7963: gate/up 892 fixed, 884 the compiler's; q/k/v 555, 551).
+    constexpr bool FIXED = NM >= 12 || (NM >= 6 && NW == 4 && !(EPI == EPI_SWIGLU && BM == 128));
     int cur = 0;  // stage being computed
     // One k iteration (one LDS stage).  refill_open: the refill begun at the previous hand-over is still being
     // issued; refill_next: this iteration's hand-over starts another one.
