@@ -446,3 +446,15 @@ def test_multi_step_flow_w8a8_matches_oracle(rs, oracle, name):
     for r in range(len(seq)):
         lo = flow.start[r]
         assert_close(ys_gpu[r][lo:], ys_ora[r][lo:], f"w8a8 flow request {r}")
+
+
+@pytest.mark.parametrize("T", [129, 160, 192, 193])
+@pytest.mark.parametrize("mlp", [640, 8320], ids=["split", "whole"])
+def test_layer_step_w8a8_one_token_tile(rs, oracle, T, mlp):
+    """129 .. 256 tokens run as one tile of 192 or 256 rows: k split over workgroups, and a gate/up projection wide enough to
+    run whole, on both weight layouts."""
+    shape = W.LayerShape(512, 4, 4, 128, mlp)
+    wl = W.Workload("one_tile", shape, W.build_batch(shape, [T - 5] + [1] * 5, [T - 5] + [9] * 5, seed=T), T)
+    weights = W.make_weights_w8a8(shape, wl.seed)
+    for packed in (False, True):   # the wide layer's own contribution is a fifth of its output: bounded as the full-size layers' is
+        _w8a8_step(rs, oracle, shape, wl, weights, packed=packed, eps=1e-3 if mlp > 640 else None)
