@@ -417,7 +417,9 @@ def measure_layer_step(rs, W, torch, args, wl, host_draws: bool, kv_fp8: bool = 
     stats = _stats(per_loop)
     ms_step = stats["median"]
 
-    kv_bytes = {"attn_own_keys": counts["kv_decode_own_bytes"] + counts["kv_prefill_own_bytes"],
+    # without a prefix pass of its own, the own-keys launch reads the shared templates too
+    own_bytes = counts["kv_decode_own_bytes"] + counts["kv_prefill_own_bytes"]
+    kv_bytes = {"attn_own_keys": own_bytes if "attn_prefix" in prof else counts["kv_unique_bytes"],
                 "attn_split": counts["kv_decode_own_bytes"], "attn_tile": counts["kv_prefill_own_bytes"]}
     kernels = {}
     for name, v in prof.items():
@@ -432,7 +434,7 @@ def measure_layer_step(rs, W, torch, args, wl, host_draws: bool, kv_fp8: bool = 
             k["kv_gbs"] = round(kv_bytes[name] / (avg_ms * 1e-3) / 1e9, 1)
             k["frac_hbm_peak"] = round(k["kv_gbs"] / PEAK_HBM_GBS, 4)
         kernels[name] = k
-    attn_ms = sum(kernels[n]["avg_ms"] for n in ("attn_prefix", "attn_own_keys", "attn_tile", "attn_split") if n in kernels)
+    attn_ms = sum(kernels[n]["avg_ms"] for n in ("attn_prefix", "attn_own_keys", "attn_tile", "attn_split", "attn_merge") if n in kernels)
     if attn_ms > 0:
         kernels["attention_all"] = {"avg_ms": round(attn_ms, 4),
                                     "tflops": round(counts["attn_flops"] / (attn_ms * 1e-3) / 1e12, 1),

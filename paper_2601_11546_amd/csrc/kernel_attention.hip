@@ -737,9 +737,9 @@ __global__ void __launch_bounds__(256, 2) attn_decode_kernel(AttnArgs p) {
     attn_decode_body<D, FP8>(p, p.items, p.n_items, blockIdx.x);
 }
 
-// Prefill rows (row-tiled items) and decode rows (wave items) over their own keys in ONE launch: the two
-// item lists are independent, each alone leaves part of the chip idle at its end, and both need the same
-// registers and LDS.  Workgroups [0, n_items n_kv) take the tiled items (the longer ones), the rest the
+// Row-tiled items (prefill rows over their own keys, or, where decode rows keep their parts in slots, chunks of the shared
+// prefixes) and wave items (decode rows over their own keys) in ONE launch: the two item lists are independent, each alone
+// leaves part of the chip idle at its end, and both need the same registers and LDS.  Workgroups [0, n_items n_kv) take the tiled items (the longer ones), the rest the
 // decode items, four per workgroup.
 template <int D, bool FP8>
 __global__ void __launch_bounds__(256, 2) attn_own_keys_kernel(AttnArgs p) {

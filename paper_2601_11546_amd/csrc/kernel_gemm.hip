@@ -123,7 +123,8 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
 // Epilogue shared by the GEMM kernels.  Register r of accumulator tile (tn, tm) holds feature
 // 32 tn + 8 (r / 4) + 4 g + r % 4 of the wave's feature range and token 32 tm + l32 of its token range.
 // TMX of the wave's BM / (32 WGM) rows of accumulator tiles are held in acc, starting at row tm_base (the GEMM kernels
-// hold all of them; the tail finish kernel one per workgroup, which lets several workgroups share a CU).
+// hold all of them; the tail finish kernel one per workgroup, which with its 64 KB of LDS lets two workgroups of four waves share
+// a CU; those of eight waves, 128 KB, have it alone).
 // SC: the sums are products of 8-bit codes and take the factor a_scale * w_scale[feature] as they are read.
 //
 // One accumulator row (32 tokens x the wave's features, fp32) at a time goes through a region of LDS that belongs to the
@@ -919,7 +920,7 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p) {
 }
 
 // Skinny path: T <= 256.  The weights are streamed once; to fill 256 CUs the k range of every
-// BM x BN tile (BM = 64 / 128 tokens, BN = 128 / 256 features) is split over several workgroups, each
+// BM x BN tile (64 / 128 / 192 / 256 tokens x 128 features; x 256 for split_rows) is split over several workgroups, each
 // storing its partial tile to its split's slab.  The LDS ring is as deep as 160 KB allow (one workgroup
 // per CU); all stages but the one being computed are in flight.
 template <int BM, int EPI, int D, int BN = 256, bool WNT = false>

@@ -25,7 +25,7 @@ struct AttnItem {
     int32_t tok_off;    // first entry of this item in the attn_tok list
     int32_t n_tok;      // query tokens of the item (rows = n_tok * heads per kv head)
     int32_t bt_req;     // request whose block-table row addresses the keys
-    int32_t key_begin;  // first key position (page aligned)
+    int32_t key_begin;  // first key position: a multiple of 64 in prefix items, a multiple of 32 past the first own key in decode items
     int32_t key_end;    // one past the last key position any row may see
     int32_t flags;
     int32_t pad0;       // decode items: the query token; prefix items with slots: where their rows' first slots are listed
