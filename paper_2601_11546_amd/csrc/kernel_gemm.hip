@@ -1131,15 +1131,17 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
 // layers).  So the cut depends on the sizes alone, for every kind of operand, and these constants are kept as they are: a
 // refit of them for 16-bit operands changed a next token in 129 (four 13B layers, 128 decode rows and a 512-token chunk).
 //
-// 2. The shape of whole tiles: any gives the same bits, so where nothing is split the fastest one runs (whole_tile).
-struct TileCand { int bm, bn, wg_per_cu; float eff_cut, eff, eff_swiglu; bool qkv; };   // qkv: usable by the fused q/k/v epilogue (128 features per wave)
+// 2. The shape of whole tiles: any gives the same bits, so where nothing is split the fastest one runs (whole_tile).  For the
+// SwiGLU projection that is the shape the cut's own model names: 0.0 % (16-bit) and 0.4 % (8-bit) off the fastest one on average
+// at hidden sizes of 5120 and more, 1.2 and 2.6 % at smaller ones (profiles/gemm_whole_tiles.txt).
+struct TileCand { int bm, bn, wg_per_cu; float eff_cut, eff; bool qkv; };   // qkv: usable by the fused q/k/v epilogue (128 features per wave)
 constexpr TileCand kTiles[] = {
-    // eff, eff_swiglu: fitted to the times of every whole tile shape, forced, of the projections that split nothing, five layer
-    // shapes at 18 token counts of 264 .. 4200, 16-bit and 8-bit.  Distance of the choice from the fastest shape, on average:
-    // 0.03 % in 16 bits, 0.05 % in 8 (eff_cut's shape: 3.1 and 5.1 %).  W_o of the 13B layer at T = 1152 86 -> 74 us; 8-bit q/k/v
-    // of the 32B one at T = 806 59 -> 43, its gate/up 237 -> 229.
-    {256, 256, 1, 1.00f, 1.00f, 1.00f, true}, {192, 256, 1, 0.92f, 0.88f, 0.96f, true}, {128, 256, 1, 0.68f, 0.90f, 0.82f, true},
-    {128, 128, 2, 0.76f, 0.50f, 0.50f, false}, {64, 128, 3, 0.60f, 0.40f, 0.40f, false}};
+    // eff: fitted to the times of every whole tile shape, forced, of the other projections that split nothing, five layer shapes
+    // at 18 token counts of 264 .. 4200, 16-bit and 8-bit.  Distance of the choice from the fastest shape, on average: 0.03 % in
+    // 16 bits, 0.1 % in 8 (eff_cut's shape: 5 and 7 %); at hidden sizes of 256 .. 3072, which the fit had not seen, 0.2 and
+    // 1.1 % (16 and 11 %).  W_o of the 13B layer at T = 1152 86 -> 74 us; 8-bit q/k/v of the 32B one at T = 806 59 -> 43.
+    {256, 256, 1, 1.00f, 1.00f, true}, {192, 256, 1, 0.92f, 0.88f, true}, {128, 256, 1, 0.68f, 0.90f, true},
+    {128, 128, 2, 0.76f, 0.50f, false}, {64, 128, 3, 0.60f, 0.40f, false}};
 constexpr int kTileCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
 constexpr double kCuFlops = 5.2e12;          // sustained MFMA rate of one CU inside a 256 x 256 tile
@@ -1184,14 +1186,14 @@ Plan choose_cut(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail) {
 
 // The cost of a round is the tile's MFMA work over the shape's in-tile efficiency (relative to 256 x 256) plus kRoundSec;
 // this trades tile quantisation in T (padding to BM), the incomplete round, and the efficiency against each other.
-int whole_tile(int T, int64_t n_eff, int K, bool need_bn256, bool swiglu) {
+int whole_tile(int T, int64_t n_eff, int K, bool need_bn256) {
     int best = 0;
     double best_cost = 1e300;
     for (int i = 0; i < kTileCount; ++i) {
         const TileCand& c = kTiles[i];
         if (need_bn256 && !c.qkv) continue;
         const int64_t tiles = tile_count(c, T, n_eff), slots = 256 * c.wg_per_cu, rounds = (tiles + slots - 1) / slots;
-        const double t_tile = tile_sec(c, K, swiglu ? c.eff_swiglu : c.eff);
+        const double t_tile = tile_sec(c, K, c.eff);
         double cost;
         if (c.wg_per_cu > 1)   // tiles of an incomplete round share fewer CUs' pipes
             cost = (double)((tiles + 255) / 256) * t_tile + (double)rounds * kRoundSec;
@@ -1207,7 +1209,7 @@ bool forced_plan(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, 
     const int cand = forced_cand(), splits = forced_splits();
     if (cand < 0 || cand >= kTileCount) return false;
     if (need_bn256 && !kTiles[cand].qkv) {   // whole tiles of the best shape that can
-        *out = Plan{whole_tile(T, n_eff, K, true, false), 0, 1};
+        *out = Plan{whole_tile(T, n_eff, K, true), 0, 1};
         return true;
     }
     const TileCand& c = kTiles[cand];
@@ -1222,7 +1224,7 @@ Plan plan_for(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, boo
     Plan plan;
     if (forced_plan(T, n_eff, K, need_bn256, allow_tail, &plan)) return plan;
     plan = choose_cut(T, n_eff, K, need_bn256, allow_tail);
-    if (plan.tail_tiles == 0) plan.cand = whole_tile(T, n_eff, K, need_bn256, swiglu);
+    if (plan.tail_tiles == 0 && !swiglu) plan.cand = whole_tile(T, n_eff, K, need_bn256);
     return plan;
 }
 

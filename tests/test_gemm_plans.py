@@ -42,8 +42,9 @@ def test_cuts_are_pinned(plans):
 
 @pytest.mark.parametrize("row,tile", [
     ((580, 27648, 5120, 0, 1), (192, 256)), ((640, 27648, 5120, 0, 1), (192, 256)), ((640, 27648, 2560, 0, 1), (192, 256)),
-    ((600, 55296, 5120, 0, 1), (256, 256)), ((806, 55296, 2560, 0, 1), (128, 256)), ((300, 57344, 8192, 0, 1), (192, 256)),
-    ((1280, 5120, 5120, 0, 0), (128, 256)), ((512, 15360, 5120, 1, 0), (128, 256)), ((4200, 15360, 5120, 1, 0), (256, 256)),
+    ((600, 55296, 5120, 0, 1), (256, 256)), ((300, 57344, 8192, 0, 1), (192, 256)), ((3000, 1408, 256, 0, 1), (64, 128)),
+    ((2500, 2816, 512, 0, 1), (128, 128)), ((1152, 5120, 5120, 0, 0), (128, 256)), ((1280, 5120, 5120, 0, 0), (128, 256)),
+    ((512, 15360, 5120, 1, 0), (128, 256)), ((4200, 15360, 5120, 1, 0), (256, 256)), ((806, 7168, 2560, 1, 0), (128, 256)),
 ])
 def test_whole_tiles_take_the_measured_fastest_shape(plans, row, tile):
     """Sizes where the measured times of the shapes lie clearly apart (profiles/gemm_whole_tiles.txt)."""
