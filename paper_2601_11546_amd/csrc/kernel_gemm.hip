@@ -1027,10 +1027,14 @@ hipError_t launch_skinny(const GemmArgs& p, hipStream_t s) {
 // The output layer of a decode batch: at most 256 rows against a weight matrix far larger than the activations, with no
 // scratch to split k into.  Wide enough that 128-feature tiles fill the CUs, it runs as ONE token tile on a deep ring, so
 // that the weights are read once; the general plan takes 64 x 128 tiles with one stage in flight and, beyond 64 rows, reads
-// the weights once per 64 rows.  32000 x 5120: 24 rows 85 -> 52 us, 129 rows 115 -> 84 us.
+// the weights once per 64 rows.  32000 x 5120: 24 rows 86 -> 54 us, 129 rows 112 -> 77.
+// The deep ring pays where a tile is long against filling it: not for k below 512 (32000 x 256, 100 rows: 9 -> 10 us), nor, one
+// workgroup per CU, for several rounds of short tiles (60000 x 2048: 160 rows 66 -> 73).  At 65 .. 128 rows of several rounds
+// the general plan's three workgroups per CU are faster (128256 x 5120, 100 rows: 252 against 293).
 bool wide_whole_applies(const GemmArgs& p) {
     const int tiles = (p.N + 127) / 128, rounds = (tiles + 255) / 256;
-    return !p.accum && p.T <= SKINNY_MAX_T && p.K % 64 == 0 && tiles >= 0.8 * 256 * rounds && forced_cand() < 0;
+    if (p.accum || p.T > SKINNY_MAX_T || p.K % 64 || tiles < 0.8 * 256 * rounds || forced_cand() >= 0) return false;
+    return rounds == 1 ? p.K >= 512 : p.K >= 3072 && (p.T <= 64 || p.T > 128);
 }
 
 template <int EPI>

@@ -154,22 +154,26 @@ def test_rotation_rounds_the_same_on_every_path(rs, d, fp8):
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (T, tile)
 
 
-@pytest.mark.parametrize("kind", ["packed", "codes", "packed codes"])
+@pytest.mark.parametrize("kind", ["rows", "packed", "codes", "packed codes"])
 @pytest.mark.parametrize("T", [1, 64, 65, 129, 192, 193, 256])
 def test_wide_output_of_other_operands(rs, oracle, T, kind):
-    """test_wide_output_of_few_rows with the weights in the streaming layout, and on 8-bit codes."""
-    N, K = 206 * 128 + 4, 256
+    """test_wide_output_of_few_rows with a k long enough for the deep ring (1024 bytes a row), in both weight layouts and on 8-bit
+    codes."""
+    N, K = 206 * 128 + 4, 1024 if "codes" in kind else 512
     rng = np.random.default_rng(T)
     rows = np.unique([0, T // 2, T - 1])
     resb = W.f32_to_bf16_bits(rng.standard_normal((T, N), dtype=np.float32))
     out = torch.full((T, N), float("nan"), dtype=torch.float32, device="cuda")
-    if kind == "packed":
+    if "codes" not in kind:
         ab = W.f32_to_bf16_bits(rng.standard_normal((T, K), dtype=np.float32))
         wb = W.f32_to_bf16_bits(rng.standard_normal((N, K), dtype=np.float32) * 0.05)
         want = oracle.linear(wb, W.bf16_bits_to_f32(ab[rows]))
-        w = torch.empty(rs.relserve_packed_weight_elems(N, K), dtype=torch.bfloat16, device="cuda")
-        rs.relserve_pack_weight(dev_bf16(wb), w)
-        rs.relserve_linear_packed(dev_bf16(ab), w, N, 1, dev_bf16(resb), out)
+        if kind == "rows":
+            rs.relserve_linear(dev_bf16(ab), dev_bf16(wb), 1, dev_bf16(resb), out)
+        else:
+            w = torch.empty(rs.relserve_packed_weight_elems(N, K), dtype=torch.bfloat16, device="cuda")
+            rs.relserve_pack_weight(dev_bf16(wb), w)
+            rs.relserve_linear_packed(dev_bf16(ab), w, N, 1, dev_bf16(resb), out)
     else:
         codes = lambda *s: W.nearest_e4m3_codes(rng.standard_normal(s).astype(np.float32) * np.float32(60))
         a, w = codes(T, K), codes(N, K)
@@ -182,5 +186,5 @@ def test_wide_output_of_other_operands(rs, oracle, T, kind):
             rs.relserve_linear_w8a8(a, rs.pack_codes(w), s_w, 0.03, 1, dev_bf16(resb), out, n=N)
     scale = max(1.0, np.abs(want).max())
     assert torch.isfinite(out).all()
-    # exact products, fp32 sums of K = 256 in another order (the matrix unit's adder on codes), then one fp32 addition
+    # exact products, fp32 sums of 512 or 1024 in another order (the matrix unit's adder on codes), then one fp32 addition
     assert_close(host_f32(out)[rows], want + W.bf16_bits_to_f32(resb[rows]), f"wide {kind}", max_abs=1e-3 * scale, rel_l2=1e-4)
