@@ -280,6 +280,7 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * W
         fetch(0, ops[0]);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
+            if (t0 + 32 * tm >= p.T) break;   // padding: nothing of this accumulator row (or the ones behind it) is stored
             unsigned char* wr = lds + l32 * ROWB;
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
