@@ -1099,7 +1099,7 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
         p.tail_tiles = std::min(plan.tail_tiles, tiles);
         p.tail_buf = p.accum;
         if ((int64_t)p.tail_tiles * p.tail_splits * BM * BN > kTailFloats)
-            return hipErrorInvalidValue;   // a plan that does not fit the scratch: choose_plan never makes one
+            return hipErrorInvalidValue;   // a plan that does not fit the scratch: choose_cut never makes one
         grid = tiles - p.tail_tiles + p.tail_tiles * p.tail_splits;
     }
     auto go = [&](auto f8) -> hipError_t {
