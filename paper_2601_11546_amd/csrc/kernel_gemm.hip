@@ -823,34 +823,76 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_tail_finish_kernel(GemmAr
 // Split-K companion kernel: adds the splits' slabs in split order (the sum does not depend on scheduling)
 // and applies the same epilogues as the fused path; each thread owns 4 consecutive features of one token.
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ float4 slab_sum(const float* first, int64_t slab_stride, int n_splits) {
-    float4 v = *reinterpret_cast<const float4*>(first);
-    for (int q = 1; q < n_splits; ++q) {
-        const float4 w = *reinterpret_cast<const float4*>(first + q * slab_stride);
-        v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
-    }
-    return v;
+//
+// A thread's work is one chain of memory round trips, and at a few tokens nothing else runs, so the launch costs its longest
+// chain: every load of up to eight slabs, and whatever the epilogue reads beside them, is issued before the first addition.
+// (One slab after the other was a round trip each, to slabs that other XCDs wrote.)
+// One 13B layer with the norms' change (rmsnorm_kernel): four decode rows 140.7 -> 135.4 us.
+template <int NV, int N>
+__device__ __forceinline__ void slab_add(const float* const (&first)[NV], int64_t slab_stride, float4 (&v)[NV]) {
+    float4 w[N][NV];
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+#pragma unroll
+        for (int j = 0; j < NV; ++j) w[q][j] = *reinterpret_cast<const float4*>(first[j] + q * slab_stride);
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+#pragma unroll
+        for (int j = 0; j < NV; ++j) v[j].x += w[q][j].x, v[j].y += w[q][j].y, v[j].z += w[q][j].z, v[j].w += w[q][j].w;
 }
 
-// sums of products of 8-bit codes take the factor a_scale * w_scale[n .. n + 3] (w_scale is null for 16-bit operands)
-__device__ __forceinline__ float4 code_scale(float4 v, const GemmArgs& p, int n) {
+// the sums over n_splits >= 1 slabs, in split order, at NV places of one row (first: the places in slab 0)
+template <int NV>
+__device__ __forceinline__ void slab_sums(const float* (&first)[NV], int64_t slab_stride, int n_splits, float4 (&v)[NV]) {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) v[j] = make_float4(-0.0f, -0.0f, -0.0f, -0.0f);   // the identity of the addition, also of -0
+    for (; n_splits > 8; n_splits -= 8) {
+        slab_add<NV, 8>(first, slab_stride, v);
+#pragma unroll
+        for (int j = 0; j < NV; ++j) first[j] += 8 * slab_stride;
+    }
+    switch (n_splits) {
+        case 1: return slab_add<NV, 1>(first, slab_stride, v);
+        case 2: return slab_add<NV, 2>(first, slab_stride, v);
+        case 3: return slab_add<NV, 3>(first, slab_stride, v);
+        case 4: return slab_add<NV, 4>(first, slab_stride, v);
+        case 5: return slab_add<NV, 5>(first, slab_stride, v);
+        case 6: return slab_add<NV, 6>(first, slab_stride, v);
+        case 7: return slab_add<NV, 7>(first, slab_stride, v);
+        default: return slab_add<NV, 8>(first, slab_stride, v);
+    }
+}
+
+// factor a_scale * w_scale[n .. n + 3] of sums of products of 8-bit codes (w_scale is null for 16-bit operands)
+__device__ __forceinline__ float4 code_factor(const GemmArgs& p, int n) {
+    float4 w = make_float4(1.f, 1.f, 1.f, 1.f);
     if (p.w_scale) {
-        const float4 w = *reinterpret_cast<const float4*>(p.w_scale + n);
-        v.x *= w.x * p.a_scale; v.y *= w.y * p.a_scale; v.z *= w.z * p.a_scale; v.w *= w.w * p.a_scale;
+        w = *reinterpret_cast<const float4*>(p.w_scale + n);
+        w.x *= p.a_scale; w.y *= p.a_scale; w.z *= p.a_scale; w.w *= p.a_scale;
     }
-    return v;
+    return w;
+}
+__device__ __forceinline__ void code_scale(float4& v, const GemmArgs& p, const float4& f) {
+    if (p.w_scale) v.x *= f.x, v.y *= f.y, v.z *= f.z, v.w *= f.w;
 }
 
+// blockIdx.y = token, blockIdx.x = 256 of its units (a unit: 4 consecutive features, or a pair of such quads that the
+// epilogue combines)
 template <int EPI, int D>
 __global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int t = blockIdx.y, u = blockIdx.x * 256 + threadIdx.x;
     const int64_t stride = (int64_t)p.T * p.N;
+    const float* row = p.accum + (int64_t)t * p.N;
     if (EPI == EPI_SWIGLU) {
-        const int q_per_row = p.n_half / 4;
-        if (i >= (int64_t)p.T * q_per_row) return;
-        const int t = (int)(i / q_per_row), c = (int)(i % q_per_row) * 4;
-        const float4 gt = code_scale(slab_sum(p.accum + (int64_t)t * p.N + c, stride, p.n_splits), p, c);
-        const float4 up = code_scale(slab_sum(p.accum + (int64_t)t * p.N + p.n_half + c, stride, p.n_splits), p, p.n_half + c);
+        const int c = u * 4;
+        if (c >= p.n_half) return;
+        const float4 fg = code_factor(p, c), fu = code_factor(p, p.n_half + c);
+        const float* src[2] = {row + c, row + p.n_half + c};
+        float4 v[2];
+        slab_sums(src, stride, p.n_splits, v);
+        code_scale(v[0], p, fg);
+        code_scale(v[1], p, fu);
+        const float4 gt = v[0], up = v[1];
         const float o0 = silu_mul(gt.x, up.x), o1 = silu_mul(gt.y, up.y), o2 = silu_mul(gt.z, up.z), o3 = silu_mul(gt.w, up.w);
         if (p.out_f8) {
             const float sc = p.out_inv;
@@ -863,20 +905,21 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p) {
         // units per token: rotated heads need (lo, hi) quads: (n_q + n_kv) * D / 8; v heads: n_kv * D / 4
         constexpr int HALF = (D > 0 ? D : 64) / 2;
         const int rot_units = (p.n_q + p.n_kv) * (HALF / 4), v_units = p.n_kv * (2 * HALF / 4);
-        const int units = rot_units + v_units;
-        if (i >= (int64_t)p.T * units) return;
-        const int t = (int)(i / units), u = (int)(i % units);
+        if (u >= rot_units + v_units) return;
         const int64_t slot = p.tok_slot[t];
         const int kv_dim = p.n_kv * 2 * HALF;
-        const float* row = p.accum + (int64_t)t * p.N;
         if (u < rot_units) {
-            const int head = u / (HALF / 4), i0 = (u % (HALF / 4)) * 4;
-            const float4 lo = code_scale(slab_sum(row + head * 2 * HALF + i0, stride, p.n_splits), p, head * 2 * HALF + i0);
-            const float4 hi = code_scale(slab_sum(row + head * 2 * HALF + HALF + i0, stride, p.n_splits), p, head * 2 * HALF + HALF + i0);
+            const int head = u / (HALF / 4), i0 = (u % (HALF / 4)) * 4, n = head * 2 * HALF + i0;
             const float2* cs = p.rope_cs + (int64_t)t * HALF + i0;
             const float4 c01 = *reinterpret_cast<const float4*>(cs), c23 = *reinterpret_cast<const float4*>(cs + 2);
+            const float4 f_lo = code_factor(p, n), f_hi = code_factor(p, n + HALF);
+            const float* src[2] = {row + n, row + n + HALF};
+            float4 v[2];
+            slab_sums(src, stride, p.n_splits, v);
+            code_scale(v[0], p, f_lo);
+            code_scale(v[1], p, f_hi);
             float4 rl, rh;
-            rotate4(lo, hi, c01, c23, rl, rh);
+            rotate4(v[0], v[1], c01, c23, rl, rh);
             if (p.kv_fp8 && head >= p.n_q) {
                 uint8_t* dst8 = reinterpret_cast<uint8_t*>(p.k_pages) + slot * kv_dim + (head - p.n_q) * 2 * HALF + i0;
                 const float s = p.k_inv;
@@ -889,8 +932,13 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p) {
             *reinterpret_cast<uint2*>(dst + i0) = make_uint2(pack_bf16x2(rl.x, rl.y), pack_bf16x2(rl.z, rl.w));
             *reinterpret_cast<uint2*>(dst + HALF + i0) = make_uint2(pack_bf16x2(rh.x, rh.y), pack_bf16x2(rh.z, rh.w));
         } else {
-            const int c = (u - rot_units) * 4;
-            const float4 v = code_scale(slab_sum(row + (p.n_q + p.n_kv) * 2 * HALF + c, stride, p.n_splits), p, (p.n_q + p.n_kv) * 2 * HALF + c);
+            const int c = (u - rot_units) * 4, n = (p.n_q + p.n_kv) * 2 * HALF + c;
+            const float4 f = code_factor(p, n);
+            const float* src[1] = {row + n};
+            float4 v1[1];
+            slab_sums(src, stride, p.n_splits, v1);
+            code_scale(v1[0], p, f);
+            const float4 v = v1[0];
             if (p.kv_fp8) {
                 const float s = p.v_inv;
                 *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(p.v_pages) + slot * kv_dim + c) =
@@ -900,21 +948,24 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p) {
             }
         }
     } else {
-        const int q_per_row = p.N / 4;
-        if (i >= (int64_t)p.T * q_per_row) return;
-        const int64_t o = i * 4;
-        float4 v = code_scale(slab_sum(p.accum + o, stride, p.n_splits), p, (int)(i % q_per_row) * 4);
+        const int c = u * 4;
+        if (c >= p.N) return;
+        const int64_t o = (int64_t)t * p.N + c;
+        uint2 rb = make_uint2(0, 0);
+        float4 rf = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (EPI == EPI_RES_BF16_OUT_F32 && p.residual) rb = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p.residual) + o);
+        if (EPI == EPI_RES_F32_OUT_BF16) rf = *reinterpret_cast<const float4*>(static_cast<const float*>(p.residual) + o);
+        const float4 f = code_factor(p, c);
+        const float* src[1] = {row + c};
+        float4 v1[1];
+        slab_sums(src, stride, p.n_splits, v1);
+        code_scale(v1[0], p, f);
+        float4 v = v1[0];
         if (EPI == EPI_RES_BF16_OUT_F32) {
-            if (p.residual) {
-                const uint2 r = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p.residual) + o);
-                v.x += bf16_lo(r.x); v.y += bf16_hi(r.x); v.z += bf16_lo(r.y); v.w += bf16_hi(r.y);
-            }
+            if (p.residual) v.x += bf16_lo(rb.x), v.y += bf16_hi(rb.x), v.z += bf16_lo(rb.y), v.w += bf16_hi(rb.y);
             *reinterpret_cast<float4*>(static_cast<float*>(p.out) + o) = v;
         } else {
-            if (EPI == EPI_RES_F32_OUT_BF16) {
-                const float4 r = *reinterpret_cast<const float4*>(static_cast<const float*>(p.residual) + o);
-                v.x += r.x; v.y += r.y; v.z += r.z; v.w += r.w;
-            }
+            if (EPI == EPI_RES_F32_OUT_BF16) v.x += rf.x, v.y += rf.y, v.z += rf.z, v.w += rf.w;
             *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + o) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
         }
     }
@@ -947,14 +998,14 @@ hipError_t launch_split(GemmArgs p, int splits, hipStream_t s) {
     };
     hipError_t e = p.f8 ? go(std::true_type{}) : go(std::false_type{});
     if (e != hipSuccess) return e;
-    int64_t units;
+    int units;   // of a token
     if (EPI == EPI_SWIGLU)
-        units = (int64_t)p.T * (p.n_half / 4);
+        units = p.n_half / 4;
     else if (EPI == EPI_QKV_ROPE)
-        units = (int64_t)p.T * ((p.n_q + p.n_kv) * (D / 8) + p.n_kv * (D / 4));
+        units = (p.n_q + p.n_kv) * (D / 8) + p.n_kv * (D / 4);
     else
-        units = (int64_t)p.T * (p.N / 4);
-    gemm_finish_kernel<EPI, D><<<dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s>>>(p);
+        units = p.N / 4;
+    gemm_finish_kernel<EPI, D><<<dim3((units + 255) / 256, p.T), dim3(256), 0, s>>>(p);
     return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
 // HBM-bound helper kernels of the layer step: rotary table, RMSNorm, rotary embedding +
 // KV append, and the stand-alone KV append.  All are pure streaming kernels: 16-byte
-// accesses per lane, one pass over the data (RMSNorm re-reads its row from cache).
+// accesses per lane, one pass over the data.
 #include "device_utils.h"
 #include "relserve_internal.h"
 
@@ -27,7 +27,34 @@ hipError_t launch_rope_table(const int32_t* tok_pos, const float* inv_freq_dev, 
 }
 
 // ---- RMSNorm: one workgroup per row --------------------------------------------------------
-template <bool IN_F32>
+// 8 elements of a row, times 1 / rms and the norm's weights: bf16, or 8-bit codes of the normed value / scale, taken from fp32
+// (quantised projections; code_inv = 1 / scale).
+__device__ __forceinline__ void norm_store8(const float (&v)[8], float inv, const uint4& wu, float code_inv, uint16_t* out, int64_t o) {
+    if (code_inv > 0.0f) {
+        const float s = code_inv;
+        uint2 o8;
+        o8.x = pack_fp8x4(v[0] * inv * bf16_lo(wu.x) * s, v[1] * inv * bf16_hi(wu.x) * s, v[2] * inv * bf16_lo(wu.y) * s,
+                          v[3] * inv * bf16_hi(wu.y) * s);
+        o8.y = pack_fp8x4(v[4] * inv * bf16_lo(wu.z) * s, v[5] * inv * bf16_hi(wu.z) * s, v[6] * inv * bf16_lo(wu.w) * s,
+                          v[7] * inv * bf16_hi(wu.w) * s);
+        *reinterpret_cast<uint2*>(reinterpret_cast<uint8_t*>(out) + o) = o8;
+        return;
+    }
+    uint4 r;
+    r.x = pack_bf16x2(v[0] * inv * bf16_lo(wu.x), v[1] * inv * bf16_hi(wu.x));
+    r.y = pack_bf16x2(v[2] * inv * bf16_lo(wu.y), v[3] * inv * bf16_hi(wu.y));
+    r.z = pack_bf16x2(v[4] * inv * bf16_lo(wu.z), v[5] * inv * bf16_hi(wu.z));
+    r.w = pack_bf16x2(v[6] * inv * bf16_lo(wu.w), v[7] * inv * bf16_hi(wu.w));
+    *reinterpret_cast<uint4*>(out + o) = r;
+}
+
+// PER > 0: a thread holds its PER chunks of 8 elements (H <= 2048 PER) in registers, so that the row and the weights come in
+// one round trip and the row is read once; PER = 0 (longer rows): chunk after chunk, the row read again from cache.  At a few
+// rows the launch is latency (5120 columns, 24 rows: 4.7 -> 3.4 us), at many the second read costs (7963 rows: bf16 in 35.9 -> 26.8 us,
+// fp32 in 54.8 -> 37.4, 6.5 TB/s).
+// Both add the squares of a thread's chunks in the same order, by fma (written out: left to the compiler, the first two
+// squares of the unrolled form were contracted the other way round).
+template <bool IN_F32, int PER>
 __global__ void __launch_bounds__(256) rmsnorm_kernel(const void* __restrict__ xv, const uint16_t* __restrict__ w,
                                                       float eps, int32_t H, uint16_t* __restrict__ out,
                                                       const int32_t* __restrict__ row_index, float code_inv) {
@@ -37,10 +64,10 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const void* __restrict__ x
     __shared__ float red[4];
     float ss = 0.f;
     const int chunks = H / 8;
-    auto load8 = [&](int c, float* v) {
+    auto load8 = [&](int c, float (&v)[8]) {
         if (IN_F32) {
             const float4* p = reinterpret_cast<const float4*>(static_cast<const float*>(xv) + row * H + (int64_t)c * 8);
-            float4 a = p[0], b = p[1];
+            const float4 a = p[0], b = p[1];
             v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
         } else {
             const uint4 u = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(xv) + row * H + (int64_t)c * 8);
@@ -48,37 +75,43 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const void* __restrict__ x
             v[4] = bf16_lo(u.z); v[5] = bf16_hi(u.z); v[6] = bf16_lo(u.w); v[7] = bf16_hi(u.w);
         }
     };
-    for (int c = tid; c < chunks; c += 256) {
-        float v[8];
-        load8(c, v);
+    auto load_w = [&](int c) { return *reinterpret_cast<const uint4*>(w + (int64_t)c * 8); };
+    float v[PER > 0 ? PER : 1][8];
+    uint4 wu[PER > 0 ? PER : 1];
+    if constexpr (PER > 0) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) ss += v[i] * v[i];
+        for (int j = 0; j < PER; ++j) {   // past the end: the last chunk again, not counted and not stored
+            const int c = min(tid + 256 * j, chunks - 1);
+            load8(c, v[j]);
+            wu[j] = load_w(c);
+        }
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (tid + 256 * j < chunks) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) ss = __builtin_fmaf(v[j][i], v[j][i], ss);
+            }
+    } else {
+        for (int c = tid; c < chunks; c += 256) {
+            load8(c, v[0]);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ss = __builtin_fmaf(v[0][i], v[0][i], ss);
+        }
     }
     ss = wave_sum(ss);
     if ((tid & 63) == 0) red[tid >> 6] = ss;
     __syncthreads();
     const float tot = red[0] + red[1] + red[2] + red[3];
     const float inv = 1.0f / sqrtf(tot / (float)H + eps);
-    for (int c = tid; c < chunks; c += 256) {
-        float v[8];
-        load8(c, v);
-        const uint4 wu = *reinterpret_cast<const uint4*>(w + (int64_t)c * 8);
-        if (code_inv > 0.0f) {   // quantised projections read 8-bit codes of the normed value / scale, taken from fp32
-            const float s = code_inv;
-            uint2 o8;
-            o8.x = pack_fp8x4(v[0] * inv * bf16_lo(wu.x) * s, v[1] * inv * bf16_hi(wu.x) * s, v[2] * inv * bf16_lo(wu.y) * s,
-                              v[3] * inv * bf16_hi(wu.y) * s);
-            o8.y = pack_fp8x4(v[4] * inv * bf16_lo(wu.z) * s, v[5] * inv * bf16_hi(wu.z) * s, v[6] * inv * bf16_lo(wu.w) * s,
-                              v[7] * inv * bf16_hi(wu.w) * s);
-            *reinterpret_cast<uint2*>(reinterpret_cast<uint8_t*>(out) + orow * H + (int64_t)c * 8) = o8;
-            continue;
+    if constexpr (PER > 0) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (tid + 256 * j < chunks) norm_store8(v[j], inv, wu[j], code_inv, out, orow * H + (int64_t)(tid + 256 * j) * 8);
+    } else {
+        for (int c = tid; c < chunks; c += 256) {
+            load8(c, v[0]);
+            norm_store8(v[0], inv, load_w(c), code_inv, out, orow * H + (int64_t)c * 8);
         }
-        uint4 o;
-        o.x = pack_bf16x2(v[0] * inv * bf16_lo(wu.x), v[1] * inv * bf16_hi(wu.x));
-        o.y = pack_bf16x2(v[2] * inv * bf16_lo(wu.y), v[3] * inv * bf16_hi(wu.y));
-        o.z = pack_bf16x2(v[4] * inv * bf16_lo(wu.z), v[5] * inv * bf16_hi(wu.z));
-        o.w = pack_bf16x2(v[6] * inv * bf16_lo(wu.w), v[7] * inv * bf16_hi(wu.w));
-        *reinterpret_cast<uint4*>(out + orow * H + (int64_t)c * 8) = o;
     }
 }
 
@@ -86,13 +119,17 @@ hipError_t launch_rmsnorm(const void* x, bool x_is_f32, const void* w, float eps
                           void* out, hipStream_t s, const int32_t* row_index, float code_scale) {
     if (rows == 0) return hipSuccess;
     const float code_inv = code_scale > 0.0f ? (float)(1.0 / (double)code_scale) : 0.0f;   // reciprocal in double, rounded once
-    if (x_is_f32)
-        rmsnorm_kernel<true><<<dim3(rows), dim3(256), 0, s>>>(x, static_cast<const uint16_t*>(w), eps, H,
-                                                              static_cast<uint16_t*>(out), row_index, code_inv);
-    else
-        rmsnorm_kernel<false><<<dim3(rows), dim3(256), 0, s>>>(x, static_cast<const uint16_t*>(w), eps, H,
-                                                               static_cast<uint16_t*>(out), row_index, code_inv);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        kernel<<<dim3(rows), dim3(256), 0, s>>>(x, static_cast<const uint16_t*>(w), eps, H, static_cast<uint16_t*>(out), row_index, code_inv);
+        return hipGetLastError();
+    };
+    switch ((H / 8 + 255) / 256) {
+        case 1: return go(x_is_f32 ? rmsnorm_kernel<true, 1> : rmsnorm_kernel<false, 1>);
+        case 2: return go(x_is_f32 ? rmsnorm_kernel<true, 2> : rmsnorm_kernel<false, 2>);
+        case 3: return go(x_is_f32 ? rmsnorm_kernel<true, 3> : rmsnorm_kernel<false, 3>);
+        case 4: return go(x_is_f32 ? rmsnorm_kernel<true, 4> : rmsnorm_kernel<false, 4>);
+        default: return go(x_is_f32 ? rmsnorm_kernel<true, 0> : rmsnorm_kernel<false, 0>);
+    }
 }
 
 // ---- bf16 -> 8-bit codes of value / scale (the attention output on its way into a quantised W_o) ------------

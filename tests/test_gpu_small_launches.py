@@ -1,0 +1,53 @@
+"""The kernels between the projections at a few tokens (GPU): row lengths and numbers of k ranges where their code changes."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_11546_amd import workloads as W
+from tests.gpu_harness import assert_close, dev_bf16, host_f32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rs():
+    assert torch.cuda.is_available(), "GPU tests need a device"
+    from paper_2601_11546_amd import binding
+    return binding
+
+
+@pytest.mark.parametrize("H", [8, 2040, 2048, 2056, 4104, 6144, 8192, 8200, 16384])
+@pytest.mark.parametrize("f32", [False, True])
+def test_rmsnorm_row_lengths(rs, H, f32):
+    """1 .. 4 chunks per thread in registers, and the loop beyond; the last chunk of a row in every place."""
+    g = torch.Generator(device="cuda").manual_seed(H)
+    x = torch.randn(3, H, generator=g, device="cuda")
+    x = x if f32 else x.bfloat16()
+    w = (1 + 0.02 * torch.randn(H, generator=g, device="cuda")).bfloat16()
+    out = torch.full((3, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+    rs.relserve_rmsnorm(x, w, 1e-5, out)
+    xd = x.double()
+    want = xd * w.double() / torch.sqrt((xd * xd).mean(1, keepdim=True) + 1e-5)
+    # one bf16 rounding (2^-8 relative) on top of fp32 arithmetic (below 1e-5 relative)
+    assert ((out.double() - want).abs() <= want.abs() * (2.0 ** -8 + 1e-5)).all()
+
+
+@pytest.mark.parametrize("mlp", [64, 512, 1152, 2112, 2304, 4352])
+@pytest.mark.parametrize("T", [1, 5, 70])
+def test_number_of_k_ranges(rs, oracle, T, mlp):
+    """W_down of a narrow layer over 1 .. 17 k ranges: the sums of one, of up to eight and of more than eight slabs."""
+    shape = W.LayerShape(256, 4, 2, 64, mlp, 16, 1e-5, 10000.0)
+    n_dec = max(1, T - 4)
+    q = [T - n_dec] * (T > n_dec) + [1] * n_dec
+    b = W.build_batch(shape, q, [n + 3 for n in q], seed=T + mlp)
+    wl = W.Workload("k_ranges", shape, b, mlp)
+    weights, x = wl.weights(), W.make_activations(b.T, shape.hidden, mlp)
+    kp, vp = W.make_cache(shape, b.num_pages, mlp)
+    layer = rs.relserve_layer_create(shape)
+    pb = rs.relserve_batch_prepare(layer, b)
+    ws = torch.full((rs.relserve_workspace_bytes(layer, b.T),), 0xff, dtype=torch.uint8, device="cuda")
+    xd = dev_bf16(x)
+    y = torch.empty_like(xd)
+    rs.relserve_layer_step(layer, pb, {k: dev_bf16(v) for k, v in weights.items()}, xd, y, dev_bf16(kp), dev_bf16(vp), ws)
+    want = oracle.layer_step(shape, b, weights, x, kp, vp).y_f32
+    assert_close(host_f32(y), want, f"step T={b.T} mlp={mlp}")     # the whole step's bar
