@@ -38,6 +38,27 @@ __device__ __forceinline__ uint32_t pack_fp8x4(float a, float b, float c, float 
     return (uint32_t)r;
 }
 
+// 8 normed elements of a row (RMSNorm: v / rms times the norm's weights) to element o of out: bf16, or 8-bit codes of the value
+// times code_inv, taken from fp32 (quantised projections).
+__device__ __forceinline__ void norm_store8(const float (&v)[8], float inv, const uint4& wu, float code_inv, uint16_t* out, int64_t o) {
+    if (code_inv > 0.0f) {
+        const float s = code_inv;
+        uint2 o8;
+        o8.x = pack_fp8x4(v[0] * inv * bf16_lo(wu.x) * s, v[1] * inv * bf16_hi(wu.x) * s, v[2] * inv * bf16_lo(wu.y) * s,
+                          v[3] * inv * bf16_hi(wu.y) * s);
+        o8.y = pack_fp8x4(v[4] * inv * bf16_lo(wu.z) * s, v[5] * inv * bf16_hi(wu.z) * s, v[6] * inv * bf16_lo(wu.w) * s,
+                          v[7] * inv * bf16_hi(wu.w) * s);
+        *reinterpret_cast<uint2*>(reinterpret_cast<uint8_t*>(out) + o) = o8;
+        return;
+    }
+    uint4 r;
+    r.x = pack_bf16x2(v[0] * inv * bf16_lo(wu.x), v[1] * inv * bf16_hi(wu.x));
+    r.y = pack_bf16x2(v[2] * inv * bf16_lo(wu.y), v[3] * inv * bf16_hi(wu.y));
+    r.z = pack_bf16x2(v[4] * inv * bf16_lo(wu.z), v[5] * inv * bf16_hi(wu.z));
+    r.w = pack_bf16x2(v[6] * inv * bf16_lo(wu.w), v[7] * inv * bf16_hi(wu.w));
+    *reinterpret_cast<uint4*>(out + o) = r;
+}
+
 // Eight such codes (8 bytes) -> eight bf16 values (every code is a bf16 number: four significant bits).
 __device__ __forceinline__ uint4 fp8x8_to_bf16x8(uint2 raw) {
     const f32x2_t a = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw.x, false), b = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw.x, true);

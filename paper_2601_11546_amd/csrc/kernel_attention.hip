@@ -53,7 +53,20 @@ struct AttnArgs {
     int32_t dec_by_head;   // decode workgroups take four adjacent kv heads of one token (n_kv % 4 == 0)
     float scale_log2;  // log2(e) / sqrt(d), times the key pool's scale when the cache is quantised
     float v_scale;     // the value pool's scale (1 for 16-bit pools): applied where a row is normalised
+    float code_inv;    // > 0: out holds 8-bit codes of the bf16 output times code_inv (a quantised W_o reads them)
 };
+
+// Four consecutive output values to element `at` of out: bf16, or 8-bit codes of their bf16 values.  (A pass of its own that
+// read the bf16 output and wrote the codes took 4.9 us at
+// 128 rows and 10.6 at 3875 of the 13B shape.)
+__device__ __forceinline__ void store_out4(const AttnArgs& p, int64_t at, float a, float b, float c, float d) {
+    const uint2 u = make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
+    if (p.code_inv > 0.0f)
+        *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(p.out) + at) =
+            pack_fp8x4(bf16_lo(u.x) * p.code_inv, bf16_hi(u.x) * p.code_inv, bf16_lo(u.y) * p.code_inv, bf16_hi(u.y) * p.code_inv);
+    else
+        *reinterpret_cast<uint2*>(p.out + at) = u;
+}
 
 // Per-lane running softmax state of one query row (shared by lanes l and l ^ 32, which hold
 // complementary halves of the keys and of the output columns).
@@ -104,14 +117,13 @@ __device__ __forceinline__ void state_store(const RowState<D>& st, const AttnArg
                     make_float4(st.o[td][4 * q4], st.o[td][4 * q4 + 1], st.o[td][4 * q4 + 2], st.o[td][4 * q4 + 3]);
     } else {
         const float inv = p.v_scale / l_tot;
-        uint16_t* orow = p.out + row_id * D + 4 * g;
+        const int64_t at = row_id * D + 4 * g;
 #pragma unroll
         for (int td = 0; td < D / 32; ++td)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4)
-                *reinterpret_cast<uint2*>(orow + 32 * td + 8 * q4) =
-                    make_uint2(pack_bf16x2(st.o[td][4 * q4] * inv, st.o[td][4 * q4 + 1] * inv),
-                               pack_bf16x2(st.o[td][4 * q4 + 2] * inv, st.o[td][4 * q4 + 3] * inv));
+                store_out4(p, at + 32 * td + 8 * q4, st.o[td][4 * q4] * inv, st.o[td][4 * q4 + 1] * inv, st.o[td][4 * q4 + 2] * inv,
+                           st.o[td][4 * q4 + 3] * inv);
     }
 }
 
@@ -690,12 +702,9 @@ __device__ __forceinline__ void attn_decode_body(const AttnArgs& p, const AttnIt
         return;
     }
     const float inv = p.v_scale / l_tot;
-    uint16_t* orow = p.out + row_id * D + 4 * gq;
 #pragma unroll
     for (int td = 0; td < TD; ++td)
-        *reinterpret_cast<uint2*>(orow + 16 * td) =
-            make_uint2(pack_bf16x2(o_acc[td][0] * inv, o_acc[td][1] * inv),
-                       pack_bf16x2(o_acc[td][2] * inv, o_acc[td][3] * inv));
+        store_out4(p, row_id * D + 4 * gq + 16 * td, o_acc[td][0] * inv, o_acc[td][1] * inv, o_acc[td][2] * inv, o_acc[td][3] * inv);
 }
 
 // Finishes the decode rows whose keys were cut into chunks: with chunk states (m_c, l_c, O_c) in the log2 domain,
@@ -723,8 +732,7 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(AttnArgs p) {
         o.x = o.x * a + w * v.x; o.y = o.y * a + w * v.y; o.z = o.z * a + w * v.z; o.w = o.w * a + w * v.w;
     }
     const float inv = p.v_scale / L;
-    *reinterpret_cast<uint2*>(p.out + ((int64_t)mi.tok * p.n_q + hq) * D + d0) =
-        make_uint2(pack_bf16x2(o.x * inv, o.y * inv), pack_bf16x2(o.z * inv, o.w * inv));
+    store_out4(p, ((int64_t)mi.tok * p.n_q + hq) * D + d0, o.x * inv, o.y * inv, o.z * inv, o.w * inv);
 }
 
 template <int D, bool FP8>
@@ -816,6 +824,7 @@ hipError_t launch_attention(const BatchDev& b, const relserve_layer& L, const vo
     // a quantised key reads back as code x k_scale: the scale moves into the score's factor, the value pool's to the end
     p.scale_log2 = (float)(1.4426950408889634 / sqrt((double)L.cfg.head_dim) * (double)kv.k_scale);
     p.v_scale = kv.v_scale;
+    p.code_inv = kv.out_scale > 0.0f ? (float)(1.0 / (double)kv.out_scale) : 0.0f;   // reciprocal in double, rounded once
     const bool d128 = L.cfg.head_dim == 128;
     hipError_t e = hipSuccess;
     auto launch = [&](int slot, const AttnItem* items, int32_t n, const AttnItem* items_b, int32_t n_b, bool decode) {

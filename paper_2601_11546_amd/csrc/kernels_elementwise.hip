@@ -27,27 +27,6 @@ hipError_t launch_rope_table(const int32_t* tok_pos, const float* inv_freq_dev, 
 }
 
 // ---- RMSNorm: one workgroup per row --------------------------------------------------------
-// 8 elements of a row, times 1 / rms and the norm's weights: bf16, or 8-bit codes of the normed value / scale, taken from fp32
-// (quantised projections; code_inv = 1 / scale).
-__device__ __forceinline__ void norm_store8(const float (&v)[8], float inv, const uint4& wu, float code_inv, uint16_t* out, int64_t o) {
-    if (code_inv > 0.0f) {
-        const float s = code_inv;
-        uint2 o8;
-        o8.x = pack_fp8x4(v[0] * inv * bf16_lo(wu.x) * s, v[1] * inv * bf16_hi(wu.x) * s, v[2] * inv * bf16_lo(wu.y) * s,
-                          v[3] * inv * bf16_hi(wu.y) * s);
-        o8.y = pack_fp8x4(v[4] * inv * bf16_lo(wu.z) * s, v[5] * inv * bf16_hi(wu.z) * s, v[6] * inv * bf16_lo(wu.w) * s,
-                          v[7] * inv * bf16_hi(wu.w) * s);
-        *reinterpret_cast<uint2*>(reinterpret_cast<uint8_t*>(out) + o) = o8;
-        return;
-    }
-    uint4 r;
-    r.x = pack_bf16x2(v[0] * inv * bf16_lo(wu.x), v[1] * inv * bf16_hi(wu.x));
-    r.y = pack_bf16x2(v[2] * inv * bf16_lo(wu.y), v[3] * inv * bf16_hi(wu.y));
-    r.z = pack_bf16x2(v[4] * inv * bf16_lo(wu.z), v[5] * inv * bf16_hi(wu.z));
-    r.w = pack_bf16x2(v[6] * inv * bf16_lo(wu.w), v[7] * inv * bf16_hi(wu.w));
-    *reinterpret_cast<uint4*>(out + o) = r;
-}
-
 // PER > 0: a thread holds its PER chunks of 8 elements (H <= 2048 PER) in registers, so that the row and the weights come in
 // one round trip and the row is read once; PER = 0 (longer rows): chunk after chunk, the row read again from cache.  At a few
 // rows the launch is latency (5120 columns, 24 rows: 4.7 -> 3.4 us), at many the second read costs (7963 rows: bf16 in 35.9 -> 26.8 us,

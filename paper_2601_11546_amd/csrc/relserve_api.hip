@@ -750,10 +750,11 @@ int32_t relserve_attention(const relserve_layer* L, const relserve_batch* b, con
     return e == hipSuccess ? RELSERVE_OK : RELSERVE_ERR_HIP;
 }
 
-int32_t relserve_layer_step(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt,
-                            const void* x, void* y, relserve_kv_cache cache, void* workspace,
-                            size_t workspace_bytes, void* stream) {
-    drop_stale_hip_error();
+namespace {
+// One layer step.  In a stack, `normed` says that the layer before has already normed this layer's input into the workspace,
+// and `next` names the norm that reads this layer's output (its `out` is the workspace's too).
+int32_t layer_step(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt, const void* x, void* y,
+                   relserve_kv_cache cache, void* workspace, size_t workspace_bytes, void* stream, bool normed, NextNorm* next) {
     if (int32_t rc = check_pair(L, b)) return rc;
     if (!wt) return RELSERVE_ERR_NULL_POINTER;
     if (int32_t rc = check_cache(b, cache)) return rc;
@@ -783,25 +784,26 @@ int32_t relserve_layer_step(const relserve_layer* L, const relserve_batch* b, co
     const BatchDev& batch = attention_batch(*b, cache);
     const PartialState part = partial_state(*L, batch, w);
     const KvFormat kv = kv_format(cache);
-    run(S_NORM1, [&] { return launch_rmsnorm(x, false, wt->w_in_norm, c.rms_eps, T, c.hidden, w.h, s); });
+    if (!normed) run(S_NORM1, [&] { return launch_rmsnorm(x, false, wt->w_in_norm, c.rms_eps, T, c.hidden, w.h, s); });
     run(S_QKV, [&] {
         return launch_qkv_rope_append(b->dev, *L, w.h, wt->w_qkv, w.q, cache.k_pages, cache.v_pages, s, accum, packed, kv);
     });
     if (e == hipSuccess)
         e = launch_attention(batch, *L, w.q, L->q_dim, cache.k_pages, cache.v_pages, w.attn, part.o, part.ml, s, prof, kv);
-    run(S_O, [&] { return launch_linear(w.attn, wt->w_o, T, c.hidden, L->q_dim, 1, x, w.x1, s, accum, packed); });
-    run(S_NORM2, [&] { return launch_rmsnorm(w.x1, true, wt->w_post_norm, c.rms_eps, T, c.hidden, w.h, s); });
+    NextNorm post{wt->w_post_norm, c.rms_eps, w.h};
+    const CodeScales o{nullptr, 1.0f, 0.0f, &post}, down{nullptr, 1.0f, 0.0f, next};   // 16-bit operands
+    run(S_O, [&] { return launch_linear(w.attn, wt->w_o, T, c.hidden, L->q_dim, 1, x, w.x1, s, accum, packed, &o); });
+    if (!post.done) run(S_NORM2, [&] { return launch_rmsnorm(w.x1, true, wt->w_post_norm, c.rms_eps, T, c.hidden, w.h, s); });
     run(S_GU, [&] {
         return launch_linear(w.h, wt->w_gate_up, T, 2 * c.mlp_dim, c.hidden, 3, nullptr, w.act, s, accum, packed);
     });
-    run(S_DOWN, [&] { return launch_linear(w.act, wt->w_down, T, c.hidden, c.mlp_dim, 2, w.x1, y, s, accum, packed); });
+    if (next) next->out = w.h;   // free by now: the gate/up projection has read it
+    run(S_DOWN, [&] { return launch_linear(w.act, wt->w_down, T, c.hidden, c.mlp_dim, 2, w.x1, y, s, accum, packed, &down); });
     return e == hipSuccess ? RELSERVE_OK : RELSERVE_ERR_HIP;
 }
 
-int32_t relserve_layer_step_w8a8(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights_w8a8* wt,
-                                 const void* x, void* y, relserve_kv_cache cache, void* workspace,
-                                 size_t workspace_bytes, void* stream) {
-    drop_stale_hip_error();
+int32_t layer_step_codes(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights_w8a8* wt, const void* x, void* y,
+                         relserve_kv_cache cache, void* workspace, size_t workspace_bytes, void* stream, bool normed, NextNorm* next) {
     if (int32_t rc = check_pair(L, b)) return rc;
     if (!wt) return RELSERVE_ERR_NULL_POINTER;
     if (int32_t rc = check_cache(b, cache)) return rc;
@@ -833,25 +835,43 @@ int32_t relserve_layer_step_w8a8(const relserve_layer* L, const relserve_batch* 
     // code, and a wide layer's output by up to 7e-3.  The attention is therefore cut as it is over quantised pools.
     const BatchDev& batch = b->dev_no_slots;
     const PartialState part = partial_state(*L, batch, w);
-    const CodeScales qkv{wt->s_qkv, wt->a_qkv, 0.0f}, o{wt->s_o, wt->a_o, 0.0f}, gu{wt->s_gate_up, wt->a_gate_up, wt->a_down},
-        down{wt->s_down, wt->a_down, 0.0f};
-    run(S_NORM1, [&] { return launch_rmsnorm(x, false, wt->w_in_norm, c.rms_eps, T, c.hidden, w.h, s, nullptr, wt->a_qkv); });
+    NextNorm post{wt->w_post_norm, c.rms_eps, w.h, wt->a_gate_up};
+    const CodeScales qkv{wt->s_qkv, wt->a_qkv}, o{wt->s_o, wt->a_o, 0.0f, &post}, gu{wt->s_gate_up, wt->a_gate_up, wt->a_down},
+        down{wt->s_down, wt->a_down, 0.0f, next};
+    KvFormat attn = kv_format(cache);
+    attn.out_scale = wt->a_o;
+    if (!normed) run(S_NORM1, [&] { return launch_rmsnorm(x, false, wt->w_in_norm, c.rms_eps, T, c.hidden, w.h, s, nullptr, wt->a_qkv); });
     run(S_QKV, [&] {
         return launch_qkv_rope_append(b->dev, *L, w.h, wt->w_qkv, w.q, cache.k_pages, cache.v_pages, s, accum, packed,
                                       kv_format(cache), &qkv);
     });
     if (e == hipSuccess)
         e = launch_attention(batch, *L, w.q, L->q_dim, cache.k_pages, cache.v_pages, w.attn, part.o,
-                             part.ml, s, prof, kv_format(cache));
-    // the attention output exists as bf16; its codes go where the rotated queries were (read by now)
-    run(S_QUANT, [&] { return launch_quantise_bf16(w.attn, (int64_t)T * L->q_dim, wt->a_o, w.q, s); });
-    run(S_O, [&] { return launch_linear(w.q, wt->w_o, T, c.hidden, L->q_dim, 1, x, w.x1, s, accum, packed, &o); });
-    run(S_NORM2, [&] { return launch_rmsnorm(w.x1, true, wt->w_post_norm, c.rms_eps, T, c.hidden, w.h, s, nullptr, wt->a_gate_up); });
+                             part.ml, s, prof, attn);
+    run(S_O, [&] { return launch_linear(w.attn, wt->w_o, T, c.hidden, L->q_dim, 1, x, w.x1, s, accum, packed, &o); });
+    if (!post.done)
+        run(S_NORM2, [&] { return launch_rmsnorm(w.x1, true, wt->w_post_norm, c.rms_eps, T, c.hidden, w.h, s, nullptr, wt->a_gate_up); });
     run(S_GU, [&] {
         return launch_linear(w.h, wt->w_gate_up, T, 2 * c.mlp_dim, c.hidden, 3, nullptr, w.act, s, accum, packed, &gu);
     });
+    if (next) next->out = w.h;   // free by now: the gate/up projection has read it
     run(S_DOWN, [&] { return launch_linear(w.act, wt->w_down, T, c.hidden, c.mlp_dim, 2, w.x1, y, s, accum, packed, &down); });
     return e == hipSuccess ? RELSERVE_OK : RELSERVE_ERR_HIP;
+}
+}  // namespace
+
+int32_t relserve_layer_step(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt,
+                            const void* x, void* y, relserve_kv_cache cache, void* workspace,
+                            size_t workspace_bytes, void* stream) {
+    drop_stale_hip_error();
+    return layer_step(L, b, wt, x, y, cache, workspace, workspace_bytes, stream, false, nullptr);
+}
+
+int32_t relserve_layer_step_w8a8(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights_w8a8* wt,
+                                 const void* x, void* y, relserve_kv_cache cache, void* workspace,
+                                 size_t workspace_bytes, void* stream) {
+    drop_stale_hip_error();
+    return layer_step_codes(L, b, wt, x, y, cache, workspace, workspace_bytes, stream, false, nullptr);
 }
 
 int32_t relserve_rmsnorm_codes(const void* x, int32_t x_is_f32, const void* w, float eps, int32_t n_rows,
@@ -943,10 +963,22 @@ int32_t model_step(const relserve_layer* L, const relserve_batch* b, const relse
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (launch_embedding(token_ids, m->embedding, m->vocab, H, T, x, s) != hipSuccess) return RELSERVE_ERR_HIP;
+    bool normed = false;
     for (int32_t l = 0; l < m->n_layers; ++l) {   // the residual stream stays in x, rounded to bf16 between layers
-        const int32_t rc = q8 ? relserve_layer_step_w8a8(L, b, &q8[l], x, x, m->caches[l], workspace, layer_ws, stream)
-                              : relserve_layer_step(L, b, &m->layers[l], x, x, m->caches[l], workspace, layer_ws, stream);
+        // the next layer's input norm, if that layer can be stepped at all (what is wrong with it is for its own step to say)
+        NextNorm nn;
+        bool have_next = l + 1 < m->n_layers;
+        if (have_next && q8) {
+            nn = NextNorm{q8[l + 1].w_in_norm, L->cfg.rms_eps, nullptr, q8[l + 1].a_qkv};
+            have_next = nn.w && nn.code_scale > 0.0f && std::isfinite(nn.code_scale);
+        } else if (have_next) {
+            nn = NextNorm{m->layers[l + 1].w_in_norm, L->cfg.rms_eps};
+        }
+        NextNorm* next = have_next ? &nn : nullptr;
+        const int32_t rc = q8 ? layer_step_codes(L, b, &q8[l], x, x, m->caches[l], workspace, layer_ws, stream, normed, next)
+                              : layer_step(L, b, &m->layers[l], x, x, m->caches[l], workspace, layer_ws, stream, normed, next);
         if (rc) return rc;
+        normed = nn.done;
     }
     if (launch_rmsnorm(x, false, m->w_final_norm, L->cfg.rms_eps, B, H, h_last, s, b->dev.last_tok) != hipSuccess)
         return RELSERVE_ERR_HIP;

@@ -143,12 +143,23 @@ void gemm_force_plan(int cand, int splits);   // test hook, see relserve_debug_f
 // of which the last tail_tiles split their k range `splits` ways.  K counts 2-byte units, so half of it for 8-bit codes.
 struct GemmPlan { int32_t rows, cols, tail_tiles, splits; };
 GemmPlan gemm_plan(int32_t T, int64_t features, int32_t K, bool qkv, bool swiglu, bool scratch);
-// Quantised projection: a [T, K] and w [N, K] hold 8-bit codes (K % 128 == 0); the sums take the factor
-// a_scale * w_scale[n]; out_scale > 0 makes a SwiGLU epilogue store codes of value / out_scale.
+// The RMSNorm that reads a projection's output rows next (epilogues 1 and 2).  Where the projection ends in a kernel that
+// adds up k ranges, that kernel runs the norm too and sets `done`; otherwise the caller launches it.
+struct NextNorm {
+    const void* w = nullptr;          // [N] bf16
+    float eps = 0.0f;
+    void* out = nullptr;              // as launch_rmsnorm's
+    float code_scale = 0.0f;
+    bool done = false;
+};
+// What a projection takes beyond its operands.  w_scale given: a quantised projection, a [T, K] and w [N, K] hold 8-bit codes
+// (K % 128 == 0); the sums take the factor a_scale * w_scale[n]; out_scale > 0 makes a SwiGLU epilogue store codes of
+// value / out_scale.
 struct CodeScales {
     const float* w_scale = nullptr;   // [N] device
     float a_scale = 1.0f;
     float out_scale = 0.0f;
+    NextNorm* next = nullptr;
 };
 hipError_t launch_linear(const void* a, const void* w, int32_t T, int32_t N, int32_t K, int32_t epilogue,
                          const void* residual, void* out, hipStream_t s, float* accum = nullptr, bool w_packed = false,
@@ -156,10 +167,12 @@ hipError_t launch_linear(const void* a, const void* w, int32_t T, int32_t N, int
 // w [N, K] row-major -> the tiled streaming layout (ceil(N / 256) * 256 * K elements), K % 64 == 0
 hipError_t launch_pack_weight(const void* w, int32_t N, int32_t K, void* out, hipStream_t s);
 // q/k/v projection with rotary embedding and KV append fused into the epilogue: q_out [T, n_q d] bf16.
-// How the cache pools store an element: 16-bit, or an 8-bit code of x / scale (relserve_kv_cache).
+// How the cache pools store an element: 16-bit, or an 8-bit code of x / scale (relserve_kv_cache).  out_scale > 0: the
+// attention's output is stored as 8-bit codes of its bf16 values / out_scale (a quantised W_o reads them).
 struct KvFormat {
     bool fp8 = false;
     float k_scale = 1.0f, v_scale = 1.0f;
+    float out_scale = 0.0f;
 };
 hipError_t launch_qkv_rope_append(const BatchDev& b, const relserve_layer& L, const void* h, const void* w_qkv,
                                   void* q_out, void* k_pages, void* v_pages, hipStream_t s, float* accum = nullptr,

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 from paper_2601_11546_amd import workloads as W
-from tests.gpu_harness import assert_close, dev_bf16, host_f32
+from tests.gpu_harness import dev_bf16, host_f32
 
 pytestmark = pytest.mark.gpu
 
@@ -32,11 +32,13 @@ def test_rmsnorm_row_lengths(rs, H, f32):
     assert ((out.double() - want).abs() <= want.abs() * (2.0 ** -8 + 1e-5)).all()
 
 
-@pytest.mark.parametrize("mlp", [64, 512, 1152, 2112, 2304, 4352])
+@pytest.mark.parametrize("hidden, mlp", [(256, 64), (256, 512), (256, 1152), (256, 2112), (256, 2304), (256, 4352),   # k ranges of W_down
+                                         (264, 64), (2048, 64), (8184, 64), (8192, 64), (8200, 64)])                # row of the fused norm
 @pytest.mark.parametrize("T", [1, 5, 70])
-def test_number_of_k_ranges(rs, oracle, T, mlp):
-    """W_down of a narrow layer over 1 .. 17 k ranges: the sums of one, of up to eight and of more than eight slabs."""
-    shape = W.LayerShape(256, 4, 2, 64, mlp, 16, 1e-5, 10000.0)
+def test_k_ranges_and_rows(rs, oracle, T, hidden, mlp):
+    """W_down over 1 .. 17 k ranges: the sums of one, of up to eight and of more than eight slabs.  W_o's rows of 33 .. 1024
+    chunks of eight, normed by the kernel that adds its slabs, and the first row too long for that."""
+    shape = W.LayerShape(hidden, 4, 2, 64, mlp, 16, 1e-5, 10000.0)
     n_dec = max(1, T - 4)
     q = [T - n_dec] * (T > n_dec) + [1] * n_dec
     b = W.build_batch(shape, q, [n + 3 for n in q], seed=T + mlp)
@@ -50,4 +52,7 @@ def test_number_of_k_ranges(rs, oracle, T, mlp):
     y = torch.empty_like(xd)
     rs.relserve_layer_step(layer, pb, {k: dev_bf16(v) for k, v in weights.items()}, xd, y, dev_bf16(kp), dev_bf16(vp), ws)
     want = oracle.layer_step(shape, b, weights, x, kp, vp).y_f32
-    assert_close(host_f32(y), want, f"step T={b.T} mlp={mlp}")     # the whole step's bar
+    # the whole step's bar, plus the rounding of an output as large as these wide layers' (|y| up to 8): half a bf16 unit, 2^-9 |y|
+    got = host_f32(y)
+    assert np.linalg.norm(got - want) <= 1e-2 * np.linalg.norm(want)
+    assert (np.abs(got - want) <= 2e-2 + np.abs(want) * 2.0 ** -9).all()
