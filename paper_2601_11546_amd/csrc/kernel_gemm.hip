@@ -120,6 +120,65 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
     tile_n = in_group / gsz;
 }
 
+// Writes a unit of 4 consecutive features n_lo .. of token t (lo), or a pair of such quads that the epilogue combines: gate and up,
+// or the two halves of a rotated head (its columns n_lo - head D .. and D / 2 further).  oa, ob: what the unit reads besides the sums
+// (a quad of the residual; the angles); slot: the token's place in the cache.
+template <int EPI, int D, bool SC>
+__device__ __forceinline__ void store_unit(const GemmArgs& p, int t, int n_lo, int head, const float4& lo, const float4& hi, const float4& oa,
+                                           const float4& ob, int slot_) {
+    constexpr int DH = D > 0 ? D : 64;
+    if constexpr (EPI == EPI_QKV_ROPE) {
+        const int64_t slot = slot_;
+        const int kv_dim = p.n_kv * DH, i = n_lo - head * DH;
+        if (head < p.n_q + p.n_kv) {
+            float4 rl, rh;
+            rotate4(lo, hi, oa, ob, rl, rh);
+            if (p.kv_fp8 && head >= p.n_q) {   // quantised cache: one byte per element, quantised from fp32
+                uint8_t* dst8 = reinterpret_cast<uint8_t*>(p.k_pages) + slot * kv_dim + (head - p.n_q) * DH + i;
+                const float s = p.k_inv;
+                *reinterpret_cast<uint32_t*>(dst8) = pack_fp8x4(rl.x * s, rl.y * s, rl.z * s, rl.w * s);
+                *reinterpret_cast<uint32_t*>(dst8 + DH / 2) = pack_fp8x4(rh.x * s, rh.y * s, rh.z * s, rh.w * s);
+            } else {
+                uint16_t* dst = (head < p.n_q ? static_cast<uint16_t*>(p.out) + (int64_t)t * (p.n_q * DH) + head * DH
+                                              : p.k_pages + slot * kv_dim + (head - p.n_q) * DH) + i;
+                *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(rl.x, rl.y), pack_bf16x2(rl.z, rl.w));
+                *reinterpret_cast<uint2*>(dst + DH / 2) = make_uint2(pack_bf16x2(rh.x, rh.y), pack_bf16x2(rh.z, rh.w));
+            }
+        } else {
+            const int64_t o = slot * kv_dim + (head - p.n_q - p.n_kv) * DH + i;
+            if (p.kv_fp8) {
+                uint8_t* dst8 = reinterpret_cast<uint8_t*>(p.v_pages) + o;
+                const float s = p.v_inv;
+                *reinterpret_cast<uint32_t*>(dst8) = pack_fp8x4(lo.x * s, lo.y * s, lo.z * s, lo.w * s);
+                *reinterpret_cast<uint32_t*>(dst8 + DH / 2) = pack_fp8x4(hi.x * s, hi.y * s, hi.z * s, hi.w * s);
+            } else {
+                *reinterpret_cast<uint2*>(p.v_pages + o) = make_uint2(pack_bf16x2(lo.x, lo.y), pack_bf16x2(lo.z, lo.w));
+                *reinterpret_cast<uint2*>(p.v_pages + o + DH / 2) = make_uint2(pack_bf16x2(hi.x, hi.y), pack_bf16x2(hi.z, hi.w));
+            }
+        }
+    } else if constexpr (EPI == EPI_SWIGLU) {
+        const float o0 = silu_mul(lo.x, hi.x), o1 = silu_mul(lo.y, hi.y), o2 = silu_mul(lo.z, hi.z), o3 = silu_mul(lo.w, hi.w);
+        const int64_t o = (int64_t)t * p.n_half + n_lo;
+        if (SC && p.out_f8) {   // the down projection reads codes
+            const float s = p.out_inv;
+            *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(p.out) + o) = pack_fp8x4(o0 * s, o1 * s, o2 * s, o3 * s);
+        } else {
+            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + o) = make_uint2(pack_bf16x2(o0, o1), pack_bf16x2(o2, o3));
+        }
+    } else {
+        const int64_t o = (int64_t)t * p.N + n_lo;
+        if constexpr (EPI == EPI_RES_BF16_OUT_F32) {
+            const uint32_t r0 = __float_as_uint(oa.x), r1 = __float_as_uint(oa.y);
+            *reinterpret_cast<float4*>(static_cast<float*>(p.out) + o) =
+                make_float4(lo.x + bf16_lo(r0), lo.y + bf16_hi(r0), lo.z + bf16_lo(r1), lo.w + bf16_hi(r1));
+        } else {
+            float4 v = lo;
+            if constexpr (EPI == EPI_RES_F32_OUT_BF16) v.x += oa.x, v.y += oa.y, v.z += oa.z, v.w += oa.w;
+            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + o) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+        }
+    }
+}
+
 // Epilogue shared by the GEMM kernels.  Register r of accumulator tile (tn, tm) holds feature
 // 32 tn + 8 (r / 4) + 4 g + r % 4 of the wave's feature range and token 32 tm + l32 of its token range.
 // TMX of the wave's BM / (32 WGM) rows of accumulator tiles are held in acc, starting at row tm_base (the GEMM kernels
@@ -225,58 +284,6 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * W
                 }
             }
         };
-        auto unit = [&](int t, const float4& lo, const float4& hi, const float4& oa, const float4& ob, int slot_) __attribute__((always_inline)) {
-            if constexpr (EPI == EPI_QKV_ROPE) {
-                const int64_t slot = slot_;
-                const int kv_dim = p.n_kv * DH, i = n_lo - head * DH;
-                if (head < p.n_q + p.n_kv) {
-                    float4 rl, rh;
-                    rotate4(lo, hi, oa, ob, rl, rh);
-                    if (p.kv_fp8 && head >= p.n_q) {   // quantised cache: one byte per element, quantised from fp32
-                        uint8_t* dst8 = reinterpret_cast<uint8_t*>(p.k_pages) + slot * kv_dim + (head - p.n_q) * DH + i;
-                        const float s = p.k_inv;
-                        *reinterpret_cast<uint32_t*>(dst8) = pack_fp8x4(rl.x * s, rl.y * s, rl.z * s, rl.w * s);
-                        *reinterpret_cast<uint32_t*>(dst8 + DH / 2) = pack_fp8x4(rh.x * s, rh.y * s, rh.z * s, rh.w * s);
-                    } else {
-                        uint16_t* dst = (head < p.n_q ? static_cast<uint16_t*>(p.out) + (int64_t)t * (p.n_q * DH) + head * DH
-                                                      : p.k_pages + slot * kv_dim + (head - p.n_q) * DH) + i;
-                        *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(rl.x, rl.y), pack_bf16x2(rl.z, rl.w));
-                        *reinterpret_cast<uint2*>(dst + DH / 2) = make_uint2(pack_bf16x2(rh.x, rh.y), pack_bf16x2(rh.z, rh.w));
-                    }
-                } else {
-                    const int64_t o = slot * kv_dim + (head - p.n_q - p.n_kv) * DH + i;
-                    if (p.kv_fp8) {
-                        uint8_t* dst8 = reinterpret_cast<uint8_t*>(p.v_pages) + o;
-                        const float s = p.v_inv;
-                        *reinterpret_cast<uint32_t*>(dst8) = pack_fp8x4(lo.x * s, lo.y * s, lo.z * s, lo.w * s);
-                        *reinterpret_cast<uint32_t*>(dst8 + DH / 2) = pack_fp8x4(hi.x * s, hi.y * s, hi.z * s, hi.w * s);
-                    } else {
-                        *reinterpret_cast<uint2*>(p.v_pages + o) = make_uint2(pack_bf16x2(lo.x, lo.y), pack_bf16x2(lo.z, lo.w));
-                        *reinterpret_cast<uint2*>(p.v_pages + o + DH / 2) = make_uint2(pack_bf16x2(hi.x, hi.y), pack_bf16x2(hi.z, hi.w));
-                    }
-                }
-            } else if constexpr (EPI == EPI_SWIGLU) {
-                const float o0 = silu_mul(lo.x, hi.x), o1 = silu_mul(lo.y, hi.y), o2 = silu_mul(lo.z, hi.z), o3 = silu_mul(lo.w, hi.w);
-                const int64_t o = (int64_t)t * p.n_half + n_lo;
-                if (SC && p.out_f8) {   // the down projection reads codes
-                    const float s = p.out_inv;
-                    *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(p.out) + o) = pack_fp8x4(o0 * s, o1 * s, o2 * s, o3 * s);
-                } else {
-                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + o) = make_uint2(pack_bf16x2(o0, o1), pack_bf16x2(o2, o3));
-                }
-            } else {
-                const int64_t o = (int64_t)t * p.N + n_lo;
-                if constexpr (EPI == EPI_RES_BF16_OUT_F32) {
-                    const uint32_t r0 = __float_as_uint(oa.x), r1 = __float_as_uint(oa.y);
-                    *reinterpret_cast<float4*>(static_cast<float*>(p.out) + o) =
-                        make_float4(lo.x + bf16_lo(r0), lo.y + bf16_hi(r0), lo.z + bf16_lo(r1), lo.w + bf16_hi(r1));
-                } else {
-                    float4 v = lo;
-                    if constexpr (EPI == EPI_RES_F32_OUT_BF16) v.x += oa.x, v.y += oa.y, v.z += oa.z, v.w += oa.w;
-                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + o) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
-                }
-            }
-        };
         fetch(0, ops[0]);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
@@ -305,7 +312,7 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * W
                     lo.x *= s_lo.x; lo.y *= s_lo.y; lo.z *= s_lo.z; lo.w *= s_lo.w;
                     if constexpr (PAIRED) hi.x *= s_hi.x, hi.y *= s_hi.y, hi.z *= s_hi.z, hi.w *= s_hi.w;
                 }
-                if (ok && t < p.T) unit(t, lo, hi, cur.a[jo], cur.b[jo], cur.slot[jo]);
+                if (ok && t < p.T) store_unit<EPI, D, SC>(p, t, n_lo, head, lo, hi, cur.a[jo], cur.b[jo], cur.slot[jo]);
             }
             asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
@@ -1042,6 +1049,125 @@ __global__ void __launch_bounds__(1024) gemm_finish_norm_kernel(GemmArgs p, cons
     if (on) norm_store8(v, inv, wu, code_inv, norm_out, o);
 }
 
+// Small problems: one WAVE per tile of 32 tokens x 32 features (two such feature tiles where the epilogue combines pairs), operands
+// straight from global memory to registers.  A projection of a narrow layer at a few hundred tokens is a few dozen MFMAs per
+// wave and bound by latencies: the launch, the first touch of every operand, and the instruction fetch of code that runs once (the
+// tiled kernels' unrolled loops and epilogue are 10 - 40 KB, this one 2 - 4).  So there is no LDS, no barrier and no ring to fill:
+// eight k steps of 16 are in flight behind the eight being multiplied, and what the epilogue reads is fetched first.
+// The sums run over k in the tiled kernels' order: same bits.  Tiny layer (hidden 256, 134 tokens): q/k/v 10.4 -> 4.6 us, W_o
+// 4.9 -> 3.5, W_down (k = 688) 10.1 -> 4.8, the step 47.8 -> 30.2.
+template <int EPI, int D = 0>
+__global__ void __launch_bounds__(64) gemm_small_kernel(GemmArgs p) {
+    constexpr bool PAIRED = EPI == EPI_SWIGLU || EPI == EPI_QKV_ROPE;
+    constexpr int NT = PAIRED ? 2 : 1, U = 8;
+    constexpr int DH = D > 0 ? D : 64;
+    const int lane = threadIdx.x, l32 = lane & 31, g = lane >> 5;
+    const int unit = blockIdx.x / p.tiles_m, t = (int)(blockIdx.x % p.tiles_m) * 32 + l32, tc = min(t, p.T - 1);
+    int head = 0, n0[NT], rows[NT];   // first feature of each tile, and how many rows of the weight matrix it has from there
+    if (EPI == EPI_QKV_ROPE) {
+        head = unit / (DH / 64);
+        n0[0] = head * DH + unit % (DH / 64) * 32;
+        n0[NT - 1] = n0[0] + DH / 2;
+        rows[0] = rows[NT - 1] = 32;
+    } else if (EPI == EPI_SWIGLU) {
+        n0[0] = unit * 32;
+        n0[NT - 1] = p.n_half + n0[0];
+        rows[0] = rows[NT - 1] = min(32, p.n_half - n0[0]);
+    } else {
+        n0[0] = unit * 32;
+        rows[0] = min(32, p.N - n0[0]);
+    }
+    // what the epilogue reads besides the sums: quad q = features 8 q + 4 g ..
+    float4 oa[4], ob[4];
+    int slot = 0;
+    if (EPI == EPI_QKV_ROPE) slot = p.tok_slot[tc];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int f = 8 * q + 4 * g;
+        oa[q] = ob[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (EPI == EPI_QKV_ROPE) {
+            const float4* cs = reinterpret_cast<const float4*>(p.rope_cs + (int64_t)tc * (DH / 2) + n0[0] - head * DH + f);
+            oa[q] = cs[0];
+            ob[q] = cs[1];
+        } else if constexpr (EPI == EPI_RES_BF16_OUT_F32) {
+            if (p.residual && f < rows[0]) {   // no residual given: plain fp32 output
+                const uint2 r = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p.residual) + (int64_t)tc * p.N + n0[0] + f);
+                oa[q].x = __uint_as_float(r.x);
+                oa[q].y = __uint_as_float(r.y);
+            }
+        } else if constexpr (EPI == EPI_RES_F32_OUT_BF16) {
+            if (f < rows[0]) oa[q] = *reinterpret_cast<const float4*>(static_cast<const float*>(p.residual) + (int64_t)tc * p.N + n0[0] + f);
+        }
+    }
+    // operands: k step s is 32 bytes of every row, this lane's half of them 16 (g)
+    const char* const ab = reinterpret_cast<const char*>(p.a);
+    const char* const wb = reinterpret_cast<const char*>(p.w);
+    const uint32_t a_off = ((uint32_t)tc * (uint32_t)p.K + 8 * g) * 2;
+    const int w_slice = p.w_packed ? 32768 : 128;   // from one 64-k slice of a row to the next
+    uint32_t w_off[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const uint32_t n = n0[j] + min(l32, rows[j] - 1);   // rows past the end: the last one again, never stored
+        w_off[j] = (p.w_packed ? (n >> 8) * (uint32_t)p.K * 512u + (n & 255) * 128u : n * (uint32_t)p.K * 2u) + 16 * g;
+    }
+    const int steps = p.K / 16;
+    uint4 a[2][U], w[2][U][NT];
+    auto load = [&](int buf, int s0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = min(s0 + u, steps - 1);
+            a[buf][u] = *reinterpret_cast<const uint4*>(ab + s * 32 + a_off);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) w[buf][u][j] = *reinterpret_cast<const uint4*>(wb + (size_t)(s >> 2) * w_slice + (s & 3) * 32 + w_off[j]);
+        }
+    };
+    f32x16_t acc[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    auto step = [&](int buf, int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[j] = mfma_32x32x16(as_bf16x8(w[buf][u][j]), as_bf16x8(a[buf][u]), acc[j]);
+    };
+    auto batch = [&](int buf, int s0) __attribute__((always_inline)) {
+        if (s0 + U <= steps) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) step(buf, u);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (s0 + u < steps) step(buf, u);
+        }
+    };
+    load(0, 0);
+    for (int s0 = 0; s0 < steps; s0 += 2 * U) {
+        if (s0 + U < steps) load(1, s0 + U);
+        batch(0, s0);
+        if (s0 + U < steps) {
+            if (s0 + 2 * U < steps) load(0, s0 + 2 * U);
+            batch(1, s0 + U);
+        }
+    }
+    if (t >= p.T) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int f = 8 * q + 4 * g;
+        if (f >= rows[0]) break;   // rows are a multiple of 4 (of 8 in pairs)
+        const float4 lo = make_float4(acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]);
+        const float4 hi = make_float4(acc[NT - 1][4 * q], acc[NT - 1][4 * q + 1], acc[NT - 1][4 * q + 2], acc[NT - 1][4 * q + 3]);
+        store_unit<EPI, D, false>(p, t, n0[0] + f, head, lo, hi, oa[q], ob[q], slot);
+    }
+}
+
+template <int EPI, int D = 0>
+hipError_t launch_small(GemmArgs p, hipStream_t s) {
+    p.tiles_m = (p.T + 31) / 32;
+    p.tiles_n = EPI == EPI_QKV_ROPE ? (p.n_q + 2 * p.n_kv) * (D / 64) : ((EPI == EPI_SWIGLU ? p.n_half : p.N) + 31) / 32;
+    gemm_small_kernel<EPI, D><<<dim3(p.tiles_m * p.tiles_n), dim3(64), 0, s>>>(p);
+    return hipGetLastError();
+}
+
 // Skinny path: T <= 256.  The weights are streamed once; to fill 256 CUs the k range of every
 // BM x BN tile (64 / 128 / 192 / 256 tokens x 128 features; x 256 for split_rows) is split over several workgroups, each
 // storing its partial tile to its split's slab.  The LDS ring is as deep as 160 KB allow (one workgroup
@@ -1200,6 +1326,20 @@ template <int EPI>
 hipError_t launch_mid_split(GemmArgs p, int bm, hipStream_t s, NextNorm* next) {
     if (bm == 128) return launch_split<128, EPI, 0>(p, choose_splits(p.T, p.N, p.K, 128), s, next);
     return launch_split<256, EPI, 0>(p, choose_splits(p.T, p.N, p.K, 256), s, next);
+}
+
+// Which problems take the small kernel: those whose k the general paths never cut (the cut fixes the order of the sums), up to
+// one wave per CU: a second wave on a CU doubles what its L1 has to deliver, and the tiled kernels read an operand once per tile.
+// 16-bit, us, general path -> small kernel: 256 x 256 5.0 -> 3.5 at 200 waves, 5.1 -> 4.5 at 304 and 5.3 -> 5.8 at 752; 256 x 512
+// 6.2 -> 4.8 at 200, 6.3 -> 6.5 at 304; 1024 x 320 4.7 -> 4.1 at 256, 4.7 -> 5.3 at 320; gate/up 1376 x 256 4.5 -> 4.4 at 220,
+// 4.6 -> 5.7 at 352; 512 x 1024 7.9 -> 7.3 at 256.  Where the general path has only its 256-feature tiles (q/k/v) or the fallback
+// for k of no multiple of 64, up to three waves per CU: q/k/v 768 x 256 10.6 -> 4.7 at 192 waves, 10.9 -> 8.4 at 756, 11.3 -> 13.0
+// at 1128; W_down 256 x 688 10.2 -> 4.9 at 200, 10.3 -> 8.1 at 752, 10.6 -> 16.3 at 1000.
+bool small_applies(const GemmArgs& p, int epi, int head_dim = 0) {
+    if (p.f8 || p.K % 16 || p.K > 1024 || forced_cand() >= 0) return false;
+    if (p.accum && p.K % 64 == 0 && p.K >= 512) return false;   // from eight k steps on the general paths may cut k
+    const int64_t units = epi == EPI_QKV_ROPE ? (p.n_q + 2 * p.n_kv) * (head_dim / 64) : ((epi == EPI_SWIGLU ? p.n_half : p.N) + 31) / 32;
+    return (p.T + 31) / 32 * units <= (epi == EPI_QKV_ROPE || p.K % 64 ? 768 : 256);
 }
 
 // What a launch does beyond whole tiles: the last tail_tiles tiles split their k range over `splits` workgroups.
@@ -1451,6 +1591,15 @@ hipError_t launch_linear(const void* a, const void* w, int32_t T, int32_t N, int
     if (hipError_t e = set_codes(p, codes)) return e;
     K = p.K;
     NextNorm* next = codes ? codes->next : nullptr;
+    if (small_applies(p, epilogue)) {
+        switch (epilogue) {
+            case EPI_BF16: return launch_small<EPI_BF16>(p, s);
+            case EPI_RES_BF16_OUT_F32: return launch_small<EPI_RES_BF16_OUT_F32>(p, s);
+            case EPI_RES_F32_OUT_BF16: return launch_small<EPI_RES_F32_OUT_BF16>(p, s);
+            case EPI_SWIGLU: return launch_small<EPI_SWIGLU>(p, s);
+            default: return hipErrorInvalidValue;
+        }
+    }
     if (skinny_applies(T, N, K, accum)) {
         switch (epilogue) {
             case EPI_BF16: return launch_skinny<EPI_BF16, 0>(p, s);
@@ -1519,6 +1668,8 @@ hipError_t launch_qkv_rope_append(const BatchDev& b, const relserve_layer& L, co
     p.v_inv = (float)(1.0 / (double)kv.v_scale);
     p.accum = accum;
     if (hipError_t e = set_codes(p, codes)) return e;
+    if (small_applies(p, EPI_QKV_ROPE, L.cfg.head_dim))
+        return L.cfg.head_dim == 128 ? launch_small<EPI_QKV_ROPE, 128>(p, s) : launch_small<EPI_QKV_ROPE, 64>(p, s);
     if (skinny_applies(p.T, p.N, p.K, accum))
         return L.cfg.head_dim == 128 ? launch_skinny<EPI_QKV_ROPE, 128>(p, s) : launch_skinny<EPI_QKV_ROPE, 64>(p, s);
     return L.cfg.head_dim == 128 ? launch_qkv_d<128>(p, s) : launch_qkv_d<64>(p, s);

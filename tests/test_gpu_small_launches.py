@@ -56,3 +56,60 @@ def test_k_ranges_and_rows(rs, oracle, T, hidden, mlp):
     got = host_f32(y)
     assert np.linalg.norm(got - want) <= 1e-2 * np.linalg.norm(want)
     assert (np.abs(got - want) <= 2e-2 + np.abs(want) * 2.0 ** -9).all()
+
+
+@pytest.mark.parametrize("T", [1, 31, 32, 33, 100])
+@pytest.mark.parametrize("N, K", [(4, 16), (36, 48), (64, 128), (96, 144), (40, 688), (32, 1024)])
+def test_small_projection_has_the_tiled_kernels_bits(rs, T, N, K):
+    """One wave per tile of 32 x 32 (a forced tile takes the general path): remainders of tokens and features, one k step to the
+    last allowed, whole and partial batches of eight steps."""
+    g = torch.Generator(device="cuda").manual_seed(T * 1000 + K)
+    a = torch.randn(T, K, generator=g, device="cuda").bfloat16()
+    for epi, n, dtype in ((0, N, torch.bfloat16), (1, N, torch.float32), (2, N, torch.bfloat16), (3, 4 * N, torch.bfloat16)):
+        w = (torch.randn(n, K, generator=g, device="cuda") * 0.05).bfloat16()
+        res = torch.randn(T, n, generator=g, device="cuda")
+        for r in {1: (None, res.bfloat16()), 2: (res,)}.get(epi, (None,)):
+            outs = []
+            for tile in (-1, 0):
+                rs.relserve_debug_force_gemm_plan(tile, 0)
+                try:
+                    outs.append(torch.full((T, n // 2 if epi == 3 else n), float("nan"), dtype=dtype, device="cuda"))
+                    rs.relserve_linear(a, w, epi, r, outs[-1])
+                finally:
+                    rs.relserve_debug_force_gemm_plan(-1, 0)
+            assert torch.isfinite(outs[0]).all()
+            assert torch.equal(outs[0].view(torch.uint8), outs[1].view(torch.uint8)), (epi, r is None)
+
+
+@pytest.mark.parametrize("shape", [W.LayerShape(256, 3, 1, 64, 704, 16, 1e-5, 10000.0), W.LayerShape(192, 3, 1, 128, 704, 16, 1e-5, 10000.0)],
+                         ids=["d64", "d128"])
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("kv8", [False, True])
+def test_small_layer_step_has_the_tiled_kernels_bits(rs, shape, packed, kv8):
+    """q/k/v with rotation and append on both pool formats, and every projection that takes the small kernel, on both weight layouts."""
+    b = W.build_batch(shape, [37, 1, 1, 24], [37, 9, 20, 30], seed=3)
+    weights = {k: dev_bf16(v) for k, v in W.Workload("small", shape, b, 5).weights().items()}
+    if packed:
+        weights = rs.pack_layer_weights(weights)
+    layer = rs.relserve_layer_create(shape)
+    pb = rs.relserve_batch_prepare(layer, b)
+    x = dev_bf16(W.make_activations(b.T, shape.hidden, 5))
+    ws = torch.empty(rs.relserve_workspace_bytes(layer, b.T), dtype=torch.uint8, device="cuda")
+    pools = (b.num_pages, shape.page_size, shape.n_kv_heads, shape.head_dim)
+    outs = []
+    for tile in (-1, 0):
+        g = torch.Generator(device="cuda").manual_seed(1)
+        if kv8:
+            k, v = (torch.randint(0, 96, pools, generator=g, device="cuda", dtype=torch.uint8) for _ in range(2))
+        else:
+            k, v = (torch.randn(*pools, generator=g, device="cuda").bfloat16() for _ in range(2))
+        y = torch.full_like(x, float("nan"))
+        rs.relserve_debug_force_gemm_plan(tile, 0)
+        try:
+            rs.relserve_layer_step(layer, pb, weights, x, y, rs.QuantPool(k, 2.0 ** -4) if kv8 else k, rs.QuantPool(v, 2.0 ** -5) if kv8 else v, ws)
+        finally:
+            rs.relserve_debug_force_gemm_plan(-1, 0)
+        outs.append((y, k, v))
+    assert torch.isfinite(outs[0][0]).all()
+    for name, got, want in zip("ykv", *outs):
+        assert torch.equal(got.view(torch.uint8), want.view(torch.uint8)), name
