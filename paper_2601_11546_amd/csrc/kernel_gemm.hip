@@ -8,7 +8,7 @@
 //
 // Workgroup = a grid of waves (2 x 2 in production) over a BM (tokens) x BN (features) tile, BK = 64.
 // Main kernel (gemm_dma_kernel, K % 64 == 0): tiles go global -> LDS directly, XOR-swizzled 16-byte
-// chunks, two stages, one barrier per k iteration, every k step issued in a fixed order that
+// chunks, two or three stages, one barrier per k iteration, every k step issued in a fixed order that
 // slots the refill loads and the next fragment reads between the MFMAs.  Fallback kernel
 // (gemm_bf16_kernel): global -> registers -> LDS with zero-filled tails for any K % 8 == 0.
 // Workgroup ids are remapped so that each of the 8 XCDs (own L2 each) walks a contiguous run of
@@ -182,8 +182,7 @@ __device__ __forceinline__ void store_unit(const GemmArgs& p, int t, int n_lo, i
 // Epilogue shared by the GEMM kernels.  Register r of accumulator tile (tn, tm) holds feature
 // 32 tn + 8 (r / 4) + 4 g + r % 4 of the wave's feature range and token 32 tm + l32 of its token range.
 // TMX of the wave's BM / (32 WGM) rows of accumulator tiles are held in acc, starting at row tm_base (the GEMM kernels
-// hold all of them; the tail finish kernel one per workgroup, which with its 64 KB of LDS lets two workgroups of four waves share
-// a CU; those of eight waves, 128 KB, have it alone).
+// hold all of them; the tail finish kernel one per workgroup, which with its 64 KB of LDS lets two workgroups share a CU).
 // SC: the sums are products of 8-bit codes and take the factor a_scale * w_scale[feature] as they are read.
 //
 // One accumulator row (32 tokens x the wave's features, fp32) at a time goes through a region of LDS that belongs to the
@@ -260,15 +259,13 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * W
                 }
             }
         }
-        // what a unit reads besides the sums, fetched one accumulator row ahead (with eight waves, which have half the
-        // registers each, half a row ahead)
-        constexpr int PER = WGM * WGN > 4 ? 2 : 1, NOP = IT / PER;
-        struct Operands { float4 a[NOP], b[NOP]; int slot[NOP]; };
+        // what a unit reads besides the sums, fetched one accumulator row ahead
+        struct Operands { float4 a[IT], b[IT]; int slot[IT]; };
         Operands ops[2];
-        auto fetch = [&](int step, Operands& o) __attribute__((always_inline)) {   // step = PER tm + part of the row
+        auto fetch = [&](int tm, Operands& o) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < NOP; ++j) {
-                const int64_t t = min(t0 + 32 * (step / PER) + RPI * (step % PER * NOP + j) + row0, p.T - 1);   // rows past T: the last token again, never stored
+            for (int j = 0; j < IT; ++j) {
+                const int64_t t = min(t0 + 32 * tm + RPI * j + row0, p.T - 1);   // rows past T: the last token again, never stored
                 if constexpr (EPI == EPI_QKV_ROPE) {
                     o.slot[j] = p.tok_slot[t];
                     const float4* cs = reinterpret_cast<const float4*>(p.rope_cs + t * (DH / 2) + 4 * (u % (DH / 8)));
@@ -300,9 +297,8 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * W
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < IT; ++j) {
-                const int step = PER * tm + j / NOP, jo = j % NOP;
-                if (jo == 0 && step + 1 < PER * TM) fetch(step + 1, ops[(step + 1) & 1]);
-                const Operands& cur = ops[step & 1];
+                if (j == 0 && tm + 1 < TM) fetch(tm + 1, ops[(tm + 1) & 1]);
+                const Operands& cur = ops[tm & 1];
                 const int row = RPI * j + row0, t = t0 + 32 * tm + row;
                 const unsigned char* rd = lds + row * ROWB;
                 float4 lo = *reinterpret_cast<const float4*>(rd + ((c_lo ^ (row & 15)) << 4));
@@ -312,7 +308,7 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * W
                     lo.x *= s_lo.x; lo.y *= s_lo.y; lo.z *= s_lo.z; lo.w *= s_lo.w;
                     if constexpr (PAIRED) hi.x *= s_hi.x, hi.y *= s_hi.y, hi.z *= s_hi.z, hi.w *= s_hi.w;
                 }
-                if (ok && t < p.T) store_unit<EPI, D, SC>(p, t, n_lo, head, lo, hi, cur.a[jo], cur.b[jo], cur.slot[jo]);
+                if (ok && t < p.T) store_unit<EPI, D, SC>(p, t, n_lo, head, lo, hi, cur.a[j], cur.b[j], cur.slot[j]);
             }
             asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
@@ -440,7 +436,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs p) {
 
 // ------------------------------------------------------------------------------------------
 // Main kernel for K % 64 == 0: tiles go global -> LDS directly (global_load_lds_dwordx4, no
-// register staging and no LDS store instructions), two LDS stages, operand fragments double
+// register staging and no LDS store instructions), two LDS stages or more, operand fragments double
 // buffered in registers.  The barrier that hands over a stage sits one k step BEFORE the stage
 // boundary: the last 16 MFMAs of a stage run while the first fragments of the next stage are
 // being read, and the loads of the stage after that are issued at once, so they have a whole
@@ -466,27 +462,38 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
 }
 
 // BKD = k extent of one LDS stage (64 or 32), NS = stages in the ring (NS - 1 are in flight).
-// WGM x WGN = grid of waves over the tile (4 or 8 waves; 8 waves = two per SIMD, each with a quarter
-// of the registers, so that one wave's MFMAs cover the other's memory-instruction issue).
+// WGM x WGN = grid of waves over the tile.
 // WNT: the weights are loaded with the non-temporal hint (launches in which no other workgroup reads them again).
 // F8: both operands hold 8-bit codes.  Nothing changes in how bytes travel (K counts pairs of codes, a stage row is
 // still 128 bytes); a k step covers 32 bytes of every row instead of 16, as one 32x32x64 MFMA whose operand is the
 // two adjacent 16-byte chunks (2 ks' + g) * 2, + 1 of the row for k half g (both operands alike, so which codes
 // meet which is fixed), and the epilogue applies the scales.
-template <int BM, int BN, int EPI, int D, int BKD, int NS, int WGM = 2, int WGN = 2, bool WNT = false, bool F8 = false>
+// NSW = stages of the weights' ring: NS, or NS + 1 ("skewed").  Loads of one wave complete in order, so a hand-over of the
+// skewed ring issues the activations of stage kt + NS first and the weights of stage kt + NS + 1 behind them: what the next
+// hand-over waits for are the activations, and the weights just issued stay in flight for another iteration.
+// Tiles of 192 and 256 rows hold two or three stages and leave 16 - 48 KB of the LDS over; two whole stages give a stage hardly
+// one iteration from its issue to its use.  With the third stage of weights, one launch, us: 256 x 256, 13B at T = 7963 W_down
+// 877 -> 838, W_o 372 -> 356; the 70B gate/up at T = 256, weights from HBM, 220 -> 198; 192 x 256 at T = 640 gate/up 202 -> 174,
+// q/k/v 109 -> 98.  Small tiles have four to six whole stages and gain nothing (128 x 128 gate/up 67.6 -> 72).
+constexpr int weight_stages(int bm, int bn, int ns) { return bm >= 192 && ns <= 3 && (ns * (bm + bn) + bn) * 128 <= 160 * 1024 ? ns + 1 : ns; }
+
+template <int BM, int BN, int EPI, int D, int BKD, int NS, int WGM = 2, int WGN = 2, bool WNT = false, bool F8 = false, int NSW = NS>
 __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
+    constexpr bool SKEW = NSW > NS;
+    static_assert(NSW == NS || NSW == NS + 1, "weight ring");
     constexpr int NW = WGM * WGN;
     constexpr int TM = BM / (32 * WGM), TN = BN / (32 * WGN);
     constexpr int ROWB = BKD * 2;                        // bytes per LDS row
     constexpr int CPR = BKD / 8;                         // 16-byte chunks per row
     constexpr int RPI = 1024 / ROWB;                     // rows one 1 KB wave load covers
     constexpr int A_IT = BM / (NW * RPI), W_IT = BN / (NW * RPI);
-    constexpr int A_BYTES = BM * ROWB, W_BYTES = BN * ROWB, STAGE = A_BYTES + W_BYTES;
+    constexpr int A_BYTES = BM * ROWB, W_BYTES = BN * ROWB, W_LDS = NS * A_BYTES;   // NS stages of activations, then NSW of weights
     constexpr int KSTEPS = F8 ? BKD / 32 : BKD / 16;
     constexpr int LOADS = A_IT + W_IT;                   // wave loads per stage
     static_assert(BKD == 64 || BKD == 32, "stage depth");
     static_assert(!F8 || BKD == 64, "the fragment double buffer needs an even number of k steps per stage");
-    static_assert((NS - 1) * LOADS < 64, "vmcnt field");
+    static_assert(NSW * LOADS < 64, "vmcnt field");
+    static_assert(!SKEW || KSTEPS > 1, "the skewed ring's weights are issued between hand-overs");
     static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU needs gate and up tiles in one wave");
     static_assert(EPI != EPI_QKV_ROPE || (BN / WGN == 128 && (D == 64 || D == 128)), "a wave must own whole heads");
     static_assert(BM % (NW * RPI) == 0 && BN % (NW * RPI) == 0, "whole wave loads");
@@ -556,14 +563,21 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
                                : ((uint32_t)n * (uint32_t)K + chunk * 8) * 2;
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
-    auto issue_stage = [&](int stage, int k0) {
-        const char* abase = reinterpret_cast<const char*>(p.a) + (size_t)k0 * 2;
-        const char* wbase = reinterpret_cast<const char*>(p.w) + (p.w_packed ? (size_t)(k0 >> 6) * 32768 + (size_t)(k0 & 63) * 2 : (size_t)k0 * 2);
-        const uint32_t la = lds0 + stage * STAGE + wave * 1024;
+    auto a_src = [&](int k0) { return reinterpret_cast<const char*>(p.a) + (size_t)k0 * 2; };
+    auto w_src = [&](int k0) {
+        return reinterpret_cast<const char*>(p.w) + (p.w_packed ? (size_t)(k0 >> 6) * 32768 + (size_t)(k0 & 63) * 2 : (size_t)k0 * 2);
+    };
+    auto issue_a = [&](int stage, int k0) {
+        const char* abase = a_src(k0);
+        const uint32_t la = lds0 + stage * A_BYTES + wave * 1024;
 #pragma unroll
         for (int j = 0; j < A_IT; ++j) dma16(abase, a_voff[j], la + j * (NW * 1024));
+    };
+    auto issue_w = [&](int stage, int k0) {
+        const char* wbase = w_src(k0);
+        const uint32_t la = lds0 + W_LDS + stage * W_BYTES + wave * 1024;
 #pragma unroll
-        for (int j = 0; j < W_IT; ++j) dma16<WNT>(wbase, w_voff[j], la + A_BYTES + j * (NW * 1024));
+        for (int j = 0; j < W_IT; ++j) dma16<WNT>(wbase, w_voff[j], la + j * (NW * 1024));
     };
 
     // ---- LDS -> MFMA operand offsets
@@ -577,7 +591,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             row = (tn < TN / 2 ? 0 : BN / 2) + wn * (BN / (2 * WGN)) + 32 * (tn % (TN / 2)) + l32;
         else
             row = wn * (BN / WGN) + 32 * tn + l32;
-        w_rd[tn] = A_BYTES + row * ROWB;
+        w_rd[tn] = W_LDS + row * ROWB;
     }
     const int swz = BKD == 64 ? ((l32 >> 1) & 7) : ((l32 >> 2) & 3);
 
@@ -600,28 +614,30 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             return as_bf16x8(*reinterpret_cast<const uint4*>(row + (((2 * ks + g) ^ swz) << 4)));
         }
     };
-    auto load_frags = [&](int buf, int stage, int ks) __attribute__((always_inline)) {
-        const unsigned char* st = smem + stage * STAGE;
+    struct Stage { int a, w; };   // indices into the two rings
+    auto load_frags = [&](int buf, Stage st, int ks) __attribute__((always_inline)) {
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) wf[buf][tn] = read_frag(st + w_rd[tn], ks);
+        for (int tn = 0; tn < TN; ++tn) wf[buf][tn] = read_frag(smem + st.w * W_BYTES + w_rd[tn], ks);
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) af[buf][tm] = read_frag(st + a_rd[tm], ks);
+        for (int tm = 0; tm < TM; ++tm) af[buf][tm] = read_frag(smem + st.a * A_BYTES + a_rd[tm], ks);
     };
 
     // k range of this workgroup (the whole K unless the launch splits it)
     const bool part = EPI == EPI_SLAB || tail;
     const int kbeg = part ? split * p.k_per_split * (64 / BKD) : 0;
     const int nk = part ? min(p.k_per_split * (64 / BKD), K / BKD - kbeg) : K / BKD;
-    // prologue: fill the whole ring, wait for stage 0 only
+    // prologue: fill both rings, wait for stage 0 only
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
-        if (s < nk) issue_stage(s, (kbeg + s) * BKD);
-    if (nk >= NS)
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * LOADS) : "memory");
+    for (int s = 0; s < NSW; ++s) {
+        if (s < nk && s < NS) issue_a(s, (kbeg + s) * BKD);
+        if (s < nk) issue_w(s, (kbeg + s) * BKD);
+    }
+    if (nk >= NSW)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * LOADS + (SKEW ? W_IT : 0)) : "memory");
     else
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    load_frags(0, 0, 0);
+    load_frags(0, Stage{0, 0}, 0);
     auto mfma_one = [&](int buf, int i) __attribute__((always_inline)) {   // i-th of the TN * TM products of a k step
         const int tn = i / TM, tm = i % TM;
         if constexpr (F8)
@@ -631,24 +647,25 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             acc[tn][tm] = EPI == EPI_SLAB ? mfma_32x32x16(af[buf][tm], wf[buf][tn], acc[tn][tm])
                                             : mfma_32x32x16(wf[buf][tn], af[buf][tm], acc[tn][tm]);
     };
-    auto load_frag_one = [&](int buf, int stage, int ks, int i) __attribute__((always_inline)) {   // i-th of the TN + TM fragment reads of a k step
-        const unsigned char* st = smem + stage * STAGE;
+    auto load_frag_one = [&](int buf, Stage st, int ks, int i) __attribute__((always_inline)) {   // i-th of the TN + TM fragment reads of a k step
         if (i < TN)
-            wf[buf][i] = read_frag(st + w_rd[i], ks);
+            wf[buf][i] = read_frag(smem + st.w * W_BYTES + w_rd[i], ks);
         else
-            af[buf][i - TN] = read_frag(st + a_rd[i - TN], ks);
+            af[buf][i - TN] = read_frag(smem + st.a * A_BYTES + a_rd[i - TN], ks);
     };
     // Source of the refill in progress (set at a hand-over): the k slice's first byte in both operands and the
-    // freed stage's LDS address, so that a load costs its own two instructions plus one scalar add.
+    // freed stages' LDS addresses, so that a load costs its own two instructions plus one scalar add.
     const char* rf_a = nullptr;
     const char* rf_w = nullptr;
-    uint32_t rf_la = 0;
-    auto issue_one = [&](int i) __attribute__((always_inline)) {   // i-th of the LOADS wave loads of a stage
-        // weights first: they come from further away (HBM) than the activations (L2)
-        if (i < W_IT)
-            dma16<WNT>(rf_w, w_voff[i], rf_la + A_BYTES + i * (NW * 1024));
+    uint32_t rf_la = 0, rf_lw = 0;
+    auto issue_one = [&](int i) __attribute__((always_inline)) {   // i-th of the LOADS wave loads of a refill
+        // weights first: they come from further away (HBM) than the activations (L2); the skewed ring has a whole
+        // iteration more for them and needs the activations first
+        const int iw = SKEW ? i - A_IT : i, ia = SKEW ? i : i - W_IT;
+        if (SKEW ? iw >= 0 : iw < W_IT)
+            dma16<WNT>(rf_w, w_voff[iw], rf_lw + iw * (NW * 1024));
         else
-            dma16(rf_a, a_voff[i - W_IT], rf_la + (i - W_IT) * (NW * 1024));
+            dma16(rf_a, a_voff[ia], rf_la + ia * (NW * 1024));
     };
     // A flag that is either a run-time bool or std::true_type: the steady-state iterations pass the latter, so their
     // loads sit in straight-line code (a branch and its scalar set-up around each load cost more issue slots than
@@ -665,19 +682,20 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // behind them.  The MFMAs sit on ONE control path on purpose: at a join the compiler would make
     // them wait for the newest reads.
     constexpr int SPREAD = KSTEPS > 1 ? KSTEPS - 1 : 1;   // the last k step before the next hand-over stays free: landing time
-    auto k_step = [&](int buf, int rd_stage, int rd_ks, int part, auto refill) __attribute__((always_inline)) {
+    auto k_step = [&](int buf, Stage rd_stage, int rd_ks, int part, auto refill) __attribute__((always_inline)) {
         // share of the stage's loads issued in each part, cumulative, in sixteenths: the weights (first half
         // of the loads) go out at once, the activations (L2 hits, quick to land) trail over two more steps
         constexpr int cut[5] = {0, 8, 13, 16, 16};
+        // (skewed: the activations at once, the weights over all the steps that remain)
         const int pc = part < SPREAD ? part : SPREAD;
-        const int d_lo = SPREAD == 3 ? cut[pc] * LOADS / 16 : pc * LOADS / SPREAD;
-        const int d_n = (SPREAD == 3 ? cut[pc + 1] * LOADS / 16 : (pc + 1) * LOADS / SPREAD) - d_lo;
+        const int d_lo = SKEW ? (part == 0 ? 0 : A_IT + (part - 1) * W_IT / (KSTEPS - 1)) : SPREAD == 3 ? cut[pc] * LOADS / 16 : pc * LOADS / SPREAD;
+        const int d_n = (SKEW ? A_IT + part * W_IT / (KSTEPS - 1) : SPREAD == 3 ? cut[pc + 1] * LOADS / 16 : (pc + 1) * LOADS / SPREAD) - d_lo;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
             mfma_one(buf, i);
             __builtin_amdgcn_sched_barrier(0);
-            if (part < SPREAD && on(refill)) {
+            if ((SKEW || part < SPREAD) && on(refill)) {
 #pragma unroll
                 for (int d = d_lo + i * d_n / NM; d < d_lo + (i + 1) * d_n / NM; ++d) issue_one(d);
             }
@@ -694,14 +712,16 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // only their hand-over step keeps the fixed order, with the whole refill in it.  Tiles of 6 and 8 products per wave run
     // alone on their CU and take the fixed order too: 13B layer, four projections, 250 -> 239 us at T = 256, 347 -> 329 at 400
     // (q/k/v on 128 x 256 tiles 88 -> 77; on 8-bit operands W_down of the 32B shape at T = 1100 180 -> 173), but the SwiGLU
-    // kernel on that tile loses (122 -> 129) and keeps the compiler's, and so does the eight-wave 8-bit 256 x 256 tile, whose
-    // second wave per SIMD fills the gaps (13B at T = 7963: gate/up 892 fixed, 884 the compiler's; q/k/v 555, 551).
-    constexpr bool FIXED = NM >= 12 || (NM >= 6 && NW == 4 && !(EPI == EPI_SWIGLU && BM == 128));
-    int cur = 0;  // stage being computed
+    // kernel on that tile loses (122 -> 129) and keeps the compiler's.
+    // (8-bit operands on 256 x 256 with eight waves, two per SIMD, hide the loads' latency without the skewed ring, but a wave's 64 x 128
+    // then reads 96 KB of fragments per k step of 1024 cycles beside the 32 KB that land, all the LDS delivers; four waves read
+    // 64 KB.  13B layer at T = 3875 on codes: eight waves 1257 us, with the skewed ring too; four 1231, skewed 1194.)
+    constexpr bool FIXED = NM >= 6 && !(EPI == EPI_SWIGLU && BM == 128);
+    Stage cur{0, 0};  // stage being computed
     // One k iteration (one LDS stage).  refill_open: the refill begun at the previous hand-over is still being
     // issued; refill_next: this iteration's hand-over starts another one.
     auto iteration = [&](int kt, auto refill_open, auto refill_next) __attribute__((always_inline)) {
-        const int nxt = cur + 1 == NS ? 0 : cur + 1;
+        const Stage nxt{cur.a + 1 == NS ? 0 : cur.a + 1, cur.w + 1 == NSW ? 0 : cur.w + 1};
 #pragma unroll
         for (int ks = 0; ks + 1 < KSTEPS; ++ks) {
             if (FIXED) {
@@ -709,7 +729,14 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             } else {
                 load_frags((ks + 1) & 1, cur, ks + 1);
 #pragma unroll
-                for (int i = 0; i < NM; ++i) mfma_one(ks & 1, i);
+                for (int i = 0; i < NM; ++i) {
+                    mfma_one(ks & 1, i);
+                    if (SKEW && on(refill_open)) {
+                        const int d_lo = A_IT + ks * W_IT / (KSTEPS - 1), d_n = A_IT + (ks + 1) * W_IT / (KSTEPS - 1) - d_lo;
+#pragma unroll
+                        for (int d = d_lo + i * d_n / NM; d < d_lo + (i + 1) * d_n / NM; ++d) issue_one(d);
+                    }
+                }
             }
         }
         // Last k step of the stage: all its fragments are in registers.  Wait for the next stage (the
@@ -717,21 +744,21 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         // After the last stage this reads fragments nobody uses.
         constexpr int LB = (KSTEPS - 1) & 1;
         constexpr bool steady = std::is_same_v<decltype(refill_next), std::true_type>;   // then kt + NS < nk
-        if (NS == 2 || (!steady && kt + NS - 1 >= nk))
+        if ((NS == 2 && !SKEW) || (!steady && kt + NSW - 1 >= nk))
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         else
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * LOADS) : "memory");
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * LOADS + (SKEW ? W_IT : 0)) : "memory");
         __syncthreads();
         if (on(refill_next)) {
-            const int k0 = (kbeg + kt + NS) * BKD;
-            rf_a = uniform_ptr(reinterpret_cast<const char*>(p.a) + (size_t)k0 * 2);
-            rf_w = uniform_ptr(reinterpret_cast<const char*>(p.w) +
-                               (p.w_packed ? (size_t)(k0 >> 6) * 32768 + (size_t)(k0 & 63) * 2 : (size_t)k0 * 2));
-            rf_la = __builtin_amdgcn_readfirstlane(lds0 + cur * STAGE + wave * 1024);
+            rf_a = uniform_ptr(a_src((kbeg + kt + NS) * BKD));
+            rf_w = uniform_ptr(w_src((kbeg + kt + NSW) * BKD));
+            rf_la = __builtin_amdgcn_readfirstlane(lds0 + cur.a * A_BYTES + wave * 1024);
+            rf_lw = __builtin_amdgcn_readfirstlane(lds0 + W_LDS + cur.w * W_BYTES + wave * 1024);
         }
         if (FIXED) {
             k_step(LB, nxt, 0, 0, refill_next);
         } else {
+            constexpr int FIRST = SKEW ? A_IT : LOADS;   // issued here; the skewed ring's weights follow in the next iteration
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
@@ -739,7 +766,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
                 __builtin_amdgcn_sched_barrier(0);
                 if (on(refill_next)) {
 #pragma unroll
-                    for (int d = i * LOADS / NM; d < (i + 1) * LOADS / NM; ++d) issue_one(d);
+                    for (int d = i * FIRST / NM; d < (i + 1) * FIRST / NM; ++d) issue_one(d);
                 }
                 if (i >= NM / 2) {
 #pragma unroll
@@ -758,7 +785,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         kt = 1;
     }
     for (; kt < nk - NS; ++kt) iteration(kt, std::true_type{}, std::true_type{});
-    for (; kt < nk; ++kt) iteration(kt, kt - 1 + NS < nk, kt + NS < nk);
+    for (; kt < nk; ++kt) iteration(kt, kt - 1 + NSW < nk, kt + NS < nk);
     if (EPI != EPI_SLAB && tail) {
         // Partial tile -> this split's slab (registers 4 c .. 4 c + 3 of accumulator tile (tn, tm) of
         // thread tid are the 16 bytes at ((tn TM + tm) 4 + c) * threads + tid: coalesced).
@@ -780,7 +807,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         return;
     }
     if constexpr (EPI != EPI_SLAB) {   // the epilogue takes over the ring: every wave is done with it
-        static_assert(NW * epi_wave_bytes<BN, WGN>() <= NS * STAGE, "the epilogue's rows fit the ring");
+        static_assert(NW * epi_wave_bytes<BN, WGN>() <= NS * A_BYTES + NSW * W_BYTES, "the epilogue's rows fit the ring");
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __syncthreads();
     }
@@ -1175,7 +1202,8 @@ hipError_t launch_small(GemmArgs p, hipStream_t s) {
 template <int BM, int EPI, int D, int BN = 256, bool WNT = false>
 hipError_t launch_split(GemmArgs p, int splits, hipStream_t s, NextNorm* next = nullptr) {
     constexpr int NS = BM + BN <= 192 ? 6 : BM + BN <= 256 ? 4 : BM + BN <= 320 ? 4 : BM + BN <= 384 ? 3 : 2;
-    constexpr int smem = NS * (BM + BN) * 64 * 2;
+    constexpr int NSW = weight_stages(BM, BN, NS);
+    constexpr int smem = (NS * BM + NSW * BN) * 64 * 2;
     static_assert(smem <= 160 * 1024, "ring exceeds the LDS");
     p.tiles_m = (p.T + BM - 1) / BM;
     p.tiles_n = (p.N + BN - 1) / BN;
@@ -1189,8 +1217,8 @@ hipError_t launch_split(GemmArgs p, int splits, hipStream_t s, NextNorm* next = 
         constexpr bool F8 = decltype(f8)::value;
         static std::once_flag once;
         static hipError_t attr_status = hipSuccess;
-        if (hipError_t e = allow_smem_once(once, attr_status, &gemm_dma_kernel<BM, BN, EPI_SLAB, 0, 64, NS, 2, 2, WNT, F8>, smem)) return e;
-        gemm_dma_kernel<BM, BN, EPI_SLAB, 0, 64, NS, 2, 2, WNT, F8><<<dim3(p.tiles_m * p.tiles_n * splits), dim3(256), smem, s>>>(p);
+        if (hipError_t e = allow_smem_once(once, attr_status, &gemm_dma_kernel<BM, BN, EPI_SLAB, 0, 64, NS, 2, 2, WNT, F8, NSW>, smem)) return e;
+        gemm_dma_kernel<BM, BN, EPI_SLAB, 0, 64, NS, 2, 2, WNT, F8, NSW><<<dim3(p.tiles_m * p.tiles_n * splits), dim3(256), smem, s>>>(p);
         return hipGetLastError();
     };
     hipError_t e = p.f8 ? go(std::true_type{}) : go(std::false_type{});
@@ -1229,10 +1257,11 @@ int choose_splits(int T, int N, int K, int BM, int BN = 256) {
 // tiles fill the CUs without any k split (the gate/up projection), so no slabs and no finish kernel.
 template <int BM, int EPI, int D = 0, int BN = 128, bool WNT = true>
 hipError_t launch_skinny_whole(GemmArgs p, hipStream_t s) {
-    // (256 x 256 tiles have room for two 64-k stages only; four 32-k stages measured no faster)
+    // (256 x 256 tiles have room for two 64-k stages and a third of the weights; four 32-k stages measured no faster)
     constexpr int BKD = 64;
     constexpr int NS = BM + BN <= 192 ? 6 : BM + BN <= 256 ? 4 : BM + BN <= 384 ? 3 : 2;
-    constexpr int smem = NS * (BM + BN) * BKD * 2;
+    constexpr int NSW = weight_stages(BM, BN, NS);
+    constexpr int smem = (NS * BM + NSW * BN) * BKD * 2;
     static_assert(smem <= 160 * 1024, "ring exceeds the LDS");
     p.tiles_m = (p.T + BM - 1) / BM;
     p.tiles_n = EPI == EPI_SWIGLU ? (p.n_half + BN / 2 - 1) / (BN / 2) : (p.N + BN - 1) / BN;
@@ -1242,9 +1271,8 @@ hipError_t launch_skinny_whole(GemmArgs p, hipStream_t s) {
         constexpr bool F8 = decltype(f8)::value;
         static std::once_flag once;
         static hipError_t attr_status = hipSuccess;
-        constexpr int GM = (F8 && BM == 256 && BN == 256) ? 4 : 2;   // eight waves for the largest 8-bit tile, as in launch_cfg
-        if (hipError_t e = allow_smem_once(once, attr_status, &gemm_dma_kernel<BM, BN, EPI, D, BKD, NS, GM, 2, WNT, F8>, smem)) return e;
-        gemm_dma_kernel<BM, BN, EPI, D, BKD, NS, GM, 2, WNT, F8><<<dim3(p.tiles_m * p.tiles_n), dim3(64 * GM * 2), smem, s>>>(p);
+        if (hipError_t e = allow_smem_once(once, attr_status, &gemm_dma_kernel<BM, BN, EPI, D, BKD, NS, 2, 2, WNT, F8, NSW>, smem)) return e;
+        gemm_dma_kernel<BM, BN, EPI, D, BKD, NS, 2, 2, WNT, F8, NSW><<<dim3(p.tiles_m * p.tiles_n), dim3(256), smem, s>>>(p);
         return hipGetLastError();
     };
     return p.f8 ? go(std::true_type{}) : go(std::false_type{});
@@ -1352,8 +1380,8 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
     p.tiles_n = EPI == EPI_SWIGLU ? (p.n_half + BN / 2 - 1) / (BN / 2) : (p.N + BN - 1) / BN;
     constexpr int smem = 2 * (BM + BN) * BK * 2;
     // 128 x 256 tiles are one workgroup per CU either way, so they take the third stage that fits (144 KB)
-    constexpr int DMA_BK = 64, DMA_NS = (BM == 128 && BN == 256) ? 3 : 2;
-    constexpr int dma_smem = DMA_NS * (BM + BN) * DMA_BK * 2;
+    constexpr int DMA_BK = 64, DMA_NS = (BM == 128 && BN == 256) ? 3 : 2, DMA_NSW = weight_stages(BM, BN, DMA_NS);
+    constexpr int dma_smem = (DMA_NS * BM + DMA_NSW * BN) * DMA_BK * 2;
     const int tiles = p.tiles_m * p.tiles_n;
     if (p.K % 64 != 0) {
         if (p.f8) return hipErrorInvalidValue;   // codes go through the direct-to-LDS kernel only
@@ -1376,22 +1404,17 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
     }
     auto go = [&](auto f8) -> hipError_t {
         constexpr bool F8 = decltype(f8)::value;
-        // 8-bit operands on the largest tile: eight waves (two per SIMD, each with half the registers), so that one
-        // wave's MFMAs cover the other's waits for its loads.  That kernel is bound by load latency (matrix pipes 58 %
-        // busy with four waves); the 16-bit one is bound by the power limit and loses with eight waves (measured both).
-        constexpr int GM = (F8 && BM == 256 && BN == 256) ? 4 : WGM;
-        constexpr int GN = WGN;
         static std::once_flag once_dma;
         static hipError_t st_dma = hipSuccess;
-        if (hipError_t e = allow_smem_once(once_dma, st_dma, &gemm_dma_kernel<BM, BN, EPI, D, DMA_BK, DMA_NS, GM, GN, false, F8>, dma_smem))
+        if (hipError_t e = allow_smem_once(once_dma, st_dma, &gemm_dma_kernel<BM, BN, EPI, D, DMA_BK, DMA_NS, WGM, WGN, false, F8, DMA_NSW>, dma_smem))
             return e;
-        gemm_dma_kernel<BM, BN, EPI, D, DMA_BK, DMA_NS, GM, GN, false, F8>
-            <<<dim3(grid), dim3(64 * GM * GN), dma_smem, s>>>(p);
+        gemm_dma_kernel<BM, BN, EPI, D, DMA_BK, DMA_NS, WGM, WGN, false, F8, DMA_NSW>
+            <<<dim3(grid), dim3(64 * WGM * WGN), dma_smem, s>>>(p);
         if (p.tail_tiles > 0) {
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
-            gemm_tail_finish_kernel<BM, BN, EPI, D, GM, GN, F8>
-                <<<dim3(p.tail_tiles * (BM / (32 * GM))), dim3(64 * GM * GN), 0, s>>>(p);
+            gemm_tail_finish_kernel<BM, BN, EPI, D, WGM, WGN, F8>
+                <<<dim3(p.tail_tiles * (BM / (32 * WGM))), dim3(64 * WGM * WGN), 0, s>>>(p);
         }
         return hipGetLastError();
     };

@@ -188,3 +188,36 @@ def test_wide_output_of_other_operands(rs, oracle, T, kind):
     assert torch.isfinite(out).all()
     # exact products, fp32 sums of 512 or 1024 in another order (the matrix unit's adder on codes), then one fp32 addition
     assert_close(host_f32(out)[rows], want + W.bf16_bits_to_f32(resb[rows]), f"wide {kind}", max_abs=1e-3 * scale, rel_l2=1e-4)
+
+
+@pytest.mark.parametrize("w8a8", [False, True], ids=["bf16", "codes"])
+@pytest.mark.parametrize("stages", [1, 2, 3, 4, 5, 8])
+def test_ring_with_a_further_stage_of_weights(rs, stages, w8a8):
+    """Tiles of 192 and 256 rows keep one stage more of the weights than of the activations: k of fewer stages than either ring
+    holds, of just as many, and of more, against the tile whose rings are alike."""
+    T, N, K = 70, 264, stages * (128 if w8a8 else 64)
+    g = torch.Generator(device="cuda").manual_seed(stages)
+    if w8a8:
+        codes = lambda *s: torch.randint(0, 120, s, generator=g, device="cuda", dtype=torch.uint8) | (torch.randint(0, 2, s, generator=g, device="cuda", dtype=torch.uint8) << 7)
+        a, w, sw = codes(T, K), codes(N, K), torch.rand(N, generator=g, device="cuda") * 1e-3
+        run = lambda out: rs.relserve_linear_w8a8(a, w, sw, 0.03, 1, None, out)
+        value = lambda c: c.view(torch.float8_e4m3fn).double()
+        want = (value(a) @ value(w).T) * sw.double() * 0.03
+    else:
+        a = torch.randn(T, K, generator=g, device="cuda").bfloat16()
+        w = (torch.randn(N, K, generator=g, device="cuda") * 0.05).bfloat16()
+        run = lambda out: rs.relserve_linear(a, w, 1, None, out)
+        want = a.double() @ w.double().T
+    outs = []
+    for tile in (3, 0, 1):
+        outs.append(torch.full((T, N), float("nan"), dtype=torch.float32, device="cuda"))
+        rs.relserve_debug_force_gemm_plan(tile, 0)
+        try:
+            run(outs[-1])
+            torch.cuda.synchronize()
+        finally:
+            rs.relserve_debug_force_gemm_plan(-1, 0)
+    # exact products; at most 1024 roundings of 2^-24 of partial sums that stay of the order of the result
+    assert float((outs[0].double() - want).norm() / want.norm()) <= 1e-4
+    for tile, out in zip((0, 1), outs[1:]):
+        assert torch.equal(out, outs[0]), tile
