@@ -14,8 +14,9 @@
 //                      rows each and share K/V blocks of 64 keys staged by all 256 threads.
 //                      Used for the joint shared-prefix pass (rows = every query token of the
 //                      requests carrying the prefix, keys = the prefix pages, read once per
-//                      group; the running state is stored) and for prefill rows (keys = the
-//                      request's own keys, causal, continuing from the stored state).
+//                      group; the running state is stored), for prefill rows (keys = the
+//                      request's own keys, causal, continuing from the stored state), and for
+//                      prefill rows of a group over both in turn, the state staying in registers.
 //   attn_decode_kernel one WAVE = one decode token x one kv head (rows = the heads of the
 //                      group); each wave streams its own 32-key blocks through a private LDS
 //                      region, so a workgroup needs no barrier and short contexts still fill
@@ -189,14 +190,18 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
     const int ti = R / p.group;
     const int hq = kvh * p.group + (R - ti * p.group);
     const int tok = valid ? p.attn_tok[it.tok_off + ti] : 0;
-    int klim = it.key_end;  // first key this row does NOT see
-    if (valid && (it.flags & ITEM_CAUSAL)) klim = min(klim, p.tok_pos[tok] + 1);
-    int wave_klim_max = klim, wave_klim_min = klim;
+    const bool joint = (it.flags & ITEM_JOINT) != 0;
+    const int causal_lim = valid && (it.flags & (ITEM_CAUSAL | ITEM_JOINT)) ? p.tok_pos[tok] + 1 : it.key_end;
+    int klim, wave_klim_max, wave_klim_min;   // first key this row does NOT see of the run of keys being walked; its extremes in the wave
+    auto set_limit = [&](int lim) {
+        klim = wave_klim_max = wave_klim_min = lim;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        wave_klim_max = max(wave_klim_max, __shfl_xor(wave_klim_max, o, 64));
-        wave_klim_min = min(wave_klim_min, __shfl_xor(wave_klim_min, o, 64));
-    }
+        for (int o = 32; o > 0; o >>= 1) {
+            wave_klim_max = max(wave_klim_max, __shfl_xor(wave_klim_max, o, 64));
+            wave_klim_min = min(wave_klim_min, __shfl_xor(wave_klim_min, o, 64));
+        }
+    };
+    set_limit(min(causal_lim, it.key_end));   // a joint item's rows all see its whole first run
     const bool wave_active = wave * 32 < it.n_tok * p.group;
 
     bf16x8_t qf[D / 16];
@@ -213,26 +218,41 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
     // ---- staging.  Wave load j of this wave fills LDS rows (4 j + wave) * RPI ..; lane l owns row
     // l / CH of those and the 16-byte slot l % CH.  Keys past the end re-read the last key: their
     // scores are masked and their probabilities are exact zeros.
+    // A joint item walks the shared keys [key_begin, key_end) first and then, request by request, the own keys of the rows it
+    // holds (from key_end on): the running state never leaves the registers.  `seg`: the blocks of all its runs together, then
+    // four numbers a request (AttnItem).
     const int32_t* bt = p.block_table + (int64_t)it.bt_req * p.max_blocks;
-    const int last_key = it.key_end - 1;
+    const int32_t* seg = p.attn_tok + it.pad0;
+    int w_kb = it.key_begin, w_end = it.key_end, w_seg = 0;   // the block to look up next: first key, end of its run, the run's number
+    auto advance = [&] {
+        w_kb += BLOCK_N;
+        if (joint && w_kb >= w_end) {
+            bt = p.block_table + (int64_t)seg[4 * w_seg + 1] * p.max_blocks;
+            w_kb = it.key_end;
+            w_end = seg[4 * w_seg + 2];
+            ++w_seg;
+        }
+    };
     const int lrow = lane / CH, lslot = lane % CH;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
     // A lookup keeps the page numbers as they were loaded; the slot arithmetic waits until the block is issued, one
     // iteration later.  (The compiler places the wait for a load in front of its first use, and it does not count the
     // direct-to-LDS loads, which sit in inline assembly: arithmetic on a page number straight after the lookup would
     // wait for every load issued before it -- the next block's keys and values -- and undo the double buffer.)
-    struct Pages { int32_t page[IT]; int kb0; };
+    struct Pages { int32_t page[IT]; int kb0, last, run; };
     Pages pg_cur, pg_nxt;
-    auto lookup = [&](int kb0, Pages& pg) {   // block-table entries of this lane's rows
-        pg.kb0 = kb0;
+    auto lookup = [&](Pages& pg) {   // block-table entries of this lane's rows
+        pg.kb0 = w_kb;
+        pg.last = w_end - 1;
+        pg.run = w_seg;
 #pragma unroll
         for (int j = 0; j < IT; ++j) {
-            const int key = min(kb0 + (4 * j + wave) * RPI + lrow, last_key);
+            const int key = min(pg.kb0 + (4 * j + wave) * RPI + lrow, pg.last);
             pg.page[j] = bt[key >> p.page_shift];
         }
     };
     auto slot_of = [&](const Pages& pg, int j) -> int64_t {
-        const int key = min(pg.kb0 + (4 * j + wave) * RPI + lrow, last_key);
+        const int key = min(pg.kb0 + (4 * j + wave) * RPI + lrow, pg.last);
         return ((int64_t)pg.page[j] << p.page_shift) + (key & p.page_mask);
     };
     auto issue = [&](int buf, const Pages& pg) {
@@ -266,9 +286,9 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
         }
     };
 
-    const int n_blocks = (it.key_end - it.key_begin + BLOCK_N - 1) / BLOCK_N;
+    const int n_blocks = joint ? seg[0] : (it.key_end - it.key_begin + BLOCK_N - 1) / BLOCK_N;
     if (n_blocks > 0) {
-        lookup(it.key_begin, pg_cur);
+        lookup(pg_cur);
 #pragma unroll
         for (int j = 0; j < IT; ++j) asm volatile("" ::"v"(pg_cur.page[j]));   // all of them before the first direct load (see the loop)
         if (FP8) {
@@ -277,7 +297,8 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
         } else {
             issue(0, pg_cur);
         }
-        lookup(min(it.key_begin + BLOCK_N, last_key), pg_nxt);
+        if (n_blocks > 1) advance();
+        lookup(pg_nxt);
     }
     // Operand addresses inside a stage that do not change from block to block.  K: key row
     // 32 t + l32, chunk (2 ks + g) ^ kswz (the swizzle only depends on l32).  V: the transposing read
@@ -380,8 +401,8 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
 #pragma unroll
             for (int td = 0; td < D / 32; ++td) st.o[td] = mfma_32x32x16(vf[td][h], pf[h], st.o[td]);
     };
+    int kb0 = it.key_begin, run = 0;
     for (int b = 0; b < n_blocks; ++b) {
-        const int kb0 = it.key_begin + b * BLOCK_N;
         // this block has landed for every wave, and every wave is done with the other buffer
         if (!FP8) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         // the page numbers looked up during the previous iteration count as used from here on: the compiler's own
@@ -390,12 +411,16 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
 #pragma unroll
         for (int j = 0; j < IT; ++j) asm volatile("" ::"v"(pg_nxt.page[j]));
         __syncthreads();
+        const int kb0_nxt = pg_nxt.kb0, run_nxt = pg_nxt.run;
         if (b + 1 < n_blocks) {
             if (FP8)
                 load_raw(pg_nxt);                               // into registers; stored behind this block's arithmetic
             else
                 issue((b + 1) & 1, pg_nxt);
-            lookup(min(kb0 + 2 * BLOCK_N, last_key), pg_nxt);   // consumed one iteration later
+            if (b + 2 < n_blocks) {
+                advance();
+                lookup(pg_nxt);                                 // consumed one iteration later
+            }
         }
         if (wave_active && kb0 < wave_klim_max) {
             const unsigned char* stage = smem + (b & 1) * SM::STAGE;
@@ -424,6 +449,18 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
         }
         // the other buffer is free since the barrier above: every wave had finished the previous block before it
         if (FP8 && b + 1 < n_blocks) store_raw((b + 1) & 1);
+        if (joint && run_nxt != run) {
+            // the next block is the first of a request's own keys, which only that request's rows see.  Behind the shared keys the
+            // row's sum is brought together, as where a pass of its own hands the state on: the same bits either way.
+            if (run == 0) {
+                const float l_tot = st.l + __shfl_xor(st.l, 32, 64);
+                st.l = g == 0 ? l_tot : 0.f;
+            }
+            const int first = seg[4 * run_nxt - 1], n = seg[4 * run_nxt];
+            set_limit(valid && ti >= first && ti < first + n ? causal_lim : 0);
+        }
+        kb0 = kb0_nxt;
+        run = run_nxt;
     }
     if (valid) {
         int64_t part_row = row_id;

@@ -18,6 +18,7 @@ enum : int32_t {
     ITEM_CAUSAL = 1,        // a row at position p sees keys <= p
     ITEM_INIT_PARTIAL = 2,  // running softmax state starts from the stored prefix partial
     ITEM_WRITE_PARTIAL = 4, // store the running state instead of the normalised output
+    ITEM_JOINT = 16,        // prefill rows of several requests of a group: the shared keys, then each request's own keys, causal
     ITEM_SLOTS = 8          // prefix items that do so in the slots of their rows: slot attn_tok[pad0 + i] + pad1 for query token i
 };
 
@@ -28,7 +29,9 @@ struct AttnItem {
     int32_t key_begin;  // first key position: a multiple of 64 in prefix items, a multiple of 32 past the first own key in decode items
     int32_t key_end;    // one past the last key position any row may see
     int32_t flags;
-    int32_t pad0;       // decode items: the query token; prefix items with slots: where their rows' first slots are listed
+    int32_t pad0;       // decode items: the query token; prefix items with slots: where their rows' first slots are listed; joint items:
+                        // where attn_tok lists the number of their blocks of 64 keys, then request, end of keys, first of the item's
+                        // tokens and their number, request by request (own keys begin at key_end)
     int32_t pad1;       // decode items that write partial state: the slot; prefix items with slots: the chunk's number
 };
 
@@ -118,6 +121,8 @@ int32_t expand_batch(const relserve_layer_config& cfg, const relserve_batch_desc
 
 // Rows of queries one attention workgroup covers (4 waves x 32 MFMA columns).
 constexpr int ATTN_BLOCK_M = 128;
+constexpr int ATTN_JOINT_REQS = 4;       // requests an item of prefill rows of a group holds on average, at most ...
+constexpr int ATTN_JOINT_WGS = 512;      // ... unless the items fill the chip (256 CUs x 2 workgroups)
 constexpr int64_t GEMM_TAIL_FLOATS = 256 * 65536;      // GEMM scratch at T > 256: partial tiles of one round of split 256 x 256 tiles
 constexpr int ATTN_SPLIT_ROWS = 16;   // query heads per kv head the decode kernel's 16-column MFMA holds
 

@@ -51,3 +51,31 @@ def test_random_batches_are_covered(cut, seed):
     own = np.exp(rng.uniform(0, np.log(9000 if seed % 3 else 300), rows)).astype(int) + 1
     page = int(rng.choice([8, 16, 64, 256]))
     cut(shape, own, int(rng.integers(0, 4000)) // page * page, int(rng.integers(1, rows + 1)), page)
+
+
+@pytest.fixture(scope="module")
+def joint(tmp_path_factory):
+    exe = host_program.build(tmp_path_factory.mktemp("joint"), "joint_items")
+
+    def ask(shape, q, own, prefix, page=16):
+        rows = " ".join(f"{a} {b}" for a, b in zip(q, own))
+        return host_program.run(exe, f"{shape.n_q_heads} {shape.n_kv_heads} {shape.head_dim} {page} {prefix} {len(q)} {rows}\n")[0]
+    return ask
+
+
+def test_prefill_rows_of_a_group_take_joint_items(joint):
+    assert joint(W.LLAMA_13B, [120] * 16, [120] * 16, 512) == (15, 15)
+    assert joint(W.LLAMA_13B, [120] * 16 + [1] * 100, [120] * 16 + [60] * 100, 512) == (15, 15)
+    assert joint(W.LLAMA_13B, [8] * 50, [8] * 50, 512) == (50, 0)              # short requests, few items: two passes
+    assert joint(W.LLAMA_13B, [8] * 250, [8] * 250, 512) == (16, 16)           # the same, enough items to fill the chip
+    assert joint(W.LLAMA_13B, [200, 1], [200, 9], 512) == (2, 2)
+
+
+@pytest.mark.parametrize("seed", range(30))
+def test_random_mixed_batches_are_covered(joint, seed):
+    rng = np.random.default_rng(seed)
+    shape = [W.TINY, W.TINY_GQA, W.TINY_G5, W.LLAMA_13B, W.LLAMA_70B, W.QWEN_32B_TP2][seed % 6]
+    rows = int(rng.integers(2, 60))
+    q = np.where(rng.random(rows) < 0.3, 1, np.exp(rng.uniform(0, np.log(300), rows)).astype(int) + 1)
+    page = int(rng.choice([8, 16, 64]))
+    joint(shape, q, q + rng.integers(0, 200, rows) * (rng.random(rows) < 0.5), int(rng.integers(1, 20)) * page, page)
