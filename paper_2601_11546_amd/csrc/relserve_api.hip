@@ -305,20 +305,6 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
             }
             return 0;
         };
-        const int32_t rows_len = rows_chunk_len();
-        SlotPlan plan;
-        if (slots_allowed && hb.n_prefill == 0 && T > 0 && T <= SKINNY_MAX_T) plan = plan_slots(cfg, d, joint, own_keys, chunks_of, rows_len);
-
-        std::vector<int32_t> row_slot;      // per request: its first slot (slot plan only)
-        if (plan.use) {
-            row_slot.resize(B);
-            for (int32_t r = 0; r < B; ++r) {
-                const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
-                const int32_t n = (pid >= 0 && joint[pid] ? plan.prefix_chunks[pid] : 0) + chunks_of(own_keys(r), plan.chunk_len);
-                row_slot[r] = il.n_scratch_slots;
-                if (n > 1) il.n_scratch_slots += n;
-            }
-        }
         // Prefill rows of a group take the shared keys and their own in ONE item: its rows are packed over requests as in a pass of
         // its own over the template, but the running state (n_q (d + 2) floats a row, written and read back) stays in registers.
         // Attention of 65 requests of 50 .. 200 tokens behind 1024 (13B): 266 + 139 us (two passes) -> 337; of 31, 146 + 71 -> 179.
@@ -334,6 +320,43 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
                 if (d.prefix_id[r] == p && d.q_start[r + 1] - d.q_start[r] > 1) toks += d.q_start[r + 1] - d.q_start[r], ++reqs;
             fused[p] = reqs > 0 && (toks * ATTN_JOINT_REQS >= reqs * tile_tok || toks / tile_tok * cfg.n_kv_heads >= ATTN_JOINT_WGS);
         }
+        const int32_t rows_len = rows_chunk_len();
+        SlotPlan plan;
+        if (slots_allowed && hb.n_prefill == 0 && T > 0 && T <= SKINNY_MAX_T) plan = plan_slots(cfg, d, joint, own_keys, chunks_of, rows_len);
+
+        // Decode rows behind a template in a batch that prefills too: the template is an item of the one launch as well, its state and
+        // those of the rows' own keys in the workspace's slots (T + ..), and the merge finishes the rows.  As a launch of its own
+        // it was few workgroups with everything else waiting.
+        bool mixed = slots_allowed && hb.n_prefill > 0 && hb.n_decode > 0;
+        bool behind = false;
+        for (int32_t r = 0; r < B; ++r) {
+            const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
+            if (pid < 0 || !joint[pid]) continue;
+            if (d.q_start[r + 1] - d.q_start[r] == 1) behind = true;
+            else if (!fused[pid]) mixed = false;     // its rows read a state that an earlier launch has to leave
+        }
+        mixed &= behind;
+        if (mixed) {
+            plan.prefix_chunks.assign(d.num_prefixes, 1);
+            plan.prefix_len.assign(d.prefix_len, d.prefix_len + d.num_prefixes);
+            plan.chunk_len = std::max(0, rows_len);
+            plan.use = true;
+        }
+        std::vector<int32_t> row_slot;      // per request: its first slot (slot plans only)
+        if (plan.use) {
+            row_slot.resize(B);
+            int32_t slots = 0;
+            for (int32_t r = 0; r < B; ++r) {
+                if (d.q_start[r + 1] - d.q_start[r] > 1) continue;
+                const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
+                const int32_t n = (pid >= 0 && joint[pid] ? plan.prefix_chunks[pid] : 0) + chunks_of(own_keys(r), plan.chunk_len);
+                row_slot[r] = slots;
+                if (n > 1) slots += n;
+            }
+            if (mixed && slots > split_slot_cap(T)) plan.use = mixed = false;
+            else if (!mixed) il.n_scratch_slots = slots;
+        }
+        il.in_slots = plan.use;
         auto joint_items = [&](int32_t p) {
             AttnItem it{};
             std::vector<int32_t> runs;   // request, end of keys, first token, tokens
@@ -373,15 +396,16 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
             if (!joint[p]) continue;
             ++hb.n_groups;
             if (fused[p]) joint_items(p);
+            auto in_pass = [&](int32_t r, int32_t p) { return d.prefix_id[r] == p && !(fused[p] && d.q_start[r + 1] - d.q_start[r] > 1); };
             const int32_t start = (int32_t)il.attn_tok.size();
             for (int32_t r = 0; r < B; ++r)
-                if (d.prefix_id[r] == p && !(fused[p] && d.q_start[r + 1] - d.q_start[r] > 1))
+                if (in_pass(r, p))
                     for (int32_t t = d.q_start[r]; t < d.q_start[r + 1]; ++t) il.attn_tok.push_back(t);
             const int32_t n = (int32_t)il.attn_tok.size() - start;
             const int32_t slots = (int32_t)il.attn_tok.size();
             if (plan.use)
                 for (int32_t r = 0; r < B; ++r)
-                    if (d.prefix_id[r] == p) il.attn_tok.push_back(row_slot[r]);
+                    if (in_pass(r, p)) il.attn_tok.push_back(row_slot[r]);
             const int32_t n_chunks = plan.use ? plan.prefix_chunks[p] : 1;
             const int32_t per = plan.use ? plan.prefix_len[p] : d.prefix_len[p];
             for (int32_t c = 0; c < n_chunks; ++c)
@@ -398,7 +422,7 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
                         it.pad0 = slots + o;
                         it.pad1 = c;
                     }
-                    il.items_prefix.push_back(it);
+                    (mixed ? il.items_tile : il.items_prefix).push_back(it);
                 }
         }
         const int32_t chunk_len = plan.use ? plan.chunk_len : std::max(0, rows_len);   // 0 = no row is cut
@@ -460,7 +484,7 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
     };
     if (build_items) {
         build(true, hb.items);
-        if (hb.items.n_scratch_slots > 0) build(false, hb.no_slots);
+        if (hb.items.in_slots) build(false, hb.no_slots);
     }
     *out = std::move(hb);
     return RELSERVE_OK;
@@ -654,7 +678,7 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
     };
     view_lists(dv, o_items, hb.items);
     b->dev_no_slots = dv;
-    if (dv.n_scratch_slots > 0) view_lists(b->dev_no_slots, o_seq, hb.no_slots);
+    if (hb.items.in_slots) view_lists(b->dev_no_slots, o_seq, hb.no_slots);
     b->info = relserve_batch_info{T, B, hb.n_decode, hb.n_prefill, hb.n_groups,
                                   dv.n_items_prefix + dv.n_items_tile + dv.n_items_split};
 

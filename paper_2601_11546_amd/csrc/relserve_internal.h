@@ -105,6 +105,7 @@ struct ItemLists {
     std::vector<AttnItem> items_prefix, items_tile, items_split;
     std::vector<MergeItem> merge_items;
     int32_t n_scratch_slots = 0;
+    bool in_slots = false;       // parts of rows behind a template are kept in slots (of the GEMM scratch if n_scratch_slots > 0)
 };
 
 // Host-side expansion of a descriptor (no device calls); shared by validate / slots / prepare.

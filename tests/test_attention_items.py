@@ -64,11 +64,12 @@ def joint(tmp_path_factory):
 
 
 def test_prefill_rows_of_a_group_take_joint_items(joint):
-    assert joint(W.LLAMA_13B, [120] * 16, [120] * 16, 512) == (15, 15)
-    assert joint(W.LLAMA_13B, [120] * 16 + [1] * 100, [120] * 16 + [60] * 100, 512) == (15, 15)
-    assert joint(W.LLAMA_13B, [8] * 50, [8] * 50, 512) == (50, 0)              # short requests, few items: two passes
-    assert joint(W.LLAMA_13B, [8] * 250, [8] * 250, 512) == (16, 16)           # the same, enough items to fill the chip
-    assert joint(W.LLAMA_13B, [200, 1], [200, 9], 512) == (2, 2)
+    assert joint(W.LLAMA_13B, [120] * 16, [120] * 16, 512) == (15, 15, 0)
+    assert joint(W.LLAMA_13B, [120] * 16 + [1] * 100, [120] * 16 + [60] * 100, 512) == (16, 15, 1)   # the decode rows' template beside them
+    assert joint(W.LLAMA_13B, [8] * 50, [8] * 50, 512) == (50, 0, 0)              # short requests, few items: two passes
+    assert joint(W.LLAMA_13B, [8] * 50 + [1] * 9, [8] * 50 + [30] * 9, 512) == (50, 0, 0)
+    assert joint(W.LLAMA_13B, [8] * 250, [8] * 250, 512) == (16, 16, 0)           # the same, enough items to fill the chip
+    assert joint(W.LLAMA_13B, [200, 1], [200, 9], 512) == (3, 2, 1)
 
 
 @pytest.mark.parametrize("seed", range(30))
