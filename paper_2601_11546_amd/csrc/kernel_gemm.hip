@@ -1009,14 +1009,18 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p) {
 // next layer's input norm): a workgroup per token adds the slabs of its whole row, writes the row and norms it.  What is saved
 // is a launch and its chain of round trips: 24 rows of 5120 3.9 + 4.6 -> 4.9 us, 256 rows of 8192 8.4 + 5.3 -> 10.8, a layer of 128
 // rows on 8-bit operands 330.2 -> 326.2 (with the attention's own codes), four layers of 24 rows 857 -> 819 (with the step before).
+// The row's place in the LDS has its own length: with 32 KB for every row 128 decode rows and a 512-token chunk took 1 % longer.
 // A thread owns one chunk of 8 features (N <= 8192).  The sum of squares runs in rmsnorm_kernel's order -- 256 threads, chunk
 // after chunk, from the row in LDS -- so that the normed values have the same bits on both paths.
-constexpr int FINISH_NORM_MAX_N = 8192;
+// Many rows are narrow ones here (the split path bounds rows x columns), and their workgroups mostly idle threads: rows of 256, finish +
+// norm / fused: 2496 4.3 + 4.0 / 6.3, 3621 4.2 + 4.2 / 9.7, 4744 3.0 + 5.3 / 11.7.
+constexpr int FINISH_NORM_MAX_N = 8192, FINISH_NORM_MAX_T = 2560;
 template <int EPI>
 __global__ void __launch_bounds__(1024) gemm_finish_norm_kernel(GemmArgs p, const uint16_t* __restrict__ norm_w, float eps,
                                                                 uint16_t* __restrict__ norm_out, float code_inv) {
     static_assert(EPI == EPI_RES_BF16_OUT_F32 || EPI == EPI_RES_F32_OUT_BF16, "epilogues with whole rows of the residual stream");
-    __shared__ __align__(16) float vals[FINISH_NORM_MAX_N];
+    extern __shared__ __align__(16) unsigned char smem[];   // the row; its own length, so that narrow rows leave room for more workgroups
+    float* const vals = reinterpret_cast<float*>(smem);
     __shared__ float red[4];
     const int t = blockIdx.x, tid = threadIdx.x, chunks = p.N / 8;
     const bool on = tid < chunks;
@@ -1224,10 +1228,10 @@ hipError_t launch_split(GemmArgs p, int splits, hipStream_t s, NextNorm* next = 
     hipError_t e = p.f8 ? go(std::true_type{}) : go(std::false_type{});
     if (e != hipSuccess) return e;
     if constexpr (EPI == EPI_RES_BF16_OUT_F32 || EPI == EPI_RES_F32_OUT_BF16) {
-        if (next && p.N % 8 == 0 && p.N <= FINISH_NORM_MAX_N) {
+        if (next && p.N % 8 == 0 && p.N <= FINISH_NORM_MAX_N && p.T <= FINISH_NORM_MAX_T) {
             const int threads = std::max(256, (p.N / 8 + 63) / 64 * 64);
             const float code_inv = next->code_scale > 0.0f ? (float)(1.0 / (double)next->code_scale) : 0.0f;   // as launch_rmsnorm
-            gemm_finish_norm_kernel<EPI><<<dim3(p.T), dim3(threads), 0, s>>>(p, static_cast<const uint16_t*>(next->w), next->eps,
+            gemm_finish_norm_kernel<EPI><<<dim3(p.T), dim3(threads), p.N * sizeof(float), s>>>(p, static_cast<const uint16_t*>(next->w), next->eps,
                                                                              static_cast<uint16_t*>(next->out), code_inv);
             next->done = true;
             return hipGetLastError();
