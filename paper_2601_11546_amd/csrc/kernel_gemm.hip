@@ -1444,7 +1444,9 @@ constexpr TileCand kTiles[] = {
     // at 18 token counts of 264 .. 4200, 16-bit and 8-bit.  Distance of the choice from the fastest shape, on average: 0.03 % in
     // 16 bits, 0.1 % in 8 (eff_cut's shape: 5 and 7 %); at hidden sizes of 256 .. 3072, which the fit had not seen, 0.2 and
     // 1.1 % (16 and 11 %).  W_o of the 13B layer at T = 1152 86 -> 74 us; 8-bit q/k/v of the 32B one at T = 806 59 -> 43.
-    {256, 256, 1, 1.00f, 1.00f, true}, {192, 256, 1, 0.92f, 0.88f, true}, {128, 256, 1, 0.68f, 0.90f, true},
+    // With the third stage of weights 192 x 256 gained most (0.88 before): measured again at 17 token counts, 0.0 % off the fastest in
+    // 16 bits (0.13 % with 0.88) and 0.4 % in 8; q/k/v of the 70B layer at T = 2304 322 (128 x 256) -> 308 us, 7168 x 8192 at 2700 289 -> 280.
+    {256, 256, 1, 1.00f, 1.00f, true}, {192, 256, 1, 0.92f, 0.98f, true}, {128, 256, 1, 0.68f, 0.90f, true},
     {128, 128, 2, 0.76f, 0.50f, false}, {64, 128, 3, 0.60f, 0.40f, false}};
 constexpr int kTileCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
