@@ -36,3 +36,49 @@ def test_joint_items(rs, oracle, shape, prefix, q_len):
     rs.relserve_layer_step(layer, pb, {k: dev_bf16(v) for k, v in weights.items()}, xd, y, dev_bf16(kp), dev_bf16(vp), ws)
     want = oracle.layer_step(shape, b, weights, x, kp, vp).y_f32
     assert_close(host_f32(y), want, f"joint {q_len} behind {prefix}")     # the whole step's bar
+
+
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+@pytest.mark.parametrize("shape", [W.TINY, W.TINY_G5, W.TINY_D128, W.TINY_G3_D128], ids=["group1", "group5", "d128", "g3d128"])
+def test_a_request_spoils_its_own_rows_alone(rs, shape, fp8):
+    """Requests that share an item, and waves of it, with one whose cached keys or values are not finite: the others' rows have
+    the bits they have beside finite ones."""
+    q = np.array([20, 50, 7, 33, 1, 90, 12])
+    own = q + np.array([0, 100, 3, 0, 40, 70, 0])
+    prefix, bad_v, bad_k = 80, [1, 3], [5]
+    b = W.build_batch(shape, q, own + prefix, [0] * len(q), [prefix], seed=4)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    size = (b.num_pages, shape.page_size, shape.n_kv_heads, shape.head_dim)
+    if fp8:
+        pools = [torch.randint(0, 120, size, generator=g, device="cuda", dtype=torch.uint8) for _ in "kv"]
+        bad = [0x7f, 0xff]                      # the 8-bit format has NaN alone
+    else:
+        pools = [torch.randn(*size, generator=g, device="cuda").bfloat16() for _ in "kv"]
+        bad = [float("inf"), float("nan")]
+    table = np.asarray(b.block_table).reshape(len(q), -1)
+    qs = torch.randn(b.T, shape.q_dim, generator=g, device="cuda").bfloat16()
+    layer = rs.relserve_layer_create(shape)
+    pb = rs.relserve_batch_prepare(layer, b)
+
+    def attend(k, v):
+        ws = torch.full((rs.relserve_workspace_bytes(layer, b.T),), 0xff, dtype=torch.uint8, device="cuda")
+        out = torch.zeros(b.T, shape.q_dim, dtype=torch.bfloat16, device="cuda")
+        rs.relserve_attention(layer, pb, qs, shape.q_dim, *((rs.QuantPool(k, 0.125), rs.QuantPool(v, 0.07)) if fp8 else (k, v)), out, ws)
+        torch.cuda.synchronize()
+        return out.float().cpu().numpy()
+
+    clean = attend(*pools)
+    assert np.isfinite(clean).all()
+    k, v = (p.clone() for p in pools)
+    for pool, requests in ((v, bad_v), (k, bad_k)):
+        for i, r in enumerate(requests):
+            pages = table[r, prefix // shape.page_size:(prefix + own[r] + shape.page_size - 1) // shape.page_size]
+            pool[torch.from_numpy(pages.astype(np.int64)).cuda()] = bad[i]
+    got = attend(k, v)
+    start = np.concatenate([[0], np.cumsum(q)])
+    for r in range(len(q)):
+        rows = slice(start[r], start[r + 1])
+        if r in bad_v + bad_k:
+            assert not np.isfinite(got[rows]).all()
+        else:
+            assert np.array_equal(got[rows], clean[rows]), r
