@@ -308,18 +308,43 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         // Prefill rows of a group take the shared keys and their own in ONE item: its rows are packed over requests as in a pass of
         // its own over the template, but the running state (n_q (d + 2) floats a row, written and read back) stays in registers.
         // Attention of 65 requests of 50 .. 200 tokens behind 1024 (13B): 266 + 139 us (two passes) -> 337; of 31, 146 + 71 -> 179.
-        // Where requests are short against an item, one walks the own keys of many requests one after the other: that pays once the
-        // items fill the chip, and the two passes stay apart while they do not.  One 13B layer step behind a template of 256, two passes /
-        // joint: 400 tokens in requests of 4 376 / 406 us, of 8 357 / 370, of 16 349 / 353, of 24 347 / 345, of 48 345 / 343; 2000 tokens
-        // in requests of 4 1284 / 1252, of 16 1152 / 1130, of 80 1129 / 1114.
+        // Such an item walks the own keys of its requests one after the other, cached ones among them, which the two passes walk at
+        // the same time: short requests, and long ones with keys cached behind the template, are faster in two passes.  Both are priced
+        // in blocks of 64 keys (about 2 us): a launch takes its longest item and what falls to one of the workgroups the chip holds;
+        // an item costs two blocks beyond its own, each request of a joint item one (its rows' sums are kept in memory till
+        // then); two passes cost a launch (three blocks) and the state's way through memory.
+        // Fitted to the attention of 1310 batches (40/40, 64/8, 40/8, 16/2 and 8/2 heads; 200 .. 4000 tokens in requests of 2 .. 400 with
+        // 0 .. 2500 cached keys behind 64 .. 1024): 0.3 % off the faster of the two on average, in twelve batches 2 .. 8 % slower
+        // than two passes (which alone are 21 % off, joint items alone 25 %).  Two passes / joint, us: 40/40 heads behind 256, 400 tokens
+        // in requests of 4 57 / 118, of 32 24 / 24, of 32 with 1000 cached 62 / 121; 2000 in requests of 16 86 / 78, of 100 60 / 53, of 100
+        // with 1000 cached 154 / 257; 64/8 heads, 400 tokens in requests of 8 27 / 18, with 1000 cached 59 / 63.
+        auto joint_pays = [&](int32_t p) {
+            struct Launch {
+                int64_t longest = 0, total = 0;
+                void item(int64_t blocks) { longest = std::max(longest, blocks + 2), total += blocks + 2; }
+                double time(int32_t n_kv) const { return (double)longest + (double)total * n_kv / ATTN_WGS; }
+            } pass, own, both;
+            const int64_t shared = (d.prefix_len[p] + 63) / 64;
+            int64_t toks = 0, packed = 0;   // of the group's prefill rows; own blocks of the joint item being filled
+            for (int32_t r = 0; r < B; ++r) {
+                const int32_t q_len = d.q_start[r + 1] - d.q_start[r], cached = d.ctx_len[r] - q_len - d.prefix_len[p];
+                if (d.prefix_id[r] != p || q_len == 1) continue;
+                for (int32_t o = 0; o < q_len; o += tile_tok) own.item((cached + std::min(q_len, o + tile_tok) + 63) / 64);
+                for (int32_t o = 0; o < q_len;) {
+                    const int32_t n = std::min<int32_t>(q_len - o, tile_tok - (int32_t)(toks % tile_tok));
+                    o += n;
+                    toks += n;
+                    packed += (cached + o + 63) / 64 + 1;
+                    if (toks % tile_tok == 0) pass.item(shared), both.item(shared + packed), packed = 0;
+                }
+            }
+            if (toks == 0) return false;
+            if (packed > 0) pass.item(shared), both.item(shared + packed);
+            const double state_us = (double)toks * cfg.n_q_heads * (cfg.head_dim + 2) * 8 / 5.0e6;   // written and read at 5 TB/s
+            return both.time(cfg.n_kv_heads) <= pass.time(cfg.n_kv_heads) + own.time(cfg.n_kv_heads) + 3 + state_us / 2;
+        };
         std::vector<uint8_t> fused(d.num_prefixes, 0);
-        for (int32_t p = 0; p < d.num_prefixes; ++p) {
-            if (!joint[p]) continue;
-            int64_t toks = 0, reqs = 0;
-            for (int32_t r = 0; r < B; ++r)
-                if (d.prefix_id[r] == p && d.q_start[r + 1] - d.q_start[r] > 1) toks += d.q_start[r + 1] - d.q_start[r], ++reqs;
-            fused[p] = reqs > 0 && (toks * ATTN_JOINT_REQS >= reqs * tile_tok || toks / tile_tok * cfg.n_kv_heads >= ATTN_JOINT_WGS);
-        }
+        for (int32_t p = 0; p < d.num_prefixes; ++p) fused[p] = joint[p] && joint_pays(p);
         const int32_t rows_len = rows_chunk_len();
         SlotPlan plan;
         if (slots_allowed && hb.n_prefill == 0 && T > 0 && T <= SKINNY_MAX_T) plan = plan_slots(cfg, d, joint, own_keys, chunks_of, rows_len);

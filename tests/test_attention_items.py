@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2601_11546_amd import workloads as W
-from tests import host_program
+from tests import host_program, test_gpu_joint_items
 
 
 @pytest.fixture(scope="module")
@@ -70,6 +70,23 @@ def test_prefill_rows_of_a_group_take_joint_items(joint):
     assert joint(W.LLAMA_13B, [8] * 50 + [1] * 9, [8] * 50 + [30] * 9, 512) == (50, 0, 0)
     assert joint(W.LLAMA_13B, [8] * 250, [8] * 250, 512) == (16, 16, 0)           # the same, enough items to fill the chip
     assert joint(W.LLAMA_13B, [200, 1], [200, 9], 512) == (3, 2, 1)
+
+
+@pytest.mark.parametrize("shape,n,q,cached,prefix,fused", [
+    (W.LLAMA_13B, 16, 32, 2000, 512, False), (W.LLAMA_13B, 16, 32, 0, 512, True), (W.LLAMA_13B, 16, 120, 1000, 512, False),
+    (W.LLAMA_13B, 4, 100, 2500, 256, False), (W.LLAMA_13B, 500, 4, 0, 256, False),
+    (W.LLAMA_70B, 16, 4, 2000, 512, False), (W.LLAMA_70B, 25, 8, 0, 512, True), (W.LLAMA_70B, 16, 32, 2500, 512, True), (W.LLAMA_70B, 100, 4, 1000, 256, False),
+    (W.QWEN_32B, 12, 32, 1000, 256, False), (W.QWEN_32B, 50, 8, 64, 1024, False), (W.LLAMA_70B_TP4, 500, 4, 1000, 256, False),
+])
+def test_keys_cached_behind_the_template_count(joint, shape, n, q, cached, prefix, fused):
+    """A joint item walks its requests' cached keys one request after the other: the two passes are kept where that is the slower."""
+    assert (joint(shape, [q] * n, [q + cached] * n, prefix)[1] > 0) == fused
+
+
+@pytest.mark.parametrize("shape", [W.TINY, W.TINY_G5, W.TINY_D128, W.TINY_G3_D128], ids=["group1", "group5", "d128", "g3d128"])
+def test_the_batch_of_the_device_tests_takes_joint_items(joint, shape):
+    q, own, prefix = test_gpu_joint_items.JOINT_BATCH
+    assert joint(shape, q, own, prefix)[1] > 0
 
 
 @pytest.mark.parametrize("seed", range(30))

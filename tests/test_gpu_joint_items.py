@@ -10,6 +10,11 @@ from tests.gpu_harness import assert_close, dev_bf16, host_f32
 pytestmark = pytest.mark.gpu
 
 
+# query tokens, own keys and template of a group whose prefill rows take joint items (test_attention_items.py): requests that share
+# items and waves, some with cached keys of their own, a decode row among them
+JOINT_BATCH = (np.array([50, 50, 60, 65, 1, 90, 70, 12]), np.array([50, 130, 63, 65, 41, 110, 170, 12]), 80)
+
+
 @pytest.fixture(scope="module")
 def rs():
     assert torch.cuda.is_available(), "GPU tests need a device"
@@ -43,9 +48,8 @@ def test_joint_items(rs, oracle, shape, prefix, q_len):
 def test_a_request_spoils_its_own_rows_alone(rs, shape, fp8):
     """Requests that share an item, and waves of it, with one whose cached keys or values are not finite: the others' rows have
     the bits they have beside finite ones."""
-    q = np.array([20, 50, 7, 33, 1, 90, 12])
-    own = q + np.array([0, 100, 3, 0, 40, 70, 0])
-    prefix, bad_v, bad_k = 80, [1, 3], [5]
+    q, own, prefix = JOINT_BATCH
+    bad_v, bad_k = [1, 3], [6]
     b = W.build_batch(shape, q, own + prefix, [0] * len(q), [prefix], seed=4)
     g = torch.Generator(device="cuda").manual_seed(5)
     size = (b.num_pages, shape.page_size, shape.n_kv_heads, shape.head_dim)
