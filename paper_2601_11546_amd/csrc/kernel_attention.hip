@@ -57,16 +57,26 @@ struct AttnArgs {
     float code_inv;    // > 0: out holds 8-bit codes of the bf16 output times code_inv (a quantised W_o reads them)
 };
 
-// Four consecutive output values to element `at` of out: bf16, or 8-bit codes of their bf16 values.  (A pass of its own that
-// read the bf16 output and wrote the codes took 4.9 us at
-// 128 rows and 10.6 at 3875 of the 13B shape.)
-__device__ __forceinline__ void store_out4(const AttnArgs& p, int64_t at, float a, float b, float c, float d) {
-    const uint2 u = make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
-    if (p.code_inv > 0.0f)
-        *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(p.out) + at) =
-            pack_fp8x4(bf16_lo(u.x) * p.code_inv, bf16_hi(u.x) * p.code_inv, bf16_lo(u.y) * p.code_inv, bf16_hi(u.y) * p.code_inv);
-    else
-        *reinterpret_cast<uint2*>(p.out + at) = u;
+// N quads of consecutive output values, quad q to element at + step q of out: bf16, or 8-bit codes of their bf16 values.  (A pass of
+// its own that read the bf16 output and wrote the codes took 4.9 us at 128 rows and 10.6 at 3875 of the 13B shape.)
+// The choice is made once for all of them: made at each store, it cost short items 10 % (1000 requests of 2 tokens, 13B).
+template <int N, typename Quad>
+__device__ __forceinline__ void store_out(const AttnArgs& p, int64_t at, int step, Quad quad) {
+    if (p.code_inv > 0.0f) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const float4 v = quad(q);
+            const uint2 u = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+            *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(p.out) + at + step * q) =
+                pack_fp8x4(bf16_lo(u.x) * p.code_inv, bf16_hi(u.x) * p.code_inv, bf16_lo(u.y) * p.code_inv, bf16_hi(u.y) * p.code_inv);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const float4 v = quad(q);
+            *reinterpret_cast<uint2*>(p.out + at + step * q) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+        }
+    }
 }
 
 // Per-lane running softmax state of one query row (shared by lanes l and l ^ 32, which hold
@@ -128,13 +138,11 @@ __device__ __forceinline__ void state_store(const RowState<D>& st, const AttnArg
         sums_store<D>(st, p, part_row, g);
     } else {
         const float inv = p.v_scale / l_tot;
-        const int64_t at = row_id * D + 4 * g;
-#pragma unroll
-        for (int td = 0; td < D / 32; ++td)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-                store_out4(p, at + 32 * td + 8 * q4, st.o[td][4 * q4] * inv, st.o[td][4 * q4 + 1] * inv, st.o[td][4 * q4 + 2] * inv,
-                           st.o[td][4 * q4 + 3] * inv);
+        store_out<D / 8>(p, row_id * D + 4 * g, 8, [&](int q) {
+            const f32x16_t& o = st.o[q / 4];
+            const int r = 4 * (q % 4);
+            return make_float4(o[r] * inv, o[r + 1] * inv, o[r + 2] * inv, o[r + 3] * inv);
+        });
     }
 }
 
@@ -768,9 +776,9 @@ __device__ __forceinline__ void attn_decode_body(const AttnArgs& p, const AttnIt
         return;
     }
     const float inv = p.v_scale / l_tot;
-#pragma unroll
-    for (int td = 0; td < TD; ++td)
-        store_out4(p, row_id * D + 4 * gq + 16 * td, o_acc[td][0] * inv, o_acc[td][1] * inv, o_acc[td][2] * inv, o_acc[td][3] * inv);
+    store_out<TD>(p, row_id * D + 4 * gq, 16, [&](int td) {
+        return make_float4(o_acc[td][0] * inv, o_acc[td][1] * inv, o_acc[td][2] * inv, o_acc[td][3] * inv);
+    });
 }
 
 // Finishes the decode rows whose keys were cut into chunks: with chunk states (m_c, l_c, O_c) in the log2 domain,
@@ -798,7 +806,7 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(AttnArgs p) {
         o.x = o.x * a + w * v.x; o.y = o.y * a + w * v.y; o.z = o.z * a + w * v.z; o.w = o.w * a + w * v.w;
     }
     const float inv = p.v_scale / L;
-    store_out4(p, ((int64_t)mi.tok * p.n_q + hq) * D + d0, o.x * inv, o.y * inv, o.z * inv, o.w * inv);
+    store_out<1>(p, ((int64_t)mi.tok * p.n_q + hq) * D + d0, 0, [&](int) { return make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv); });
 }
 
 template <int D, bool FP8>
