@@ -211,17 +211,12 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
     const bool joint = (it.flags & ITEM_JOINT) != 0;
     const int causal_lim = valid && (it.flags & (ITEM_CAUSAL | ITEM_JOINT)) ? p.tok_pos[tok] + 1 : it.key_end;
     int klim, wave_klim_max, wave_klim_min;   // first key this row does NOT see of the run of keys being walked; its extremes in the wave
-    auto set_limit = [&](int lim, bool row) {   // row: counts among the extremes
-        klim = lim;
-        wave_klim_max = row ? lim : 0;
-        wave_klim_min = row ? lim : INT_MAX;
+    klim = wave_klim_max = wave_klim_min = min(causal_lim, it.key_end);   // a joint item's rows all see its whole first run
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            wave_klim_max = max(wave_klim_max, __shfl_xor(wave_klim_max, o, 64));
-            wave_klim_min = min(wave_klim_min, __shfl_xor(wave_klim_min, o, 64));
-        }
-    };
-    set_limit(min(causal_lim, it.key_end), true);   // a joint item's rows all see its whole first run
+    for (int o = 32; o > 0; o >>= 1) {
+        wave_klim_max = max(wave_klim_max, __shfl_xor(wave_klim_max, o, 64));
+        wave_klim_min = min(wave_klim_min, __shfl_xor(wave_klim_min, o, 64));
+    }
     const bool wave_active = wave * 32 < it.n_tok * p.group;
 
     bf16x8_t qf[D / 16];
@@ -487,14 +482,18 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
             // the block loop, which has none left at D = 128.)  65 requests of 50 .. 200 tokens behind 1024, 13B layer: 4206 -> 4217 us.
             const int first = seg[4 * run_nxt - 1], n = seg[4 * run_nxt];
             mine = valid && ti >= first && ti < first + n;
-            if (__any(mine) && valid && ti >= first + n && !kept) {
+            const uint64_t rows = __ballot(mine);   // of this request in the wave
+            if (rows && valid && ti >= first + n && !kept) {
                 sums_store<D>(st, p, row, g);
                 kept = true;
             }
             if (mine && kept) sums_load<D>(st, p, row, g);
-            // rows past the item's end see no key and have no say: they made the whole wave take the mask in every block (40 query, 8 kv
-            // heads, 25 tokens to an item: 4 requests of 100 tokens with 2500 cached 88 -> 77 us)
-            set_limit(mine ? causal_lim : 0, valid);
+            // Positions rise along the rows of a request: its first and last row in the wave have the extremes.  (Ten lane exchanges, one
+            // behind the other, otherwise.)  Rows past the item's end see no key and have no say: they made the whole wave take the mask
+            // in every block (40 query, 8 kv heads, 25 tokens to an item: 4 requests of 100 tokens with 2500 cached 88 -> 77 us).
+            klim = mine ? causal_lim : 0;
+            wave_klim_max = rows ? __builtin_amdgcn_readlane(causal_lim, 63 - __builtin_clzll(rows)) : 0;
+            wave_klim_min = rows && !__any(valid && !mine) ? __builtin_amdgcn_readlane(causal_lim, __builtin_ctzll(rows)) : 0;
         }
         kb0 = kb0_nxt;
         run = run_nxt;
