@@ -188,7 +188,10 @@ typedef short short4_t __attribute__((ext_vector_type(4)));
 // FP8: the pools hold one byte per element (8-bit codes).  A block then goes global -> registers -> LDS: each lane loads
 // the 8 bytes of the chunk it would have received directly, widens them to bf16 (exact) and stores the 16 bytes where the
 // direct load would have put them, so that everything behind the staging is the 16-bit kernel.
-template <int D, bool FP8>
+// JOINT: items may be ITEM_JOINT.  Launches without such items take a body without what these need in the block loop and its registers:
+// with it they were up to 6 % slower where a CU holds one workgroup (16/2 heads, 4 requests of 100 tokens with 2500 cached keys
+// behind 1024 97 against 91 us).
+template <int D, bool FP8, bool JOINT>
 __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, int kvh) {
     using SM = TileSmem<D>;
     constexpr int BLOCK_N = SM::BLOCK_N;
@@ -208,8 +211,8 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
     const int ti = R / p.group;
     const int hq = kvh * p.group + (R - ti * p.group);
     const int tok = valid ? p.attn_tok[it.tok_off + ti] : 0;
-    const bool joint = (it.flags & ITEM_JOINT) != 0;
-    const int causal_lim = valid && (it.flags & (ITEM_CAUSAL | ITEM_JOINT)) ? p.tok_pos[tok] + 1 : it.key_end;
+    const bool joint = JOINT && (it.flags & ITEM_JOINT);
+    const int causal_lim = valid && (joint || (it.flags & ITEM_CAUSAL)) ? p.tok_pos[tok] + 1 : it.key_end;
     int klim, wave_klim_max, wave_klim_min;   // first key this row does NOT see of the run of keys being walked; its extremes in the wave
     klim = wave_klim_max = wave_klim_min = min(causal_lim, it.key_end);   // a joint item's rows all see its whole first run
 #pragma unroll
@@ -247,6 +250,7 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
             w_end = seg[4 * w_seg + 2];
             ++w_seg;
         }
+        if (!JOINT) w_kb = min(w_kb, it.key_end - 1);
     };
     const int lrow = lane / CH, lslot = lane % CH;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
@@ -254,11 +258,11 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
     // iteration later.  (The compiler places the wait for a load in front of its first use, and it does not count the
     // direct-to-LDS loads, which sit in inline assembly: arithmetic on a page number straight after the lookup would
     // wait for every load issued before it -- the next block's keys and values -- and undo the double buffer.)
-    struct Pages { int32_t page[IT]; int kb0, last, run; };
+    struct Pages { int32_t page[IT]; int kb0, last, run; };   // last key of the block's run (of the item, if it has but one)
     Pages pg_cur, pg_nxt;
     auto lookup = [&](Pages& pg) {   // block-table entries of this lane's rows
         pg.kb0 = w_kb;
-        pg.last = w_end - 1;
+        pg.last = (JOINT ? w_end : it.key_end) - 1;
         pg.run = w_seg;
 #pragma unroll
         for (int j = 0; j < IT; ++j) {
@@ -312,7 +316,7 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
         } else {
             issue(0, pg_cur);
         }
-        if (n_blocks > 1) advance();
+        if (!JOINT || n_blocks > 1) advance();
         lookup(pg_nxt);
     }
     // Operand addresses inside a stage that do not change from block to block.  K: key row
@@ -427,13 +431,13 @@ __device__ __forceinline__ void attn_tile_body(const AttnArgs& p, int item_idx, 
 #pragma unroll
         for (int j = 0; j < IT; ++j) asm volatile("" ::"v"(pg_nxt.page[j]));
         __syncthreads();
-        const int kb0_nxt = pg_nxt.kb0, run_nxt = pg_nxt.run;
+        const int kb0_nxt = JOINT ? pg_nxt.kb0 : kb0 + BLOCK_N, run_nxt = pg_nxt.run;
         if (b + 1 < n_blocks) {
             if (FP8)
                 load_raw(pg_nxt);                               // into registers; stored behind this block's arithmetic
             else
                 issue((b + 1) & 1, pg_nxt);
-            if (b + 2 < n_blocks) {
+            if (!JOINT || b + 2 < n_blocks) {
                 advance();
                 lookup(pg_nxt);                                 // consumed one iteration later
             }
@@ -808,9 +812,9 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(AttnArgs p) {
     store_out<1>(p, ((int64_t)mi.tok * p.n_q + hq) * D + d0, 0, [&](int) { return make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv); });
 }
 
-template <int D, bool FP8>
+template <int D, bool FP8, bool JOINT>
 __global__ void __launch_bounds__(256, 2) attn_tile_kernel(AttnArgs p) {
-    attn_tile_body<D, FP8>(p, blockIdx.x, blockIdx.y);
+    attn_tile_body<D, FP8, JOINT>(p, blockIdx.x, blockIdx.y);
 }
 
 template <int D, bool FP8>
@@ -822,12 +826,12 @@ __global__ void __launch_bounds__(256, 2) attn_decode_kernel(AttnArgs p) {
 // prefixes) and wave items (decode rows over their own keys) in ONE launch: the two item lists are independent, each alone
 // leaves part of the chip idle at its end, and both need the same registers and LDS.  Workgroups [0, n_items n_kv) take the tiled items (the longer ones), the rest the
 // decode items, four per workgroup.
-template <int D, bool FP8>
+template <int D, bool FP8, bool JOINT>
 __global__ void __launch_bounds__(256, 2) attn_own_keys_kernel(AttnArgs p) {
     const int n_tile_wg = p.n_items * p.n_kv;
     const int b = blockIdx.x;
     if (b < n_tile_wg) {
-        attn_tile_body<D, FP8>(p, b % p.n_items, b / p.n_items);
+        attn_tile_body<D, FP8, JOINT>(p, b % p.n_items, b / p.n_items);
     } else {
         attn_decode_body<D, FP8>(p, p.items_b, p.n_items_b, b - n_tile_wg);
     }
@@ -839,22 +843,22 @@ inline int decode_wgs(const AttnArgs& p, int n_items) {
 
 template <int D, bool FP8>
 hipError_t launch_d(const AttnArgs& base, const AttnItem* items, int32_t n_items, const AttnItem* items_b,
-                    int32_t n_items_b, bool decode, hipStream_t s) {
+                    int32_t n_items_b, bool decode, bool joint, hipStream_t s) {
     constexpr int tile_smem = 2 * TileSmem<D>::STAGE, dec_smem = 4 * DecodeSmem<D>::WAVE_BYTES;
     constexpr int both_smem = tile_smem > dec_smem ? tile_smem : dec_smem;
     // the dynamic-LDS limits are raised once per process, whichever host thread launches first
     static std::once_flag once;
     static hipError_t attr_status = hipSuccess;
     std::call_once(once, [] {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_tile_kernel<D, FP8>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, tile_smem);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_decode_kernel<D, FP8>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, dec_smem);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_own_keys_kernel<D, FP8>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, both_smem);
-        attr_status = e;
+        auto allow = [](auto kernel, int smem) {
+            if (attr_status == hipSuccess)
+                attr_status = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        };
+        allow(&attn_tile_kernel<D, FP8, false>, tile_smem);
+        allow(&attn_tile_kernel<D, FP8, true>, tile_smem);
+        allow(&attn_decode_kernel<D, FP8>, dec_smem);
+        allow(&attn_own_keys_kernel<D, FP8, false>, both_smem);
+        allow(&attn_own_keys_kernel<D, FP8, true>, both_smem);
     });
     if (attr_status != hipSuccess) return attr_status;
     AttnArgs p = base;
@@ -862,12 +866,17 @@ hipError_t launch_d(const AttnArgs& base, const AttnItem* items, int32_t n_items
     p.n_items = n_items;
     p.items_b = items_b;
     p.n_items_b = n_items_b;
-    if (items_b)
-        attn_own_keys_kernel<D, FP8><<<dim3(n_items * p.n_kv + decode_wgs(p, n_items_b)), dim3(256), both_smem, s>>>(p);
+    const dim3 both_grid(n_items * p.n_kv + (items_b ? decode_wgs(p, n_items_b) : 0)), block(256);
+    if (items_b && joint)
+        attn_own_keys_kernel<D, FP8, true><<<both_grid, block, both_smem, s>>>(p);
+    else if (items_b)
+        attn_own_keys_kernel<D, FP8, false><<<both_grid, block, both_smem, s>>>(p);
     else if (decode)
-        attn_decode_kernel<D, FP8><<<dim3(decode_wgs(p, n_items)), dim3(256), dec_smem, s>>>(p);
+        attn_decode_kernel<D, FP8><<<dim3(decode_wgs(p, n_items)), block, dec_smem, s>>>(p);
+    else if (joint)
+        attn_tile_kernel<D, FP8, true><<<dim3(n_items, p.n_kv), block, tile_smem, s>>>(p);
     else
-        attn_tile_kernel<D, FP8><<<dim3(n_items, p.n_kv), dim3(256), tile_smem, s>>>(p);
+        attn_tile_kernel<D, FP8, false><<<dim3(n_items, p.n_kv), block, tile_smem, s>>>(p);
     return hipGetLastError();
 }
 
@@ -903,10 +912,13 @@ hipError_t launch_attention(const BatchDev& b, const relserve_layer& L, const vo
     auto launch = [&](int slot, const AttnItem* items, int32_t n, const AttnItem* items_b, int32_t n_b, bool decode) {
         if (e != hipSuccess || n == 0) return;
         profile_mark(prof, slot, s, true);
+        const bool joint = items == b.items_tile && b.has_joint;
         if (kv.fp8)
-            e = d128 ? launch_d<128, true>(p, items, n, items_b, n_b, decode, s) : launch_d<64, true>(p, items, n, items_b, n_b, decode, s);
+            e = d128 ? launch_d<128, true>(p, items, n, items_b, n_b, decode, joint, s)
+                     : launch_d<64, true>(p, items, n, items_b, n_b, decode, joint, s);
         else
-            e = d128 ? launch_d<128, false>(p, items, n, items_b, n_b, decode, s) : launch_d<64, false>(p, items, n, items_b, n_b, decode, s);
+            e = d128 ? launch_d<128, false>(p, items, n, items_b, n_b, decode, joint, s)
+                     : launch_d<64, false>(p, items, n, items_b, n_b, decode, joint, s);
         profile_mark(prof, slot, s, false);
     };
     p.T = b.T;

@@ -314,10 +314,10 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         // an item costs two blocks beyond its own, each request of a joint item one (its rows' sums are kept in memory till
         // then); two passes cost a launch (three blocks) and the state's way through memory.
         // Fitted to the attention of 1310 batches (40/40, 64/8, 40/8, 16/2 and 8/2 heads; 200 .. 4000 tokens in requests of 2 .. 400 with
-        // 0 .. 2500 cached keys behind 64 .. 1024): 0.3 % off the faster of the two on average, in twelve batches 2 .. 8 % slower
-        // than two passes (which alone are 21 % off, joint items alone 25 %).  Two passes / joint, us: 40/40 heads behind 256, 400 tokens
-        // in requests of 4 57 / 118, of 32 24 / 24, of 32 with 1000 cached 62 / 121; 2000 in requests of 16 86 / 78, of 100 60 / 53, of 100
-        // with 1000 cached 154 / 257; 64/8 heads, 400 tokens in requests of 8 27 / 18, with 1000 cached 59 / 63.
+        // 0 .. 2500 cached keys behind 64 .. 1024): 0.3 % off the faster of the two on average, in twenty batches 2 .. 10 % slower
+        // than two passes (which alone are 20 % off, joint items alone 25 %).  Two passes / joint, us: 40/40 heads behind 256, 400 tokens
+        // in requests of 4 52 / 108, of 32 24 / 23, of 32 with 1000 cached 62 / 120; 2000 in requests of 16 82 / 73, of 100 61 / 53, of 100
+        // with 1000 cached 155 / 258; 64/8 heads, 400 tokens in requests of 8 28 / 18, with 1000 cached 59 / 62.
         auto joint_pays = [&](int32_t p) {
             struct Launch {
                 int64_t longest = 0, total = 0;
@@ -420,7 +420,7 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         for (int32_t p = 0; p < d.num_prefixes; ++p) {
             if (!joint[p]) continue;
             ++hb.n_groups;
-            if (fused[p]) joint_items(p);
+            if (fused[p]) joint_items(p), il.has_joint = true;
             auto in_pass = [&](int32_t r, int32_t p) { return d.prefix_id[r] == p && !(fused[p] && d.q_start[r + 1] - d.q_start[r] > 1); };
             const int32_t start = (int32_t)il.attn_tok.size();
             for (int32_t r = 0; r < B; ++r)
@@ -699,6 +699,7 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
         v.n_items_tile = (int32_t)il.items_tile.size();
         v.n_items_split = (int32_t)il.items_split.size();
         v.n_merge = (int32_t)il.merge_items.size();
+        v.has_joint = il.has_joint;
         v.n_scratch_slots = il.n_scratch_slots;
     };
     view_lists(dv, o_items, hb.items);

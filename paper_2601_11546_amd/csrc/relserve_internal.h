@@ -69,6 +69,7 @@ struct BatchDev {
     const AttnItem* items_split;   // wave items (decode rows, or chunks of their keys)
     const MergeItem* merge_items;  // decode rows cut into chunks
     int32_t n_items_prefix, n_items_tile, n_items_split, n_merge;
+    bool has_joint;              // items_tile holds joint items
     int32_t n_scratch_slots;     // > 0: the partial state lives in that many slots of the GEMM scratch, not in rows of part_o
 };
 
@@ -104,6 +105,7 @@ struct ItemLists {
     std::vector<int32_t> attn_tok;
     std::vector<AttnItem> items_prefix, items_tile, items_split;
     std::vector<MergeItem> merge_items;
+    bool has_joint = false;
     int32_t n_scratch_slots = 0;
     bool in_slots = false;       // parts of rows behind a template are kept in slots (of the GEMM scratch if n_scratch_slots > 0)
 };
