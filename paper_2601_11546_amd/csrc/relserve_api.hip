@@ -284,7 +284,7 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         // few workgroups that walk the whole template one block after the other, with the own keys waiting behind it.
         // Attention of a 13B layer, template of 512: 4 rows 13.5 + 11.8 us (prefix pass, own keys) -> 8.7 + 4.5 (launch,
         // merge), 24 rows 14.4 + 14.2 -> 13.9 + 4.7; 70B shape, 256 rows, templates of 768: 26.4 + 76.2 + 5.1 -> 82.0 + 6.5.
-        // With prefill rows in the batch the partial states are the larger part of the traffic and the passes stay apart.
+        // (Batches with prefill rows: below.)
         // Without slots, decode rows with many own keys are cut into chunks too (one wave item each, merged afterwards), so that
         // one long context does not set the kernel's duration and the waves come in several even rounds.  The chunk length is
         // the smallest of 128 .. 1024 keys whose chunks fit the partial-state slots of the workspace.
@@ -351,16 +351,20 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
 
         // Decode rows behind a template in a batch that prefills too: the template is an item of the one launch as well, its state and
         // those of the rows' own keys in the workspace's slots (T + ..), and the merge finishes the rows.  As a launch of its own
-        // it was few workgroups with everything else waiting.
+        // it was few workgroups with everything else waiting.  With many rows that launch fills the chip, and the second state of every
+        // row and the merge cost more than it: attention of 200 / 500 / 1000 / 2000 rows of about 150 own keys behind 512 beside a
+        // chunk of 512 tokens, launch of its own -> one launch, us: 64/8 heads 58 -> 44, 95 -> 98, 155 -> 168, 286 -> 304; 40/40
+        // 132 -> 122, 286 -> 287, 532 -> 553, 1042 -> 1098.  So up to 8 MB of state; over 1560 batches of four shapes that is 1.4 % off the
+        // faster of the two on average (15 % with none), in twelve of them 2 .. 5 % slower than the launch of its own.
         bool mixed = slots_allowed && hb.n_prefill > 0 && hb.n_decode > 0;
-        bool behind = false;
+        int64_t behind = 0;
         for (int32_t r = 0; r < B; ++r) {
             const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
             if (pid < 0 || !joint[pid]) continue;
-            if (d.q_start[r + 1] - d.q_start[r] == 1) behind = true;
+            if (d.q_start[r + 1] - d.q_start[r] == 1) ++behind;
             else if (!fused[pid]) mixed = false;     // its rows read a state that an earlier launch has to leave
         }
-        mixed &= behind;
+        mixed &= behind > 0 && behind * cfg.n_q_heads * cfg.head_dim <= ATTN_MIXED_FLOATS;
         if (mixed) {
             plan.prefix_chunks.assign(d.num_prefixes, 1);
             plan.prefix_len.assign(d.prefix_len, d.prefix_len + d.num_prefixes);

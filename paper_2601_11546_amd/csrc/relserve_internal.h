@@ -125,6 +125,7 @@ int32_t expand_batch(const relserve_layer_config& cfg, const relserve_batch_desc
 // Rows of queries one attention workgroup covers (4 waves x 32 MFMA columns).
 constexpr int ATTN_BLOCK_M = 128;
 constexpr int ATTN_WGS = 512;            // workgroups of the row-tiled kernel the chip holds: 256 CUs x 2
+constexpr int64_t ATTN_MIXED_FLOATS = 1 << 21;   // state of decode rows behind templates up to which mixed batches keep it in slots
 constexpr int64_t GEMM_TAIL_FLOATS = 256 * 65536;      // GEMM scratch at T > 256: partial tiles of one round of split 256 x 256 tiles
 constexpr int ATTN_SPLIT_ROWS = 16;   // query heads per kv head the decode kernel's 16-column MFMA holds
 

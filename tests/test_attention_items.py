@@ -83,6 +83,13 @@ def test_keys_cached_behind_the_template_count(joint, shape, n, q, cached, prefi
     assert (joint(shape, [q] * n, [q + cached] * n, prefix)[1] > 0) == fused
 
 
+@pytest.mark.parametrize("shape,rows,slots", [(W.LLAMA_13B, 100, 1), (W.LLAMA_13B, 409, 1), (W.LLAMA_13B, 410, 0), (W.LLAMA_70B, 256, 1), (W.LLAMA_70B, 257, 0),
+                                              (W.LLAMA_70B_TP4, 1024, 1), (W.LLAMA_70B_TP4, 2000, 0)])
+def test_many_decode_rows_keep_the_pass_over_their_template(joint, shape, rows, slots):
+    """Beside prefill rows: a second state for every row is dearer than a launch that fills the chip."""
+    assert joint(shape, [90] * 16 + [1] * rows, [90] * 16 + [60] * rows, 512)[1:] == (joint(shape, [90] * 16, [90] * 16, 512)[1], slots)
+
+
 @pytest.mark.parametrize("shape", [W.TINY, W.TINY_G5, W.TINY_D128, W.TINY_G3_D128], ids=["group1", "group5", "d128", "g3d128"])
 def test_the_batch_of_the_device_tests_takes_joint_items(joint, shape):
     q, own, prefix = test_gpu_joint_items.JOINT_BATCH
