@@ -910,11 +910,17 @@ __device__ __forceinline__ void code_scale(float4& v, const GemmArgs& p, const f
     if (p.w_scale) v.x *= f.x, v.y *= f.y, v.z *= f.z, v.w *= f.w;
 }
 
-// blockIdx.y = token, blockIdx.x = 256 of its units (a unit: 4 consecutive features, or a pair of such quads that the
-// epilogue combines)
+// A unit: 4 consecutive features, or a pair of such quads that the epilogue combines.  flat_units = 0: blockIdx.y = token, blockIdx.x =
+// 256 of its units.  Where a token's units do not fill workgroups (flat_units > 0: their number) the units of all tokens are one run:
+// with a workgroup per token, 7980 rows of 256 features took 5.8 us instead of 5.2.
 template <int EPI, int D>
-__global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p) {
-    const int t = blockIdx.y, u = blockIdx.x * 256 + threadIdx.x;
+__global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p, int flat_units) {
+    int t = blockIdx.y, u = blockIdx.x * 256 + threadIdx.x;
+    if (flat_units > 0) {
+        t = u / flat_units;
+        u -= t * flat_units;
+        if (t >= p.T) return;
+    }
     const int64_t stride = (int64_t)p.T * p.N;
     const float* row = p.accum + (int64_t)t * p.N;
     if (EPI == EPI_SWIGLU) {
@@ -1244,7 +1250,9 @@ hipError_t launch_split(GemmArgs p, int splits, hipStream_t s, NextNorm* next = 
         units = (p.n_q + p.n_kv) * (D / 8) + p.n_kv * (D / 4);
     else
         units = p.N / 4;
-    gemm_finish_kernel<EPI, D><<<dim3((units + 255) / 256, p.T), dim3(256), 0, s>>>(p);
+    const bool flat = units % 256 != 0;   // (the split paths bound tokens x features by 2^24)
+    gemm_finish_kernel<EPI, D><<<flat ? dim3((unsigned)(((int64_t)p.T * units + 255) / 256)) : dim3(units / 256, p.T), dim3(256), 0, s>>>(
+        p, flat ? units : 0);
     return hipGetLastError();
 }
 
