@@ -1018,9 +1018,12 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p, int flat_u
 // The row's place in the LDS has its own length: with 32 KB for every row 128 decode rows and a 512-token chunk took 1 % longer.
 // A thread owns one chunk of 8 features (N <= 8192).  The sum of squares runs in rmsnorm_kernel's order -- 256 threads, chunk
 // after chunk, from the row in LDS -- so that the normed values have the same bits on both paths.
-// Many rows are narrow ones here (the split path bounds rows x columns), and their workgroups mostly idle threads: rows of 256, finish +
-// norm / fused: 2496 4.3 + 4.0 / 6.3, 3621 4.2 + 4.2 / 9.7, 4744 3.0 + 5.3 / 11.7.
-constexpr int FINISH_NORM_MAX_N = 8192, FINISH_NORM_MAX_T = 2560;
+// Narrow rows leave most of a workgroup's threads (256 at least) without a chunk, which counts once the rows fill the chip.  A layer step,
+// finish + norm / fused, us: 1000 rows of 128 56.3 / 54.8, 256 62.0 / 60.5, 512 72.4 / 70.8, 1024 84.5 / 82.8; 1500 69.5 / 69.7, 67.8 / 68.2,
+// 76.6 / 76.4, 88.5 / 89.2; 2500 68.6 / 69.9, 75.4 / 76.2, 86.7 / 87.5, 102.7 / 102.6.  (3500: 72.7 / 75.3, 82.6 / 84.7, 93.6 / 95.3,
+// 114.8 / 113.4: of 1024 features on it would still pay.)
+constexpr int FINISH_NORM_MAX_N = 8192;
+constexpr int finish_norm_max_rows(int n) { return n >= 1024 ? 2560 : 1280; }
 template <int EPI>
 __global__ void __launch_bounds__(1024) gemm_finish_norm_kernel(GemmArgs p, const uint16_t* __restrict__ norm_w, float eps,
                                                                 uint16_t* __restrict__ norm_out, float code_inv) {
@@ -1234,7 +1237,7 @@ hipError_t launch_split(GemmArgs p, int splits, hipStream_t s, NextNorm* next = 
     hipError_t e = p.f8 ? go(std::true_type{}) : go(std::false_type{});
     if (e != hipSuccess) return e;
     if constexpr (EPI == EPI_RES_BF16_OUT_F32 || EPI == EPI_RES_F32_OUT_BF16) {
-        if (next && p.N % 8 == 0 && p.N <= FINISH_NORM_MAX_N && p.T <= FINISH_NORM_MAX_T) {
+        if (next && p.N % 8 == 0 && p.N <= FINISH_NORM_MAX_N && p.T <= finish_norm_max_rows(p.N)) {
             const int threads = std::max(256, (p.N / 8 + 63) / 64 * 64);
             const float code_inv = next->code_scale > 0.0f ? (float)(1.0 / (double)next->code_scale) : 0.0f;   // as launch_rmsnorm
             gemm_finish_norm_kernel<EPI><<<dim3(p.T), dim3(threads), p.N * sizeof(float), s>>>(p, static_cast<const uint16_t*>(next->w), next->eps,
