@@ -6,7 +6,7 @@
 // the tokens the column index, so that an accumulator quad holds 4 consecutive output
 // features of one token (one 8/16-byte store).
 //
-// Workgroup = a grid of waves (2 x 2 in production) over a BM (tokens) x BN (features) tile, BK = 64.
+// Workgroup = a grid of 2 x 2 waves over a BM (tokens) x BN (features) tile, BK = 64.
 // Main kernel (gemm_dma_kernel, K % 64 == 0): tiles go global -> LDS directly, XOR-swizzled 16-byte
 // chunks, two or three stages, one barrier per k iteration, every k step issued in a fixed order that
 // slots the refill loads and the next fragment reads between the MFMAs.  Fallback kernel
@@ -193,10 +193,11 @@ __device__ __forceinline__ void store_unit(const GemmArgs& p, int t, int n_lo, i
 // accumulators leaving no registers for more (they spilled; now nothing does with four waves).
 // 13B layer, T = 7963: q/k/v 1056 -> 967 us, W_o 384 -> 353, W_down 894 -> 861, gate/up 1680 -> 1650; on 8-bit operands at
 // T = 3875 q/k/v 317 -> 279 us, W_down with its tail 278 -> 253.
-template <int BN, int WGN>
+constexpr int WGM = 2, WGN = 2;   // grid of waves over a tile
+template <int BN>
 constexpr int epi_wave_bytes() { return 32 * (BN / WGN) * 4; }
 
-template <int BM, int BN, int EPI, int D, int WGM = 2, int WGN = 2, int TMX = BM / (32 * WGM), bool SC = false>
+template <int BM, int BN, int EPI, int D, int TMX = BM / (32 * WGM), bool SC = false>
 __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * WGN)][TMX], const GemmArgs& p,
                                               int tile_m, int tile_n, int wm, int wn, int l32, int g, int tm_base,
                                               int split, unsigned char* lds) {
@@ -430,8 +431,8 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs p) {
         if (more) store_lds((kt + 1) & 1);
         __syncthreads();
     }
-    static_assert(4 * epi_wave_bytes<BN, 2>() <= 2 * STAGE, "the epilogue's rows fit the stages");
-    gemm_epilogue<BM, BN, EPI, D>(acc, p, tile_m, tile_n, wm, wn, l32, g, 0, 0, smem + wave * epi_wave_bytes<BN, 2>());
+    static_assert(4 * epi_wave_bytes<BN>() <= 2 * STAGE, "the epilogue's rows fit the stages");
+    gemm_epilogue<BM, BN, EPI, D>(acc, p, tile_m, tile_n, wm, wn, l32, g, 0, 0, smem + wave * epi_wave_bytes<BN>());
 }
 
 // ------------------------------------------------------------------------------------------
@@ -462,7 +463,6 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
 }
 
 // BKD = k extent of one LDS stage (64 or 32), NS = stages in the ring (NS - 1 are in flight).
-// WGM x WGN = grid of waves over the tile.
 // WNT: the weights are loaded with the non-temporal hint (launches in which no other workgroup reads them again).
 // F8: both operands hold 8-bit codes.  Nothing changes in how bytes travel (K counts pairs of codes, a stage row is
 // still 128 bytes); a k step covers 32 bytes of every row instead of 16, as one 32x32x64 MFMA whose operand is the
@@ -477,7 +477,7 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
 // q/k/v 109 -> 98.  Small tiles have four to six whole stages and gain nothing (128 x 128 gate/up 67.6 -> 72).
 constexpr int weight_stages(int bm, int bn, int ns) { return bm >= 192 && ns <= 3 && (ns * (bm + bn) + bn) * 128 <= 160 * 1024 ? ns + 1 : ns; }
 
-template <int BM, int BN, int EPI, int D, int BKD, int NS, int WGM = 2, int WGN = 2, bool WNT = false, bool F8 = false, int NSW = NS>
+template <int BM, int BN, int EPI, int D, int BKD, int NS, bool WNT = false, bool F8 = false, int NSW = NS>
 __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     constexpr bool SKEW = NSW > NS;
     static_assert(NSW == NS || NSW == NS + 1, "weight ring");
@@ -717,6 +717,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // then reads 96 KB of fragments per k step of 1024 cycles beside the 32 KB that land, all the LDS delivers; four waves read
     // 64 KB.  13B layer at T = 3875 on codes: eight waves 1257 us, with the skewed ring too; four 1231, skewed 1194.)
     constexpr bool FIXED = NM >= 6 && !(EPI == EPI_SWIGLU && BM == 128);
+    static_assert(!SKEW || FIXED, "the skewed ring's weights are issued in the fixed order only");
     Stage cur{0, 0};  // stage being computed
     // One k iteration (one LDS stage).  refill_open: the refill begun at the previous hand-over is still being
     // issued; refill_next: this iteration's hand-over starts another one.
@@ -729,14 +730,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             } else {
                 load_frags((ks + 1) & 1, cur, ks + 1);
 #pragma unroll
-                for (int i = 0; i < NM; ++i) {
-                    mfma_one(ks & 1, i);
-                    if (SKEW && on(refill_open)) {
-                        const int d_lo = A_IT + ks * W_IT / (KSTEPS - 1), d_n = A_IT + (ks + 1) * W_IT / (KSTEPS - 1) - d_lo;
-#pragma unroll
-                        for (int d = d_lo + i * d_n / NM; d < d_lo + (i + 1) * d_n / NM; ++d) issue_one(d);
-                    }
-                }
+                for (int i = 0; i < NM; ++i) mfma_one(ks & 1, i);
             }
         }
         // Last k step of the stage: all its fragments are in registers.  Wait for the next stage (the
@@ -758,7 +752,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         if (FIXED) {
             k_step(LB, nxt, 0, 0, refill_next);
         } else {
-            constexpr int FIRST = SKEW ? A_IT : LOADS;   // issued here; the skewed ring's weights follow in the next iteration
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
@@ -766,7 +759,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
                 __builtin_amdgcn_sched_barrier(0);
                 if (on(refill_next)) {
 #pragma unroll
-                    for (int d = i * FIRST / NM; d < (i + 1) * FIRST / NM; ++d) issue_one(d);
+                    for (int d = i * LOADS / NM; d < (i + 1) * LOADS / NM; ++d) issue_one(d);
                 }
                 if (i >= NM / 2) {
 #pragma unroll
@@ -807,18 +800,18 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         return;
     }
     if constexpr (EPI != EPI_SLAB) {   // the epilogue takes over the ring: every wave is done with it
-        static_assert(NW * epi_wave_bytes<BN, WGN>() <= NS * A_BYTES + NSW * W_BYTES, "the epilogue's rows fit the ring");
+        static_assert(NW * epi_wave_bytes<BN>() <= NS * A_BYTES + NSW * W_BYTES, "the epilogue's rows fit the ring");
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __syncthreads();
     }
-    gemm_epilogue<BM, BN, EPI, D, WGM, WGN, TM, F8>(acc, p, tile_m, tile_n, wm, wn, l32, g, 0, split,
-                                                    smem + wave * epi_wave_bytes<BN, WGN>());
+    gemm_epilogue<BM, BN, EPI, D, TM, F8>(acc, p, tile_m, tile_n, wm, wn, l32, g, 0, split,
+                                                    smem + wave * epi_wave_bytes<BN>());
 }
 
 // Second half of a tail split: workgroup (tail tile, row tm of accumulator tiles) has the thread layout of
 // the GEMM workgroup that wrote the slabs, adds its part of the tile's slabs in split order (so the sum
 // does not depend on scheduling) and runs the GEMM's own epilogue on it.
-template <int BM, int BN, int EPI, int D, int WGM, int WGN, bool SC = false>
+template <int BM, int BN, int EPI, int D, bool SC = false>
 __global__ void __launch_bounds__(64 * WGM * WGN) gemm_tail_finish_kernel(GemmArgs p) {
     constexpr int NW = WGM * WGN, NT = 64 * NW, TM = BM / (32 * WGM), TN = BN / (32 * WGN), AREA4 = BM * BN / 4;
     typedef float vec4_t __attribute__((ext_vector_type(4)));
@@ -848,9 +841,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_tail_finish_kernel(GemmAr
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[tn][0][4 * c + e] += v[tn][c][e];
     }
-    __shared__ __align__(16) unsigned char rows[NW * epi_wave_bytes<BN, WGN>()];
-    gemm_epilogue<BM, BN, EPI, D, WGM, WGN, 1, SC>(acc, p, tile_m, tile_n, wm, wn, l32, g, tm_sel, 0,
-                                                   rows + wave * epi_wave_bytes<BN, WGN>());
+    __shared__ __align__(16) unsigned char rows[NW * epi_wave_bytes<BN>()];
+    gemm_epilogue<BM, BN, EPI, D, 1, SC>(acc, p, tile_m, tile_n, wm, wn, l32, g, tm_sel, 0,
+                                                   rows + wave * epi_wave_bytes<BN>());
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1230,8 +1223,8 @@ hipError_t launch_split(GemmArgs p, int splits, hipStream_t s, NextNorm* next = 
         constexpr bool F8 = decltype(f8)::value;
         static std::once_flag once;
         static hipError_t attr_status = hipSuccess;
-        if (hipError_t e = allow_smem_once(once, attr_status, &gemm_dma_kernel<BM, BN, EPI_SLAB, 0, 64, NS, 2, 2, WNT, F8, NSW>, smem)) return e;
-        gemm_dma_kernel<BM, BN, EPI_SLAB, 0, 64, NS, 2, 2, WNT, F8, NSW><<<dim3(p.tiles_m * p.tiles_n * splits), dim3(256), smem, s>>>(p);
+        if (hipError_t e = allow_smem_once(once, attr_status, &gemm_dma_kernel<BM, BN, EPI_SLAB, 0, 64, NS, WNT, F8, NSW>, smem)) return e;
+        gemm_dma_kernel<BM, BN, EPI_SLAB, 0, 64, NS, WNT, F8, NSW><<<dim3(p.tiles_m * p.tiles_n * splits), dim3(256), smem, s>>>(p);
         return hipGetLastError();
     };
     hipError_t e = p.f8 ? go(std::true_type{}) : go(std::false_type{});
@@ -1286,8 +1279,8 @@ hipError_t launch_skinny_whole(GemmArgs p, hipStream_t s) {
         constexpr bool F8 = decltype(f8)::value;
         static std::once_flag once;
         static hipError_t attr_status = hipSuccess;
-        if (hipError_t e = allow_smem_once(once, attr_status, &gemm_dma_kernel<BM, BN, EPI, D, BKD, NS, 2, 2, WNT, F8, NSW>, smem)) return e;
-        gemm_dma_kernel<BM, BN, EPI, D, BKD, NS, 2, 2, WNT, F8, NSW><<<dim3(p.tiles_m * p.tiles_n), dim3(256), smem, s>>>(p);
+        if (hipError_t e = allow_smem_once(once, attr_status, &gemm_dma_kernel<BM, BN, EPI, D, BKD, NS, WNT, F8, NSW>, smem)) return e;
+        gemm_dma_kernel<BM, BN, EPI, D, BKD, NS, WNT, F8, NSW><<<dim3(p.tiles_m * p.tiles_n), dim3(256), smem, s>>>(p);
         return hipGetLastError();
     };
     return p.f8 ? go(std::true_type{}) : go(std::false_type{});
@@ -1388,7 +1381,7 @@ bool small_applies(const GemmArgs& p, int epi, int head_dim = 0) {
 // What a launch does beyond whole tiles: the last tail_tiles tiles split their k range over `splits` workgroups.
 struct Plan { int cand, tail_tiles, splits; };
 
-template <int BM, int BN, int EPI, int D = 0, int WGM = 2, int WGN = 2>
+template <int BM, int BN, int EPI, int D = 0>
 hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Plan{0, 0, 1}) {
     GemmArgs p = base;
     p.tiles_m = (p.T + BM - 1) / BM;
@@ -1421,14 +1414,14 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
         constexpr bool F8 = decltype(f8)::value;
         static std::once_flag once_dma;
         static hipError_t st_dma = hipSuccess;
-        if (hipError_t e = allow_smem_once(once_dma, st_dma, &gemm_dma_kernel<BM, BN, EPI, D, DMA_BK, DMA_NS, WGM, WGN, false, F8, DMA_NSW>, dma_smem))
+        if (hipError_t e = allow_smem_once(once_dma, st_dma, &gemm_dma_kernel<BM, BN, EPI, D, DMA_BK, DMA_NS, false, F8, DMA_NSW>, dma_smem))
             return e;
-        gemm_dma_kernel<BM, BN, EPI, D, DMA_BK, DMA_NS, WGM, WGN, false, F8, DMA_NSW>
+        gemm_dma_kernel<BM, BN, EPI, D, DMA_BK, DMA_NS, false, F8, DMA_NSW>
             <<<dim3(grid), dim3(64 * WGM * WGN), dma_smem, s>>>(p);
         if (p.tail_tiles > 0) {
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
-            gemm_tail_finish_kernel<BM, BN, EPI, D, WGM, WGN, F8>
+            gemm_tail_finish_kernel<BM, BN, EPI, D, F8>
                 <<<dim3(p.tail_tiles * (BM / (32 * WGM))), dim3(64 * WGM * WGN), 0, s>>>(p);
         }
         return hipGetLastError();

@@ -18,7 +18,8 @@ inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 const char* const kSlotNames[RELSERVE_PROFILE_SLOTS] = {
     "rmsnorm_in", "gemm_qkv_rope_append", "attn_own_keys", "attn_prefix", "attn_tile", "attn_split",
     "gemm_o",     "rmsnorm_post", "gemm_gate_up", "gemm_down",  "attn_merge", "quantise_attn"};
-enum { S_NORM1 = 0, S_QKV, S_ATTN_OWN, S_ATTN_PREFIX, S_ATTN_TILE, S_ATTN_SPLIT, S_O, S_NORM2, S_GU, S_DOWN, S_ATTN_MERGE, S_QUANT };
+// the last slot stays empty: the attention kernels store a quantised step's codes themselves (slots and names are part of the interface)
+enum { S_NORM1 = 0, S_QKV, S_ATTN_OWN, S_ATTN_PREFIX, S_ATTN_TILE, S_ATTN_SPLIT, S_O, S_NORM2, S_GU, S_DOWN, S_ATTN_MERGE };
 
 struct Workspace {
     char* h;         // [T, H] bf16 (normed activations; reused for the post norm)
