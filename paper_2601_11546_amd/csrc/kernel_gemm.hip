@@ -1441,7 +1441,8 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
 //
 // 2. The shape of whole tiles: any gives the same bits, so where nothing is split the fastest one runs (whole_tile).  For the
 // SwiGLU projection that is the shape the cut's own model names: 0.0 % (16-bit) and 0.4 % (8-bit) off the fastest one on average
-// at hidden sizes of 5120 and more, 1.2 and 2.6 % at smaller ones (profiles/gemm_whole_tiles.txt).
+// at hidden sizes of 5120 and more, 1.2 and 2.6 % at smaller ones (profiles/gemm_whole_tiles.txt; measured before the tiles of
+// 192 and 256 rows kept a third stage of weights, and not again since).
 struct TileCand { int bm, bn, wg_per_cu; float eff_cut, eff; bool qkv; };   // qkv: usable by the fused q/k/v epilogue (128 features per wave)
 constexpr TileCand kTiles[] = {
     // eff: fitted to the times of every whole tile shape, forced, of the other projections that split nothing, five layer shapes

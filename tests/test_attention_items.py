@@ -94,6 +94,8 @@ def test_many_decode_rows_keep_the_pass_over_their_template(joint, shape, rows, 
 def test_the_batch_of_the_device_tests_takes_joint_items(joint, shape):
     q, own, prefix = test_gpu_joint_items.JOINT_BATCH
     assert joint(shape, q, own, prefix)[1] > 0
+    more_q, more_own = test_gpu_joint_items.TWO_PASSES
+    assert joint(shape, [*q, *more_q], [*own, *more_own], prefix)[1:] == (0, 0)
 
 
 @pytest.mark.parametrize("seed", range(30))

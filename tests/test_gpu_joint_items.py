@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2601_11546_amd import workloads as W
-from tests.gpu_harness import assert_close, dev_bf16, host_f32
+from tests.gpu_harness import assert_close, dev_bf16, host_bits, host_f32
 
 pytestmark = pytest.mark.gpu
 
@@ -13,6 +13,9 @@ pytestmark = pytest.mark.gpu
 # query tokens, own keys and template of a group whose prefill rows take joint items (test_attention_items.py): requests that share
 # items and waves, some with cached keys of their own, a decode row among them
 JOINT_BATCH = (np.array([50, 50, 60, 65, 1, 90, 70, 12]), np.array([50, 130, 63, 65, 41, 110, 170, 12]), 80)
+# query tokens and own keys of requests with which the same group takes two passes: their cached keys, one request after the other
+# in a joint item, would take too long
+TWO_PASSES = (np.array([4] * 4), np.array([1500] * 4))
 
 
 @pytest.fixture(scope="module")
@@ -86,3 +89,52 @@ def test_a_request_spoils_its_own_rows_alone(rs, shape, fp8):
             assert not np.isfinite(got[rows]).all()
         else:
             assert np.array_equal(got[rows], clean[rows]), r
+
+
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+@pytest.mark.parametrize("shape", [W.TINY, W.TINY_G5, W.TINY_D128, W.TINY_G3_D128], ids=["group1", "group5", "d128", "g3d128"])
+def test_joint_items_have_the_two_passes_bits(rs, oracle, shape, fp8):
+    """The attention of the same requests, over the same pages, in joint items and (beside others) in two passes, and the oracle's."""
+    q, own, prefix = JOINT_BATCH
+    n = len(q)
+    q_all, own_all = np.concatenate([q, TWO_PASSES[0]]), np.concatenate([own, TWO_PASSES[1]])
+    both = W.build_batch(shape, q_all, own_all + prefix, [0] * len(q_all), [prefix], seed=6)
+    alone = both.select(range(n))
+    g = torch.Generator(device="cuda").manual_seed(7)
+    size = (both.num_pages, shape.page_size, shape.n_kv_heads, shape.head_dim)
+    if fp8:
+        kd, vd = (torch.randint(0, 96, size, generator=g, device="cuda", dtype=torch.uint8) for _ in "kv")
+        pools = rs.QuantPool(kd, 0.125), rs.QuantPool(vd, 0.07)
+        kp, vp = kd.cpu().numpy(), vd.cpu().numpy()
+    else:
+        kd, vd = pools = [torch.randn(*size, generator=g, device="cuda").bfloat16() for _ in "kv"]
+        kp, vp = host_bits(kd), host_bits(vd)
+    qs = torch.randn(both.T, shape.q_dim, generator=g, device="cuda").bfloat16()
+    layer = rs.relserve_layer_create(shape)
+
+    def attend(b):
+        pb = rs.relserve_batch_prepare(layer, b)
+        ws = torch.full((rs.relserve_workspace_bytes(layer, b.T),), 0xff, dtype=torch.uint8, device="cuda")
+        out = torch.zeros(b.T, shape.q_dim, dtype=torch.bfloat16, device="cuda")
+        rs.relserve_attention(layer, pb, qs, shape.q_dim, *pools, out, ws)
+        return host_f32(out)
+
+    joint, passes = attend(alone), attend(both)
+    start = np.concatenate([[0], np.cumsum(q)])
+    qf = host_f32(qs)
+    past = np.repeat(own + prefix - q, q) + np.arange(alone.T) - np.repeat(start[:-1], q)   # position of every query token
+    for r in range(n):
+        rows = slice(start[r], start[r + 1])
+        if q[r] > 1:
+            assert np.array_equal(joint[rows], passes[rows]), r
+        else:
+            # a decode row's two states are merged in the one and one state runs on in the other: fp32 sums either way, but the
+            # probabilities are rounded to bf16 against other reference values: 2^-9 of a weighted mean of |v| on each side, and the
+            # output's own rounding, 2^-9 of it on each side
+            v_max = float((vd.view(torch.float8_e4m3fn).float() * 0.07 if fp8 else vd.float()).abs().max())
+            assert (np.abs(joint[rows] - passes[rows]) <= 2.0 ** -8 * (v_max + np.abs(passes[rows]))).all(), r
+        for t in (start[r], start[r + 1] - 1):
+            args = (shape, alone, r, int(past[t]), qf[t].reshape(shape.n_q_heads, -1), kp, vp)
+            want = oracle.attention_token_fp8kv(*args, 0.125, 0.07) if fp8 else oracle.attention_token(*args)
+            # the attention stage's bar
+            assert_close(joint[t], want.reshape(-1), f"request {r}, token {t}", max_abs=2e-2, rel_l2=1e-2)
