@@ -314,17 +314,31 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         // in blocks of 64 keys (about 2 us): a launch takes its longest item and what falls to one of the workgroups the chip holds;
         // an item costs two blocks beyond its own, each request of a joint item one (its rows' sums are kept in memory till
         // then); two passes cost a launch (three blocks) and the state's way through memory.
-        // Fitted to the attention of 1310 batches (40/40, 64/8, 40/8, 16/2 and 8/2 heads; 200 .. 4000 tokens in requests of 2 .. 400 with
+        // Decode rows behind a template need the pass over it as well, and it stays a launch for them (pass_stays) unless their template's
+        // items join the one launch (below): then two passes cost no launch more, the joint items' launch waits for the pass either way,
+        // and the prefill rows in it run beside the decode rows.  So it is priced with the decode rows' items, and two blocks are
+        // taken off for what the price misses; in the one launch the merge is as dear as the pass's launch.
+        // Fitted to the attention of 1310 batches of prefill rows (40/40, 64/8, 40/8, 16/2 and 8/2 heads; 200 .. 4000 tokens in requests of 2 .. 400 with
         // 0 .. 2500 cached keys behind 64 .. 1024): 0.3 % off the faster of the two on average, in twenty batches 2 .. 10 % slower
         // than two passes (which alone are 20 % off, joint items alone 25 %).  Two passes / joint, us: 40/40 heads behind 256, 400 tokens
         // in requests of 4 52 / 108, of 32 24 / 23, of 32 with 1000 cached 62 / 120; 2000 in requests of 16 82 / 73, of 100 61 / 53, of 100
         // with 1000 cached 155 / 258; 64/8 heads, 400 tokens in requests of 8 28 / 18, with 1000 cached 59 / 62.
-        auto joint_pays = [&](int32_t p) {
+        // With decode rows of the group, 700 batches of eight shapes that these constants were not fitted to: 0.9 % off the faster over
+        // quantised pools (whose pass stays; two passes alone 1.3 %, joint items alone 41 %), 1.9 % over 16-bit ones (6 and 25 %); on average
+        // 0.3 and 4.3 % faster than two passes throughout, six batches 3 .. 8 % slower.  Two passes / joint, us: quantised, 64/8 heads, 8
+        // requests of 7 tokens and 29 rows behind 1024 39 / 72; 16-bit, 8/4 heads, 3 requests of 3 and 34 rows behind 512 22 / 30.
+        std::vector<int32_t> dec_rows(d.num_prefixes, 0);   // decode rows behind each template that is handled jointly
+        int64_t behind = 0;
+        for (int32_t r = 0; r < B; ++r) {
+            const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
+            if (pid >= 0 && joint[pid] && d.q_start[r + 1] - d.q_start[r] == 1) ++dec_rows[pid], ++behind;
+        }
+        auto joint_pays = [&](int32_t p, bool pass_stays) {
             struct Launch {
                 int64_t longest = 0, total = 0;
                 void item(int64_t blocks) { longest = std::max(longest, blocks + 2), total += blocks + 2; }
                 double time(int32_t n_kv) const { return (double)longest + (double)total * n_kv / ATTN_WGS; }
-            } pass, own, both;
+            } pass, own, both, dec;
             const int64_t shared = (d.prefix_len[p] + 63) / 64;
             int64_t toks = 0, packed = 0;   // of the group's prefill rows; own blocks of the joint item being filled
             for (int32_t r = 0; r < B; ++r) {
@@ -341,11 +355,15 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
             }
             if (toks == 0) return false;
             if (packed > 0) pass.item(shared), both.item(shared + packed);
+            if (behind > 0) {
+                pass = Launch();
+                for (int64_t o = 0; o < toks + dec_rows[p]; o += tile_tok) pass.item(shared);
+                for (int32_t o = 0; o < dec_rows[p]; o += tile_tok) (pass_stays ? dec : both).item(shared);
+            }
             const double state_us = (double)toks * cfg.n_q_heads * (cfg.head_dim + 2) * 8 / 5.0e6;   // written and read at 5 TB/s
-            return both.time(cfg.n_kv_heads) <= pass.time(cfg.n_kv_heads) + own.time(cfg.n_kv_heads) + 3 + state_us / 2;
+            const int32_t launch = behind == 0 ? 3 : pass_stays ? -2 : 0;
+            return both.time(cfg.n_kv_heads) + dec.time(cfg.n_kv_heads) <= pass.time(cfg.n_kv_heads) + own.time(cfg.n_kv_heads) + launch + state_us / 2;
         };
-        std::vector<uint8_t> fused(d.num_prefixes, 0);
-        for (int32_t p = 0; p < d.num_prefixes; ++p) fused[p] = joint[p] && joint_pays(p);
         const int32_t rows_len = rows_chunk_len();
         SlotPlan plan;
         if (slots_allowed && hb.n_prefill == 0 && T > 0 && T <= SKINNY_MAX_T) plan = plan_slots(cfg, d, joint, own_keys, chunks_of, rows_len);
@@ -357,20 +375,30 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         // chunk of 512 tokens, launch of its own -> one launch, us: 64/8 heads 58 -> 44, 95 -> 98, 155 -> 168, 286 -> 304; 40/40
         // 132 -> 122, 286 -> 287, 532 -> 553, 1042 -> 1098.  So up to 8 MB of state; over 1560 batches of four shapes that is 1.4 % off the
         // faster of the two on average (15 % with none), in twelve of them 2 .. 5 % slower than the launch of its own.
-        bool mixed = slots_allowed && hb.n_prefill > 0 && hb.n_decode > 0;
-        int64_t behind = 0;
-        for (int32_t r = 0; r < B; ++r) {
-            const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
-            if (pid < 0 || !joint[pid]) continue;
-            if (d.q_start[r + 1] - d.q_start[r] == 1) ++behind;
-            else if (!fused[pid]) mixed = false;     // its rows read a state that an earlier launch has to leave
-        }
-        mixed &= behind > 0 && behind * cfg.n_q_heads * cfg.head_dim <= ATTN_MIXED_FLOATS;
+        bool mixed = slots_allowed && hb.n_prefill > 0 && behind > 0 && behind * cfg.n_q_heads * cfg.head_dim <= ATTN_MIXED_FLOATS;
+        std::vector<uint8_t> fused(d.num_prefixes, 0);
+        auto choose_joint = [&] {
+            for (int32_t p = 0; p < d.num_prefixes; ++p) fused[p] = joint[p] && joint_pays(p, !mixed);
+        };
+        choose_joint();
         if (mixed) {
             plan.prefix_chunks.assign(d.num_prefixes, 1);
             plan.prefix_len.assign(d.prefix_len, d.prefix_len + d.num_prefixes);
             plan.chunk_len = std::max(0, rows_len);
-            plan.use = true;
+            int64_t slots = 0;
+            for (int32_t r = 0; r < B; ++r) {
+                const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
+                const bool grouped = pid >= 0 && joint[pid];
+                if (d.q_start[r + 1] - d.q_start[r] > 1) {
+                    mixed &= !grouped || fused[pid];     // its rows read a state that an earlier launch has to leave
+                } else {
+                    const int32_t n = grouped + chunks_of(own_keys(r), plan.chunk_len);
+                    if (n > 1) slots += n;
+                }
+            }
+            mixed &= slots <= split_slot_cap(T);
+            plan.use = mixed;
+            if (!mixed) choose_joint();
         }
         std::vector<int32_t> row_slot;      // per request: its first slot (slot plans only)
         if (plan.use) {
@@ -383,8 +411,7 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
                 row_slot[r] = slots;
                 if (n > 1) slots += n;
             }
-            if (mixed && slots > split_slot_cap(T)) plan.use = mixed = false;
-            else if (!mixed) il.n_scratch_slots = slots;
+            if (!mixed) il.n_scratch_slots = slots;
         }
         il.in_slots = plan.use;
         auto joint_items = [&](int32_t p) {

@@ -1,6 +1,6 @@
 // Reads mixed batches "n_q n_kv d page | prefix rows | query tokens and own keys of every row" (all rows carry the prefix) and prints how
-// many row-tiled items their attention has, how many of them are joint, and whether the template's state of decode rows is kept in
-// slots (expand_batch; host arithmetic alone).  Ends with a message if some query token does not see the template once and its own
+// many row-tiled items their attention has, how many of them are joint, whether the template's state of decode rows is kept in
+// slots, and how many items are joint without slots (expand_batch; host arithmetic alone).  Ends with a message if some query token does not see the template once and its own
 // keys once, up to itself, through its request's block table, or if a slot is out of range, written twice or not merged.
 #include <algorithm>
 #include <cstdio>
@@ -106,7 +106,7 @@ int main() {
         int n_joint = 0, other = 0;
         if (check(hb, hb.items, q, own, ctx, prefix, ATTN_BLOCK_M / (n_q / n_kv), n_joint)) return 1;
         if (hb.items.in_slots && check(hb, hb.no_slots, q, own, ctx, prefix, ATTN_BLOCK_M / (n_q / n_kv), other)) return 1;
-        std::printf("%d %d %d\n", (int)hb.items.items_tile.size(), n_joint, (int)hb.items.in_slots);
+        std::printf("%d %d %d %d\n", (int)hb.items.items_tile.size(), n_joint, (int)hb.items.in_slots, hb.items.in_slots ? other : n_joint);
     }
     return 0;
 }

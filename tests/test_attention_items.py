@@ -57,9 +57,10 @@ def test_random_batches_are_covered(cut, seed):
 def joint(tmp_path_factory):
     exe = host_program.build(tmp_path_factory.mktemp("joint"), "joint_items")
 
-    def ask(shape, q, own, prefix, page=16):
+    def ask(shape, q, own, prefix, page=16, without_slots=False):
         rows = " ".join(f"{a} {b}" for a, b in zip(q, own))
-        return host_program.run(exe, f"{shape.n_q_heads} {shape.n_kv_heads} {shape.head_dim} {page} {prefix} {len(q)} {rows}\n")[0]
+        *cut, other = host_program.run(exe, f"{shape.n_q_heads} {shape.n_kv_heads} {shape.head_dim} {page} {prefix} {len(q)} {rows}\n")[0]
+        return other if without_slots else tuple(cut)
     return ask
 
 
@@ -87,15 +88,38 @@ def test_keys_cached_behind_the_template_count(joint, shape, n, q, cached, prefi
                                               (W.LLAMA_70B_TP4, 1024, 1), (W.LLAMA_70B_TP4, 2000, 0)])
 def test_many_decode_rows_keep_the_pass_over_their_template(joint, shape, rows, slots):
     """Beside prefill rows: a second state for every row is dearer than a launch that fills the chip."""
-    assert joint(shape, [90] * 16 + [1] * rows, [90] * 16 + [60] * rows, 512)[1:] == (joint(shape, [90] * 16, [90] * 16, 512)[1], slots)
+    assert joint(shape, [90] * 16 + [1] * rows, [90] * 16 + [60] * rows, 512)[2] == slots
 
 
 @pytest.mark.parametrize("shape", [W.TINY, W.TINY_G5, W.TINY_D128, W.TINY_G3_D128], ids=["group1", "group5", "d128", "g3d128"])
 def test_the_batch_of_the_device_tests_takes_joint_items(joint, shape):
-    q, own, prefix = test_gpu_joint_items.JOINT_BATCH
-    assert joint(shape, q, own, prefix)[1] > 0
     more_q, more_own = test_gpu_joint_items.TWO_PASSES
-    assert joint(shape, [*q, *more_q], [*own, *more_own], prefix)[1:] == (0, 0)
+    for batch, slots in ((test_gpu_joint_items.JOINT_BATCH, 0), (test_gpu_joint_items.MIXED_BATCH, 1)):
+        q, own, prefix = batch
+        tiles, n_joint, in_slots = joint(shape, q, own, prefix)
+        assert n_joint > 0 and in_slots == slots
+        assert joint(shape, [*q, *more_q], [*own, *more_own], prefix)[1:] == (0, 0)
+
+
+@pytest.mark.parametrize("shape,q,own,prefix,fused", [
+    # 16-bit pools: the template's items are in the one launch either way, so the joint items' length counts against two passes of it
+    (W.LLAMA_13B, [90] * 16 + [1] * 100, [90] * 16 + [60] * 100, 512, True), (W.LLAMA_70B, [90] * 16 + [1] * 100, [90] * 16 + [60] * 100, 512, True),
+    (W.TINY_GQA, [3] * 3 + [1] * 34, [3] * 3 + [30] * 34, 512, False),
+    # too many decode rows for slots: the pass over the template stays
+    (W.LLAMA_13B, [90] * 16 + [1] * 410, [90] * 16 + [60] * 410, 512, False), (W.LLAMA_70B, [30] * 4 + [1] * 300, [30] * 4 + [60] * 300, 256, False),
+])
+def test_decode_rows_need_the_pass_as_well(joint, shape, q, own, prefix, fused):
+    """Joint items save no launch where decode rows of their group keep the pass over the template."""
+    assert (joint(shape, q, own, prefix)[1] > 0) == fused
+
+
+@pytest.mark.parametrize("shape,q,own,prefix,fused", [
+    (W.LLAMA_70B, [7] * 8 + [1] * 29, [7] * 8 + [60] * 29, 1024, False), (W.TINY_GQA, [50] * 4 + [1] * 9, [50] * 4 + [100] * 9, 512, False),
+    (W.QWEN_32B_TP2, [8] * 5 + [1] * 223, [64] * 5 + [34] * 223, 1024, False), (W.LLAMA_13B, [120] * 60 + [1] * 9, [120] * 60 + [30] * 9, 1024, True),
+])
+def test_decode_rows_over_quantised_pools_keep_the_pass(joint, shape, q, own, prefix, fused):
+    """There the pass over the template is never an item of the one launch: joint items run behind it."""
+    assert (joint(shape, q, own, prefix, without_slots=True) > 0) == fused
 
 
 @pytest.mark.parametrize("seed", range(30))

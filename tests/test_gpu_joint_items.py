@@ -11,8 +11,10 @@ pytestmark = pytest.mark.gpu
 
 
 # query tokens, own keys and template of a group whose prefill rows take joint items (test_attention_items.py): requests that share
-# items and waves, some with cached keys of their own, a decode row among them
-JOINT_BATCH = (np.array([50, 50, 60, 65, 1, 90, 70, 12]), np.array([50, 130, 63, 65, 41, 110, 170, 12]), 80)
+# items and waves, some with cached keys of their own
+JOINT_BATCH = (np.array([50, 50, 60, 65, 90, 70, 12]), np.array([50, 130, 63, 65, 110, 170, 12]), 80)
+# the same with a decode row behind the template: over 16-bit pools the template is an item of the one launch for it
+MIXED_BATCH = (np.array([300, 1]), np.array([300, 41]), 80)
 # query tokens and own keys of requests with which the same group takes two passes: their cached keys, one request after the other
 # in a joint item, would take too long
 TWO_PASSES = (np.array([4] * 4), np.array([1500] * 4))
@@ -52,7 +54,7 @@ def test_a_request_spoils_its_own_rows_alone(rs, shape, fp8):
     """Requests that share an item, and waves of it, with one whose cached keys or values are not finite: the others' rows have
     the bits they have beside finite ones."""
     q, own, prefix = JOINT_BATCH
-    bad_v, bad_k = [1, 3], [6]
+    bad_v, bad_k = [1, 3], [5]
     b = W.build_batch(shape, q, own + prefix, [0] * len(q), [prefix], seed=4)
     g = torch.Generator(device="cuda").manual_seed(5)
     size = (b.num_pages, shape.page_size, shape.n_kv_heads, shape.head_dim)
@@ -91,11 +93,12 @@ def test_a_request_spoils_its_own_rows_alone(rs, shape, fp8):
             assert np.array_equal(got[rows], clean[rows]), r
 
 
+@pytest.mark.parametrize("batch", [JOINT_BATCH, MIXED_BATCH], ids=["joint", "mixed"])
 @pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
 @pytest.mark.parametrize("shape", [W.TINY, W.TINY_G5, W.TINY_D128, W.TINY_G3_D128], ids=["group1", "group5", "d128", "g3d128"])
-def test_joint_items_have_the_two_passes_bits(rs, oracle, shape, fp8):
+def test_joint_items_have_the_two_passes_bits(rs, oracle, shape, fp8, batch):
     """The attention of the same requests, over the same pages, in joint items and (beside others) in two passes, and the oracle's."""
-    q, own, prefix = JOINT_BATCH
+    q, own, prefix = batch
     n = len(q)
     q_all, own_all = np.concatenate([q, TWO_PASSES[0]]), np.concatenate([own, TWO_PASSES[1]])
     both = W.build_batch(shape, q_all, own_all + prefix, [0] * len(q_all), [prefix], seed=6)
