@@ -313,56 +313,58 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         // the same time: short requests, and long ones with keys cached behind the template, are faster in two passes.  Both are priced
         // in blocks of 64 keys (about 2 us): a launch takes its longest item and what falls to one of the workgroups the chip holds;
         // an item costs two blocks beyond its own, each request of a joint item one (its rows' sums are kept in memory till
-        // then); two passes cost a launch (three blocks) and the state's way through memory.
-        // Decode rows behind a template need the pass over it as well, and it stays a launch for them (pass_stays) unless their template's
-        // items join the one launch (below): then two passes cost no launch more, the joint items' launch waits for the pass either way,
-        // and the prefill rows in it run beside the decode rows.  So it is priced with the decode rows' items, and two blocks are
-        // taken off for what the price misses; in the one launch the merge is as dear as the pass's launch.
-        // Fitted to the attention of 1310 batches of prefill rows (40/40, 64/8, 40/8, 16/2 and 8/2 heads; 200 .. 4000 tokens in requests of 2 .. 400 with
-        // 0 .. 2500 cached keys behind 64 .. 1024): 0.3 % off the faster of the two on average, in twenty batches 2 .. 10 % slower
-        // than two passes (which alone are 20 % off, joint items alone 25 %).  Two passes / joint, us: 40/40 heads behind 256, 400 tokens
-        // in requests of 4 52 / 108, of 32 24 / 23, of 32 with 1000 cached 62 / 120; 2000 in requests of 16 82 / 73, of 100 61 / 53, of 100
-        // with 1000 cached 155 / 258; 64/8 heads, 400 tokens in requests of 8 28 / 18, with 1000 cached 59 / 62.
-        // With decode rows of the group, 700 batches of eight shapes that these constants were not fitted to: 0.9 % off the faster over
-        // quantised pools (whose pass stays; two passes alone 1.3 %, joint items alone 41 %), 1.9 % over 16-bit ones (6 and 25 %); on average
-        // 0.3 and 4.3 % faster than two passes throughout, six batches 3 .. 8 % slower.  Two passes / joint, us: quantised, 64/8 heads, 8
-        // requests of 7 tokens and 29 rows behind 1024 39 / 72; 16-bit, 8/4 heads, 3 requests of 3 and 34 rows behind 512 22 / 30.
-        std::vector<int32_t> dec_rows(d.num_prefixes, 0);   // decode rows behind each template that is handled jointly
-        int64_t behind = 0;
+        // then); two passes cost the state's way through memory, and a launch if nothing else needs the pass (two blocks beyond
+        // the two of its longest item).  All groups go one way: while one group keeps the pass, the joint items of the others, which walk
+        // their templates once more, run behind it (64/8 heads, 15 requests of 30 tokens in three groups behind 768: 50 us in two
+        // passes, 51 in joint items, 76 in both).  Decode rows need the pass as well: it stays (pass_stays), or their template's items join the
+        // one launch (below) and the merge is as dear as the pass's launch.
+        // Fitted to the attention of 1321 batches over 16-bit and 1213 over quantised pools (40/40, 64/8, 40/8, 20/4, 16/2, 8/8, 8/4 and 4/2
+        // heads; up to 5000 tokens in requests of 2 .. 280 with 0 .. 500 cached keys, half of them with 1 .. 1200 decode rows, behind one to three
+        // templates of 64 .. 1024).  1200 other batches, off the faster of the two on average: prefill rows alone 0.0 % (two passes
+        // alone 8 %, joint items alone 32 %), beside decode rows over quantised pools 0.5 % (1 and 40 %), over 16-bit ones 1.4 % (7 and 23 %); on
+        // average 8, 1 and 6 % faster than two passes throughout, 22 of the 1200 by 3 .. 11 % slower.  Two passes / joint, us: 40/40 heads
+        // behind 256, 400 tokens in requests of 4 52 / 108, of 32 24 / 23, of 32 with 1000 cached 62 / 120; 2000 in requests of 16 82 / 73, of 100
+        // 61 / 53, of 100 with 1000 cached 155 / 258; 8-bit pools, 64/8 heads, 8 requests of 7 tokens and 29 decode rows behind 1024 39 / 72.
+        std::vector<int32_t> pre_toks(d.num_prefixes, 0), dec_rows(d.num_prefixes, 0);   // behind each template that is handled jointly
+        int64_t behind = 0;                                                              // decode rows behind any of them
         for (int32_t r = 0; r < B; ++r) {
-            const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1;
-            if (pid >= 0 && joint[pid] && d.q_start[r + 1] - d.q_start[r] == 1) ++dec_rows[pid], ++behind;
+            const int32_t pid = d.prefix_id ? d.prefix_id[r] : -1, q_len = d.q_start[r + 1] - d.q_start[r];
+            if (pid < 0 || !joint[pid]) continue;
+            if (q_len == 1) ++dec_rows[pid], ++behind;
+            else pre_toks[pid] += q_len;
         }
-        auto joint_pays = [&](int32_t p, bool pass_stays) {
+        auto joint_pays = [&](bool pass_stays) {
             struct Launch {
                 int64_t longest = 0, total = 0;
                 void item(int64_t blocks) { longest = std::max(longest, blocks + 2), total += blocks + 2; }
                 double time(int32_t n_kv) const { return (double)longest + (double)total * n_kv / ATTN_WGS; }
             } pass, own, both, dec;
-            const int64_t shared = (d.prefix_len[p] + 63) / 64;
-            int64_t toks = 0, packed = 0;   // of the group's prefill rows; own blocks of the joint item being filled
+            int64_t state_rows = 0;
+            std::vector<int32_t> filled(d.num_prefixes, 0);      // of each group's joint item being filled: its tokens ...
+            std::vector<int64_t> packed(d.num_prefixes, 0);      // ... and the blocks of its requests' own keys
             for (int32_t r = 0; r < B; ++r) {
-                const int32_t q_len = d.q_start[r + 1] - d.q_start[r], cached = d.ctx_len[r] - q_len - d.prefix_len[p];
-                if (d.prefix_id[r] != p || q_len == 1) continue;
+                const int32_t p = d.prefix_id ? d.prefix_id[r] : -1, q_len = d.q_start[r + 1] - d.q_start[r];
+                if (p < 0 || !joint[p] || q_len == 1) continue;
+                const int32_t cached = d.ctx_len[r] - q_len - d.prefix_len[p];
                 for (int32_t o = 0; o < q_len; o += tile_tok) own.item((cached + std::min(q_len, o + tile_tok) + 63) / 64);
                 for (int32_t o = 0; o < q_len;) {
-                    const int32_t n = std::min<int32_t>(q_len - o, tile_tok - (int32_t)(toks % tile_tok));
+                    const int32_t n = std::min(q_len - o, tile_tok - filled[p]);
                     o += n;
-                    toks += n;
-                    packed += (cached + o + 63) / 64 + 1;
-                    if (toks % tile_tok == 0) pass.item(shared), both.item(shared + packed), packed = 0;
+                    packed[p] += (cached + o + 63) / 64 + 1;
+                    if ((filled[p] += n) == tile_tok) both.item((d.prefix_len[p] + 63) / 64 + packed[p]), filled[p] = 0, packed[p] = 0;
                 }
             }
-            if (toks == 0) return false;
-            if (packed > 0) pass.item(shared), both.item(shared + packed);
-            if (behind > 0) {
-                pass = Launch();
-                for (int64_t o = 0; o < toks + dec_rows[p]; o += tile_tok) pass.item(shared);
+            for (int32_t p = 0; p < d.num_prefixes; ++p) {
+                if (!joint[p]) continue;
+                const int64_t shared = (d.prefix_len[p] + 63) / 64;
+                if (filled[p] > 0) both.item(shared + packed[p]);
+                for (int64_t o = 0; o < (int64_t)pre_toks[p] + dec_rows[p]; o += tile_tok) pass.item(shared);
                 for (int32_t o = 0; o < dec_rows[p]; o += tile_tok) (pass_stays ? dec : both).item(shared);
+                state_rows += pre_toks[p];
             }
-            const double state_us = (double)toks * cfg.n_q_heads * (cfg.head_dim + 2) * 8 / 5.0e6;   // written and read at 5 TB/s
-            const int32_t launch = behind == 0 ? 3 : pass_stays ? -2 : 0;
-            return both.time(cfg.n_kv_heads) + dec.time(cfg.n_kv_heads) <= pass.time(cfg.n_kv_heads) + own.time(cfg.n_kv_heads) + launch + state_us / 2;
+            const double state_us = (double)state_rows * cfg.n_q_heads * (cfg.head_dim + 2) * 8 / 5.0e6;   // written and read at 5 TB/s
+            const int32_t n_kv = cfg.n_kv_heads;
+            return both.time(n_kv) + dec.time(n_kv) <= pass.time(n_kv) + own.time(n_kv) + (behind == 0 ? 2 : 0) + state_us / 2;
         };
         const int32_t rows_len = rows_chunk_len();
         SlotPlan plan;
@@ -378,7 +380,8 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         bool mixed = slots_allowed && hb.n_prefill > 0 && behind > 0 && behind * cfg.n_q_heads * cfg.head_dim <= ATTN_MIXED_FLOATS;
         std::vector<uint8_t> fused(d.num_prefixes, 0);
         auto choose_joint = [&] {
-            for (int32_t p = 0; p < d.num_prefixes; ++p) fused[p] = joint[p] && joint_pays(p, !mixed);
+            const bool pays = joint_pays(!mixed);
+            for (int32_t p = 0; p < d.num_prefixes; ++p) fused[p] = pays && pre_toks[p] > 0;
         };
         choose_joint();
         if (mixed) {

@@ -1,4 +1,5 @@
-// Reads mixed batches "n_q n_kv d page | prefix rows | query tokens and own keys of every row" (all rows carry the prefix) and prints how
+// Reads mixed batches "n_q n_kv d page | prefix groups rows | query tokens and own keys of every row" (every row carries the prefix of its
+// group, the groups one behind the other) and prints how
 // many row-tiled items their attention has, how many of them are joint, whether the template's state of decode rows is kept in
 // slots, and how many items are joint without slots (expand_batch; host arithmetic alone).  Ends with a message if some query token does not see the template once and its own
 // keys once, up to itself, through its request's block table, or if a slot is out of range, written twice or not merged.
@@ -82,25 +83,28 @@ static int check(const HostBatch& hb, const ItemLists& il, const std::vector<int
 }
 
 int main() {
-    int n_q, n_kv, d, page, prefix, rows;
-    while (std::scanf("%d %d %d %d %d %d", &n_q, &n_kv, &d, &page, &prefix, &rows) == 6) {
+    int n_q, n_kv, d, page, prefix, groups, rows;
+    while (std::scanf("%d %d %d %d %d %d %d", &n_q, &n_kv, &d, &page, &prefix, &groups, &rows) == 7) {
         std::vector<int32_t> q(rows), own(rows), q_start(1, 0), ctx, pid(rows, 0);
         int max_blocks = 0;
         for (int r = 0; r < rows; ++r) {
             if (std::scanf("%d %d", &q[r], &own[r]) != 2) return 1;
             q_start.push_back(q_start.back() + q[r]);
             ctx.push_back(prefix + own[r]);
+            pid[r] = r * groups / rows;
             max_blocks = std::max(max_blocks, (ctx[r] + page - 1) / page);
         }
         std::vector<int32_t> table((size_t)rows * max_blocks, 0);
-        int next = prefix / page;
+        const std::vector<int32_t> prefix_len(groups, prefix);
+        const int shared = prefix / page;
+        int next = groups * shared;
         for (int r = 0; r < rows; ++r)
-            for (int i = 0; i < (ctx[r] + page - 1) / page; ++i) table[(size_t)r * max_blocks + i] = i < prefix / page ? i : next++;
+            for (int i = 0; i < (ctx[r] + page - 1) / page; ++i) table[(size_t)r * max_blocks + i] = i < shared ? pid[r] * shared + i : next++;
         relserve_layer_config cfg{};
         cfg.hidden = n_q * d; cfg.n_q_heads = n_q; cfg.n_kv_heads = n_kv; cfg.head_dim = d; cfg.mlp_dim = 8; cfg.page_size = page;
         relserve_batch_desc desc{};
         desc.num_reqs = rows; desc.q_start = q_start.data(); desc.ctx_len = ctx.data(); desc.block_table = table.data();
-        desc.max_blocks = max_blocks; desc.num_pages = next; desc.prefix_id = pid.data(); desc.num_prefixes = 1; desc.prefix_len = &prefix;
+        desc.max_blocks = max_blocks; desc.num_pages = next; desc.prefix_id = pid.data(); desc.num_prefixes = groups; desc.prefix_len = prefix_len.data();
         HostBatch hb;
         if (const int32_t st = expand_batch(cfg, desc, true, &hb)) { std::printf("status %d\n", st); return 1; }
         int n_joint = 0, other = 0;

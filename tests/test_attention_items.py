@@ -57,9 +57,9 @@ def test_random_batches_are_covered(cut, seed):
 def joint(tmp_path_factory):
     exe = host_program.build(tmp_path_factory.mktemp("joint"), "joint_items")
 
-    def ask(shape, q, own, prefix, page=16, without_slots=False):
+    def ask(shape, q, own, prefix, page=16, without_slots=False, groups=1):
         rows = " ".join(f"{a} {b}" for a, b in zip(q, own))
-        *cut, other = host_program.run(exe, f"{shape.n_q_heads} {shape.n_kv_heads} {shape.head_dim} {page} {prefix} {len(q)} {rows}\n")[0]
+        *cut, other = host_program.run(exe, f"{shape.n_q_heads} {shape.n_kv_heads} {shape.head_dim} {page} {prefix} {groups} {len(q)} {rows}\n")[0]
         return other if without_slots else tuple(cut)
     return ask
 
@@ -91,7 +91,7 @@ def test_many_decode_rows_keep_the_pass_over_their_template(joint, shape, rows, 
     assert joint(shape, [90] * 16 + [1] * rows, [90] * 16 + [60] * rows, 512)[2] == slots
 
 
-@pytest.mark.parametrize("shape", [W.TINY, W.TINY_G5, W.TINY_D128, W.TINY_G3_D128], ids=["group1", "group5", "d128", "g3d128"])
+@pytest.mark.parametrize("shape", test_gpu_joint_items.JOINT_SHAPES.values(), ids=test_gpu_joint_items.JOINT_SHAPES)
 def test_the_batch_of_the_device_tests_takes_joint_items(joint, shape):
     more_q, more_own = test_gpu_joint_items.TWO_PASSES
     for batch, slots in ((test_gpu_joint_items.JOINT_BATCH, 0), (test_gpu_joint_items.MIXED_BATCH, 1)):
@@ -120,6 +120,16 @@ def test_decode_rows_need_the_pass_as_well(joint, shape, q, own, prefix, fused):
 def test_decode_rows_over_quantised_pools_keep_the_pass(joint, shape, q, own, prefix, fused):
     """There the pass over the template is never an item of the one launch: joint items run behind it."""
     assert (joint(shape, q, own, prefix, without_slots=True) > 0) == fused
+
+
+@pytest.mark.parametrize("shape,q,own,prefix,groups,fused", [
+    (W.LLAMA_70B, [24, 33, 35, 30, 28, 26, 30, 31, 35, 20, 24, 33, 35, 30, 28], [235, 460, 130, 300, 28, 26, 30, 231, 35, 20, 324, 33, 35, 30, 28], 768, 3, True),
+    (W.LLAMA_13B, [120] * 16 + [4] * 16, [120] * 16 + [1500] * 16, 512, 2, False), (W.LLAMA_13B, [120] * 16 + [90] * 16, [120] * 16 + [90] * 16, 512, 2, True),
+])
+def test_groups_take_joint_items_together(joint, shape, q, own, prefix, groups, fused):
+    """Where one group keeps the pass over its template, joint items of another would run behind it."""
+    tiles, n_joint, _ = joint(shape, q, own, prefix, groups=groups)
+    assert n_joint == (tiles if fused else 0)
 
 
 @pytest.mark.parametrize("seed", range(30))

@@ -1,5 +1,7 @@
 """Prefill rows of a group whose items walk the shared keys and then each request's own (GPU), against the CPU oracle: requests that
 end inside, at and behind an item, templates of no multiple of 64 keys, decode rows and other groups beside them."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 import torch
@@ -12,12 +14,13 @@ pytestmark = pytest.mark.gpu
 
 # query tokens, own keys and template of a group whose prefill rows take joint items (test_attention_items.py): requests that share
 # items and waves, some with cached keys of their own
-JOINT_BATCH = (np.array([50, 50, 60, 65, 90, 70, 12]), np.array([50, 130, 63, 65, 110, 170, 12]), 80)
+JOINT_BATCH = (np.array([50, 50, 60, 65, 90, 70, 12]), np.array([50, 110, 63, 65, 100, 110, 12]), 80)
 # the same with a decode row behind the template: over 16-bit pools the template is an item of the one launch for it
 MIXED_BATCH = (np.array([300, 1]), np.array([300, 41]), 80)
 # query tokens and own keys of requests with which the same group takes two passes: their cached keys, one request after the other
 # in a joint item, would take too long
 TWO_PASSES = (np.array([4] * 4), np.array([1500] * 4))
+JOINT_SHAPES = {"group1": replace(W.TINY, n_q_heads=48, n_kv_heads=48), "group5": W.TINY_G5, "d128": W.TINY_D128, "g3d128": W.TINY_G3_D128}
 
 
 @pytest.fixture(scope="module")
@@ -49,7 +52,7 @@ def test_joint_items(rs, oracle, shape, prefix, q_len):
 
 
 @pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
-@pytest.mark.parametrize("shape", [W.TINY, W.TINY_G5, W.TINY_D128, W.TINY_G3_D128], ids=["group1", "group5", "d128", "g3d128"])
+@pytest.mark.parametrize("shape", JOINT_SHAPES.values(), ids=JOINT_SHAPES)
 def test_a_request_spoils_its_own_rows_alone(rs, shape, fp8):
     """Requests that share an item, and waves of it, with one whose cached keys or values are not finite: the others' rows have
     the bits they have beside finite ones."""
@@ -95,7 +98,7 @@ def test_a_request_spoils_its_own_rows_alone(rs, shape, fp8):
 
 @pytest.mark.parametrize("batch", [JOINT_BATCH, MIXED_BATCH], ids=["joint", "mixed"])
 @pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
-@pytest.mark.parametrize("shape", [W.TINY, W.TINY_G5, W.TINY_D128, W.TINY_G3_D128], ids=["group1", "group5", "d128", "g3d128"])
+@pytest.mark.parametrize("shape", JOINT_SHAPES.values(), ids=JOINT_SHAPES)
 def test_joint_items_have_the_two_passes_bits(rs, oracle, shape, fp8, batch):
     """The attention of the same requests, over the same pages, in joint items and (beside others) in two passes, and the oracle's."""
     q, own, prefix = batch
