@@ -317,14 +317,17 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
         // the two of its longest item).  All groups go one way: while one group keeps the pass, the joint items of the others, which walk
         // their templates once more, run behind it (64/8 heads, 15 requests of 30 tokens in three groups behind 768: 50 us in two
         // passes, 51 in joint items, 76 in both).  Decode rows need the pass as well: it stays (pass_stays), or their template's items join the
-        // one launch (below) and the merge is as dear as the pass's launch.
-        // Fitted to the attention of 1321 batches over 16-bit and 1213 over quantised pools (40/40, 64/8, 40/8, 20/4, 16/2, 8/8, 8/4 and 4/2
-        // heads; up to 5000 tokens in requests of 2 .. 280 with 0 .. 500 cached keys, half of them with 1 .. 1200 decode rows, behind one to three
-        // templates of 64 .. 1024).  1200 other batches, off the faster of the two on average: prefill rows alone 0.0 % (two passes
-        // alone 8 %, joint items alone 32 %), beside decode rows over quantised pools 0.5 % (1 and 40 %), over 16-bit ones 1.4 % (7 and 23 %); on
-        // average 8, 1 and 6 % faster than two passes throughout, 22 of the 1200 by 3 .. 11 % slower.  Two passes / joint, us: 40/40 heads
+        // one launch (below) and the merge is as dear as the pass's launch.  The last launch reads the decode rows' own keys beside its
+        // tiled items, and the shorter of the two costs about 0.3 of its time: behind a long stream of keys joint items are nearly free.
+        // Fitted to the attention of 1660 batches over 16-bit and 1488 over quantised pools (40/40, 64/8, 40/8, 20/4, 16/2, 8/8, 8/4 and 4/2
+        // heads; up to 5000 tokens in requests of 2 .. 280 with 0 .. 500 cached keys, two thirds of them with 1 .. 1200 decode rows, behind one to
+        // three templates of 64 .. 1024).  1200 other batches, off the faster of the two on average: prefill rows alone 0.3 % (two passes
+        // alone 7 %, joint items alone 28 %), beside decode rows over quantised pools 0.5 % (2 and 40 %), over 16-bit ones 0.9 % (7 and 22 %); on
+        // average 7, 1 and 6 % faster than two passes throughout, 26 of the 1200 by 3 .. 13 % slower, one by 21.  Batches such as a relQuery's,
+        // 40/40, 64/8 and 40/8 heads, 3 .. 24 requests of 30 .. 120 tokens beside 30 .. 250 rows: 19 % faster.  Two passes / joint, us: 40/40 heads
         // behind 256, 400 tokens in requests of 4 52 / 108, of 32 24 / 23, of 32 with 1000 cached 62 / 120; 2000 in requests of 16 82 / 73, of 100
-        // 61 / 53, of 100 with 1000 cached 155 / 258; 8-bit pools, 64/8 heads, 8 requests of 7 tokens and 29 decode rows behind 1024 39 / 72.
+        // 61 / 53, of 100 with 1000 cached 155 / 258; 8-bit pools, 64/8 heads, 8 requests of 7 tokens and 29 decode rows behind 1024 39 / 72;
+        // 16-bit, 40/40, 16 requests of 75 and 184 rows behind 512 109 / 97.
         std::vector<int32_t> pre_toks(d.num_prefixes, 0), dec_rows(d.num_prefixes, 0);   // behind each template that is handled jointly
         int64_t behind = 0;                                                              // decode rows behind any of them
         for (int32_t r = 0; r < B; ++r) {
@@ -339,11 +342,12 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
                 void item(int64_t blocks) { longest = std::max(longest, blocks + 2), total += blocks + 2; }
                 double time(int32_t n_kv) const { return (double)longest + (double)total * n_kv / ATTN_WGS; }
             } pass, own, both, dec;
-            int64_t state_rows = 0;
+            int64_t state_rows = 0, stream_keys = 0;             // the decode rows' own keys, read beside the last launch's items
             std::vector<int32_t> filled(d.num_prefixes, 0);      // of each group's joint item being filled: its tokens ...
             std::vector<int64_t> packed(d.num_prefixes, 0);      // ... and the blocks of its requests' own keys
             for (int32_t r = 0; r < B; ++r) {
                 const int32_t p = d.prefix_id ? d.prefix_id[r] : -1, q_len = d.q_start[r + 1] - d.q_start[r];
+                if (q_len == 1) stream_keys += own_keys(r);
                 if (p < 0 || !joint[p] || q_len == 1) continue;
                 const int32_t cached = d.ctx_len[r] - q_len - d.prefix_len[p];
                 for (int32_t o = 0; o < q_len; o += tile_tok) own.item((cached + std::min(q_len, o + tile_tok) + 63) / 64);
@@ -363,8 +367,10 @@ int32_t relserve::expand_batch(const relserve_layer_config& cfg, const relserve_
                 state_rows += pre_toks[p];
             }
             const double state_us = (double)state_rows * cfg.n_q_heads * (cfg.head_dim + 2) * 8 / 5.0e6;   // written and read at 5 TB/s
+            const double stream = (double)stream_keys * cfg.n_kv_heads * cfg.head_dim * 4 / 3.0e6 / 2;     // at 3 TB/s of 16-bit pools
+            auto beside = [&](double items) { return std::max(items, stream) + 0.3 * std::min(items, stream); };
             const int32_t n_kv = cfg.n_kv_heads;
-            return both.time(n_kv) + dec.time(n_kv) <= pass.time(n_kv) + own.time(n_kv) + (behind == 0 ? 2 : 0) + state_us / 2;
+            return dec.time(n_kv) + beside(both.time(n_kv)) <= pass.time(n_kv) + beside(own.time(n_kv)) + (behind == 0 ? 2 : 0) + state_us / 2;
         };
         const int32_t rows_len = rows_chunk_len();
         SlotPlan plan;

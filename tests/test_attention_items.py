@@ -105,8 +105,10 @@ def test_the_batch_of_the_device_tests_takes_joint_items(joint, shape):
     # 16-bit pools: the template's items are in the one launch either way, so the joint items' length counts against two passes of it
     (W.LLAMA_13B, [90] * 16 + [1] * 100, [90] * 16 + [60] * 100, 512, True), (W.LLAMA_70B, [90] * 16 + [1] * 100, [90] * 16 + [60] * 100, 512, True),
     (W.TINY_GQA, [3] * 3 + [1] * 34, [3] * 3 + [30] * 34, 512, False),
+    # beside a long stream of the decode rows' own keys: nearly free
+    (W.LLAMA_13B, [70] * 16 + [1] * 184, [70] * 16 + [84] * 184, 512, True), (W.LLAMA_13B, [75] * 8 + [1] * 100, [75] * 8 + [84] * 100, 512, True),
     # too many decode rows for slots: the pass over the template stays
-    (W.LLAMA_13B, [90] * 16 + [1] * 410, [90] * 16 + [60] * 410, 512, False), (W.LLAMA_70B, [30] * 4 + [1] * 300, [30] * 4 + [60] * 300, 256, False),
+    (W.LLAMA_70B, [30] * 4 + [1] * 300, [30] * 4 + [60] * 300, 256, False),
 ])
 def test_decode_rows_need_the_pass_as_well(joint, shape, q, own, prefix, fused):
     """Joint items save no launch where decode rows of their group keep the pass over the template."""
