@@ -96,6 +96,12 @@ __device__ __forceinline__ f32x16_t mfma_32x32x16(bf16x8_t a, bf16x8_t b, f32x16
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// The same on a 16x16 output, k = 32: lane l holds A[l % 16][8 (l / 16) ..+7], B[8 (l / 16) ..+7][l % 16]; register r holds
+// D[4 (l / 16) + r][l % 16].
+__device__ __forceinline__ f32x4_t mfma_16x16x32(bf16x8_t a, bf16x8_t b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 // 32x32x64 product of 8-bit floating point codes (1-4-3 bits, both operands), fp32 accumulate: lane (l32, g) supplies
 // row l32 and 32 of the 64 k values (half g) of each operand.  The scale operands are zero: the unscaled instruction.
 __device__ __forceinline__ f32x16_t mfma_32x32x64_f8(i32x8_t a, i32x8_t b, f32x16_t c) {

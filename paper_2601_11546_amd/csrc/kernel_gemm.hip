@@ -88,6 +88,12 @@ hipError_t allow_smem_once(std::once_flag& once, hipError_t& status, Kernel kern
 
 enum { EPI_BF16 = 0, EPI_RES_BF16_OUT_F32 = 1, EPI_RES_F32_OUT_BF16 = 2, EPI_SWIGLU = 3, EPI_QKV_ROPE = 4, EPI_SLAB = 5 };
 
+// Which launches of gemm_dma_kernel multiply on 16 x 16 x 32 products instead of 32 x 32 x 16.  A chain of the former gives the same
+// bits as the chain of twice as many of the latter (measured, k of 32 .. 5120), but a 16 x 16 result passes through the accumulators
+// half as often per product, and the chip is power-limited in these kernels: all CUs on register operands alone reach 2.07 PFLOP/s
+// against 1.83.  T = 7963, 13B: clock 1.70 -> 2.0 GHz, gate/up 1632 -> 1579 us, W_down 813 -> 776, q/k/v 941 -> 910, the layer 4207 -> 4088.
+constexpr bool mfma16(int epi, bool f8) { return !f8 && epi != EPI_SLAB; }
+
 __device__ __forceinline__ int remap_xcd(int bid, int num) {
     const int per = num / NUM_XCD, rem = num % NUM_XCD;
     const int xcd = bid % NUM_XCD, idx = bid / NUM_XCD;
@@ -179,10 +185,11 @@ __device__ __forceinline__ void store_unit(const GemmArgs& p, int t, int n_lo, i
     }
 }
 
-// Epilogue shared by the GEMM kernels.  Register r of accumulator tile (tn, tm) holds feature
-// 32 tn + 8 (r / 4) + 4 g + r % 4 of the wave's feature range and token 32 tm + l32 of its token range.
-// TMX of the wave's BM / (32 WGM) rows of accumulator tiles are held in acc, starting at row tm_base (the GEMM kernels
-// hold all of them; the tail finish kernel one per workgroup, which with its 64 KB of LDS lets two workgroups share a CU).
+// Epilogue shared by the GEMM kernels.  Register r of a 32 x 32 accumulator tile (tn, tm) holds feature
+// 32 tn + 8 (r / 4) + 4 g + r % 4 of the wave's feature range and token 32 tm + l32 of its token range; of a 16 x 16 one (M16),
+// feature 16 tn + 4 (lane / 16) + r and token 16 tm + lane % 16.
+// acc holds whole rows of 32 tokens, starting at row tm_base (the GEMM kernels hold all of the wave's; the tail finish kernel one
+// per workgroup, which with its 64 KB of LDS lets two workgroups share a CU).
 // SC: the sums are products of 8-bit codes and take the factor a_scale * w_scale[feature] as they are read.
 //
 // One accumulator row (32 tokens x the wave's features, fp32) at a time goes through a region of LDS that belongs to the
@@ -197,13 +204,16 @@ constexpr int WGM = 2, WGN = 2;   // grid of waves over a tile
 template <int BN>
 constexpr int epi_wave_bytes() { return 32 * (BN / WGN) * 4; }
 
-template <int BM, int BN, int EPI, int D, int TMX = BM / (32 * WGM), bool SC = false>
-__device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * WGN)][TMX], const GemmArgs& p,
-                                              int tile_m, int tile_n, int wm, int wn, int l32, int g, int tm_base,
-                                              int split, unsigned char* lds) {
-    constexpr int TM = TMX, TN = BN / (32 * WGN);
+template <int BM, int BN, int EPI, int D, bool SC = false, typename Acc, int TNA, int TMA>
+__device__ __forceinline__ void gemm_epilogue(const Acc (&acc)[TNA][TMA], const GemmArgs& p, int tile_m, int tile_n, int wm, int wn,
+                                              int lane, int tm_base, int split, unsigned char* lds) {
+    constexpr bool M16 = std::is_same_v<Acc, f32x4_t>;
+    constexpr int TM = M16 ? TMA / 2 : TMA, TN = BN / (32 * WGN);
+    static_assert(TNA == (M16 ? 2 * TN : TN), "the wave's features");
     const int t0 = tile_m * BM + 32 * tm_base + wm * (BM / WGM);
+    const int l32 = lane & 31, g = lane >> 5;
     if constexpr (EPI == EPI_SLAB) {
+        static_assert(!M16, "slab stores of 32 consecutive floats");
         // Split-K partial sums -> this split's slab.  These tiles were accumulated with the operands
         // swapped: register r holds token 8 (r / 4) + 4 g + r % 4 and feature l32, so one store
         // instruction writes two runs of 32 consecutive floats.  Plain stores: nothing is read back in
@@ -229,7 +239,7 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * W
         constexpr int UPR = PAIRED ? CPR / 2 : CPR;      // units per token
         constexpr int RPI = 64 / UPR, IT = 32 / RPI;     // tokens per wave access, accesses per accumulator row
         static_assert(CPR >= 16, "the row swizzle permutes 16 chunks");
-        const int lane = l32 + 32 * g, u = lane % UPR, row0 = lane / UPR;
+        const int u = lane % UPR, row0 = lane / UPR;
         constexpr int DH = D > 0 ? D : 64;
         int c_lo, c_hi, n_lo, n_hi;                      // chunks and first features (rows of the weight matrix)
         int head = 0;
@@ -286,13 +296,25 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[BN / (32 * W
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             if (t0 + 32 * tm >= p.T) break;   // padding: nothing of this accumulator row (or the ones behind it) is stored
-            unsigned char* wr = lds + l32 * ROWB;
+            if constexpr (M16) {
+                unsigned char* wr = lds + (lane & 15) * ROWB;
 #pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
+                for (int tn = 0; tn < TNA; ++tn)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<float4*>(wr + (((8 * tn + 2 * q + g) ^ (l32 & 15)) << 4)) =
-                        make_float4(acc[tn][tm][4 * q], acc[tn][tm][4 * q + 1], acc[tn][tm][4 * q + 2], acc[tn][tm][4 * q + 3]);
+                    for (int h = 0; h < 2; ++h) {
+                        const f32x4_t v = acc[tn][2 * tm + h];
+                        *reinterpret_cast<float4*>(wr + 16 * h * ROWB + (((4 * tn + (lane >> 4)) ^ (lane & 15)) << 4)) =
+                            make_float4(v[0], v[1], v[2], v[3]);
+                    }
+            } else {
+                unsigned char* wr = lds + l32 * ROWB;
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<float4*>(wr + (((8 * tn + 2 * q + g) ^ (l32 & 15)) << 4)) =
+                            make_float4(acc[tn][tm][4 * q], acc[tn][tm][4 * q + 1], acc[tn][tm][4 * q + 2], acc[tn][tm][4 * q + 3]);
+            }
             // the wave's LDS accesses stay in program order: writes, reads, the next row's writes
             asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
@@ -432,7 +454,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs p) {
         __syncthreads();
     }
     static_assert(4 * epi_wave_bytes<BN>() <= 2 * STAGE, "the epilogue's rows fit the stages");
-    gemm_epilogue<BM, BN, EPI, D>(acc, p, tile_m, tile_n, wm, wn, l32, g, 0, 0, smem + wave * epi_wave_bytes<BN>());
+    gemm_epilogue<BM, BN, EPI, D>(acc, p, tile_m, tile_n, wm, wn, lane, 0, 0, smem + wave * epi_wave_bytes<BN>());
 }
 
 // ------------------------------------------------------------------------------------------
@@ -482,16 +504,18 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     constexpr bool SKEW = NSW > NS;
     static_assert(NSW == NS || NSW == NS + 1, "weight ring");
     constexpr int NW = WGM * WGN;
-    constexpr int TM = BM / (32 * WGM), TN = BN / (32 * WGN);
+    constexpr bool M16 = mfma16(EPI, F8);
+    constexpr int MR = M16 ? 16 : 32;                    // rows of either operand in one MFMA
+    constexpr int TM = BM / (MR * WGM), TN = BN / (MR * WGN);
     constexpr int ROWB = BKD * 2;                        // bytes per LDS row
     constexpr int CPR = BKD / 8;                         // 16-byte chunks per row
     constexpr int RPI = 1024 / ROWB;                     // rows one 1 KB wave load covers
     constexpr int A_IT = BM / (NW * RPI), W_IT = BN / (NW * RPI);
     constexpr int A_BYTES = BM * ROWB, W_BYTES = BN * ROWB, W_LDS = NS * A_BYTES;   // NS stages of activations, then NSW of weights
-    constexpr int KSTEPS = F8 ? BKD / 32 : BKD / 16;
+    constexpr int KSTEPS = F8 || M16 ? BKD / 32 : BKD / 16;
     constexpr int LOADS = A_IT + W_IT;                   // wave loads per stage
     static_assert(BKD == 64 || BKD == 32, "stage depth");
-    static_assert(!F8 || BKD == 64, "the fragment double buffer needs an even number of k steps per stage");
+    static_assert(!(F8 || M16) || BKD == 64, "the fragment double buffer needs an even number of k steps per stage");
     static_assert(NSW * LOADS < 64, "vmcnt field");
     static_assert(!SKEW || KSTEPS > 1, "the skewed ring's weights are issued between hand-overs");
     static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU needs gate and up tiles in one wave");
@@ -502,7 +526,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
-    const int l32 = lane & 31, g = lane >> 5;
+    const int fr = lane % MR, g = lane / MR;             // this lane's row of an operand fragment, and its part of the k step
 
     const int n_tiles = p.tiles_m * p.tiles_n;
     int tile, split;
@@ -583,25 +607,26 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // ---- LDS -> MFMA operand offsets
     int a_rd[TM], w_rd[TN];
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm) a_rd[tm] = (wm * (BM / WGM) + 32 * tm + l32) * ROWB;
+    for (int tm = 0; tm < TM; ++tm) a_rd[tm] = (wm * (BM / WGM) + MR * tm + fr) * ROWB;
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
         int row;
         if (EPI == EPI_SWIGLU)
-            row = (tn < TN / 2 ? 0 : BN / 2) + wn * (BN / (2 * WGN)) + 32 * (tn % (TN / 2)) + l32;
+            row = (tn < TN / 2 ? 0 : BN / 2) + wn * (BN / (2 * WGN)) + MR * (tn % (TN / 2)) + fr;
         else
-            row = wn * (BN / WGN) + 32 * tn + l32;
+            row = wn * (BN / WGN) + MR * tn + fr;
         w_rd[tn] = W_LDS + row * ROWB;
     }
-    const int swz = BKD == 64 ? ((l32 >> 1) & 7) : ((l32 >> 2) & 3);
+    const int swz = BKD == 64 ? ((fr >> 1) & 7) : ((fr >> 2) & 3);
 
-    f32x16_t acc[TN][TM];
+    using acc_t = std::conditional_t<M16, f32x4_t, f32x16_t>;
+    acc_t acc[TN][TM];
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[tn][tm][r] = 0.f;
+            for (int r = 0; r < MR * MR / 64; ++r) acc[tn][tm][r] = 0.f;
 
     using frag_t = std::conditional_t<F8, i32x8_t, bf16x8_t>;
     frag_t wf[2][TN], af[2][TM];
@@ -611,7 +636,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             const uint4 hi = *reinterpret_cast<const uint4*>(row + (((4 * ks + 2 * g + 1) ^ swz) << 4));
             return i32x8_t{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
         } else {
-            return as_bf16x8(*reinterpret_cast<const uint4*>(row + (((2 * ks + g) ^ swz) << 4)));
+            return as_bf16x8(*reinterpret_cast<const uint4*>(row + ((((64 / MR) * ks + g) ^ swz) << 4)));
         }
     };
     struct Stage { int a, w; };   // indices into the two rings
@@ -643,6 +668,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         if constexpr (F8)
             acc[tn][tm] = EPI == EPI_SLAB ? mfma_32x32x64_f8(af[buf][tm], wf[buf][tn], acc[tn][tm])
                                             : mfma_32x32x64_f8(wf[buf][tn], af[buf][tm], acc[tn][tm]);
+        else if constexpr (M16)
+            acc[tn][tm] = mfma_16x16x32(wf[buf][tn], af[buf][tm], acc[tn][tm]);
         else
             acc[tn][tm] = EPI == EPI_SLAB ? mfma_32x32x16(af[buf][tm], wf[buf][tn], acc[tn][tm])
                                             : mfma_32x32x16(wf[buf][tn], af[buf][tm], acc[tn][tm]);
@@ -677,27 +704,30 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     constexpr int NM = TN * TM, NF = TN + TM;
     // One k step, issued in a fixed order: MFMA i, then the share of the refill loads and of the next
     // step's fragment reads that falls between MFMA i and i + 1.  A CU's address unit takes one
-    // 1 KB load per ~16 cycles and an MFMA lasts 32, so the refill loads of a stage (LOADS per wave,
-    // four waves) are spread over SPREAD k steps; issued back to back they would hold up the MFMAs
-    // behind them.  The MFMAs sit on ONE control path on purpose: at a join the compiler would make
+    // 1 KB load per ~16 cycles and a 32 x 32 MFMA lasts 32, so the refill loads of a stage (LOADS per wave,
+    // four waves) are spread over SPREAD quarters of the iteration (a k step of 32 x 32 MFMAs is one, of
+    // 16 x 16 two); issued back to back they would hold up the MFMAs behind them.  The MFMAs sit on ONE control path on purpose: at a join the compiler would make
     // them wait for the newest reads.
-    constexpr int SPREAD = KSTEPS > 1 ? KSTEPS - 1 : 1;   // the last k step before the next hand-over stays free: landing time
-    auto k_step = [&](int buf, Stage rd_stage, int rd_ks, int part, auto refill) __attribute__((always_inline)) {
+    constexpr int PARTS = M16 ? 2 * KSTEPS : KSTEPS, SUB = PARTS / KSTEPS, NMP = NM / SUB;   // parts of an iteration
+    constexpr int SPREAD = PARTS > 1 ? PARTS - 1 : 1;   // the last part before the next hand-over stays free: landing time
+    auto k_step = [&](int buf, Stage rd_stage, int rd_ks, int step, auto refill_a, auto refill_w) __attribute__((always_inline)) {
         // share of the stage's loads issued in each part, cumulative, in sixteenths: the weights (first half
-        // of the loads) go out at once, the activations (L2 hits, quick to land) trail over two more steps
+        // of the loads) go out at once, the activations (L2 hits, quick to land) trail over two more parts
         constexpr int cut[5] = {0, 8, 13, 16, 16};
-        // (skewed: the activations at once, the weights over all the steps that remain)
-        const int pc = part < SPREAD ? part : SPREAD;
-        const int d_lo = SKEW ? (part == 0 ? 0 : A_IT + (part - 1) * W_IT / (KSTEPS - 1)) : SPREAD == 3 ? cut[pc] * LOADS / 16 : pc * LOADS / SPREAD;
-        const int d_n = (SKEW ? A_IT + part * W_IT / (KSTEPS - 1) : SPREAD == 3 ? cut[pc + 1] * LOADS / 16 : (pc + 1) * LOADS / SPREAD) - d_lo;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
             mfma_one(buf, i);
             __builtin_amdgcn_sched_barrier(0);
-            if ((SKEW || part < SPREAD) && on(refill)) {
+            const int part = step * SUB + i / NMP, ip = i % NMP;
+            if (SKEW || part < SPREAD) {
+                // (skewed: the activations at once, the weights over all the parts that remain)
+                const int pc = part < SPREAD ? part : SPREAD;
+                const int d_lo = SKEW ? (part == 0 ? 0 : A_IT + (part - 1) * W_IT / (PARTS - 1)) : SPREAD == 3 ? cut[pc] * LOADS / 16 : pc * LOADS / SPREAD;
+                const int d_n = (SKEW ? A_IT + part * W_IT / (PARTS - 1) : SPREAD == 3 ? cut[pc + 1] * LOADS / 16 : (pc + 1) * LOADS / SPREAD) - d_lo;
 #pragma unroll
-                for (int d = d_lo + i * d_n / NM; d < d_lo + (i + 1) * d_n / NM; ++d) issue_one(d);
+                for (int d = d_lo + ip * d_n / NMP; d < d_lo + (ip + 1) * d_n / NMP; ++d)
+                    if (SKEW && d >= A_IT ? on(refill_w) : on(refill_a)) issue_one(d);
             }
             if (i < NM / 2) {   // all reads in the first half: the last one has half a step to come back
 #pragma unroll
@@ -716,17 +746,18 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // (8-bit operands on 256 x 256 with eight waves, two per SIMD, hide the loads' latency without the skewed ring, but a wave's 64 x 128
     // then reads 96 KB of fragments per k step of 1024 cycles beside the 32 KB that land, all the LDS delivers; four waves read
     // 64 KB.  13B layer at T = 3875 on codes: eight waves 1257 us, with the skewed ring too; four 1231, skewed 1194.)
-    constexpr bool FIXED = NM >= 6 && !(EPI == EPI_SWIGLU && BM == 128);
+    constexpr bool FIXED = BM * BN >= 6 * 4096 && !(EPI == EPI_SWIGLU && BM == 128);
     static_assert(!SKEW || FIXED, "the skewed ring's weights are issued in the fixed order only");
     Stage cur{0, 0};  // stage being computed
-    // One k iteration (one LDS stage).  refill_open: the refill begun at the previous hand-over is still being
-    // issued; refill_next: this iteration's hand-over starts another one.
-    auto iteration = [&](int kt, auto refill_open, auto refill_next) __attribute__((always_inline)) {
+    // One k iteration (one LDS stage).  open_a, open_w: what the refill begun at the previous hand-over still issues (stage
+    // kt - 1 + NS of the activations, kt - 1 + NSW of the weights, if there is one); next_a, next_w: what this iteration's
+    // hand-over starts (stages kt + NS and kt + NSW).  Without the skew both flags of a pair are the same.
+    auto iteration = [&](int kt, auto open_a, auto open_w, auto next_a, auto next_w) __attribute__((always_inline)) {
         const Stage nxt{cur.a + 1 == NS ? 0 : cur.a + 1, cur.w + 1 == NSW ? 0 : cur.w + 1};
 #pragma unroll
         for (int ks = 0; ks + 1 < KSTEPS; ++ks) {
             if (FIXED) {
-                k_step(ks & 1, cur, ks + 1, ks + 1, refill_open);
+                k_step(ks & 1, cur, ks + 1, ks + 1, open_a, open_w);
             } else {
                 load_frags((ks + 1) & 1, cur, ks + 1);
 #pragma unroll
@@ -737,27 +768,27 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         // NS - 2 younger ones may stay in flight), hand over, and start refilling the freed buffer.
         // After the last stage this reads fragments nobody uses.
         constexpr int LB = (KSTEPS - 1) & 1;
-        constexpr bool steady = std::is_same_v<decltype(refill_next), std::true_type>;   // then kt + NS < nk
+        constexpr bool steady = std::is_same_v<decltype(next_w), std::true_type>;   // then kt + NSW < nk
         if ((NS == 2 && !SKEW) || (!steady && kt + NSW - 1 >= nk))
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         else
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * LOADS + (SKEW ? W_IT : 0)) : "memory");
         __syncthreads();
-        if (on(refill_next)) {
+        if (on(next_a)) {
             rf_a = uniform_ptr(a_src((kbeg + kt + NS) * BKD));
             rf_w = uniform_ptr(w_src((kbeg + kt + NSW) * BKD));
             rf_la = __builtin_amdgcn_readfirstlane(lds0 + cur.a * A_BYTES + wave * 1024);
             rf_lw = __builtin_amdgcn_readfirstlane(lds0 + W_LDS + cur.w * W_BYTES + wave * 1024);
         }
         if (FIXED) {
-            k_step(LB, nxt, 0, 0, refill_next);
+            k_step(LB, nxt, 0, 0, next_a, next_w);
         } else {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
                 mfma_one(LB, i);
                 __builtin_amdgcn_sched_barrier(0);
-                if (on(refill_next)) {
+                if (on(next_a)) {   // (never skewed)
 #pragma unroll
                     for (int d = i * LOADS / NM; d < (i + 1) * LOADS / NM; ++d) issue_one(d);
                 }
@@ -771,17 +802,17 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         }
         cur = nxt;
     };
-    // first iteration (nothing to refill yet), steady state (every hand-over refills), drain
+    // first iteration (nothing to refill yet), steady state (every hand-over refills both rings), drain
     int kt = 0;
     if (nk > 0) {
-        iteration(0, false, NS < nk);
+        iteration(0, false, false, NS < nk, NSW < nk);
         kt = 1;
     }
-    for (; kt < nk - NS; ++kt) iteration(kt, std::true_type{}, std::true_type{});
-    for (; kt < nk; ++kt) iteration(kt, kt - 1 + NSW < nk, kt + NS < nk);
+    for (; kt < nk - NSW; ++kt) iteration(kt, std::true_type{}, std::true_type{}, std::true_type{}, std::true_type{});
+    for (; kt < nk; ++kt) iteration(kt, kt - 1 + NS < nk, kt - 1 + NSW < nk, kt + NS < nk, kt + NSW < nk);
     if (EPI != EPI_SLAB && tail) {
         // Partial tile -> this split's slab (registers 4 c .. 4 c + 3 of accumulator tile (tn, tm) of
-        // thread tid are the 16 bytes at ((tn TM + tm) 4 + c) * threads + tid: coalesced).
+        // thread tid are the 16 bytes at ((tn TM + tm) C + c) * threads + tid: coalesced).
         // gemm_tail_finish_kernel, launched behind this kernel, adds the slabs of a tile in split order and
         // runs the epilogue; the kernel boundary is what makes the slabs of workgroups on other XCDs
         // (other L2s) visible, so nothing here waits or fences.
@@ -791,12 +822,14 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
+            for (int tm = 0; tm < TM; ++tm) {
+                constexpr int C = MR * MR / 256;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
+                for (int c = 0; c < C; ++c) {
                     vec4_t v = {acc[tn][tm][4 * c], acc[tn][tm][4 * c + 1], acc[tn][tm][4 * c + 2], acc[tn][tm][4 * c + 3]};
-                    slab[((tn * TM + tm) * 4 + c) * NT] = v;
+                    slab[((tn * TM + tm) * C + c) * NT] = v;
                 }
+            }
         return;
     }
     if constexpr (EPI != EPI_SLAB) {   // the epilogue takes over the ring: every wave is done with it
@@ -804,8 +837,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __syncthreads();
     }
-    gemm_epilogue<BM, BN, EPI, D, TM, F8>(acc, p, tile_m, tile_n, wm, wn, l32, g, 0, split,
-                                                    smem + wave * epi_wave_bytes<BN>());
+    gemm_epilogue<BM, BN, EPI, D, F8>(acc, p, tile_m, tile_n, wm, wn, lane, 0, split, smem + wave * epi_wave_bytes<BN>());
 }
 
 // Second half of a tail split: workgroup (tail tile, row tm of accumulator tiles) has the thread layout of
@@ -813,37 +845,45 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
 // does not depend on scheduling) and runs the GEMM's own epilogue on it.
 template <int BM, int BN, int EPI, int D, bool SC = false>
 __global__ void __launch_bounds__(64 * WGM * WGN) gemm_tail_finish_kernel(GemmArgs p) {
-    constexpr int NW = WGM * WGN, NT = 64 * NW, TM = BM / (32 * WGM), TN = BN / (32 * WGN), AREA4 = BM * BN / 4;
+    constexpr bool M16 = mfma16(EPI, SC);
+    constexpr int MR = M16 ? 16 : 32, C = MR * MR / 256;   // 16-byte pieces of an accumulator tile
+    constexpr int NW = WGM * WGN, NT = 64 * NW, TM = BM / (MR * WGM), TN = BN / (MR * WGN), AREA4 = BM * BN / 4;
+    constexpr int H = 32 / MR;                             // rows of accumulator tiles a workgroup finishes: 32 tokens per wave
     typedef float vec4_t __attribute__((ext_vector_type(4)));
+    using acc_t = std::conditional_t<M16, f32x4_t, f32x16_t>;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
-    const int l32 = lane & 31, g = lane >> 5;
-    const int tail_idx = blockIdx.x / TM, tm_sel = blockIdx.x % TM;
+    const int tail_idx = blockIdx.x / (TM / H), tm_sel = blockIdx.x % (TM / H);
     int tile_m, tile_n;
     tile_coords(p.tiles_m * p.tiles_n - p.tail_tiles + tail_idx, p.tiles_m, p.tiles_n, tile_m, tile_n);
-    f32x16_t acc[TN][1];
+    acc_t acc[TN][H];
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[tn][0][r] = 0.f;
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int r = 0; r < 4 * C; ++r) acc[tn][h][r] = 0.f;
     for (int q = 0; q < p.tail_splits; ++q) {
         const vec4_t* src = reinterpret_cast<const vec4_t*>(p.tail_buf) + ((size_t)q * p.tail_tiles + tail_idx) * AREA4 + tid;
-        vec4_t v[TN][4];
+        vec4_t v[TN][H][C];
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) v[tn][c] = src[((tn * TM + tm_sel) * 4 + c) * NT];
+            for (int h = 0; h < H; ++h)
+#pragma unroll
+                for (int c = 0; c < C; ++c) v[tn][h][c] = src[((tn * TM + H * tm_sel + h) * C + c) * NT];
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
+            for (int h = 0; h < H; ++h)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[tn][0][4 * c + e] += v[tn][c][e];
+                for (int c = 0; c < C; ++c)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[tn][h][4 * c + e] += v[tn][h][c][e];
     }
     __shared__ __align__(16) unsigned char rows[NW * epi_wave_bytes<BN>()];
-    gemm_epilogue<BM, BN, EPI, D, 1, SC>(acc, p, tile_m, tile_n, wm, wn, l32, g, tm_sel, 0,
-                                                   rows + wave * epi_wave_bytes<BN>());
+    gemm_epilogue<BM, BN, EPI, D, SC>(acc, p, tile_m, tile_n, wm, wn, lane, tm_sel, 0, rows + wave * epi_wave_bytes<BN>());
 }
 
 // ------------------------------------------------------------------------------------------

@@ -91,6 +91,44 @@ def test_whole_tiles_of_any_shape_give_the_same_bits(rs, T, w8a8):
             assert torch.equal(out, outs[0]), (epi, tile)
 
 
+@pytest.mark.parametrize("w8a8", [False, True], ids=["bf16", "codes"])
+@pytest.mark.parametrize("packed", [False, True], ids=["rows", "packed"])
+@pytest.mark.parametrize("nk", [1, 2, 3, 4, 5, 7])
+def test_rings_of_few_stages(rs, nk, packed, w8a8):
+    """Every tile shape where k is as short as its rings of stages and shorter: what a hand-over refills ends with the matrix.  Integers
+    and multiples of 1/64 (codes: 0, 1 and 2): every order of the sums is exact, so every tile has the product's own bits."""
+    T, N = 257, 520
+    g = torch.Generator(device="cuda").manual_seed(nk)
+    if w8a8:
+        K = 128 * nk
+        codes = lambda *s: torch.tensor([0, 0x38, 0x40], dtype=torch.uint8, device="cuda")[torch.randint(0, 3, s, generator=g, device="cuda")]
+        value = lambda c: c.view(torch.float8_e4m3fn).double()
+        a, w, sw = codes(T, K), codes(N, K), torch.full((N,), 0.5, device="cuda")
+        want = (value(a).cpu() @ value(w).cpu().T * 0.25).float()
+        wp = rs.pack_codes(w) if packed else w
+        run = lambda out: rs.relserve_linear_w8a8(a, wp, sw, 0.5, 1, None, out, n=N if packed else 0)
+    else:
+        K = 64 * nk
+        a = torch.randint(-4, 5, (T, K), generator=g, device="cuda").bfloat16()
+        w = (torch.randint(-4, 5, (N, K), generator=g, device="cuda").float() / 64).bfloat16()
+        want = (a.double().cpu() @ w.double().cpu().T).float()
+        if packed:
+            wp = torch.empty(rs.relserve_packed_weight_elems(N, K), dtype=torch.bfloat16, device="cuda")
+            rs.relserve_pack_weight(w, wp)
+            run = lambda out: rs.relserve_linear_packed(a, wp, N, 1, None, out)
+        else:
+            run = lambda out: rs.relserve_linear(a, w, 1, None, out)
+    for tile in (-1, 0, 1, 2, 3, 4):
+        out = torch.full((T, N), float("nan"), dtype=torch.float32, device="cuda")
+        rs.relserve_debug_force_gemm_plan(tile, 0)
+        try:
+            run(out)
+            torch.cuda.synchronize()
+        finally:
+            rs.relserve_debug_force_gemm_plan(-1, 0)
+        assert torch.equal(out.cpu(), want), tile
+
+
 def test_iteration_of_640_tokens_keeps_its_sums_whole(rs):
     """The q/k/v projection of a 13B layer at T = 640 (128 decode rows and a 512-token chunk) fills its rounds well enough to
     split nothing: the appended keys and values carry the bits of whole tiles, as its gate/up projection's sums do."""
