@@ -185,9 +185,8 @@ __device__ __forceinline__ void store_unit(const GemmArgs& p, int t, int n_lo, i
     }
 }
 
-// Epilogue shared by the GEMM kernels.  Register r of a 32 x 32 accumulator tile (tn, tm) holds feature
-// 32 tn + 8 (r / 4) + 4 g + r % 4 of the wave's feature range and token 32 tm + l32 of its token range; of a 16 x 16 one (M16),
-// feature 16 tn + 4 (lane / 16) + r and token 16 tm + lane % 16.
+// Epilogue of the kernels whose results are 32 x 32.  Register r of accumulator tile (tn, tm) holds feature
+// 32 tn + 8 (r / 4) + 4 g + r % 4 of the wave's feature range and token 32 tm + l32 of its token range.
 // acc holds whole rows of 32 tokens, starting at row tm_base (the GEMM kernels hold all of the wave's; the tail finish kernel one
 // per workgroup, which with its 64 KB of LDS lets two workgroups share a CU).
 // SC: the sums are products of 8-bit codes and take the factor a_scale * w_scale[feature] as they are read.
@@ -197,9 +196,7 @@ __device__ __forceinline__ void store_unit(const GemmArgs& p, int t, int n_lo, i
 // 128-byte lines (128 - 512 consecutive bytes per token), and the residual and the rotary table are read the same way, one
 // accumulator row ahead.  Straight from the accumulator layout a store instruction wrote 32 pieces of 16 bytes, and an L2
 // that serves 32 CUs took each piece as a request of its own; the loads were one serial round trip per quad, the
-// accumulators leaving no registers for more (they spilled; now nothing does with four waves).
-// 13B layer, T = 7963: q/k/v 1056 -> 967 us, W_o 384 -> 353, W_down 894 -> 861, gate/up 1680 -> 1650; on 8-bit operands at
-// T = 3875 q/k/v 317 -> 279 us, W_down with its tail 278 -> 253.
+// accumulators leaving no registers for more.  On 8-bit operands at T = 3875 q/k/v 317 -> 279 us, W_down with its tail 278 -> 253.
 constexpr int WGM = 2, WGN = 2;   // grid of waves over a tile
 template <int BN>
 constexpr int epi_wave_bytes() { return 32 * (BN / WGN) * 4; }
@@ -207,13 +204,11 @@ constexpr int epi_wave_bytes() { return 32 * (BN / WGN) * 4; }
 template <int BM, int BN, int EPI, int D, bool SC = false, typename Acc, int TNA, int TMA>
 __device__ __forceinline__ void gemm_epilogue(const Acc (&acc)[TNA][TMA], const GemmArgs& p, int tile_m, int tile_n, int wm, int wn,
                                               int lane, int tm_base, int split, unsigned char* lds) {
-    constexpr bool M16 = std::is_same_v<Acc, f32x4_t>;
-    constexpr int TM = M16 ? TMA / 2 : TMA, TN = BN / (32 * WGN);
-    static_assert(TNA == (M16 ? 2 * TN : TN), "the wave's features");
+    constexpr int TM = TMA, TN = BN / (32 * WGN);
+    static_assert(TNA == TN, "the wave's features");
     const int t0 = tile_m * BM + 32 * tm_base + wm * (BM / WGM);
     const int l32 = lane & 31, g = lane >> 5;
     if constexpr (EPI == EPI_SLAB) {
-        static_assert(!M16, "slab stores of 32 consecutive floats");
         // Split-K partial sums -> this split's slab.  These tiles were accumulated with the operands
         // swapped: register r holds token 8 (r / 4) + 4 g + r % 4 and feature l32, so one store
         // instruction writes two runs of 32 consecutive floats.  Plain stores: nothing is read back in
@@ -296,17 +291,7 @@ __device__ __forceinline__ void gemm_epilogue(const Acc (&acc)[TNA][TMA], const 
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             if (t0 + 32 * tm >= p.T) break;   // padding: nothing of this accumulator row (or the ones behind it) is stored
-            if constexpr (M16) {
-                unsigned char* wr = lds + (lane & 15) * ROWB;
-#pragma unroll
-                for (int tn = 0; tn < TNA; ++tn)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const f32x4_t v = acc[tn][2 * tm + h];
-                        *reinterpret_cast<float4*>(wr + 16 * h * ROWB + (((4 * tn + (lane >> 4)) ^ (lane & 15)) << 4)) =
-                            make_float4(v[0], v[1], v[2], v[3]);
-                    }
-            } else {
+            {
                 unsigned char* wr = lds + l32 * ROWB;
 #pragma unroll
                 for (int tn = 0; tn < TN; ++tn)
@@ -337,6 +322,245 @@ __device__ __forceinline__ void gemm_epilogue(const Acc (&acc)[TNA][TMA], const 
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+}
+
+// Which feature of a wave's range MFMA row i (= 4 (lane / 16) + r of the result) of weight fragment tn stands for, where results are
+// 16 x 16 (M16).  fp32 rows leave as they come: a lane has 4 consecutive features, the four lanes of a token 64 consecutive bytes.
+// Where bf16 or codes are written (PAIRED16) two fragments share 32 features so that a lane has 8 consecutive ones: 64 bytes again.
+// The permutation costs nothing: it is which rows of the weights in the LDS a lane reads.
+constexpr bool paired16(int epi) { return epi != EPI_RES_BF16_OUT_F32; }
+template <int EPI>
+__device__ __forceinline__ int frag_row16(int i) { return paired16(EPI) ? 8 * (i >> 2) + (i & 3) : i; }
+template <int EPI>
+constexpr int frag_base16(int tn) { return paired16(EPI) ? 32 * (tn >> 1) + 4 * (tn & 1) : 16 * tn; }
+
+// Epilogue of the 16 x 16 kernels, straight from the accumulators: acc[tn][tm] holds fragment tn's features of token
+// 16 tm + lane % 16 (of 32 tm_base on).  A workgroup has one wave per SIMD, so the epilogue lasts as long as its instructions take to
+// issue: there is no pass through the LDS, a row of tiles has one scalar base address and the distances of its accesses are constants,
+// and tiles that end inside the matrix (FULL) test nothing per access.  Every access covers runs of 64 bytes (see frag_row16); what a
+// row of tiles reads besides the sums is fetched one row ahead.  Cycles of a 256 x 256 tile of bf16 outputs: 13600 through the LDS, 8600
+// here, which is what an XCD's 32 CUs, all writing at once, get through to memory (490 bytes a cycle).  8192 x 28672 x 5120 with the k
+// loop's fewer instructions (k_step) 1820 -> 1675 us; layer steps, with 16 x 16 products: 13B at T = 7963 4248 -> 3973, 70B at T = 2304
+// 3163 -> 2919.  (Workgroups that stay and load their next tile's first stages beside the epilogue gained nothing on this: the next
+// tile's first waits then include the stores.)
+template <int BM, int BN, int EPI, int D, bool SC, bool FULL, int TN, int TM>
+__device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM], const GemmArgs& p, int tile_n, int t0, int wn, int lane) {
+    constexpr int FEAT = BN / WGN;
+    static_assert(TN == FEAT / 16, "the wave's features");
+    const int l16 = lane & 15, gq = lane >> 4;
+    auto quad = [&](int tn, int tm) __attribute__((always_inline)) {
+        f32x4_t v = acc[tn][tm];
+        asm volatile("" : "+v"(v));   // copied here: left to itself the compiler moves all sums to the other register file first, and spills
+        return make_float4(v[0], v[1], v[2], v[3]);
+    };
+    auto scaled = [](float4 v, const float4& s) __attribute__((always_inline)) { return make_float4(v.x * s.x, v.y * s.y, v.z * s.z, v.w * s.w); };
+    auto code_scale = [&](int n) __attribute__((always_inline)) {
+        float4 s = *reinterpret_cast<const float4*>(p.w_scale + n);
+        s.x *= p.a_scale; s.y *= p.a_scale; s.z *= p.a_scale; s.w *= p.a_scale;
+        return s;
+    };
+    auto pack8 = [](const float4& a, const float4& b) __attribute__((always_inline)) {
+        return make_uint4(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w), pack_bf16x2(b.x, b.y), pack_bf16x2(b.z, b.w));
+    };
+    auto codes8 = [](const float4& a, const float4& b, float s) __attribute__((always_inline)) {
+        return make_uint2(pack_fp8x4(a.x * s, a.y * s, a.z * s, a.w * s), pack_fp8x4(b.x * s, b.y * s, b.z * s, b.w * s));
+    };
+    // rows of tokens: base (uniform) + this lane's offset; lanes past T take the last token's operands and store nothing
+    auto row_off = [&](int tm, int64_t pitch) __attribute__((always_inline)) -> uint32_t {   // bytes from row t0 + 16 tm
+        return (uint32_t)(FULL ? l16 : min(l16, max(p.T - 1 - t0 - 16 * tm, 0))) * (uint32_t)pitch;
+    };
+    if constexpr (EPI == EPI_RES_BF16_OUT_F32) {
+        const int n0 = tile_n * BN + wn * FEAT;
+        auto ok = [&](int tn) { return FULL || n0 + 4 * gq + 16 * tn < p.N; };
+        float4 sc[SC ? TN : 1];
+        if constexpr (SC) {
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+                if (ok(tn)) sc[tn] = code_scale(n0 + 4 * gq + 16 * tn);
+        }
+        uint2 res[2][TN];
+        const bool add = p.residual != nullptr;   // no residual given: plain fp32 output
+        auto fetch = [&](int tm) __attribute__((always_inline)) {
+            const char* base = static_cast<const char*>(p.residual) + ((int64_t)min(t0 + 16 * tm, p.T - 1) * p.N + n0) * 2;
+            const uint32_t off = row_off(tm, (int64_t)p.N * 2) + 8 * gq;
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+                res[tm & 1][tn] = make_uint2(0, 0);
+                if (add && ok(tn)) res[tm & 1][tn] = *reinterpret_cast<const uint2*>(base + off + 32 * tn);
+            }
+        };
+        fetch(0);
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            if (!FULL && t0 + 16 * tm >= p.T) break;   // padding: nothing of this row of tiles (or the ones behind it) is stored
+            __builtin_amdgcn_sched_barrier(0);   // row after row: every register is taken by sums still to be stored
+            if (tm + 1 < TM) fetch(tm + 1);
+            char* base = static_cast<char*>(p.out) + ((int64_t)(t0 + 16 * tm) * p.N + n0) * 4;
+            const uint32_t off = row_off(tm, (int64_t)p.N * 4) + 16 * gq;
+            if (!FULL && t0 + 16 * tm + l16 >= p.T) continue;
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+                float4 v = quad(tn, tm);
+                if constexpr (SC) v = scaled(v, sc[tn]);
+                const uint2 r = res[tm & 1][tn];
+                if (ok(tn)) *reinterpret_cast<float4*>(base + off + 64 * tn) =
+                    make_float4(v.x + bf16_lo(r.x), v.y + bf16_hi(r.x), v.z + bf16_lo(r.y), v.w + bf16_hi(r.y));
+            }
+        }
+    } else if constexpr (EPI == EPI_QKV_ROPE) {
+        constexpr int HEADS = FEAT / D, GH = D / 64, TH = D / 16;   // heads of the wave, 8-feature groups of half a head, tiles of a head
+        const int head0 = (tile_n * BN + wn * FEAT) / D, kv_dim = p.n_kv * D;
+        float4 sc[SC ? TN : 1];
+        if constexpr (SC) {
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+                if (head0 + tn / TH < p.n_q + 2 * p.n_kv) sc[tn] = code_scale(head0 * D + frag_base16<EPI>(tn) + 8 * gq);
+        }
+        float4 cs[2][GH][4];
+        int slot[2];
+        auto fetch = [&](int tm) __attribute__((always_inline)) {
+            const int first = min(t0 + 16 * tm, p.T - 1);
+            slot[tm & 1] = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(p.tok_slot + first) + row_off(tm, 4));
+            const char* base = reinterpret_cast<const char*>(p.rope_cs + (int64_t)first * (D / 2));
+            const uint32_t off = row_off(tm, D * 4) + 64 * gq;
+#pragma unroll
+            for (int u = 0; u < GH; ++u)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) cs[tm & 1][u][c] = *reinterpret_cast<const float4*>(base + off + 256 * u + 16 * c);
+        };
+        fetch(0);
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            if (!FULL && t0 + 16 * tm >= p.T) break;
+            __builtin_amdgcn_sched_barrier(0);
+            if (tm + 1 < TM) fetch(tm + 1);
+            if (!FULL && t0 + 16 * tm + l16 >= p.T) continue;
+#pragma unroll
+            for (int hh = 0; hh < HEADS; ++hh) {
+                const int head = __builtin_amdgcn_readfirstlane(head0 + hh);
+                if (head >= p.n_q + 2 * p.n_kv) continue;
+                const bool is_q = head < p.n_q, is_k = !is_q && head < p.n_q + p.n_kv;
+                float4 lo[GH][2], hi[GH][2];
+#pragma unroll
+                for (int u = 0; u < GH; ++u)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const int tl = hh * TH + 2 * u + h, th = tl + TH / 2;
+                        lo[u][h] = quad(tl, tm);
+                        hi[u][h] = quad(th, tm);
+                        if constexpr (SC) lo[u][h] = scaled(lo[u][h], sc[tl]), hi[u][h] = scaled(hi[u][h], sc[th]);
+                    }
+                if (is_q || is_k) {
+#pragma unroll
+                    for (int u = 0; u < GH; ++u)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            const float4 a = lo[u][h], b = hi[u][h];
+                            rotate4(a, b, cs[tm & 1][u][2 * h], cs[tm & 1][u][2 * h + 1], lo[u][h], hi[u][h]);
+                        }
+                }
+                if (p.kv_fp8 && !is_q) {   // quantised cache: one byte per element, quantised from fp32
+                    uint8_t* dst = reinterpret_cast<uint8_t*>(is_k ? p.k_pages : p.v_pages) + (head - p.n_q - (is_k ? 0 : p.n_kv)) * D +
+                                   (int64_t)slot[tm & 1] * kv_dim + 8 * gq;
+                    const float s = is_k ? p.k_inv : p.v_inv;
+#pragma unroll
+                    for (int u = 0; u < GH; ++u) {
+                        *reinterpret_cast<uint2*>(dst + 32 * u) = codes8(lo[u][0], lo[u][1], s);
+                        *reinterpret_cast<uint2*>(dst + 32 * u + D / 2) = codes8(hi[u][0], hi[u][1], s);
+                    }
+                } else {
+                    uint16_t* dst = is_q ? static_cast<uint16_t*>(p.out) + (int64_t)(t0 + 16 * tm + l16) * (p.n_q * D) + head * D
+                                         : (is_k ? p.k_pages : p.v_pages) + (head - p.n_q - (is_k ? 0 : p.n_kv)) * D + (int64_t)slot[tm & 1] * kv_dim;
+                    dst += 8 * gq;
+#pragma unroll
+                    for (int u = 0; u < GH; ++u) {
+                        *reinterpret_cast<uint4*>(dst + 32 * u) = pack8(lo[u][0], lo[u][1]);
+                        *reinterpret_cast<uint4*>(dst + 32 * u + D / 2) = pack8(hi[u][0], hi[u][1]);
+                    }
+                }
+            }
+        }
+    } else {
+        // bf16 rows (or codes of a SwiGLU product): groups of 8 features a lane
+        constexpr bool SWI = EPI == EPI_SWIGLU;
+        constexpr int GROUPS = SWI ? TN / 4 : TN / 2;
+        const int cols = SWI ? p.n_half : p.N;
+        const int n0 = SWI ? tile_n * (BN / 2) + wn * (FEAT / 2) : tile_n * BN + wn * FEAT;
+        auto ok = [&](int u, int h) { return FULL || n0 + 8 * gq + 32 * u + 4 * h < cols; };
+        float4 sc[SC ? TN : 1];
+        if constexpr (SC) {
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+                const int i = SWI ? tn % (TN / 2) : tn, n = n0 + 8 * gq + frag_base16<EPI>(i);
+                if (ok(i / 2, i % 2)) sc[tn] = code_scale(SWI && tn >= TN / 2 ? p.n_half + n : n);
+            }
+        }
+        const bool codes = SC && SWI && p.out_f8;   // the down projection reads codes (n_half is a multiple of 8)
+        const int esize = codes ? 1 : 2;
+        float4 res[2][EPI == EPI_RES_F32_OUT_BF16 ? GROUPS : 1][2];
+        auto fetch = [&](int tm) __attribute__((always_inline)) {
+            if constexpr (EPI == EPI_RES_F32_OUT_BF16) {
+                const char* base = static_cast<const char*>(p.residual) + ((int64_t)min(t0 + 16 * tm, p.T - 1) * p.N + n0) * 4;
+                const uint32_t off = row_off(tm, (int64_t)p.N * 4) + 32 * gq;
+#pragma unroll
+                for (int u = 0; u < GROUPS; ++u)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        if (ok(u, h)) res[tm & 1][u][h] = *reinterpret_cast<const float4*>(base + off + 128 * u + 16 * h);
+            }
+        };
+        fetch(0);
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            if (!FULL && t0 + 16 * tm >= p.T) break;
+            __builtin_amdgcn_sched_barrier(0);
+            if (tm + 1 < TM) fetch(tm + 1);
+            char* base = static_cast<char*>(p.out) + ((int64_t)(t0 + 16 * tm) * cols + n0) * esize;
+            const uint32_t off = row_off(tm, (int64_t)cols * esize) + 8 * gq * esize;
+            if (!FULL && t0 + 16 * tm + l16 >= p.T) continue;
+#pragma unroll
+            for (int u = 0; u < GROUPS; ++u) {
+                float4 v[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    v[h] = quad(2 * u + h, tm);
+                    if constexpr (SC) v[h] = scaled(v[h], sc[2 * u + h]);
+                    if constexpr (SWI) {
+                        float4 up = quad(TN / 2 + 2 * u + h, tm);
+                        if constexpr (SC) up = scaled(up, sc[TN / 2 + 2 * u + h]);
+                        v[h] = make_float4(silu_mul(v[h].x, up.x), silu_mul(v[h].y, up.y), silu_mul(v[h].z, up.z), silu_mul(v[h].w, up.w));
+                    }
+                    if constexpr (EPI == EPI_RES_F32_OUT_BF16) {
+                        const float4 r = res[tm & 1][u][h];
+                        v[h].x += r.x; v[h].y += r.y; v[h].z += r.z; v[h].w += r.w;
+                    }
+                }
+                if (codes) {
+                    if (ok(u, 0)) *reinterpret_cast<uint2*>(base + off + 32 * u) = codes8(v[0], v[1], p.out_inv);
+                    continue;
+                }
+                const uint4 b = pack8(v[0], v[1]);
+                if constexpr (FULL) {
+                    *reinterpret_cast<uint4*>(base + off + 64 * u) = b;
+                } else {   // 4 by 4: rows may end inside a group or begin at 8-byte boundaries
+                    if (ok(u, 0)) *reinterpret_cast<uint2*>(base + off + 64 * u) = make_uint2(b.x, b.y);
+                    if (ok(u, 1)) *reinterpret_cast<uint2*>(base + off + 64 * u + 8) = make_uint2(b.z, b.w);
+                }
+            }
+        }
+    }
+}
+
+template <int BM, int BN, int EPI, int D, bool SC, int TN, int TM>
+__device__ __forceinline__ void gemm_epilogue16(const f32x4_t (&acc)[TN][TM], const GemmArgs& p, int tile_m, int tile_n, int wm, int wn,
+                                                int lane, int tm_base) {
+    const int t0 = tile_m * BM + 32 * tm_base + wm * (BM / WGM);
+    const int cols = EPI == EPI_SWIGLU ? p.n_half : p.N, last = (tile_n + 1) * (EPI == EPI_SWIGLU ? BN / 2 : BN);
+    const bool aligned = EPI == EPI_QKV_ROPE || EPI == EPI_RES_BF16_OUT_F32 || (cols % 8 == 0 && reinterpret_cast<uintptr_t>(p.out) % 16 == 0);
+    if (t0 + 16 * TM <= p.T && last <= cols && aligned)
+        gemm_epilogue16_rows<BM, BN, EPI, D, SC, true>(acc, p, tile_n, t0, wn, lane);
+    else if (t0 < p.T)
+        gemm_epilogue16_rows<BM, BN, EPI, D, SC, false>(acc, p, tile_n, t0, wn, lane);
 }
 
 template <int BM, int BN, int EPI, int D = 0>
@@ -476,12 +700,24 @@ __device__ __forceinline__ const char* uniform_ptr(const char* ptr) {
 // NT = non-temporal: for bytes that are read once (the weights of a batch of one token tile).  A streaming read of
 // HBM reaches 7.1-7.4 TB/s with the hint against 6.3-6.4 TB/s without (measured with 32 KB per workgroup in flight);
 // operands that other workgroups read again keep the default policy, which lets the L2 hold them.
+// In two halves: dma16_to names the LDS address lds_addr + at (the constant) in m0, dma16_from loads; one instruction at least has to
+// stand between the two (a load reads m0 too early right behind the scalar instruction that writes it).
+__device__ __forceinline__ void dma16_to(uint32_t lds_addr, int at) {
+    asm volatile("s_add_u32 m0, %0, %1" ::"s"(lds_addr), "i"(at) : "memory", "scc");
+}
 template <bool NT = false>
-__device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_addr) {
+__device__ __forceinline__ void dma16_from(const void* base, uint32_t voff) {
     if (NT)
-        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "s"(lds_addr) : "memory");
+        asm volatile("global_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base) : "memory");
     else
-        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds_addr) : "memory");
+        asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base) : "memory");
+}
+template <bool NT = false>
+__device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_addr, int at) {
+    if (NT)
+        asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "s"(lds_addr), "i"(at) : "memory", "scc");
+    else
+        asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds_addr), "i"(at) : "memory", "scc");
 }
 
 // BKD = k extent of one LDS stage (64 or 32), NS = stages in the ring (NS - 1 are in flight).
@@ -514,8 +750,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     constexpr int A_BYTES = BM * ROWB, W_BYTES = BN * ROWB, W_LDS = NS * A_BYTES;   // NS stages of activations, then NSW of weights
     constexpr int KSTEPS = F8 || M16 ? BKD / 32 : BKD / 16;
     constexpr int LOADS = A_IT + W_IT;                   // wave loads per stage
-    static_assert(BKD == 64 || BKD == 32, "stage depth");
-    static_assert(!(F8 || M16) || BKD == 64, "the fragment double buffer needs an even number of k steps per stage");
+    static_assert(BKD == 64, "stage depth: a slice of the packed weights");
     static_assert(NSW * LOADS < 64, "vmcnt field");
     static_assert(!SKEW || KSTEPS > 1, "the skewed ring's weights are issued between hand-overs");
     static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU needs gate and up tiles in one wave");
@@ -528,17 +763,16 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     const int wm = wave / WGN, wn = wave % WGN;
     const int fr = lane % MR, g = lane / MR;             // this lane's row of an operand fragment, and its part of the k step
 
-    const int n_tiles = p.tiles_m * p.tiles_n;
-    int tile, split;
+    const int K = p.K;
+    const int n_tiles = p.tiles_m * p.tiles_n, tail_units = p.tail_tiles * p.tail_splits, dp_tiles = n_tiles - p.tail_tiles;
+    int tile, split = 0, tail_idx = 0;
     bool tail = false;
-    int tail_idx = 0;
     if (EPI == EPI_SLAB) {
         tile = remap_xcd(blockIdx.x % n_tiles, n_tiles);
         split = blockIdx.x / n_tiles;
     } else {
         // the tail units come first in the grid: their short k ranges and slab stores are over before the
         // last whole tiles finish
-        const int tail_units = p.tail_tiles * p.tail_splits, dp_tiles = n_tiles - p.tail_tiles;
         tail = (int)blockIdx.x < tail_units;
         if (tail) {
             const int u = remap_xcd(blockIdx.x, tail_units);   // runs of one split, consecutive tiles, per XCD
@@ -546,14 +780,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             tail_idx = u % p.tail_tiles;
             tile = dp_tiles + tail_idx;
         } else {
-            split = 0;
             tile = remap_xcd(blockIdx.x - tail_units, dp_tiles);
         }
     }
     int tile_m, tile_n;
     tile_coords(tile, p.tiles_m, p.tiles_n, tile_m, tile_n);
-    const int t0 = tile_m * BM;
-    const int K = p.K;
 
     // ---- per-lane source offsets: wave load j of this wave fills LDS rows (NW j + wave) * RPI .. ;
     // lane l owns row l / CPR of those and slot l % CPR, which holds the row's chunk slot ^ swz(row).
@@ -564,60 +795,54 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     const uint32_t lrow = lane / CPR;
     const uint32_t row_lo = (uint32_t)(wave * RPI) + lrow;   // LDS row modulo NW * RPI (>= 32): all the swizzle needs
     const uint32_t chunk = (lane % CPR) ^ (BKD == 64 ? ((row_lo >> 1) & 7) : ((row_lo >> 2) & 3));
+    // (16 x 16 results of permuted features read rows 0-3, 8-11, 16-19 and 24-27 of 32, four further on, or so)
+    constexpr bool PERM = M16 && paired16(EPI);
+    auto perm_swz = [](int row) { return ((row >> 1) & 1) | ((row >> 2) & 6); };
+    const uint32_t w_chunk = PERM ? (lane % CPR) ^ perm_swz(row_lo) : chunk;
     uint32_t a_voff[A_IT], w_voff[W_IT];
+    // row-major: row n starts at n * K; packed: block n / 256 holds, k slice after k slice, 256 rows of 128 bytes
+    const uint32_t w_shift = p.w_packed ? 8 : 0, w_block = (uint32_t)K * (p.w_packed ? 512u : 2u), w_mask = p.w_packed ? 255 : 0;
 #pragma unroll
     for (int j = 0; j < A_IT; ++j) {
-        const int t = min(t0 + (NW * j + wave) * RPI + (int)lrow, p.T - 1);
+        const int t = min(tile_m * BM + (NW * j + wave) * RPI + (int)lrow, p.T - 1);
         a_voff[j] = ((uint32_t)t * (uint32_t)K + chunk * 8) * 2;
     }
 #pragma unroll
     for (int j = 0; j < W_IT; ++j) {
         const int lr = (NW * j + wave) * RPI + (int)lrow;
-        int n;
+        uint32_t n;
         if (EPI == EPI_SWIGLU) {
-            constexpr int HALF = BN / 2;
+            constexpr int HALF = BN / 2;   // (a wave load's rows lie in one half)
             const int gi = min(tile_n * HALF + (lr % HALF), p.n_half - 1);
-            n = lr < HALF ? gi : p.n_half + gi;
+            n = NW * j * RPI < HALF ? gi : p.n_half + gi;
         } else {
             n = min(tile_n * BN + lr, p.N - 1);
         }
-        // row-major: row n starts at n * K; packed: block n / 256 holds, k slice after k slice, 256 rows of 128 bytes
-        // (a 32-wide stage is the first or the second half of every row of a slice)
-        w_voff[j] = p.w_packed ? (uint32_t)(n >> 8) * (uint32_t)K * 512u + (uint32_t)(n & 255) * 128u + chunk * 16
-                               : ((uint32_t)n * (uint32_t)K + chunk * 8) * 2;
+        w_voff[j] = (n >> w_shift) * w_block + (n & w_mask) * 128u + w_chunk * 16;
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
-    auto a_src = [&](int k0) { return reinterpret_cast<const char*>(p.a) + (size_t)k0 * 2; };
-    auto w_src = [&](int k0) {
-        return reinterpret_cast<const char*>(p.w) + (p.w_packed ? (size_t)(k0 >> 6) * 32768 + (size_t)(k0 & 63) * 2 : (size_t)k0 * 2);
-    };
-    auto issue_a = [&](int stage, int k0) {
-        const char* abase = a_src(k0);
-        const uint32_t la = lds0 + stage * A_BYTES + wave * 1024;
-#pragma unroll
-        for (int j = 0; j < A_IT; ++j) dma16(abase, a_voff[j], la + j * (NW * 1024));
-    };
-    auto issue_w = [&](int stage, int k0) {
-        const char* wbase = w_src(k0);
-        const uint32_t la = lds0 + W_LDS + stage * W_BYTES + wave * 1024;
-#pragma unroll
-        for (int j = 0; j < W_IT; ++j) dma16<WNT>(wbase, w_voff[j], la + j * (NW * 1024));
-    };
+    const int w_stage = p.w_packed ? 32768 : 128;   // bytes from one k slice of the weights to the next
 
-    // ---- LDS -> MFMA operand offsets
-    int a_rd[TM], w_rd[TN];
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm) a_rd[tm] = (wm * (BM / WGM) + MR * tm + fr) * ROWB;
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn) {
-        int row;
-        if (EPI == EPI_SWIGLU)
-            row = (tn < TN / 2 ? 0 : BN / 2) + wn * (BN / (2 * WGN)) + MR * (tn % (TN / 2)) + fr;
-        else
-            row = wn * (BN / WGN) + MR * tn + fr;
-        w_rd[tn] = W_LDS + row * ROWB;
-    }
+    // ---- LDS -> MFMA operands: this lane's address of the first fragment of a k step inside stage 0; the other fragments lie at
+    // constant distances, which the read instruction holds.
     const int swz = BKD == 64 ? ((fr >> 1) & 7) : ((fr >> 2) & 3);
+    constexpr int w_wave = EPI == EPI_SWIGLU ? BN / (2 * WGN) : BN / WGN;   // first row of the wave's features (SwiGLU: in either half)
+    uint32_t a_lane[KSTEPS], w_lane[KSTEPS];
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+        const uint32_t at = lds0 + fr * ROWB + (((F8 ? 4 * ks + 2 * g : (64 / MR) * ks + g) ^ swz) << 4);
+        a_lane[ks] = at + wm * (BM / WGM) * ROWB;
+        w_lane[ks] = at + W_LDS + wn * w_wave * ROWB;
+        if constexpr (PERM) {
+            const int row = frag_row16<EPI>(fr);
+            w_lane[ks] = lds0 + W_LDS + (wn * w_wave + row) * ROWB + (((4 * ks + g) ^ perm_swz(row)) << 4);
+        }
+    }
+    auto a_dist = [](int tm) { return MR * tm * ROWB; };
+    auto w_dist = [](int tn) {
+        const int half = EPI == EPI_SWIGLU && tn >= TN / 2 ? 1 : 0, i = tn - half * (TN / 2);
+        return (half * (BN / 2) + (M16 ? frag_base16<EPI>(i) : MR * i)) * ROWB;
+    };
 
     using acc_t = std::conditional_t<M16, f32x4_t, f32x16_t>;
     acc_t acc[TN][TM];
@@ -627,42 +852,43 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
             for (int r = 0; r < MR * MR / 64; ++r) acc[tn][tm][r] = 0.f;
-
     using frag_t = std::conditional_t<F8, i32x8_t, bf16x8_t>;
     frag_t wf[2][TN], af[2][TM];
-    auto read_frag = [&](const unsigned char* row, int ks) __attribute__((always_inline)) -> frag_t {
+    typedef const i32x4_t __attribute__((address_space(3))) * lds_chunk;
+    auto read_frag = [&](uint32_t at, int dist) __attribute__((always_inline)) -> frag_t {
         if constexpr (F8) {
-            const uint4 lo = *reinterpret_cast<const uint4*>(row + (((4 * ks + 2 * g) ^ swz) << 4));
-            const uint4 hi = *reinterpret_cast<const uint4*>(row + (((4 * ks + 2 * g + 1) ^ swz) << 4));
-            return i32x8_t{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+            const i32x4_t lo = *(lds_chunk)(uintptr_t)(at + dist), hi = *(lds_chunk)(uintptr_t)((at ^ 16) + dist);
+            return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         } else {
-            return as_bf16x8(*reinterpret_cast<const uint4*>(row + ((((64 / MR) * ks + g) ^ swz) << 4)));
+            return __builtin_bit_cast(bf16x8_t, *(lds_chunk)(uintptr_t)(at + dist));
         }
     };
     struct Stage { int a, w; };   // indices into the two rings
+    struct Source { uint32_t a, w; };
+    auto source = [&](Stage st, int ks) __attribute__((always_inline)) {
+        Source r{a_lane[ks] + st.a * A_BYTES, w_lane[ks] + st.w * W_BYTES};
+        asm("" : "+v"(r.a), "+v"(r.w));   // one sum each, not one for every fragment
+        return r;
+    };
+    auto load_frag_one = [&](int buf, Source src, int i) __attribute__((always_inline)) {   // i-th of the TN + TM fragment reads of a k step
+        if constexpr (M16) {   // the first products of a step need all tokens and one row of features
+            if (i < TM)
+                af[buf][i] = read_frag(src.a, a_dist(i));
+            else
+                wf[buf][i - TM] = read_frag(src.w, w_dist(i - TM));
+        } else {
+            if (i < TN)
+                wf[buf][i] = read_frag(src.w, w_dist(i));
+            else
+                af[buf][i - TN] = read_frag(src.a, a_dist(i - TN));
+        }
+    };
     auto load_frags = [&](int buf, Stage st, int ks) __attribute__((always_inline)) {
+        const Source src = source(st, ks);
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) wf[buf][tn] = read_frag(smem + st.w * W_BYTES + w_rd[tn], ks);
-#pragma unroll
-        for (int tm = 0; tm < TM; ++tm) af[buf][tm] = read_frag(smem + st.a * A_BYTES + a_rd[tm], ks);
+        for (int i = 0; i < TN + TM; ++i) load_frag_one(buf, src, i);
     };
 
-    // k range of this workgroup (the whole K unless the launch splits it)
-    const bool part = EPI == EPI_SLAB || tail;
-    const int kbeg = part ? split * p.k_per_split * (64 / BKD) : 0;
-    const int nk = part ? min(p.k_per_split * (64 / BKD), K / BKD - kbeg) : K / BKD;
-    // prologue: fill both rings, wait for stage 0 only
-#pragma unroll
-    for (int s = 0; s < NSW; ++s) {
-        if (s < nk && s < NS) issue_a(s, (kbeg + s) * BKD);
-        if (s < nk) issue_w(s, (kbeg + s) * BKD);
-    }
-    if (nk >= NSW)
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * LOADS + (SKEW ? W_IT : 0)) : "memory");
-    else
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    load_frags(0, Stage{0, 0}, 0);
     auto mfma_one = [&](int buf, int i) __attribute__((always_inline)) {   // i-th of the TN * TM products of a k step
         const int tn = i / TM, tm = i % TM;
         if constexpr (F8)
@@ -674,25 +900,31 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             acc[tn][tm] = EPI == EPI_SLAB ? mfma_32x32x16(af[buf][tm], wf[buf][tn], acc[tn][tm])
                                             : mfma_32x32x16(wf[buf][tn], af[buf][tm], acc[tn][tm]);
     };
-    auto load_frag_one = [&](int buf, Stage st, int ks, int i) __attribute__((always_inline)) {   // i-th of the TN + TM fragment reads of a k step
-        if (i < TN)
-            wf[buf][i] = read_frag(smem + st.w * W_BYTES + w_rd[i], ks);
-        else
-            af[buf][i - TN] = read_frag(smem + st.a * A_BYTES + a_rd[i - TN], ks);
-    };
     // Source of the refill in progress (set at a hand-over): the k slice's first byte in both operands and the
     // freed stages' LDS addresses, so that a load costs its own two instructions plus one scalar add.
-    const char* rf_a = nullptr;
-    const char* rf_w = nullptr;
+    const bool part = EPI == EPI_SLAB || tail;   // k range of this workgroup (the whole K unless the launch splits it)
+    const int kbeg = part ? split * p.k_per_split : 0;
+    const int nk = part ? min(p.k_per_split, K / BKD - kbeg) : K / BKD;
+    const char* rf_a = uniform_ptr(reinterpret_cast<const char*>(p.a) + (size_t)kbeg * ROWB);
+    const char* rf_w = uniform_ptr(reinterpret_cast<const char*>(p.w) + (size_t)kbeg * w_stage);
+    const uint32_t lds_a0 = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024), lds_w0 = lds_a0 + W_LDS;
     uint32_t rf_la = 0, rf_lw = 0;
-    auto issue_one = [&](int i) __attribute__((always_inline)) {   // i-th of the LOADS wave loads of a refill
-        // weights first: they come from further away (HBM) than the activations (L2); the skewed ring has a whole
-        // iteration more for them and needs the activations first
-        const int iw = SKEW ? i - A_IT : i, ia = SKEW ? i : i - W_IT;
-        if (SKEW ? iw >= 0 : iw < W_IT)
-            dma16<WNT>(rf_w, w_voff[iw], rf_lw + iw * (NW * 1024));
+    // The i-th of the LOADS wave loads of a refill.  Weights first: they come from further away (HBM) than the activations (L2); the
+    // skewed ring has a whole iteration more for them and needs the activations first.
+    auto is_w = [](int i) { return SKEW ? i >= A_IT : i < W_IT; };
+    auto nth = [](int i) { return SKEW ? (i >= A_IT ? i - A_IT : i) : (i < W_IT ? i : i - W_IT); };   // of its own operand
+    auto issue_to = [&](int i) __attribute__((always_inline)) { dma16_to(is_w(i) ? rf_lw : rf_la, nth(i) * (NW * 1024)); };
+    auto issue_from = [&](int i) __attribute__((always_inline)) {
+        if (is_w(i))
+            dma16_from<WNT>(rf_w, w_voff[nth(i)]);
         else
-            dma16(rf_a, a_voff[ia], rf_la + ia * (NW * 1024));
+            dma16_from(rf_a, a_voff[nth(i)]);
+    };
+    auto issue_one = [&](int i) __attribute__((always_inline)) {
+        if (is_w(i))
+            dma16<WNT>(rf_w, w_voff[nth(i)], rf_lw, nth(i) * (NW * 1024));
+        else
+            dma16(rf_a, a_voff[nth(i)], rf_la, nth(i) * (NW * 1024));
     };
     // A flag that is either a run-time bool or std::true_type: the steady-state iterations pass the latter, so their
     // loads sit in straight-line code (a branch and its scalar set-up around each load cost more issue slots than
@@ -703,7 +935,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     };
     constexpr int NM = TN * TM, NF = TN + TM;
     // One k step, issued in a fixed order: MFMA i, then the share of the refill loads and of the next
-    // step's fragment reads that falls between MFMA i and i + 1.  A CU's address unit takes one
+    // step's fragment reads that falls between MFMA i and i + 1.  A 16 x 16 MFMA lasts 16 cycles, in which a wave issues three
+    // other instructions: a read or a load goes behind each, never both, a read is one instruction (its address a sum made once a
+    // step) and a load two: 93 instructions beside the 128 MFMAs of an iteration, where 136 left 2450 cycles for 2048 of MFMAs, now 2280.  A CU's address unit takes one
     // 1 KB load per ~16 cycles and a 32 x 32 MFMA lasts 32, so the refill loads of a stage (LOADS per wave,
     // four waves) are spread over SPREAD quarters of the iteration (a k step of 32 x 32 MFMAs is one, of
     // 16 x 16 two); issued back to back they would hold up the MFMAs behind them.  The MFMAs sit on ONE control path on purpose: at a join the compiler would make
@@ -714,25 +948,29 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         // share of the stage's loads issued in each part, cumulative, in sixteenths: the weights (first half
         // of the loads) go out at once, the activations (L2 hits, quick to land) trail over two more parts
         constexpr int cut[5] = {0, 8, 13, 16, 16};
+        const Source src = source(rd_stage, rd_ks);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
+            const int part = step * SUB + i / NMP, ip = i % NMP, pc = part < SPREAD ? part : SPREAD;
+            // (skewed: the activations at once, the weights over all the parts that remain)
+            const int d_lo = SKEW ? (part == 0 ? 0 : A_IT + (part - 1) * W_IT / (PARTS - 1)) : SPREAD == 3 ? cut[pc] * LOADS / 16 : pc * LOADS / SPREAD;
+            const int d_n = (SKEW ? A_IT + part * W_IT / (PARTS - 1) : SPREAD == 3 ? cut[pc + 1] * LOADS / 16 : (pc + 1) * LOADS / SPREAD) - d_lo;
+            const int d0 = d_lo + ip * d_n / NMP, d1 = SKEW || part < SPREAD ? d_lo + (ip + 1) * d_n / NMP : d0;   // the slot's loads
+            auto wanted = [&](int d) __attribute__((always_inline)) { return SKEW && d >= A_IT ? on(refill_w) : on(refill_a); };
+            if (d0 < d1 && wanted(d0)) issue_to(d0);
+            __builtin_amdgcn_sched_barrier(0);
             mfma_one(buf, i);
             __builtin_amdgcn_sched_barrier(0);
-            const int part = step * SUB + i / NMP, ip = i % NMP;
-            if (SKEW || part < SPREAD) {
-                // (skewed: the activations at once, the weights over all the parts that remain)
-                const int pc = part < SPREAD ? part : SPREAD;
-                const int d_lo = SKEW ? (part == 0 ? 0 : A_IT + (part - 1) * W_IT / (PARTS - 1)) : SPREAD == 3 ? cut[pc] * LOADS / 16 : pc * LOADS / SPREAD;
-                const int d_n = (SKEW ? A_IT + part * W_IT / (PARTS - 1) : SPREAD == 3 ? cut[pc + 1] * LOADS / 16 : (pc + 1) * LOADS / SPREAD) - d_lo;
+            if (d0 < d1 && wanted(d0)) issue_from(d0);
 #pragma unroll
-                for (int d = d_lo + ip * d_n / NMP; d < d_lo + (ip + 1) * d_n / NMP; ++d)
-                    if (SKEW && d >= A_IT ? on(refill_w) : on(refill_a)) issue_one(d);
-            }
-            if (i < NM / 2) {   // all reads in the first half: the last one has half a step to come back
+            for (int d = d0 + 1; d < d1; ++d)
+                if (wanted(d)) issue_one(d);
+            if constexpr (M16) {   // behind every other MFMA, the refill's loads behind the ones between
+                if (i % 2 == 0 && i / 2 < NF) load_frag_one(buf ^ 1, src, i / 2);
+            } else if (i < NM / 2) {   // all reads in the first half: the last one has half a step to come back
 #pragma unroll
-                for (int f = i * NF / (NM / 2); f < (i + 1) * NF / (NM / 2); ++f)
-                    load_frag_one(buf ^ 1, rd_stage, rd_ks, f);
+                for (int f = i * NF / (NM / 2); f < (i + 1) * NF / (NM / 2); ++f) load_frag_one(buf ^ 1, src, f);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -747,6 +985,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // then reads 96 KB of fragments per k step of 1024 cycles beside the 32 KB that land, all the LDS delivers; four waves read
     // 64 KB.  13B layer at T = 3875 on codes: eight waves 1257 us, with the skewed ring too; four 1231, skewed 1194.)
     constexpr bool FIXED = BM * BN >= 6 * 4096 && !(EPI == EPI_SWIGLU && BM == 128);
+    static_assert(!(M16 && FIXED) || 2 * NF <= NM, "a fragment read behind every other MFMA");
     static_assert(!SKEW || FIXED, "the skewed ring's weights are issued in the fixed order only");
     Stage cur{0, 0};  // stage being computed
     // One k iteration (one LDS stage).  open_a, open_w: what the refill begun at the previous hand-over still issues (stage
@@ -774,15 +1013,14 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         else
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * LOADS + (SKEW ? W_IT : 0)) : "memory");
         __syncthreads();
-        if (on(next_a)) {
-            rf_a = uniform_ptr(a_src((kbeg + kt + NS) * BKD));
-            rf_w = uniform_ptr(w_src((kbeg + kt + NSW) * BKD));
-            rf_la = __builtin_amdgcn_readfirstlane(lds0 + cur.a * A_BYTES + wave * 1024);
-            rf_lw = __builtin_amdgcn_readfirstlane(lds0 + W_LDS + cur.w * W_BYTES + wave * 1024);
-        }
+        rf_a += ROWB;
+        rf_w += w_stage;
+        rf_la = lds_a0 + cur.a * A_BYTES;
+        rf_lw = lds_w0 + cur.w * W_BYTES;
         if (FIXED) {
             k_step(LB, nxt, 0, 0, next_a, next_w);
         } else {
+            const Source src = source(nxt, 0);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
@@ -795,13 +1033,32 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
                 if (i >= NM / 2) {
 #pragma unroll
                     for (int f = (i - NM / 2) * NF / (NM - NM / 2); f < (i + 1 - NM / 2) * NF / (NM - NM / 2); ++f)
-                        load_frag_one(LB ^ 1, nxt, 0, f);
+                        load_frag_one(LB ^ 1, src, f);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
         cur = nxt;
     };
+    // fill both rings, wait for stage 0 only
+#pragma unroll
+    for (int s = 0; s < NSW; ++s) {
+        if (s >= nk) break;
+        if (s < NS) {
+#pragma unroll
+            for (int j = 0; j < A_IT; ++j) dma16(rf_a + s * ROWB, a_voff[j], lds_a0, s * A_BYTES + j * (NW * 1024));
+        }
+#pragma unroll
+        for (int j = 0; j < W_IT; ++j) dma16<WNT>(rf_w + s * w_stage, w_voff[j], lds_w0, s * W_BYTES + j * (NW * 1024));
+    }
+    rf_a += (NS - 1) * ROWB;
+    rf_w += (NSW - 1) * w_stage;
+    if (nk >= NSW)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * LOADS + (SKEW ? W_IT : 0)) : "memory");
+    else
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    load_frags(0, Stage{0, 0}, 0);
     // first iteration (nothing to refill yet), steady state (every hand-over refills both rings), drain
     int kt = 0;
     if (nk > 0) {
@@ -817,27 +1074,29 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         // runs the epilogue; the kernel boundary is what makes the slabs of workgroups on other XCDs
         // (other L2s) visible, so nothing here waits or fences.
         typedef float vec4_t __attribute__((ext_vector_type(4)));
-        constexpr int AREA4 = BM * BN / 4, NT = 64 * NW;
+        constexpr int AREA4 = BM * BN / 4, NT = 64 * NW, C = MR * MR / 256;
         vec4_t* slab = reinterpret_cast<vec4_t*>(p.tail_buf) + ((size_t)split * p.tail_tiles + tail_idx) * AREA4 + tid;
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm) {
-                constexpr int C = MR * MR / 256;
+            for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
                     vec4_t v = {acc[tn][tm][4 * c], acc[tn][tm][4 * c + 1], acc[tn][tm][4 * c + 2], acc[tn][tm][4 * c + 3]};
                     slab[((tn * TM + tm) * C + c) * NT] = v;
                 }
-            }
         return;
     }
-    if constexpr (EPI != EPI_SLAB) {   // the epilogue takes over the ring: every wave is done with it
-        static_assert(NW * epi_wave_bytes<BN>() <= NS * A_BYTES + NSW * W_BYTES, "the epilogue's rows fit the ring");
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __syncthreads();
+    if constexpr (M16) {
+        gemm_epilogue16<BM, BN, EPI, D, F8>(acc, p, tile_m, tile_n, wm, wn, lane, 0);
+    } else {
+        if constexpr (EPI != EPI_SLAB) {   // the epilogue takes over the ring: every wave is done with it
+            static_assert(NW * epi_wave_bytes<BN>() <= NS * A_BYTES + NSW * W_BYTES, "the epilogue's rows fit the ring");
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
+        gemm_epilogue<BM, BN, EPI, D, F8>(acc, p, tile_m, tile_n, wm, wn, lane, 0, split, smem + wave * epi_wave_bytes<BN>());
     }
-    gemm_epilogue<BM, BN, EPI, D, F8>(acc, p, tile_m, tile_n, wm, wn, lane, 0, split, smem + wave * epi_wave_bytes<BN>());
 }
 
 // Second half of a tail split: workgroup (tail tile, row tm of accumulator tiles) has the thread layout of
@@ -882,8 +1141,12 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_tail_finish_kernel(GemmAr
 #pragma unroll
                     for (int e = 0; e < 4; ++e) acc[tn][h][4 * c + e] += v[tn][h][c][e];
     }
-    __shared__ __align__(16) unsigned char rows[NW * epi_wave_bytes<BN>()];
-    gemm_epilogue<BM, BN, EPI, D, SC>(acc, p, tile_m, tile_n, wm, wn, lane, tm_sel, 0, rows + wave * epi_wave_bytes<BN>());
+    if constexpr (M16) {
+        gemm_epilogue16<BM, BN, EPI, D, SC>(acc, p, tile_m, tile_n, wm, wn, lane, tm_sel);
+    } else {
+        __shared__ __align__(16) unsigned char rows[NW * epi_wave_bytes<BN>()];
+        gemm_epilogue<BM, BN, EPI, D, SC>(acc, p, tile_m, tile_n, wm, wn, lane, tm_sel, 0, rows + wave * epi_wave_bytes<BN>());
+    }
 }
 
 // ------------------------------------------------------------------------------------------

@@ -129,6 +129,30 @@ def test_rings_of_few_stages(rs, nk, packed, w8a8):
         assert torch.equal(out.cpu(), want), tile
 
 
+@pytest.mark.parametrize("N, shift", [(512, 0), (512, 4), (516, 0), (516, 4), (252, 4)])
+def test_rows_that_end_or_begin_inside_a_group_of_8(rs, N, shift):
+    """bf16 rows are stored 8 features at a time where whole groups begin at 16-byte boundaries: rows of no multiple of 8, and rows that
+    begin 8 bytes further on, are stored 4 by 4.  Exact sums, as above; nothing behind the last row is touched."""
+    T, K = 259, 128
+    g = torch.Generator(device="cuda").manual_seed(N + shift)
+    a = torch.randint(-4, 5, (T, K), generator=g, device="cuda").bfloat16()
+    w = (torch.randint(-4, 5, (N, K), generator=g, device="cuda").float() / 64).bfloat16()
+    res = torch.randint(-8, 9, (T, N), generator=g, device="cuda").float()
+    sums = (a.double().cpu() @ w.double().cpu().T).float()
+    for epi, want in ((0, sums.bfloat16()), (2, (sums + res.cpu()).bfloat16())):
+        for tile in (0, 1, 2, 3, 4):
+            buf = torch.full((shift + T * N + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
+            out = buf[shift:shift + T * N].view(T, N)
+            rs.relserve_debug_force_gemm_plan(tile, 0)
+            try:
+                rs.relserve_linear(a, w, epi, res if epi == 2 else None, out)
+                torch.cuda.synchronize()
+            finally:
+                rs.relserve_debug_force_gemm_plan(-1, 0)
+            assert torch.equal(out.cpu(), want), (epi, tile)
+            assert (buf[:shift] == 7).all() and (buf[shift + T * N:] == 7).all(), (epi, tile)
+
+
 def test_iteration_of_640_tokens_keeps_its_sums_whole(rs):
     """The q/k/v projection of a 13B layer at T = 640 (128 decode rows and a 512-token chunk) fills its rounds well enough to
     split nothing: the appended keys and values carry the bits of whole tiles, as its gate/up projection's sums do."""
