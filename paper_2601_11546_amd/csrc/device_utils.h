@@ -103,10 +103,10 @@ __device__ __forceinline__ f32x4_t mfma_16x16x32(bf16x8_t a, bf16x8_t b, f32x4_t
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// 32x32x64 product of 8-bit floating point codes (1-4-3 bits, both operands), fp32 accumulate: lane (l32, g) supplies
-// row l32 and 32 of the 64 k values (half g) of each operand.  The scale operands are zero: the unscaled instruction.
-__device__ __forceinline__ f32x16_t mfma_32x32x64_f8(i32x8_t a, i32x8_t b, f32x16_t c) {
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
+// 16x16 product of 8-bit floating point codes (1-4-3 bits, both operands), k = 128, fp32 accumulate: lane l supplies row l % 16 and 32
+// of the 128 k values (quarter l / 16) of each operand.  The scale operands are zero: the unscaled instruction.
+__device__ __forceinline__ f32x4_t mfma_16x16x128_f8(i32x8_t a, i32x8_t b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
 }
 
 }  // namespace relserve

@@ -88,11 +88,11 @@ hipError_t allow_smem_once(std::once_flag& once, hipError_t& status, Kernel kern
 
 enum { EPI_BF16 = 0, EPI_RES_BF16_OUT_F32 = 1, EPI_RES_F32_OUT_BF16 = 2, EPI_SWIGLU = 3, EPI_QKV_ROPE = 4, EPI_SLAB = 5 };
 
-// Which launches of gemm_dma_kernel multiply on 16 x 16 x 32 products instead of 32 x 32 x 16.  A chain of the former gives the same
-// bits as the chain of twice as many of the latter (measured, k of 32 .. 5120), but a 16 x 16 result passes through the accumulators
-// half as often per product, and the chip is power-limited in these kernels: all CUs on register operands alone reach 2.07 PFLOP/s
-// against 1.83.  T = 7963, 13B: clock 1.70 -> 2.0 GHz, gate/up 1632 -> 1579 us, W_down 813 -> 776, q/k/v 941 -> 910, the layer 4207 -> 4088.
-constexpr bool mfma16(int epi, bool f8) { return !f8 && epi != EPI_SLAB; }
+// Products are 16 x 16 x 32 (on 8-bit codes 16 x 16 x 128).  A chain of them gives the same bits as the chain of twice as many
+// 32 x 32 x 16 (measured, k of 32 .. 5120; on codes as 32 x 32 x 64 but for last bits where the codes span their whole range, equally
+// far from 64 bits), but a 16 x 16 result passes through the accumulators half as often per product, and the chip is power-limited in
+// these kernels: all CUs on register operands alone reach 2.07 PFLOP/s against 1.83 (4.42 against 4.06).  T = 7963, 13B: clock 1.70 -> 2.0
+// GHz, gate/up 1632 -> 1579 us, W_down 813 -> 776, q/k/v 941 -> 910, the layer 4207 -> 4088.
 
 __device__ __forceinline__ int remap_xcd(int bid, int num) {
     const int per = num / NUM_XCD, rem = num % NUM_XCD;
@@ -185,150 +185,13 @@ __device__ __forceinline__ void store_unit(const GemmArgs& p, int t, int n_lo, i
     }
 }
 
-// Epilogue of the kernels whose results are 32 x 32.  Register r of accumulator tile (tn, tm) holds feature
-// 32 tn + 8 (r / 4) + 4 g + r % 4 of the wave's feature range and token 32 tm + l32 of its token range.
-// acc holds whole rows of 32 tokens, starting at row tm_base (the GEMM kernels hold all of the wave's; the tail finish kernel one
-// per workgroup, which with its 64 KB of LDS lets two workgroups share a CU).
-// SC: the sums are products of 8-bit codes and take the factor a_scale * w_scale[feature] as they are read.
-//
-// One accumulator row (32 tokens x the wave's features, fp32) at a time goes through a region of LDS that belongs to the
-// wave alone (epi_wave_bytes, no barrier) and comes back with the lanes along the features: every store then writes whole
-// 128-byte lines (128 - 512 consecutive bytes per token), and the residual and the rotary table are read the same way, one
-// accumulator row ahead.  Straight from the accumulator layout a store instruction wrote 32 pieces of 16 bytes, and an L2
-// that serves 32 CUs took each piece as a request of its own; the loads were one serial round trip per quad, the
-// accumulators leaving no registers for more.  On 8-bit operands at T = 3875 q/k/v 317 -> 279 us, W_down with its tail 278 -> 253.
 constexpr int WGM = 2, WGN = 2;   // grid of waves over a tile
-template <int BN>
-constexpr int epi_wave_bytes() { return 32 * (BN / WGN) * 4; }
 
-template <int BM, int BN, int EPI, int D, bool SC = false, typename Acc, int TNA, int TMA>
-__device__ __forceinline__ void gemm_epilogue(const Acc (&acc)[TNA][TMA], const GemmArgs& p, int tile_m, int tile_n, int wm, int wn,
-                                              int lane, int tm_base, int split, unsigned char* lds) {
-    constexpr int TM = TMA, TN = BN / (32 * WGN);
-    static_assert(TNA == TN, "the wave's features");
-    const int t0 = tile_m * BM + 32 * tm_base + wm * (BM / WGM);
-    const int l32 = lane & 31, g = lane >> 5;
-    if constexpr (EPI == EPI_SLAB) {
-        // Split-K partial sums -> this split's slab.  These tiles were accumulated with the operands
-        // swapped: register r holds token 8 (r / 4) + 4 g + r % 4 and feature l32, so one store
-        // instruction writes two runs of 32 consecutive floats.  Plain stores: nothing is read back in
-        // this kernel, and fp32 atomics into a shared accumulator ran at a quarter of the rate.
-        float* slab = p.accum + (int64_t)split * p.T * p.N;
-#pragma unroll
-        for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn) {
-                const int n = tile_n * BN + wn * (BN / WGN) + 32 * tn + l32;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int t = t0 + 32 * tm + 8 * (r >> 2) + 4 * g + (r & 3);
-                    if (t < p.T && n < p.N) slab[(int64_t)t * p.N + n] = acc[tn][tm][r];
-                }
-            }
-        return;
-    } else {
-        // A lane's unit of work: chunk c_lo (4 consecutive features) of a token, or, where features are combined in pairs
-        // (gate and up, the two halves of a rotated head), chunks c_lo and c_hi.
-        constexpr int FEAT = BN / WGN, CPR = FEAT / 4, ROWB = FEAT * 4;
-        constexpr bool PAIRED = EPI == EPI_SWIGLU || EPI == EPI_QKV_ROPE;
-        constexpr int UPR = PAIRED ? CPR / 2 : CPR;      // units per token
-        constexpr int RPI = 64 / UPR, IT = 32 / RPI;     // tokens per wave access, accesses per accumulator row
-        static_assert(CPR >= 16, "the row swizzle permutes 16 chunks");
-        const int u = lane % UPR, row0 = lane / UPR;
-        constexpr int DH = D > 0 ? D : 64;
-        int c_lo, c_hi, n_lo, n_hi;                      // chunks and first features (rows of the weight matrix)
-        int head = 0;
-        bool ok;
-        if (EPI == EPI_QKV_ROPE) {
-            const int hh = u / (DH / 8), ii = u % (DH / 8);
-            c_lo = hh * (DH / 4) + ii, c_hi = c_lo + DH / 8;
-            head = (tile_n * BN + wn * FEAT) / DH + hh;
-            n_lo = head * DH + 4 * ii, n_hi = n_lo + DH / 2;
-            ok = head < p.n_q + 2 * p.n_kv;
-        } else if (EPI == EPI_SWIGLU) {
-            c_lo = u, c_hi = u + CPR / 2;
-            n_lo = tile_n * (BN / 2) + wn * (FEAT / 2) + 4 * u, n_hi = p.n_half + n_lo;
-            ok = n_lo < p.n_half;   // n_half is a multiple of 8: whole units in or out
-        } else {
-            c_lo = c_hi = u;
-            n_lo = n_hi = tile_n * BN + wn * FEAT + 4 * u;
-            ok = n_lo < p.N;        // N is a multiple of 4 on every path that reaches here
-        }
-        float4 s_lo = make_float4(1.f, 1.f, 1.f, 1.f), s_hi = s_lo;
-        if constexpr (SC) {
-            if (ok) {
-                s_lo = *reinterpret_cast<const float4*>(p.w_scale + n_lo);
-                s_lo.x *= p.a_scale; s_lo.y *= p.a_scale; s_lo.z *= p.a_scale; s_lo.w *= p.a_scale;
-                if constexpr (PAIRED) {
-                    s_hi = *reinterpret_cast<const float4*>(p.w_scale + n_hi);
-                    s_hi.x *= p.a_scale; s_hi.y *= p.a_scale; s_hi.z *= p.a_scale; s_hi.w *= p.a_scale;
-                }
-            }
-        }
-        // what a unit reads besides the sums, fetched one accumulator row ahead
-        struct Operands { float4 a[IT], b[IT]; int slot[IT]; };
-        Operands ops[2];
-        auto fetch = [&](int tm, Operands& o) __attribute__((always_inline)) {
-#pragma unroll
-            for (int j = 0; j < IT; ++j) {
-                const int64_t t = min(t0 + 32 * tm + RPI * j + row0, p.T - 1);   // rows past T: the last token again, never stored
-                if constexpr (EPI == EPI_QKV_ROPE) {
-                    o.slot[j] = p.tok_slot[t];
-                    const float4* cs = reinterpret_cast<const float4*>(p.rope_cs + t * (DH / 2) + 4 * (u % (DH / 8)));
-                    o.a[j] = cs[0];
-                    o.b[j] = cs[1];
-                } else if constexpr (EPI == EPI_RES_BF16_OUT_F32) {
-                    uint2 r = make_uint2(0, 0);   // no residual given: plain fp32 output
-                    if (p.residual && ok) r = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p.residual) + t * p.N + n_lo);
-                    o.a[j].x = __uint_as_float(r.x);
-                    o.a[j].y = __uint_as_float(r.y);
-                } else if constexpr (EPI == EPI_RES_F32_OUT_BF16) {
-                    if (ok) o.a[j] = *reinterpret_cast<const float4*>(static_cast<const float*>(p.residual) + t * p.N + n_lo);
-                }
-            }
-        };
-        fetch(0, ops[0]);
-#pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
-            if (t0 + 32 * tm >= p.T) break;   // padding: nothing of this accumulator row (or the ones behind it) is stored
-            {
-                unsigned char* wr = lds + l32 * ROWB;
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *reinterpret_cast<float4*>(wr + (((8 * tn + 2 * q + g) ^ (l32 & 15)) << 4)) =
-                            make_float4(acc[tn][tm][4 * q], acc[tn][tm][4 * q + 1], acc[tn][tm][4 * q + 2], acc[tn][tm][4 * q + 3]);
-            }
-            // the wave's LDS accesses stay in program order: writes, reads, the next row's writes
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = 0; j < IT; ++j) {
-                if (j == 0 && tm + 1 < TM) fetch(tm + 1, ops[(tm + 1) & 1]);
-                const Operands& cur = ops[tm & 1];
-                const int row = RPI * j + row0, t = t0 + 32 * tm + row;
-                const unsigned char* rd = lds + row * ROWB;
-                float4 lo = *reinterpret_cast<const float4*>(rd + ((c_lo ^ (row & 15)) << 4));
-                float4 hi = lo;
-                if constexpr (PAIRED) hi = *reinterpret_cast<const float4*>(rd + ((c_hi ^ (row & 15)) << 4));
-                if constexpr (SC) {
-                    lo.x *= s_lo.x; lo.y *= s_lo.y; lo.z *= s_lo.z; lo.w *= s_lo.w;
-                    if constexpr (PAIRED) hi.x *= s_hi.x, hi.y *= s_hi.y, hi.z *= s_hi.z, hi.w *= s_hi.w;
-                }
-                if (ok && t < p.T) store_unit<EPI, D, SC>(p, t, n_lo, head, lo, hi, cur.a[j], cur.b[j], cur.slot[j]);
-            }
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-}
-
-// Which feature of a wave's range MFMA row i (= 4 (lane / 16) + r of the result) of weight fragment tn stands for, where results are
-// 16 x 16 (M16).  fp32 rows leave as they come: a lane has 4 consecutive features, the four lanes of a token 64 consecutive bytes.
+// Which feature of a wave's range MFMA row i (= 4 (lane / 16) + r of the result) of weight fragment tn stands for, and of the
+// results.  fp32 rows leave as they come: a lane has 4 consecutive features, the four lanes of a token 64 consecutive bytes.
 // Where bf16 or codes are written (PAIRED16) two fragments share 32 features so that a lane has 8 consecutive ones: 64 bytes again.
 // The permutation costs nothing: it is which rows of the weights in the LDS a lane reads.
-constexpr bool paired16(int epi) { return epi != EPI_RES_BF16_OUT_F32; }
+constexpr bool paired16(int epi) { return epi != EPI_RES_BF16_OUT_F32 && epi != EPI_SLAB; }
 template <int EPI>
 __device__ __forceinline__ int frag_row16(int i) { return paired16(EPI) ? 8 * (i >> 2) + (i & 3) : i; }
 template <int EPI>
@@ -354,6 +217,13 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
         return make_float4(v[0], v[1], v[2], v[3]);
     };
     auto scaled = [](float4 v, const float4& s) __attribute__((always_inline)) { return make_float4(v.x * s.x, v.y * s.y, v.z * s.z, v.w * s.w); };
+    // a sum and its residual: with a factor one fused multiply-add, written out (left to the compiler it is one in some kernels only)
+    auto plus = [](const float4& v, const float4& s, const float4& r) __attribute__((always_inline)) {
+        if constexpr (SC)
+            return make_float4(__builtin_fmaf(v.x, s.x, r.x), __builtin_fmaf(v.y, s.y, r.y), __builtin_fmaf(v.z, s.z, r.z), __builtin_fmaf(v.w, s.w, r.w));
+        else
+            return make_float4(v.x + r.x, v.y + r.y, v.z + r.z, v.w + r.w);
+    };
     auto code_scale = [&](int n) __attribute__((always_inline)) {
         float4 s = *reinterpret_cast<const float4*>(p.w_scale + n);
         s.x *= p.a_scale; s.y *= p.a_scale; s.z *= p.a_scale; s.w *= p.a_scale;
@@ -400,11 +270,11 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
             if (!FULL && t0 + 16 * tm + l16 >= p.T) continue;
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
-                float4 v = quad(tn, tm);
-                if constexpr (SC) v = scaled(v, sc[tn]);
+                const float4 v = quad(tn, tm);
                 const uint2 r = res[tm & 1][tn];
-                if (ok(tn)) *reinterpret_cast<float4*>(base + off + 64 * tn) =
-                    make_float4(v.x + bf16_lo(r.x), v.y + bf16_hi(r.x), v.z + bf16_lo(r.y), v.w + bf16_hi(r.y));
+                if (ok(tn))
+                    *reinterpret_cast<float4*>(base + off + 64 * tn) =
+                        plus(v, sc[SC ? tn : 0], make_float4(bf16_lo(r.x), bf16_hi(r.x), bf16_lo(r.y), bf16_hi(r.y)));
             }
         }
     } else if constexpr (EPI == EPI_QKV_ROPE) {
@@ -524,15 +394,14 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     v[h] = quad(2 * u + h, tm);
-                    if constexpr (SC) v[h] = scaled(v[h], sc[2 * u + h]);
+                    if constexpr (EPI == EPI_RES_F32_OUT_BF16)
+                        v[h] = plus(v[h], sc[SC ? 2 * u + h : 0], res[tm & 1][u][h]);
+                    else if constexpr (SC)
+                        v[h] = scaled(v[h], sc[2 * u + h]);
                     if constexpr (SWI) {
                         float4 up = quad(TN / 2 + 2 * u + h, tm);
                         if constexpr (SC) up = scaled(up, sc[TN / 2 + 2 * u + h]);
                         v[h] = make_float4(silu_mul(v[h].x, up.x), silu_mul(v[h].y, up.y), silu_mul(v[h].z, up.z), silu_mul(v[h].w, up.w));
-                    }
-                    if constexpr (EPI == EPI_RES_F32_OUT_BF16) {
-                        const float4 r = res[tm & 1][u][h];
-                        v[h].x += r.x; v[h].y += r.y; v[h].z += r.z; v[h].w += r.w;
                     }
                 }
                 if (codes) {
@@ -565,7 +434,7 @@ __device__ __forceinline__ void gemm_epilogue16(const f32x4_t (&acc)[TN][TM], co
 
 template <int BM, int BN, int EPI, int D = 0>
 __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs p) {
-    constexpr int TM = BM / 64, TN = BN / 64;          // 32x32 MFMA tiles per wave
+    constexpr int TM = BM / 32, TN = BN / 32;          // 16x16 MFMA tiles per wave
     constexpr int A_IT = BM / 32, W_IT = BN / 32;      // 16-byte chunks per thread and k step
     constexpr int A_BYTES = BM * BK * 2, W_BYTES = BN * BK * 2, STAGE = A_BYTES + W_BYTES;
     static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU needs gate and up tiles in one wave");
@@ -574,7 +443,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs p) {
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int l32 = lane & 31, g = lane >> 5;
+    const int l16 = lane & 15, g = lane >> 4;
 
     const int tile = remap_xcd(blockIdx.x, p.tiles_m * p.tiles_n);
     int tile_m, tile_n;
@@ -629,28 +498,20 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs p) {
         for (int i = 0; i < W_IT; ++i) *reinterpret_cast<uint4*>(sw + i * 32 * 128 + st_off) = w_reg[i];
     };
 
-    // ---- LDS -> MFMA operand offsets
-    int a_rd[TM], w_rd[TN];
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm) a_rd[tm] = (wm * (BM / 2) + 32 * tm + l32) * 128;
+    // ---- LDS -> MFMA operands: rows l16 of the wave's tokens, frag_row16 of its features; both swizzled by row & 7
+    const int a_row = wm * (BM / 2) + l16, w_lane = frag_row16<EPI>(l16);
+    int w_row[TN];
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
-        int row;
-        if (EPI == EPI_SWIGLU)
-            row = (tn < TN / 2 ? 0 : BN / 2) + wn * (BN / 4) + 32 * (tn % (TN / 2)) + l32;
-        else
-            row = wn * (BN / 2) + 32 * tn + l32;
-        w_rd[tn] = row * 128;
+        const int half = EPI == EPI_SWIGLU && tn >= TN / 2 ? 1 : 0;
+        w_row[tn] = half * (BN / 2) + wn * (EPI == EPI_SWIGLU ? BN / 4 : BN / 2) + frag_base16<EPI>(tn - half * (TN / 2)) + w_lane;
     }
-    const int sw7 = l32 & 7;
 
-    f32x16_t acc[TN][TM];
+    f32x4_t acc[TN][TM];
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[tn][tm][r] = 0.f;
+        for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     const int nk = (K + BK - 1) / BK;
     load_global(0);
@@ -662,23 +523,23 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs p) {
         const unsigned char* sa = smem + (kt & 1) * STAGE;
         const unsigned char* sw = sa + A_BYTES;
 #pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            const int ch = ((2 * ks + g) ^ sw7) << 4;
+        for (int ks = 0; ks < BK / 32; ++ks) {
             bf16x8_t wf[TN], af[TM];
 #pragma unroll
-            for (int tn = 0; tn < TN; ++tn) wf[tn] = as_bf16x8(*reinterpret_cast<const uint4*>(sw + w_rd[tn] + ch));
+            for (int tn = 0; tn < TN; ++tn)
+                wf[tn] = as_bf16x8(*reinterpret_cast<const uint4*>(sw + w_row[tn] * 128 + (((4 * ks + g) ^ (w_row[tn] & 7)) << 4)));
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm) af[tm] = as_bf16x8(*reinterpret_cast<const uint4*>(sa + a_rd[tm] + ch));
+            for (int tm = 0; tm < TM; ++tm)
+                af[tm] = as_bf16x8(*reinterpret_cast<const uint4*>(sa + (a_row + 16 * tm) * 128 + (((4 * ks + g) ^ (a_row & 7)) << 4)));
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-                for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = mfma_32x32x16(wf[tn], af[tm], acc[tn][tm]);
+                for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = mfma_16x16x32(wf[tn], af[tm], acc[tn][tm]);
         }
         if (more) store_lds((kt + 1) & 1);
         __syncthreads();
     }
-    static_assert(4 * epi_wave_bytes<BN>() <= 2 * STAGE, "the epilogue's rows fit the stages");
-    gemm_epilogue<BM, BN, EPI, D>(acc, p, tile_m, tile_n, wm, wn, lane, 0, 0, smem + wave * epi_wave_bytes<BN>());
+    gemm_epilogue16<BM, BN, EPI, D, false>(acc, p, tile_m, tile_n, wm, wn, lane, 0);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -740,19 +601,16 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     constexpr bool SKEW = NSW > NS;
     static_assert(NSW == NS || NSW == NS + 1, "weight ring");
     constexpr int NW = WGM * WGN;
-    constexpr bool M16 = mfma16(EPI, F8);
-    constexpr int MR = M16 ? 16 : 32;                    // rows of either operand in one MFMA
-    constexpr int TM = BM / (MR * WGM), TN = BN / (MR * WGN);
+    constexpr int TM = BM / (16 * WGM), TN = BN / (16 * WGN);
     constexpr int ROWB = BKD * 2;                        // bytes per LDS row
     constexpr int CPR = BKD / 8;                         // 16-byte chunks per row
     constexpr int RPI = 1024 / ROWB;                     // rows one 1 KB wave load covers
     constexpr int A_IT = BM / (NW * RPI), W_IT = BN / (NW * RPI);
     constexpr int A_BYTES = BM * ROWB, W_BYTES = BN * ROWB, W_LDS = NS * A_BYTES;   // NS stages of activations, then NSW of weights
-    constexpr int KSTEPS = F8 || M16 ? BKD / 32 : BKD / 16;
+    constexpr int KSTEPS = F8 ? 1 : BKD / 32;
     constexpr int LOADS = A_IT + W_IT;                   // wave loads per stage
     static_assert(BKD == 64, "stage depth: a slice of the packed weights");
     static_assert(NSW * LOADS < 64, "vmcnt field");
-    static_assert(!SKEW || KSTEPS > 1, "the skewed ring's weights are issued between hand-overs");
     static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU needs gate and up tiles in one wave");
     static_assert(EPI != EPI_QKV_ROPE || (BN / WGN == 128 && (D == 64 || D == 128)), "a wave must own whole heads");
     static_assert(BM % (NW * RPI) == 0 && BN % (NW * RPI) == 0, "whole wave loads");
@@ -761,7 +619,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
-    const int fr = lane % MR, g = lane / MR;             // this lane's row of an operand fragment, and its part of the k step
+    const int fr = lane % 16, g = lane / 16;             // this lane's row of an operand fragment, and its part of the k step
 
     const int K = p.K;
     const int n_tiles = p.tiles_m * p.tiles_n, tail_units = p.tail_tiles * p.tail_splits, dp_tiles = n_tiles - p.tail_tiles;
@@ -796,7 +654,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     const uint32_t row_lo = (uint32_t)(wave * RPI) + lrow;   // LDS row modulo NW * RPI (>= 32): all the swizzle needs
     const uint32_t chunk = (lane % CPR) ^ (BKD == 64 ? ((row_lo >> 1) & 7) : ((row_lo >> 2) & 3));
     // (16 x 16 results of permuted features read rows 0-3, 8-11, 16-19 and 24-27 of 32, four further on, or so)
-    constexpr bool PERM = M16 && paired16(EPI);
+    constexpr bool PERM = paired16(EPI);
     auto perm_swz = [](int row) { return ((row >> 1) & 1) | ((row >> 2) & 6); };
     const uint32_t w_chunk = PERM ? (lane % CPR) ^ perm_swz(row_lo) : chunk;
     uint32_t a_voff[A_IT], w_voff[W_IT];
@@ -830,30 +688,28 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     uint32_t a_lane[KSTEPS], w_lane[KSTEPS];
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
-        const uint32_t at = lds0 + fr * ROWB + (((F8 ? 4 * ks + 2 * g : (64 / MR) * ks + g) ^ swz) << 4);
+        const int c = F8 ? 2 * g : 4 * ks + g;   // the lane's (first) chunk of a row
+        const uint32_t at = lds0 + fr * ROWB + ((c ^ swz) << 4);
         a_lane[ks] = at + wm * (BM / WGM) * ROWB;
         w_lane[ks] = at + W_LDS + wn * w_wave * ROWB;
         if constexpr (PERM) {
             const int row = frag_row16<EPI>(fr);
-            w_lane[ks] = lds0 + W_LDS + (wn * w_wave + row) * ROWB + (((4 * ks + g) ^ perm_swz(row)) << 4);
+            w_lane[ks] = lds0 + W_LDS + (wn * w_wave + row) * ROWB + ((c ^ perm_swz(row)) << 4);
         }
     }
-    auto a_dist = [](int tm) { return MR * tm * ROWB; };
+    auto a_dist = [](int tm) { return 16 * tm * ROWB; };
     auto w_dist = [](int tn) {
         const int half = EPI == EPI_SWIGLU && tn >= TN / 2 ? 1 : 0, i = tn - half * (TN / 2);
-        return (half * (BN / 2) + (M16 ? frag_base16<EPI>(i) : MR * i)) * ROWB;
+        return (half * (BN / 2) + frag_base16<EPI>(i)) * ROWB;
     };
 
-    using acc_t = std::conditional_t<M16, f32x4_t, f32x16_t>;
-    acc_t acc[TN][TM];
+    f32x4_t acc[TN][TM];
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-            for (int r = 0; r < MR * MR / 64; ++r) acc[tn][tm][r] = 0.f;
+        for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     using frag_t = std::conditional_t<F8, i32x8_t, bf16x8_t>;
-    frag_t wf[2][TN], af[2][TM];
+    frag_t wf[F8 ? 1 : 2][TN], af[F8 ? 1 : 2][TM];
     typedef const i32x4_t __attribute__((address_space(3))) * lds_chunk;
     auto read_frag = [&](uint32_t at, int dist) __attribute__((always_inline)) -> frag_t {
         if constexpr (F8) {
@@ -871,17 +727,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         return r;
     };
     auto load_frag_one = [&](int buf, Source src, int i) __attribute__((always_inline)) {   // i-th of the TN + TM fragment reads of a k step
-        if constexpr (M16) {   // the first products of a step need all tokens and one row of features
-            if (i < TM)
-                af[buf][i] = read_frag(src.a, a_dist(i));
-            else
-                wf[buf][i - TM] = read_frag(src.w, w_dist(i - TM));
-        } else {
-            if (i < TN)
-                wf[buf][i] = read_frag(src.w, w_dist(i));
-            else
-                af[buf][i - TN] = read_frag(src.a, a_dist(i - TN));
-        }
+        if (i < TM)   // the first products of a step need all tokens and one row of features
+            af[buf][i] = read_frag(src.a, a_dist(i));
+        else
+            wf[buf][i - TM] = read_frag(src.w, w_dist(i - TM));
     };
     auto load_frags = [&](int buf, Stage st, int ks) __attribute__((always_inline)) {
         const Source src = source(st, ks);
@@ -892,13 +741,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     auto mfma_one = [&](int buf, int i) __attribute__((always_inline)) {   // i-th of the TN * TM products of a k step
         const int tn = i / TM, tm = i % TM;
         if constexpr (F8)
-            acc[tn][tm] = EPI == EPI_SLAB ? mfma_32x32x64_f8(af[buf][tm], wf[buf][tn], acc[tn][tm])
-                                            : mfma_32x32x64_f8(wf[buf][tn], af[buf][tm], acc[tn][tm]);
-        else if constexpr (M16)
-            acc[tn][tm] = mfma_16x16x32(wf[buf][tn], af[buf][tm], acc[tn][tm]);
+            acc[tn][tm] = mfma_16x16x128_f8(wf[buf][tn], af[buf][tm], acc[tn][tm]);
         else
-            acc[tn][tm] = EPI == EPI_SLAB ? mfma_32x32x16(af[buf][tm], wf[buf][tn], acc[tn][tm])
-                                            : mfma_32x32x16(wf[buf][tn], af[buf][tm], acc[tn][tm]);
+            acc[tn][tm] = mfma_16x16x32(wf[buf][tn], af[buf][tm], acc[tn][tm]);
     };
     // Source of the refill in progress (set at a hand-over): the k slice's first byte in both operands and the
     // freed stages' LDS addresses, so that a load costs its own two instructions plus one scalar add.
@@ -913,7 +758,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // skewed ring has a whole iteration more for them and needs the activations first.
     auto is_w = [](int i) { return SKEW ? i >= A_IT : i < W_IT; };
     auto nth = [](int i) { return SKEW ? (i >= A_IT ? i - A_IT : i) : (i < W_IT ? i : i - W_IT); };   // of its own operand
-    auto issue_to = [&](int i) __attribute__((always_inline)) { dma16_to(is_w(i) ? rf_lw : rf_la, nth(i) * (NW * 1024)); };
+    auto issue_to = [&](int i) __attribute__((always_inline)) { dma16_to(__builtin_amdgcn_readfirstlane(is_w(i) ? rf_lw : rf_la), nth(i) * (NW * 1024)); };
     auto issue_from = [&](int i) __attribute__((always_inline)) {
         if (is_w(i))
             dma16_from<WNT>(rf_w, w_voff[nth(i)]);
@@ -921,10 +766,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             dma16_from(rf_a, a_voff[nth(i)]);
     };
     auto issue_one = [&](int i) __attribute__((always_inline)) {
+        const uint32_t to = __builtin_amdgcn_readfirstlane(is_w(i) ? rf_lw : rf_la);
         if (is_w(i))
-            dma16<WNT>(rf_w, w_voff[nth(i)], rf_lw, nth(i) * (NW * 1024));
+            dma16<WNT>(rf_w, w_voff[nth(i)], to, nth(i) * (NW * 1024));
         else
-            dma16(rf_a, a_voff[nth(i)], rf_la, nth(i) * (NW * 1024));
+            dma16(rf_a, a_voff[nth(i)], to, nth(i) * (NW * 1024));
     };
     // A flag that is either a run-time bool or std::true_type: the steady-state iterations pass the latter, so their
     // loads sit in straight-line code (a branch and its scalar set-up around each load cost more issue slots than
@@ -942,35 +788,64 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // four waves) are spread over SPREAD quarters of the iteration (a k step of 32 x 32 MFMAs is one, of
     // 16 x 16 two); issued back to back they would hold up the MFMAs behind them.  The MFMAs sit on ONE control path on purpose: at a join the compiler would make
     // them wait for the newest reads.
-    constexpr int PARTS = M16 ? 2 * KSTEPS : KSTEPS, SUB = PARTS / KSTEPS, NMP = NM / SUB;   // parts of an iteration
-    constexpr int SPREAD = PARTS > 1 ? PARTS - 1 : 1;   // the last part before the next hand-over stays free: landing time
-    auto k_step = [&](int buf, Stage rd_stage, int rd_ks, int step, auto refill_a, auto refill_w) __attribute__((always_inline)) {
+    constexpr int STEPS = 2, NMS = NM * KSTEPS / STEPS;                        // steps of an iteration, NMS products each
+    constexpr int PARTS = 4, SPREAD = 3, SUB = PARTS / STEPS, NMP = NMS / SUB;   // parts of an iteration; the last before the next hand-over stays free: landing time
+    // product number i of step `step` after a hand-over (mfma), with the loads of the refill that fall behind it
+    auto slot = [&](int step, int i, auto refill_a, auto refill_w, auto mfma) __attribute__((always_inline)) {
         // share of the stage's loads issued in each part, cumulative, in sixteenths: the weights (first half
         // of the loads) go out at once, the activations (L2 hits, quick to land) trail over two more parts
         constexpr int cut[5] = {0, 8, 13, 16, 16};
+        const int part = step * SUB + i / NMP, ip = i % NMP, pc = part < SPREAD ? part : SPREAD;
+        // (skewed: the activations at once, the weights over all the parts that remain)
+        const int d_lo = SKEW ? (part == 0 ? 0 : A_IT + (part - 1) * W_IT / (PARTS - 1)) : cut[pc] * LOADS / 16;
+        const int d_n = (SKEW ? A_IT + part * W_IT / (PARTS - 1) : cut[pc + 1] * LOADS / 16) - d_lo;
+        const int d0 = d_lo + ip * d_n / NMP, d1 = SKEW || part < SPREAD ? d_lo + (ip + 1) * d_n / NMP : d0;   // the slot's loads
+        auto wanted = [&](int d) __attribute__((always_inline)) { return SKEW && d >= A_IT ? on(refill_w) : on(refill_a); };
+        if (d0 < d1 && wanted(d0)) issue_to(d0);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma();
+        __builtin_amdgcn_sched_barrier(0);
+        if (d0 < d1 && wanted(d0)) issue_from(d0);
+#pragma unroll
+        for (int d = d0 + 1; d < d1; ++d)
+            if (wanted(d)) issue_one(d);
+    };
+    auto k_step = [&](int buf, Stage rd_stage, int rd_ks, int step, auto refill_a, auto refill_w) __attribute__((always_inline)) {
         const Source src = source(rd_stage, rd_ks);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
-            const int part = step * SUB + i / NMP, ip = i % NMP, pc = part < SPREAD ? part : SPREAD;
-            // (skewed: the activations at once, the weights over all the parts that remain)
-            const int d_lo = SKEW ? (part == 0 ? 0 : A_IT + (part - 1) * W_IT / (PARTS - 1)) : SPREAD == 3 ? cut[pc] * LOADS / 16 : pc * LOADS / SPREAD;
-            const int d_n = (SKEW ? A_IT + part * W_IT / (PARTS - 1) : SPREAD == 3 ? cut[pc + 1] * LOADS / 16 : (pc + 1) * LOADS / SPREAD) - d_lo;
-            const int d0 = d_lo + ip * d_n / NMP, d1 = SKEW || part < SPREAD ? d_lo + (ip + 1) * d_n / NMP : d0;   // the slot's loads
-            auto wanted = [&](int d) __attribute__((always_inline)) { return SKEW && d >= A_IT ? on(refill_w) : on(refill_a); };
-            if (d0 < d1 && wanted(d0)) issue_to(d0);
+            slot(step, i, refill_a, refill_w, [&]() __attribute__((always_inline)) { mfma_one(buf, i); });
+            if (i % 2 == 0 && i / 2 < NF) load_frag_one(buf ^ 1, src, i / 2);   // behind every other MFMA, the refill's loads behind the ones between
             __builtin_amdgcn_sched_barrier(0);
-            mfma_one(buf, i);
-            __builtin_amdgcn_sched_barrier(0);
-            if (d0 < d1 && wanted(d0)) issue_from(d0);
+        }
+    };
+    // 8-bit operands on 16 x 16 x 128 products: a stage is one k step, and two buffers of its fragments (256 registers on a 256 x 256
+    // tile) do not fit beside the sums.  The wave's products go quarter by quarter instead, weights' halves lo and hi against tokens'
+    // halves h and h' = 1 - h: (lo, h), (lo, h'), (hi, h'), (hi, h), and behind each quarter's products come the four fragments or so
+    // that the next one adds, into registers whose last reader is over: tokens h' , weights hi, the next stage's lo and, where tokens h'
+    // were, the next stage's tokens h'; so the next stage begins with h'.  Every fragment is read once, at an even rate, and the
+    // stage is free (and the next one needed) at the hand-over between the second and third quarter.
+    constexpr int WH = TN / 2, AH = TM / 2, NQ = WH * AH;
+    auto read_w = [&](Source src, int half, int i) __attribute__((always_inline)) { wf[0][half * WH + i] = read_frag(src.w, w_dist(half * WH + i)); };
+    auto read_a = [&](Source src, int half, int i) __attribute__((always_inline)) { af[0][half * AH + i] = read_frag(src.a, a_dist(half * AH + i)); };
+    auto half_step = [&](bool second, int h, Stage rd_stage, auto refill_a, auto refill_w) __attribute__((always_inline)) {
+        const Source src = source(rd_stage, 0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int d = d0 + 1; d < d1; ++d)
-                if (wanted(d)) issue_one(d);
-            if constexpr (M16) {   // behind every other MFMA, the refill's loads behind the ones between
-                if (i % 2 == 0 && i / 2 < NF) load_frag_one(buf ^ 1, src, i / 2);
-            } else if (i < NM / 2) {   // all reads in the first half: the last one has half a step to come back
+        for (int i = 0; i < 2 * NQ; ++i) {
+            const int q = i / NQ, j = i % NQ, a_half = second == (q == 0) ? 1 - h : h;
+            slot(second ? 0 : 1, i, refill_a, refill_w, [&]() __attribute__((always_inline)) { mfma_one(0, ((second ? WH : 0) + j / AH) * TM + a_half * AH + j % AH); });
+            // behind every other product, or, on tiles of few products, evenly
+            const bool rd_w = second == (q == 0);
+            const int nf = rd_w ? WH : AH;
+            const int f0 = 2 * nf <= NQ + 1 ? (j + 1) / 2 : j * nf / NQ, f1 = 2 * nf <= NQ + 1 ? j / 2 + 1 : (j + 1) * nf / NQ;
 #pragma unroll
-                for (int f = i * NF / (NM / 2); f < (i + 1) * NF / (NM / 2); ++f) load_frag_one(buf ^ 1, src, f);
+            for (int f = f0; f < min(f1, nf); ++f) {
+                if (rd_w)
+                    read_w(src, second ? 0 : 1, f);
+                else
+                    read_a(src, 1 - h, f);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -985,17 +860,21 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // then reads 96 KB of fragments per k step of 1024 cycles beside the 32 KB that land, all the LDS delivers; four waves read
     // 64 KB.  13B layer at T = 3875 on codes: eight waves 1257 us, with the skewed ring too; four 1231, skewed 1194.)
     constexpr bool FIXED = BM * BN >= 6 * 4096 && !(EPI == EPI_SWIGLU && BM == 128);
-    static_assert(!(M16 && FIXED) || 2 * NF <= NM, "a fragment read behind every other MFMA");
+    static_assert(F8 || !FIXED || 2 * NF <= NM, "a fragment read behind every other MFMA");
+    static_assert(TN % 2 == 0 && TM % 2 == 0, "halves");
     static_assert(!SKEW || FIXED, "the skewed ring's weights are issued in the fixed order only");
     Stage cur{0, 0};  // stage being computed
     // One k iteration (one LDS stage).  open_a, open_w: what the refill begun at the previous hand-over still issues (stage
     // kt - 1 + NS of the activations, kt - 1 + NSW of the weights, if there is one); next_a, next_w: what this iteration's
     // hand-over starts (stages kt + NS and kt + NSW).  Without the skew both flags of a pair are the same.
-    auto iteration = [&](int kt, auto open_a, auto open_w, auto next_a, auto next_w) __attribute__((always_inline)) {
+    // H (codes): which half of the tokens the stage begins with.
+    auto iteration = [&](int kt, auto H, auto open_a, auto open_w, auto next_a, auto next_w) __attribute__((always_inline)) {
         const Stage nxt{cur.a + 1 == NS ? 0 : cur.a + 1, cur.w + 1 == NSW ? 0 : cur.w + 1};
 #pragma unroll
-        for (int ks = 0; ks + 1 < KSTEPS; ++ks) {
-            if (FIXED) {
+        for (int ks = 0; ks + 1 < STEPS; ++ks) {
+            if constexpr (F8) {
+                half_step(false, H.value, cur, open_a, open_w);
+            } else if (FIXED) {
                 k_step(ks & 1, cur, ks + 1, ks + 1, open_a, open_w);
             } else {
                 load_frags((ks + 1) & 1, cur, ks + 1);
@@ -1017,7 +896,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         rf_w += w_stage;
         rf_la = lds_a0 + cur.a * A_BYTES;
         rf_lw = lds_w0 + cur.w * W_BYTES;
-        if (FIXED) {
+        if constexpr (F8) {
+            half_step(true, H.value, nxt, next_a, next_w);
+        } else if (FIXED) {
             k_step(LB, nxt, 0, 0, next_a, next_w);
         } else {
             const Source src = source(nxt, 0);
@@ -1058,44 +939,61 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     else
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    load_frags(0, Stage{0, 0}, 0);
+    if constexpr (F8) {
+        const Source src = source(Stage{0, 0}, 0);
+#pragma unroll
+        for (int i = 0; i < AH; ++i) read_a(src, 0, i);
+#pragma unroll
+        for (int i = 0; i < WH; ++i) read_w(src, 0, i);
+    } else {
+        load_frags(0, Stage{0, 0}, 0);
+    }
     // first iteration (nothing to refill yet), steady state (every hand-over refills both rings), drain
+    const std::integral_constant<int, 0> even;
+    const std::integral_constant<int, 1> odd;
+    const std::true_type yes;
     int kt = 0;
     if (nk > 0) {
-        iteration(0, false, false, NS < nk, NSW < nk);
+        iteration(0, even, false, false, NS < nk, NSW < nk);
         kt = 1;
     }
-    for (; kt < nk - NSW; ++kt) iteration(kt, std::true_type{}, std::true_type{}, std::true_type{}, std::true_type{});
-    for (; kt < nk; ++kt) iteration(kt, kt - 1 + NS < nk, kt - 1 + NSW < nk, kt + NS < nk, kt + NSW < nk);
+    if constexpr (F8) {
+        for (; kt + 1 < nk - NSW; kt += 2) {
+            iteration(kt, odd, yes, yes, yes, yes);
+            iteration(kt + 1, even, yes, yes, yes, yes);
+        }
+    } else {
+        for (; kt < nk - NSW; ++kt) iteration(kt, even, yes, yes, yes, yes);
+    }
+    while (kt < nk) {
+        iteration(kt, std::integral_constant<int, F8 ? 1 : 0>{}, kt - 1 + NS < nk, kt - 1 + NSW < nk, kt + NS < nk, kt + NSW < nk);
+        ++kt;
+        if (F8) {   // (kt was odd)
+            if (kt == nk) break;
+            iteration(kt, even, kt - 1 + NS < nk, kt - 1 + NSW < nk, kt + NS < nk, kt + NSW < nk);
+            ++kt;
+        }
+    }
     if (EPI != EPI_SLAB && tail) {
-        // Partial tile -> this split's slab (registers 4 c .. 4 c + 3 of accumulator tile (tn, tm) of
-        // thread tid are the 16 bytes at ((tn TM + tm) C + c) * threads + tid: coalesced).
+        // Partial tile -> this split's slab (accumulator tile (tn, tm) of thread tid is the 16 bytes at
+        // (tn TM + tm) * threads + tid: coalesced).
         // gemm_tail_finish_kernel, launched behind this kernel, adds the slabs of a tile in split order and
         // runs the epilogue; the kernel boundary is what makes the slabs of workgroups on other XCDs
         // (other L2s) visible, so nothing here waits or fences.
-        typedef float vec4_t __attribute__((ext_vector_type(4)));
-        constexpr int AREA4 = BM * BN / 4, NT = 64 * NW, C = MR * MR / 256;
-        vec4_t* slab = reinterpret_cast<vec4_t*>(p.tail_buf) + ((size_t)split * p.tail_tiles + tail_idx) * AREA4 + tid;
+        constexpr int AREA4 = BM * BN / 4, NT = 64 * NW;
+        f32x4_t* slab = reinterpret_cast<f32x4_t*>(p.tail_buf) + ((size_t)split * p.tail_tiles + tail_idx) * AREA4 + tid;
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    vec4_t v = {acc[tn][tm][4 * c], acc[tn][tm][4 * c + 1], acc[tn][tm][4 * c + 2], acc[tn][tm][4 * c + 3]};
-                    slab[((tn * TM + tm) * C + c) * NT] = v;
-                }
+            for (int tm = 0; tm < TM; ++tm) slab[(tn * TM + tm) * NT] = acc[tn][tm];
         return;
     }
-    if constexpr (M16) {
-        gemm_epilogue16<BM, BN, EPI, D, F8>(acc, p, tile_m, tile_n, wm, wn, lane, 0);
+    if constexpr (EPI == EPI_SLAB) {   // split-K partial sums -> this split's slab: plain rows of fp32
+        p.out = p.accum + (int64_t)split * p.T * p.N;
+        p.residual = nullptr;
+        gemm_epilogue16<BM, BN, EPI_RES_BF16_OUT_F32, 0, false>(acc, p, tile_m, tile_n, wm, wn, lane, 0);
     } else {
-        if constexpr (EPI != EPI_SLAB) {   // the epilogue takes over the ring: every wave is done with it
-            static_assert(NW * epi_wave_bytes<BN>() <= NS * A_BYTES + NSW * W_BYTES, "the epilogue's rows fit the ring");
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-            __syncthreads();
-        }
-        gemm_epilogue<BM, BN, EPI, D, F8>(acc, p, tile_m, tile_n, wm, wn, lane, 0, split, smem + wave * epi_wave_bytes<BN>());
+        gemm_epilogue16<BM, BN, EPI, D, F8>(acc, p, tile_m, tile_n, wm, wn, lane, 0);
     }
 }
 
@@ -1104,49 +1002,32 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
 // does not depend on scheduling) and runs the GEMM's own epilogue on it.
 template <int BM, int BN, int EPI, int D, bool SC = false>
 __global__ void __launch_bounds__(64 * WGM * WGN) gemm_tail_finish_kernel(GemmArgs p) {
-    constexpr bool M16 = mfma16(EPI, SC);
-    constexpr int MR = M16 ? 16 : 32, C = MR * MR / 256;   // 16-byte pieces of an accumulator tile
-    constexpr int NW = WGM * WGN, NT = 64 * NW, TM = BM / (MR * WGM), TN = BN / (MR * WGN), AREA4 = BM * BN / 4;
-    constexpr int H = 32 / MR;                             // rows of accumulator tiles a workgroup finishes: 32 tokens per wave
-    typedef float vec4_t __attribute__((ext_vector_type(4)));
-    using acc_t = std::conditional_t<M16, f32x4_t, f32x16_t>;
+    constexpr int NW = WGM * WGN, NT = 64 * NW, TM = BM / (16 * WGM), TN = BN / (16 * WGN), AREA4 = BM * BN / 4;
+    constexpr int H = 2;   // rows of accumulator tiles a workgroup finishes: 32 tokens per wave
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
     const int tail_idx = blockIdx.x / (TM / H), tm_sel = blockIdx.x % (TM / H);
     int tile_m, tile_n;
     tile_coords(p.tiles_m * p.tiles_n - p.tail_tiles + tail_idx, p.tiles_m, p.tiles_n, tile_m, tile_n);
-    acc_t acc[TN][H];
+    f32x4_t acc[TN][H];
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-        for (int h = 0; h < H; ++h)
-#pragma unroll
-            for (int r = 0; r < 4 * C; ++r) acc[tn][h][r] = 0.f;
+        for (int h = 0; h < H; ++h) acc[tn][h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     for (int q = 0; q < p.tail_splits; ++q) {
-        const vec4_t* src = reinterpret_cast<const vec4_t*>(p.tail_buf) + ((size_t)q * p.tail_tiles + tail_idx) * AREA4 + tid;
-        vec4_t v[TN][H][C];
+        const f32x4_t* src = reinterpret_cast<const f32x4_t*>(p.tail_buf) + ((size_t)q * p.tail_tiles + tail_idx) * AREA4 + tid;
+        f32x4_t v[TN][H];
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int h = 0; h < H; ++h)
-#pragma unroll
-                for (int c = 0; c < C; ++c) v[tn][h][c] = src[((tn * TM + H * tm_sel + h) * C + c) * NT];
+            for (int h = 0; h < H; ++h) v[tn][h] = src[(tn * TM + H * tm_sel + h) * NT];
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int h = 0; h < H; ++h)
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[tn][h][4 * c + e] += v[tn][h][c][e];
+            for (int h = 0; h < H; ++h) acc[tn][h] += v[tn][h];
     }
-    if constexpr (M16) {
-        gemm_epilogue16<BM, BN, EPI, D, SC>(acc, p, tile_m, tile_n, wm, wn, lane, tm_sel);
-    } else {
-        __shared__ __align__(16) unsigned char rows[NW * epi_wave_bytes<BN>()];
-        gemm_epilogue<BM, BN, EPI, D, SC>(acc, p, tile_m, tile_n, wm, wn, lane, tm_sel, 0, rows + wave * epi_wave_bytes<BN>());
-    }
+    gemm_epilogue16<BM, BN, EPI, D, SC>(acc, p, tile_m, tile_n, wm, wn, lane, tm_sel);
 }
 
 // ------------------------------------------------------------------------------------------
