@@ -197,6 +197,21 @@ __device__ __forceinline__ int frag_row16(int i) { return paired16(EPI) ? 8 * (i
 template <int EPI>
 constexpr int frag_base16(int tn) { return paired16(EPI) ? 32 * (tn >> 1) + 4 * (tn & 1) : 16 * tn; }
 
+// The factors a_scale * w_scale[feature] of a wave's sums of products of codes, fragment by fragment; loaded ahead of the k loop.
+template <int BN, int EPI, int D, int TN>
+__device__ __forceinline__ void load_code_scales(const GemmArgs& p, int tile_n, int wn, int lane, float4 (&sc)[TN]) {
+    constexpr bool SWI = EPI == EPI_SWIGLU;
+    constexpr int FEAT = BN / WGN;
+    const int gq = lane >> 4, cols = SWI ? p.n_half : p.N;
+    const int n0 = (SWI ? tile_n * (BN / 2) + wn * (FEAT / 2) : tile_n * BN + wn * FEAT) + (paired16(EPI) ? 8 : 4) * gq;
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn) {
+        const int n = n0 + frag_base16<EPI>(SWI ? tn % (TN / 2) : tn);
+        sc[tn] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (n < cols) sc[tn] = *reinterpret_cast<const float4*>(p.w_scale + (SWI && tn >= TN / 2 ? p.n_half : 0) + n);
+    }
+}
+
 // Epilogue of the 16 x 16 kernels, straight from the accumulators: acc[tn][tm] holds fragment tn's features of token
 // 16 tm + lane % 16 (of 32 tm_base on).  A workgroup has one wave per SIMD, so the epilogue lasts as long as its instructions take to
 // issue: there is no pass through the LDS, a row of tiles has one scalar base address and the distances of its accesses are constants,
@@ -207,7 +222,8 @@ constexpr int frag_base16(int tn) { return paired16(EPI) ? 32 * (tn >> 1) + 4 * 
 // 3163 -> 2919.  (Workgroups that stay and load their next tile's first stages beside the epilogue gained nothing on this: the next
 // tile's first waits then include the stores.)
 template <int BM, int BN, int EPI, int D, bool SC, bool FULL, int TN, int TM>
-__device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM], const GemmArgs& p, int tile_n, int t0, int wn, int lane) {
+__device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM], const GemmArgs& p, int tile_n, int t0, int wn, int lane,
+                                                     const float4 (&sc)[SC ? TN : 1]) {
     constexpr int FEAT = BN / WGN;
     static_assert(TN == FEAT / 16, "the wave's features");
     const int l16 = lane & 15, gq = lane >> 4;
@@ -224,11 +240,6 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
         else
             return make_float4(v.x + r.x, v.y + r.y, v.z + r.z, v.w + r.w);
     };
-    auto code_scale = [&](int n) __attribute__((always_inline)) {
-        float4 s = *reinterpret_cast<const float4*>(p.w_scale + n);
-        s.x *= p.a_scale; s.y *= p.a_scale; s.z *= p.a_scale; s.w *= p.a_scale;
-        return s;
-    };
     auto pack8 = [](const float4& a, const float4& b) __attribute__((always_inline)) {
         return make_uint4(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w), pack_bf16x2(b.x, b.y), pack_bf16x2(b.z, b.w));
     };
@@ -242,12 +253,6 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
     if constexpr (EPI == EPI_RES_BF16_OUT_F32) {
         const int n0 = tile_n * BN + wn * FEAT;
         auto ok = [&](int tn) { return FULL || n0 + 4 * gq + 16 * tn < p.N; };
-        float4 sc[SC ? TN : 1];
-        if constexpr (SC) {
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
-                if (ok(tn)) sc[tn] = code_scale(n0 + 4 * gq + 16 * tn);
-        }
         uint2 res[2][TN];
         const bool add = p.residual != nullptr;   // no residual given: plain fp32 output
         auto fetch = [&](int tm) __attribute__((always_inline)) {
@@ -280,12 +285,6 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
     } else if constexpr (EPI == EPI_QKV_ROPE) {
         constexpr int HEADS = FEAT / D, GH = D / 64, TH = D / 16;   // heads of the wave, 8-feature groups of half a head, tiles of a head
         const int head0 = (tile_n * BN + wn * FEAT) / D, kv_dim = p.n_kv * D;
-        float4 sc[SC ? TN : 1];
-        if constexpr (SC) {
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
-                if (head0 + tn / TH < p.n_q + 2 * p.n_kv) sc[tn] = code_scale(head0 * D + frag_base16<EPI>(tn) + 8 * gq);
-        }
         float4 cs[2][GH][4];
         int slot[2];
         auto fetch = [&](int tm) __attribute__((always_inline)) {
@@ -357,14 +356,6 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
         const int cols = SWI ? p.n_half : p.N;
         const int n0 = SWI ? tile_n * (BN / 2) + wn * (FEAT / 2) : tile_n * BN + wn * FEAT;
         auto ok = [&](int u, int h) { return FULL || n0 + 8 * gq + 32 * u + 4 * h < cols; };
-        float4 sc[SC ? TN : 1];
-        if constexpr (SC) {
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn) {
-                const int i = SWI ? tn % (TN / 2) : tn, n = n0 + 8 * gq + frag_base16<EPI>(i);
-                if (ok(i / 2, i % 2)) sc[tn] = code_scale(SWI && tn >= TN / 2 ? p.n_half + n : n);
-            }
-        }
         const bool codes = SC && SWI && p.out_f8;   // the down projection reads codes (n_half is a multiple of 8)
         const int esize = codes ? 1 : 2;
         float4 res[2][EPI == EPI_RES_F32_OUT_BF16 ? GROUPS : 1][2];
@@ -422,14 +413,18 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
 
 template <int BM, int BN, int EPI, int D, bool SC, int TN, int TM>
 __device__ __forceinline__ void gemm_epilogue16(const f32x4_t (&acc)[TN][TM], const GemmArgs& p, int tile_m, int tile_n, int wm, int wn,
-                                                int lane, int tm_base) {
+                                                int lane, int tm_base, const float4 (&w_scales)[SC ? TN : 1] = {}) {
+    float4 sc[SC ? TN : 1];
+#pragma unroll
+    for (int i = 0; i < (SC ? TN : 0); ++i)
+        sc[i] = make_float4(w_scales[i].x * p.a_scale, w_scales[i].y * p.a_scale, w_scales[i].z * p.a_scale, w_scales[i].w * p.a_scale);
     const int t0 = tile_m * BM + 32 * tm_base + wm * (BM / WGM);
     const int cols = EPI == EPI_SWIGLU ? p.n_half : p.N, last = (tile_n + 1) * (EPI == EPI_SWIGLU ? BN / 2 : BN);
     const bool aligned = EPI == EPI_QKV_ROPE || EPI == EPI_RES_BF16_OUT_F32 || (cols % 8 == 0 && reinterpret_cast<uintptr_t>(p.out) % 16 == 0);
     if (t0 + 16 * TM <= p.T && last <= cols && aligned)
-        gemm_epilogue16_rows<BM, BN, EPI, D, SC, true>(acc, p, tile_n, t0, wn, lane);
+        gemm_epilogue16_rows<BM, BN, EPI, D, SC, true>(acc, p, tile_n, t0, wn, lane, sc);
     else if (t0 < p.T)
-        gemm_epilogue16_rows<BM, BN, EPI, D, SC, false>(acc, p, tile_n, t0, wn, lane);
+        gemm_epilogue16_rows<BM, BN, EPI, D, SC, false>(acc, p, tile_n, t0, wn, lane, sc);
 }
 
 template <int BM, int BN, int EPI, int D = 0>
@@ -709,7 +704,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     using frag_t = std::conditional_t<F8, i32x8_t, bf16x8_t>;
-    frag_t wf[F8 ? 1 : 2][TN], af[F8 ? 1 : 2][TM];
+    constexpr bool FIXED = BM * BN >= 6 * 4096 && !(EPI == EPI_SWIGLU && BM == 128);   // issue order: see below
+    constexpr bool QUARTERS = F8 && FIXED;
+    frag_t wf[QUARTERS ? 1 : 2][TN], af[QUARTERS ? 1 : 2][TM];
     typedef const i32x4_t __attribute__((address_space(3))) * lds_chunk;
     auto read_frag = [&](uint32_t at, int dist) __attribute__((always_inline)) -> frag_t {
         if constexpr (F8) {
@@ -821,7 +818,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         }
     };
     // 8-bit operands on 16 x 16 x 128 products: a stage is one k step, and two buffers of its fragments (256 registers on a 256 x 256
-    // tile) do not fit beside the sums.  The wave's products go quarter by quarter instead, weights' halves lo and hi against tokens'
+    // tile) do not fit beside the sums (small tiles do keep two).  The wave's products go quarter by quarter instead, weights' halves lo and hi against tokens'
     // halves h and h' = 1 - h: (lo, h), (lo, h'), (hi, h'), (hi, h), and behind each quarter's products come the four fragments or so
     // that the next one adds, into registers whose last reader is over: tokens h' , weights hi, the next stage's lo and, where tokens h'
     // were, the next stage's tokens h'; so the next stage begins with h'.  Every fragment is read once, at an even rate, and the
@@ -859,7 +856,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // (8-bit operands on 256 x 256 with eight waves, two per SIMD, hide the loads' latency without the skewed ring, but a wave's 64 x 128
     // then reads 96 KB of fragments per k step of 1024 cycles beside the 32 KB that land, all the LDS delivers; four waves read
     // 64 KB.  13B layer at T = 3875 on codes: eight waves 1257 us, with the skewed ring too; four 1231, skewed 1194.)
-    constexpr bool FIXED = BM * BN >= 6 * 4096 && !(EPI == EPI_SWIGLU && BM == 128);
     static_assert(F8 || !FIXED || 2 * NF <= NM, "a fragment read behind every other MFMA");
     static_assert(TN % 2 == 0 && TM % 2 == 0, "halves");
     static_assert(!SKEW || FIXED, "the skewed ring's weights are issued in the fixed order only");
@@ -867,14 +863,14 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // One k iteration (one LDS stage).  open_a, open_w: what the refill begun at the previous hand-over still issues (stage
     // kt - 1 + NS of the activations, kt - 1 + NSW of the weights, if there is one); next_a, next_w: what this iteration's
     // hand-over starts (stages kt + NS and kt + NSW).  Without the skew both flags of a pair are the same.
-    // H (codes): which half of the tokens the stage begins with.
+    // H (codes: kt % 2): which half of the tokens the stage begins with, or which buffer its fragments are in.
     auto iteration = [&](int kt, auto H, auto open_a, auto open_w, auto next_a, auto next_w) __attribute__((always_inline)) {
         const Stage nxt{cur.a + 1 == NS ? 0 : cur.a + 1, cur.w + 1 == NSW ? 0 : cur.w + 1};
 #pragma unroll
-        for (int ks = 0; ks + 1 < STEPS; ++ks) {
-            if constexpr (F8) {
+        for (int ks = 0; ks + 1 < (QUARTERS ? 2 : KSTEPS); ++ks) {
+            if constexpr (QUARTERS) {
                 half_step(false, H.value, cur, open_a, open_w);
-            } else if (FIXED) {
+            } else if constexpr (FIXED) {
                 k_step(ks & 1, cur, ks + 1, ks + 1, open_a, open_w);
             } else {
                 load_frags((ks + 1) & 1, cur, ks + 1);
@@ -885,7 +881,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         // Last k step of the stage: all its fragments are in registers.  Wait for the next stage (the
         // NS - 2 younger ones may stay in flight), hand over, and start refilling the freed buffer.
         // After the last stage this reads fragments nobody uses.
-        constexpr int LB = (KSTEPS - 1) & 1;
+        constexpr int LB = F8 ? decltype(H)::value : 1;   // the buffer of its fragments
         constexpr bool steady = std::is_same_v<decltype(next_w), std::true_type>;   // then kt + NSW < nk
         if ((NS == 2 && !SKEW) || (!steady && kt + NSW - 1 >= nk))
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -896,9 +892,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         rf_w += w_stage;
         rf_la = lds_a0 + cur.a * A_BYTES;
         rf_lw = lds_w0 + cur.w * W_BYTES;
-        if constexpr (F8) {
+        if constexpr (QUARTERS) {
             half_step(true, H.value, nxt, next_a, next_w);
-        } else if (FIXED) {
+        } else if constexpr (FIXED) {
             k_step(LB, nxt, 0, 0, next_a, next_w);
         } else {
             const Source src = source(nxt, 0);
@@ -921,6 +917,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         }
         cur = nxt;
     };
+    constexpr bool SC = F8 && EPI != EPI_SLAB;
+    float4 w_scales[SC ? TN : 1];
+    if constexpr (SC) load_code_scales<BN, EPI, D>(p, tile_n, wn, lane, w_scales);
     // fill both rings, wait for stage 0 only
 #pragma unroll
     for (int s = 0; s < NSW; ++s) {
@@ -939,7 +938,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     else
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if constexpr (F8) {
+    if constexpr (QUARTERS) {
         const Source src = source(Stage{0, 0}, 0);
 #pragma unroll
         for (int i = 0; i < AH; ++i) read_a(src, 0, i);
@@ -993,7 +992,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         p.residual = nullptr;
         gemm_epilogue16<BM, BN, EPI_RES_BF16_OUT_F32, 0, false>(acc, p, tile_m, tile_n, wm, wn, lane, 0);
     } else {
-        gemm_epilogue16<BM, BN, EPI, D, F8>(acc, p, tile_m, tile_n, wm, wn, lane, 0);
+        gemm_epilogue16<BM, BN, EPI, D, F8>(acc, p, tile_m, tile_n, wm, wn, lane, 0, w_scales);
     }
 }
 
@@ -1015,6 +1014,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_tail_finish_kernel(GemmAr
     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
         for (int h = 0; h < H; ++h) acc[tn][h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    float4 w_scales[SC ? TN : 1];
+    if constexpr (SC) load_code_scales<BN, EPI, D>(p, tile_n, wn, lane, w_scales);
     for (int q = 0; q < p.tail_splits; ++q) {
         const f32x4_t* src = reinterpret_cast<const f32x4_t*>(p.tail_buf) + ((size_t)q * p.tail_tiles + tail_idx) * AREA4 + tid;
         f32x4_t v[TN][H];
@@ -1027,7 +1028,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_tail_finish_kernel(GemmAr
 #pragma unroll
             for (int h = 0; h < H; ++h) acc[tn][h] += v[tn][h];
     }
-    gemm_epilogue16<BM, BN, EPI, D, SC>(acc, p, tile_m, tile_n, wm, wn, lane, tm_sel);
+    gemm_epilogue16<BM, BN, EPI, D, SC>(acc, p, tile_m, tile_n, wm, wn, lane, tm_sel, w_scales);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1542,6 +1543,11 @@ int split_rows(int T, int N, int K, bool has_accum) {
     return 0;
 }
 
+// k too short to cut (below 512): one k range leaves the sums of whole tiles, and the fused epilogue the bits of the finish kernel
+// (on codes it rounds once less), a launch and a pass over the slab less.  Gate/up of the tiny layer (hidden 256) with its finish kernel at
+// T = 482 / 1308 / 1947 14.8 / 14.9 / 17.0 us, whole 5.1 / 5.8 / 6.4; W_o at 1947 13.6, 6.0.
+bool one_range(const GemmArgs& p, int bm) { return !p.f8 && choose_splits(p.T, p.N, p.K, bm) == 1; }
+
 template <int EPI>
 hipError_t launch_mid_split(GemmArgs p, int bm, hipStream_t s, NextNorm* next) {
     if (bm == 128) return launch_split<128, EPI, 0>(p, choose_splits(p.T, p.N, p.K, 128), s, next);
@@ -1827,7 +1833,8 @@ hipError_t launch_linear(const void* a, const void* w, int32_t T, int32_t N, int
             default: return hipErrorInvalidValue;
         }
     }
-    if (const int bm = split_rows(T, N, K, accum != nullptr)) {
+    const int bm = split_rows(T, N, K, accum != nullptr);
+    if (bm && !one_range(p, bm)) {
         switch (epilogue) {
             case EPI_BF16: return launch_mid_split<EPI_BF16>(p, bm, s, next);
             case EPI_RES_BF16_OUT_F32: return launch_mid_split<EPI_RES_BF16_OUT_F32>(p, bm, s, next);

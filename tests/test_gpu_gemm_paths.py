@@ -153,6 +153,37 @@ def test_rows_that_end_or_begin_inside_a_group_of_8(rs, N, shift):
             assert (buf[:shift] == 7).all() and (buf[shift + T * N:] == 7).all(), (epi, tile)
 
 
+@pytest.mark.parametrize("T", [257, 482, 1308])
+@pytest.mark.parametrize("hidden", [192, 256, 448, 512])
+def test_short_k_takes_whole_tiles_at_mid_size(rs, T, hidden):
+    """Narrow layers at a few hundred tokens: k below 512 is not cut and runs as whole tiles, 512 is cut in two; both agree
+    with forced whole tiles as sums in another order do."""
+    shape = W.LayerShape(hidden, 4, 4, 64, 704, 16, 1e-5, 10000.0)
+    b = W.build_batch(shape, [T - 7] + [1] * 7, [T - 7] + [5] * 7, seed=T)
+    g = torch.Generator(device="cuda").manual_seed(hidden)
+    randn = lambda *s, std=0.05: torch.empty(*s, dtype=torch.float32, device="cuda").normal_(0, std, generator=g).bfloat16()
+    wd = {"w_in_norm": randn(hidden, std=1.0), "w_qkv": randn(shape.qkv_dim, hidden), "w_o": randn(hidden, shape.q_dim), "w_post_norm": randn(hidden, std=1.0),
+          "w_gate_up": randn(2 * 704, hidden), "w_down": randn(hidden, 704)}
+    x = randn(b.T, hidden, std=1.0)
+    pool = (b.num_pages, shape.page_size, shape.n_kv_heads, shape.head_dim)
+    k, v = randn(*pool, std=1.0), randn(*pool, std=1.0)
+    layer = rs.relserve_layer_create(shape)
+    pb = rs.relserve_batch_prepare(layer, b)
+    ws = torch.empty(rs.relserve_workspace_bytes(layer, b.T), dtype=torch.uint8, device="cuda")
+    outs = []
+    for tile in (-1, 3):
+        y = torch.empty_like(x)
+        rs.relserve_debug_force_gemm_plan(tile, 0)
+        try:
+            rs.relserve_layer_step(layer, pb, wd, x, y, k.clone(), v.clone(), ws)
+            torch.cuda.synchronize()
+        finally:
+            rs.relserve_debug_force_gemm_plan(-1, 0)
+        outs.append(y.float().cpu().numpy())
+    # W_down (k = 704) is cut in two on one side: rounded once to bf16, so a value in some thousands lies one unit apart
+    assert_close(outs[0], outs[1], f"T={T} hidden={hidden}", max_abs=2e-2 * max(1.0, np.abs(outs[1]).max()), rel_l2=2e-3)
+
+
 def test_iteration_of_640_tokens_keeps_its_sums_whole(rs):
     """The q/k/v projection of a 13B layer at T = 640 (128 decode rows and a 512-token chunk) fills its rounds well enough to
     split nothing: the appended keys and values carry the bits of whole tiles, as its gate/up projection's sums do."""
