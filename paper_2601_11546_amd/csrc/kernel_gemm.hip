@@ -1630,10 +1630,10 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
 // refit of them for 16-bit operands changed a next token in 129 (four 13B layers, 128 decode rows and a 512-token chunk).
 //
 // 2. The shape of whole tiles: any gives the same bits, so where nothing is split the fastest one runs (whole_tile).  For the
-// SwiGLU projection that is the shape the cut's own model names: 0.0 % (16-bit) and 0.4 % (8-bit) off the fastest one on average
-// at hidden sizes of 5120 and more, 1.2 and 2.6 % at smaller ones (profiles/gemm_whole_tiles.txt; measured before the tiles of
-// 192 and 256 rows kept a third stage of weights, and not again since).
-struct TileCand { int bm, bn, wg_per_cu; float eff_cut, eff; bool qkv; };   // qkv: usable by the fused q/k/v epilogue (128 features per wave)
+// SwiGLU projection of a k (in 2-byte units) below SWIGLU_FIT_K that is the shape the cut's own model names: 1.2 (16-bit) and 2.6 %
+// (8-bit) off the fastest one on average at hidden sizes of 256 .. 3072 (profiles/gemm_whole_tiles.txt).
+struct TileCand { int bm, bn, wg_per_cu; float eff_cut, eff, eff_swiglu; bool qkv; };   // qkv: usable by the fused q/k/v epilogue (128 features per wave)
+constexpr int SWIGLU_FIT_K = 2560;
 constexpr TileCand kTiles[] = {
     // eff: fitted to the times of every whole tile shape, forced, of the other projections that split nothing, five layer shapes
     // at 18 token counts of 264 .. 4200, 16-bit and 8-bit.  Distance of the choice from the fastest shape, on average: 0.03 % in
@@ -1641,8 +1641,12 @@ constexpr TileCand kTiles[] = {
     // 1.1 % (16 and 11 %).  W_o of the 13B layer at T = 1152 86 -> 74 us; 8-bit q/k/v of the 32B one at T = 806 59 -> 43.
     // With the third stage of weights 192 x 256 gained most (0.88 before): measured again at 17 token counts, 0.0 % off the fastest in
     // 16 bits (0.13 % with 0.88) and 0.4 % in 8; q/k/v of the 70B layer at T = 2304 322 (128 x 256) -> 308 us, 7168 x 8192 at 2700 289 -> 280.
-    {256, 256, 1, 1.00f, 1.00f, true}, {192, 256, 1, 0.92f, 0.98f, true}, {128, 256, 1, 0.68f, 0.90f, true},
-    {128, 128, 2, 0.76f, 0.50f, false}, {64, 128, 3, 0.60f, 0.40f, false}};
+    // With 16 x 16 products all of it was measured once more, 18 token counts of 264 .. 4500 and five layer shapes: the same
+    // choices, 0.00 % off the fastest.  eff_swiglu: the SwiGLU projection of those shapes, whose 128 x 256 tile has the compiler's
+    // order and lags: 0.00 % off in 16 bits and 0.08 % in 8, where the cut's shapes were 0.4 and 0.9 % off (the small ones have fallen
+    // behind: 806 tokens of the 32B layer on codes 258 us on 128 x 128, 221 on 256 x 256; 16-bit 32B half 227, 198).
+    {256, 256, 1, 1.00f, 1.00f, 1.00f, true}, {192, 256, 1, 0.92f, 0.98f, 0.96f, true}, {128, 256, 1, 0.68f, 0.90f, 0.75f, true},
+    {128, 128, 2, 0.76f, 0.50f, 0.45f, false}, {64, 128, 3, 0.60f, 0.40f, 0.40f, false}};
 constexpr int kTileCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
 constexpr double kCuFlops = 5.2e12;          // sustained MFMA rate of one CU inside a 256 x 256 tile
@@ -1687,14 +1691,14 @@ Plan choose_cut(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail) {
 
 // The cost of a round is the tile's MFMA work over the shape's in-tile efficiency (relative to 256 x 256) plus kRoundSec;
 // this trades tile quantisation in T (padding to BM), the incomplete round, and the efficiency against each other.
-int whole_tile(int T, int64_t n_eff, int K, bool need_bn256) {
+int whole_tile(int T, int64_t n_eff, int K, bool need_bn256, bool swiglu) {
     int best = 0;
     double best_cost = 1e300;
     for (int i = 0; i < kTileCount; ++i) {
         const TileCand& c = kTiles[i];
         if (need_bn256 && !c.qkv) continue;
         const int64_t tiles = tile_count(c, T, n_eff), slots = 256 * c.wg_per_cu, rounds = (tiles + slots - 1) / slots;
-        const double t_tile = tile_sec(c, K, c.eff);
+        const double t_tile = tile_sec(c, K, swiglu ? c.eff_swiglu : c.eff);
         double cost;
         if (c.wg_per_cu > 1)   // tiles of an incomplete round share fewer CUs' pipes
             cost = (double)((tiles + 255) / 256) * t_tile + (double)rounds * kRoundSec;
@@ -1710,7 +1714,7 @@ bool forced_plan(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, 
     const int cand = forced_cand(), splits = forced_splits();
     if (cand < 0 || cand >= kTileCount) return false;
     if (need_bn256 && !kTiles[cand].qkv) {   // whole tiles of the best shape that can
-        *out = Plan{whole_tile(T, n_eff, K, true), 0, 1};
+        *out = Plan{whole_tile(T, n_eff, K, true, false), 0, 1};
         return true;
     }
     const TileCand& c = kTiles[cand];
@@ -1725,7 +1729,7 @@ Plan plan_for(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, boo
     Plan plan;
     if (forced_plan(T, n_eff, K, need_bn256, allow_tail, &plan)) return plan;
     plan = choose_cut(T, n_eff, K, need_bn256, allow_tail);
-    if (plan.tail_tiles == 0 && !swiglu) plan.cand = whole_tile(T, n_eff, K, need_bn256);
+    if (plan.tail_tiles == 0 && !(swiglu && K < SWIGLU_FIT_K)) plan.cand = whole_tile(T, n_eff, K, need_bn256, swiglu);
     return plan;
 }
 
