@@ -41,6 +41,7 @@ struct GemmArgs {
     int32_t T, N, K;
     int32_t n_half;  // SwiGLU: gate rows [0, n_half), up rows [n_half, 2 n_half)
     int32_t tiles_m, tiles_n;
+    int32_t tile_n0;   // first feature tile of the launch (a launch of columns of tiles: plan_for)
     // fused q/k/v epilogue: rotary embedding + KV append (out = q buffer [T, n_q d])
     const int32_t* tok_slot;
     const float2* rope_cs;
@@ -638,6 +639,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     }
     int tile_m, tile_n;
     tile_coords(tile, p.tiles_m, p.tiles_n, tile_m, tile_n);
+    tile_n += p.tile_n0;
 
     // ---- per-lane source offsets: wave load j of this wave fills LDS rows (NW j + wave) * RPI .. ;
     // lane l owns row l / CPR of those and slot l % CPR, which holds the row's chunk slot ^ swz(row).
@@ -1568,14 +1570,19 @@ bool small_applies(const GemmArgs& p, int epi, int head_dim = 0) {
     return (p.T + 31) / 32 * units <= (epi == EPI_QKV_ROPE || p.K % 64 ? 768 : 256);
 }
 
-// What a launch does beyond whole tiles: the last tail_tiles tiles split their k range over `splits` workgroups.
-struct Plan { int cand, tail_tiles, splits; };
+// What a launch does beyond whole tiles: the last tail_tiles tiles split their k range over `splits` workgroups; or, where nothing is
+// split, the first cols1 columns of tiles run as cand1 and the others as cand2 (cols1 = 0: all as cand).
+struct Plan { int cand, tail_tiles, splits, cols1 = 0, cand1 = 0, cand2 = 0; };
 
 template <int BM, int BN, int EPI, int D = 0>
-hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Plan{0, 0, 1}) {
+hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Plan{0, 0, 1}, int col0 = 0, int cols = 0) {
     GemmArgs p = base;
     p.tiles_m = (p.T + BM - 1) / BM;
     p.tiles_n = EPI == EPI_SWIGLU ? (p.n_half + BN / 2 - 1) / (BN / 2) : (p.N + BN - 1) / BN;
+    if (cols > 0) {   // columns [col0, col0 + cols) of tiles
+        p.tile_n0 = col0;
+        p.tiles_n = std::min(cols, p.tiles_n - col0);
+    }
     constexpr int smem = 2 * (BM + BN) * BK * 2;
     // 128 x 256 tiles are one workgroup per CU either way, so they take the third stage that fits (144 KB)
     constexpr int DMA_BK = 64, DMA_NS = (BM == 128 && BN == 256) ? 3 : 2, DMA_NSW = weight_stages(BM, BN, DMA_NS);
@@ -1709,6 +1716,37 @@ int whole_tile(int T, int64_t n_eff, int K, bool need_bn256, bool swiglu) {
     return best;
 }
 
+// Whole tiles of two shapes: the last round of a launch is half empty on average, and what it leaves idle can be had by giving its
+// columns of tiles to a launch of smaller tiles that fill one round more evenly (any shape gives the same bits).  For each number of
+// full rounds of each 256-feature shape: as many columns as they hold, the rest on another; taken where the model that
+// whole_tile uses sees a gain of kTwoShapesGain beyond kSecondLaunchSec.  One launch / two, us, measured in turn: gate/up of the 32B layer on
+// codes at T = 806 219 / 197, of its 16-bit half 217 / 190, 70B at 577 503 / 466, 13B at 1409 315 / 303; q/k/v of the 13B layer at 2500
+// on codes 163 / 154, W_o at 3875 162 / 152; of 100 sizes of five layer shapes, 3.3 % on average.  (Below a modelled gain of 4 % the
+// second launch lost 1 - 3 % as often as it won them.)
+constexpr double kSecondLaunchSec = 6e-6, kTwoShapesGain = 0.04;
+void two_shapes(int T, int64_t n_eff, int K, bool swiglu, Plan* plan) {
+    const int cols = (int)((n_eff + 255) / 256);
+    auto cost = [&](int cand, int c) {
+        const TileCand& t = kTiles[cand];
+        const int64_t tiles = (int64_t)((T + t.bm - 1) / t.bm) * c, rounds = (tiles + 255) / 256;
+        return (double)rounds * (tile_sec(t, K, swiglu ? t.eff_swiglu : t.eff) + kRoundSec) / (t.bm >= 256 ? idle_boost(tiles, 256) : 1.0);
+    };
+    if (plan->cand > 2) return;
+    double best = cost(plan->cand, cols) * (1.0 - kTwoShapesGain) - kSecondLaunchSec;
+    for (int a = 0; a < 3; ++a) {
+        const int rows = (T + kTiles[a].bm - 1) / kTiles[a].bm;
+        for (int rounds = 1; rounds * 256 / rows < cols; ++rounds) {
+            const int c = rounds * 256 / rows;
+            if (c == 0) continue;
+            for (int b = 0; b < 3; ++b) {
+                if (b == a) continue;
+                const double t = cost(a, c) + cost(b, cols - c);
+                if (t < best) best = t, plan->cols1 = c, plan->cand1 = a, plan->cand2 = b;
+            }
+        }
+    }
+}
+
 // Test hook: the forced tile, or the nearest one the epilogue can run on; its whole incomplete round split if asked for.
 bool forced_plan(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, Plan* out) {
     const int cand = forced_cand(), splits = forced_splits();
@@ -1730,20 +1768,31 @@ Plan plan_for(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, boo
     if (forced_plan(T, n_eff, K, need_bn256, allow_tail, &plan)) return plan;
     plan = choose_cut(T, n_eff, K, need_bn256, allow_tail);
     if (plan.tail_tiles == 0 && !(swiglu && K < SWIGLU_FIT_K)) plan.cand = whole_tile(T, n_eff, K, need_bn256, swiglu);
+    if (plan.tail_tiles == 0 && K >= SWIGLU_FIT_K && K % 64 == 0) two_shapes(T, n_eff, K, swiglu, &plan);
     return plan;
+}
+
+// The plan's launch, or two.
+template <typename Launch>   // launch(candidate, first column, columns; 0: all)
+hipError_t run_plan(const Plan& plan, Launch launch) {
+    if (plan.cols1 == 0) return launch(plan.cand, 0, 0);
+    if (hipError_t e = launch(plan.cand1, 0, plan.cols1)) return e;
+    return launch(plan.cand2, plan.cols1, 1 << 30);
 }
 
 template <int EPI>
 hipError_t launch_epi(const GemmArgs& p, hipStream_t s) {
     const int64_t n_eff = EPI == EPI_SWIGLU ? 2 * (int64_t)p.n_half : p.N;
     const Plan plan = plan_for(p.T, n_eff, p.K, false, p.accum != nullptr, EPI == EPI_SWIGLU);
-    switch (plan.cand) {
-        case 0: return launch_cfg<256, 256, EPI>(p, s, plan);
-        case 1: return launch_cfg<192, 256, EPI>(p, s, plan);
-        case 2: return launch_cfg<128, 256, EPI>(p, s, plan);
-        case 3: return launch_cfg<128, 128, EPI>(p, s, plan);
-        default: return launch_cfg<64, 128, EPI>(p, s, plan);
-    }
+    return run_plan(plan, [&](int cand, int col0, int cols) {
+        switch (cand) {
+            case 0: return launch_cfg<256, 256, EPI>(p, s, plan, col0, cols);
+            case 1: return launch_cfg<192, 256, EPI>(p, s, plan, col0, cols);
+            case 2: return launch_cfg<128, 256, EPI>(p, s, plan, col0, cols);
+            case 3: return launch_cfg<128, 128, EPI>(p, s, plan);
+            default: return launch_cfg<64, 128, EPI>(p, s, plan);
+        }
+    });
 }
 
 }  // namespace
@@ -1862,11 +1911,13 @@ template <int D>
 hipError_t launch_qkv_d(const GemmArgs& p, hipStream_t s) {
     if (p.T <= 64) return launch_cfg<64, 256, EPI_QKV_ROPE, D>(p, s);
     const Plan plan = plan_for(p.T, p.N, p.K, true, p.accum != nullptr, false);   // the rotation needs 128 features per wave
-    switch (plan.cand) {
-        case 0: return launch_cfg<256, 256, EPI_QKV_ROPE, D>(p, s, plan);
-        case 1: return launch_cfg<192, 256, EPI_QKV_ROPE, D>(p, s, plan);
-        default: return launch_cfg<128, 256, EPI_QKV_ROPE, D>(p, s, plan);
-    }
+    return run_plan(plan, [&](int cand, int col0, int cols) {
+        switch (cand) {
+            case 0: return launch_cfg<256, 256, EPI_QKV_ROPE, D>(p, s, plan, col0, cols);
+            case 1: return launch_cfg<192, 256, EPI_QKV_ROPE, D>(p, s, plan, col0, cols);
+            default: return launch_cfg<128, 256, EPI_QKV_ROPE, D>(p, s, plan, col0, cols);
+        }
+    });
 }
 }  // namespace
 

@@ -184,6 +184,36 @@ def test_short_k_takes_whole_tiles_at_mid_size(rs, T, hidden):
     assert_close(outs[0], outs[1], f"T={T} hidden={hidden}", max_abs=2e-2 * max(1.0, np.abs(outs[1]).max()), rel_l2=2e-3)
 
 
+@pytest.mark.parametrize("w8a8", [False, True], ids=["bf16", "codes"])
+@pytest.mark.parametrize("T", [385, 577, 640, 806, 1409])
+@pytest.mark.parametrize("epi, N", [(1, 11012), (3, 27648), (0, 7176)])
+def test_columns_of_two_tile_shapes_give_the_same_bits(rs, T, epi, N, w8a8):
+    """Sizes whose whole tiles fill their last round badly run as two launches, each its own columns and tile shape: the bits of one shape,
+    every column written once.  (1409 tokens of the last two and 385 of the first keep one launch.)"""
+    K = 5120 if w8a8 else 2560
+    g = torch.Generator(device="cuda").manual_seed(T + N)
+    if w8a8:
+        codes = lambda *s: (torch.randn(s, generator=g, device="cuda") * 60).to(torch.float8_e4m3fn).view(torch.uint8)
+        a, w, sw = codes(T, K), codes(N, K), torch.rand(N, generator=g, device="cuda") * 1e-4
+        run = lambda res, out: rs.relserve_linear_w8a8(a, w, sw, 0.03, epi, res, out)
+    else:
+        a = torch.randn(T, K, generator=g, device="cuda").bfloat16()
+        w = (torch.randn(N, K, generator=g, device="cuda") * 0.02).bfloat16()
+        run = lambda res, out: rs.relserve_linear(a, w, epi, res, out)
+    res = torch.randn(T, N, generator=g, device="cuda").bfloat16() if epi == 1 else None
+    outs = []
+    for tile in (-1, 0):
+        out = torch.full((T, N // 2 if epi == 3 else N), float("nan"), dtype=torch.float32 if epi == 1 else torch.bfloat16, device="cuda")
+        rs.relserve_debug_force_gemm_plan(tile, 0)
+        try:
+            run(res, out)
+            torch.cuda.synchronize()
+        finally:
+            rs.relserve_debug_force_gemm_plan(-1, 0)
+        outs.append(out)
+    assert torch.isfinite(outs[1]).all() and torch.equal(outs[0], outs[1])
+
+
 def test_iteration_of_640_tokens_keeps_its_sums_whole(rs):
     """The q/k/v projection of a 13B layer at T = 640 (128 decode rows and a 512-token chunk) fills its rounds well enough to
     split nothing: the appended keys and values carry the bits of whole tiles, as its gate/up projection's sums do."""
