@@ -1,6 +1,7 @@
 // Host boundary of the layer-step library: validation, descriptor expansion, upload,
 // workspace carving and kernel sequencing.  No arithmetic of the method lives here.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -178,10 +179,83 @@ int32_t check_cache(const relserve_batch* b, const relserve_kv_cache& cache, boo
     return RELSERVE_OK;
 }
 
-int32_t check_pair(const relserve_layer* L, const relserve_batch* b) {
+// stream: where the caller submits work that reads the batch
+int32_t check_pair(const relserve_layer* L, const relserve_batch* b, const void* stream) {
     if (!L || !b) return RELSERVE_ERR_NULL_POINTER;
     if (std::memcmp(&L->cfg, &b->cfg, sizeof(relserve_layer_config)) != 0) return RELSERVE_ERR_MISMATCH;
+    if (stream) b->other_stream.store(true, std::memory_order_relaxed);
     return RELSERVE_OK;
+}
+
+// Device allocations of destroyed batches, kept for the next ones.  hipFree waits for the whole device and gives the pages back:
+// 45 - 75 us of an iteration that prepares and destroys a batch (24 rows, four 13B layers: 820), with the GPU idle.
+// A blob comes here only if all work on its batch went to the default stream, where an event recorded as the batch is destroyed
+// stands behind it; it is handed out again when that event has passed, so neither side waits.  (Streams of the caller may be gone
+// by then; their batches take hipFree.)  At most kSpareBlobs of at most kSpareBlobBytes each; freed when the last layer handle goes.
+struct SpareBlob { void* blob; size_t bytes; int device; hipEvent_t idle; };
+constexpr size_t kSpareBlobs = 8, kSpareBlobBytes = (size_t)4 << 20;
+struct SpareBlobs {
+    std::mutex m;
+    std::vector<SpareBlob> blobs;   // oldest first
+};
+SpareBlobs& spare_blobs() {
+    static SpareBlobs* s = new SpareBlobs;   // never destroyed: no call into the runtime at the process's end
+    return *s;
+}
+std::atomic<int> g_layers{0};
+
+hipError_t free_blob(const SpareBlob& s) {
+    if (s.idle) (void)hipEventDestroy(s.idle);
+    return s.blob ? hipFree(s.blob) : hipSuccess;
+}
+
+bool take_spare_blob(size_t bytes, int device, SpareBlob* out) {
+    SpareBlobs& sp = spare_blobs();
+    std::lock_guard<std::mutex> lock(sp.m);
+    for (size_t i = 0; i < sp.blobs.size(); ++i) {
+        if (sp.blobs[i].device != device || sp.blobs[i].bytes < bytes) continue;
+        if (hipEventQuery(sp.blobs[i].idle) != hipSuccess) {
+            (void)hipGetLastError();   // not ready
+            continue;
+        }
+        *out = sp.blobs[i];
+        sp.blobs.erase(sp.blobs.begin() + (std::ptrdiff_t)i);
+        return true;
+    }
+    return false;
+}
+
+// False: it is still the caller's.
+bool give_spare_blob(SpareBlob& s) {
+    int device = -1;
+    if (s.bytes > kSpareBlobBytes || hipGetDevice(&device) != hipSuccess || device != s.device) return false;
+    if (!s.idle && hipEventCreateWithFlags(&s.idle, hipEventDisableTiming) != hipSuccess) return false;
+    if (hipEventRecord(s.idle, nullptr) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    SpareBlob oldest{};
+    {
+        SpareBlobs& sp = spare_blobs();
+        std::lock_guard<std::mutex> lock(sp.m);
+        if (sp.blobs.size() >= kSpareBlobs) {
+            oldest = sp.blobs.front();
+            sp.blobs.erase(sp.blobs.begin());
+        }
+        sp.blobs.push_back(s);
+    }
+    (void)free_blob(oldest);
+    return true;
+}
+
+void free_spare_blobs() {
+    std::vector<SpareBlob> all;
+    {
+        SpareBlobs& sp = spare_blobs();
+        std::lock_guard<std::mutex> lock(sp.m);
+        all.swap(sp.blobs);
+    }
+    for (const SpareBlob& s : all) (void)free_blob(s);
 }
 
 }  // namespace
@@ -615,6 +689,7 @@ int32_t relserve_layer_create(const relserve_layer_config* cfg, relserve_layer**
     L->inv_freq.resize(half);
     for (int i = 0; i < half; ++i)
         L->inv_freq[i] = (float)std::pow((double)cfg->rope_base, -2.0 * i / (double)cfg->head_dim);
+    ++g_layers;
     *out = L;
     return RELSERVE_OK;
 }
@@ -627,6 +702,7 @@ int32_t relserve_layer_destroy(relserve_layer* L) {
     }
     for (hipEvent_t e : L->event_pool) (void)hipEventDestroy(e);
     delete L;
+    if (--g_layers == 0) free_spare_blobs();
     return RELSERVE_OK;
 }
 
@@ -656,8 +732,8 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
     if (int32_t rc = expand_batch(L->cfg, *desc, true, &hb)) return rc;
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev == 0) return RELSERVE_ERR_NO_DEVICE;
+    int dev = 0;
     {
-        int dev = 0;
         hipDeviceProp_t prop;
         if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
             return RELSERVE_ERR_HIP;
@@ -714,9 +790,27 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
     relserve_batch* b = new (std::nothrow) relserve_batch();
     if (!b) return RELSERVE_ERR_BAD_ARGUMENT;
     b->cfg = L->cfg;
-    if (hipMalloc(&b->blob, total) != hipSuccess) {
-        delete b;
-        return RELSERVE_ERR_HIP;
+    b->device = dev;
+    b->other_stream = stream != nullptr;
+    SpareBlob spare{};
+    if (take_spare_blob(total, dev, &spare)) {
+        b->blob = spare.blob;
+        b->blob_bytes = spare.bytes;
+        b->idle = spare.idle;
+    } else {
+        b->blob_bytes = 65536;   // sizes that fit again: powers of two
+        while (b->blob_bytes < total) b->blob_bytes *= 2;
+        if (b->blob_bytes > kSpareBlobBytes) b->blob_bytes = total;
+        hipError_t got = hipMalloc(&b->blob, b->blob_bytes);
+        if (got != hipSuccess) {   // the spare ones may be what is missing
+            (void)hipGetLastError();
+            free_spare_blobs();
+            got = hipMalloc(&b->blob, b->blob_bytes);
+        }
+        if (got != hipSuccess) {
+            delete b;
+            return RELSERVE_ERR_HIP;
+        }
     }
     char* base = static_cast<char*>(b->blob);
     BatchDev& dv = b->dev;
@@ -755,7 +849,7 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
                               reinterpret_cast<float2*>(base + o_cs), s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
-        (void)hipFree(b->blob);
+        (void)free_blob(SpareBlob{b->blob, 0, 0, b->idle});
         delete b;
         return RELSERVE_ERR_HIP;
     }
@@ -765,7 +859,9 @@ int32_t relserve_batch_prepare(const relserve_layer* L, const relserve_batch_des
 
 int32_t relserve_batch_destroy(relserve_batch* b) {
     if (!b) return RELSERVE_OK;
-    hipError_t e = b->blob ? hipFree(b->blob) : hipSuccess;
+    SpareBlob blob{b->blob, b->blob_bytes, b->device, b->idle};
+    const bool kept = b->blob && !b->other_stream.load(std::memory_order_relaxed) && give_spare_blob(blob);
+    const hipError_t e = kept ? hipSuccess : free_blob(blob);
     delete b;
     return e == hipSuccess ? RELSERVE_OK : RELSERVE_ERR_HIP;
 }
@@ -786,7 +882,7 @@ int32_t relserve_workspace_bytes(const relserve_layer* L, int32_t max_tokens, si
 int32_t relserve_kv_append(const relserve_layer* L, const relserve_batch* b, const void* k, const void* v,
                            relserve_kv_cache cache, void* stream) {
     drop_stale_hip_error();
-    if (int32_t rc = check_pair(L, b)) return rc;
+    if (int32_t rc = check_pair(L, b, stream)) return rc;
     if (int32_t rc = check_cache(b, cache, false)) return rc;
     if (b->dev.T == 0) return RELSERVE_OK;
     if (!k || !v) return RELSERVE_ERR_NULL_POINTER;
@@ -852,7 +948,7 @@ int32_t relserve_pack_weight(const void* w, int32_t N, int32_t K, void* out, voi
 int32_t relserve_rope_append(const relserve_layer* L, const relserve_batch* b, void* qkv,
                              relserve_kv_cache cache, void* stream) {
     drop_stale_hip_error();
-    if (int32_t rc = check_pair(L, b)) return rc;
+    if (int32_t rc = check_pair(L, b, stream)) return rc;
     if (int32_t rc = check_cache(b, cache, false)) return rc;
     if (b->dev.T == 0) return RELSERVE_OK;
     if (!qkv) return RELSERVE_ERR_NULL_POINTER;
@@ -863,7 +959,7 @@ int32_t relserve_rope_append(const relserve_layer* L, const relserve_batch* b, v
 int32_t relserve_qkv_rope_append(const relserve_layer* L, const relserve_batch* b, const void* h, const void* w_qkv,
                                  void* q_out, relserve_kv_cache cache, void* stream) {
     drop_stale_hip_error();
-    if (int32_t rc = check_pair(L, b)) return rc;
+    if (int32_t rc = check_pair(L, b, stream)) return rc;
     if (int32_t rc = check_cache(b, cache)) return rc;
     if (b->dev.T == 0) return RELSERVE_OK;
     if (!h || !w_qkv || !q_out) return RELSERVE_ERR_NULL_POINTER;
@@ -876,7 +972,7 @@ int32_t relserve_attention(const relserve_layer* L, const relserve_batch* b, con
                            relserve_kv_cache cache, void* out, void* workspace, size_t workspace_bytes,
                            void* stream) {
     drop_stale_hip_error();
-    if (int32_t rc = check_pair(L, b)) return rc;
+    if (int32_t rc = check_pair(L, b, stream)) return rc;
     if (int32_t rc = check_cache(b, cache)) return rc;
     if (b->dev.T == 0) return RELSERVE_OK;
     if (!q || !out) return RELSERVE_ERR_NULL_POINTER;
@@ -896,7 +992,7 @@ namespace {
 // and `next` names the norm that reads this layer's output (its `out` is the workspace's too).
 int32_t layer_step(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt, const void* x, void* y,
                    relserve_kv_cache cache, void* workspace, size_t workspace_bytes, void* stream, bool normed, NextNorm* next) {
-    if (int32_t rc = check_pair(L, b)) return rc;
+    if (int32_t rc = check_pair(L, b, stream)) return rc;
     if (!wt) return RELSERVE_ERR_NULL_POINTER;
     if (int32_t rc = check_cache(b, cache)) return rc;
     const int32_t T = b->dev.T;
@@ -945,7 +1041,7 @@ int32_t layer_step(const relserve_layer* L, const relserve_batch* b, const relse
 
 int32_t layer_step_codes(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights_w8a8* wt, const void* x, void* y,
                          relserve_kv_cache cache, void* workspace, size_t workspace_bytes, void* stream, bool normed, NextNorm* next) {
-    if (int32_t rc = check_pair(L, b)) return rc;
+    if (int32_t rc = check_pair(L, b, stream)) return rc;
     if (!wt) return RELSERVE_ERR_NULL_POINTER;
     if (int32_t rc = check_cache(b, cache)) return rc;
     const relserve_layer_config& c = L->cfg;
@@ -1059,7 +1155,7 @@ int32_t relserve_static_scratch_bytes(size_t* out) {
 int32_t relserve_layer_step_static(const relserve_layer* L, const relserve_batch* b, const relserve_layer_weights* wt,
                                    const void* x, void* y, relserve_kv_cache cache, void* stream) {
     drop_stale_hip_error();
-    if (int32_t rc = check_pair(L, b)) return rc;
+    if (int32_t rc = check_pair(L, b, stream)) return rc;
     if (carve(*L, b->dev.T, nullptr).total > kStaticScratchBytes) return RELSERVE_ERR_TOO_LARGE;
     void* ws = nullptr;
     if (int32_t rc = static_scratch(&ws)) return rc;
@@ -1079,7 +1175,7 @@ namespace {
 int32_t model_step(const relserve_layer* L, const relserve_batch* b, const relserve_model* m,
                    const relserve_layer_weights_w8a8* q8, const int32_t* token_ids, void* logits, void* workspace,
                    size_t workspace_bytes, void* stream) {
-    if (int32_t rc = check_pair(L, b)) return rc;
+    if (int32_t rc = check_pair(L, b, stream)) return rc;
     if (!m) return RELSERVE_ERR_NULL_POINTER;
     if (m->n_layers < 0 || m->vocab <= 0 || m->vocab % 4) return RELSERVE_ERR_BAD_ARGUMENT;
     const int32_t T = b->dev.T, B = b->dev.num_reqs, H = L->cfg.hidden;

@@ -1,6 +1,7 @@
 // Internal declarations shared by the host boundary and the gfx950 kernels.
 #pragma once
 
+#include <atomic>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -95,6 +96,10 @@ struct relserve_batch {
     relserve::BatchDev dev;
     relserve::BatchDev dev_no_slots;      // the same batch without slots (see HostBatch); equals dev where dev has none
     void* blob = nullptr;  // the one device allocation
+    size_t blob_bytes = 0;
+    int device = 0;
+    hipEvent_t idle = nullptr;                     // of a blob that has been spare before
+    mutable std::atomic<bool> other_stream{false}; // work on it was submitted to another stream than the default one
     relserve_batch_info info;
 };
 

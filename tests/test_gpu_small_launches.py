@@ -113,3 +113,45 @@ def test_small_layer_step_has_the_tiled_kernels_bits(rs, shape, packed, kv8):
     assert torch.isfinite(outs[0][0]).all()
     for name, got, want in zip("ykv", *outs):
         assert torch.equal(got.view(torch.uint8), want.view(torch.uint8)), name
+
+
+@pytest.mark.parametrize("other_stream", [False, True], ids=["default", "other"])
+def test_batches_destroyed_behind_their_work(rs, other_stream):
+    """A destroyed batch's device allocation serves later ones: batches of different sizes prepared, stepped and destroyed one behind the
+    other, with nothing waited for, give what each gives alone; on another stream than the default one they do so too."""
+    shape = W.TINY_GQA
+    g = torch.Generator(device="cuda").manual_seed(3)
+    randn = lambda *s, std=0.05: torch.empty(*s, dtype=torch.float32, device="cuda").normal_(0, std, generator=g).bfloat16()
+    H, I = shape.hidden, shape.mlp_dim
+    wd = {"w_in_norm": randn(H, std=1.0), "w_qkv": randn(shape.qkv_dim, H), "w_o": randn(H, shape.q_dim), "w_post_norm": randn(H, std=1.0),
+          "w_gate_up": randn(2 * I, H), "w_down": randn(H, I)}
+    layer = rs.relserve_layer_create(shape)
+    cases = []
+    for T in (9, 64, 150, 333):
+        b = W.build_batch(shape, [T - 7] + [1] * 7, [T - 7] + [5 + T // 8] * 7, seed=T)
+        pool = (b.num_pages, shape.page_size, shape.n_kv_heads, shape.head_dim)
+        cases.append((b, randn(b.T, H, std=1.0), randn(*pool, std=1.0), randn(*pool, std=1.0)))
+    ws = torch.empty(max(rs.relserve_workspace_bytes(layer, c[0].T) for c in cases), dtype=torch.uint8, device="cuda")
+
+    def step(c, stream=None):
+        b, x, k, v = c
+        y = torch.empty_like(x)
+        pb = rs.relserve_batch_prepare(layer, b, stream=stream)
+        rs.relserve_layer_step(layer, pb, wd, x, y, k, v, ws, stream=stream)
+        pb.close()
+        return y
+
+    want = []
+    for c in cases:
+        want.append(step(c))
+        torch.cuda.synchronize()
+    s = torch.cuda.Stream() if other_stream else None
+    if s:
+        s.wait_stream(torch.cuda.current_stream())
+    got = []
+    for i in range(48):   # the keys and values a step appends are the same every time
+        c = cases[(i * 7 + i // 4) % 4]
+        got.append(((i * 7 + i // 4) % 4, step(c, s)))
+    torch.cuda.synchronize()
+    for i, y in got:
+        assert torch.equal(y, want[i]), i
