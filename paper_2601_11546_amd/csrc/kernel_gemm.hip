@@ -909,7 +909,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
 #pragma unroll
                     for (int d = i * LOADS / NM; d < (i + 1) * LOADS / NM; ++d) issue_one(d);
                 }
-                if (i >= NM / 2) {
+                if constexpr (F8) {   // the next hand-over waits for these: at once
+#pragma unroll
+                    for (int f = 2 * i; f < min(2 * i + 2, NF); ++f) load_frag_one(LB ^ 1, src, f);
+                } else if (i >= NM / 2) {
 #pragma unroll
                     for (int f = (i - NM / 2) * NF / (NM - NM / 2); f < (i + 1 - NM / 2) * NF / (NM - NM / 2); ++f)
                         load_frag_one(LB ^ 1, src, f);
