@@ -592,7 +592,9 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
 // q/k/v 109 -> 98.  Small tiles have four to six whole stages and gain nothing (128 x 128 gate/up 67.6 -> 72).
 constexpr int weight_stages(int bm, int bn, int ns) { return bm >= 192 && ns <= 3 && (ns * (bm + bn) + bn) * 128 <= 160 * 1024 ? ns + 1 : ns; }
 
-template <int BM, int BN, int EPI, int D, int BKD, int NS, bool WNT = false, bool F8 = false, int NSW = NS>
+// HALVES: the tail of a launch of 256-row tiles whose k ranges are two (launch_halves): each of its tiles is two of this kernel's, which
+// run over both ranges and add their sums as the finish kernel would.
+template <int BM, int BN, int EPI, int D, int BKD, int NS, bool WNT = false, bool F8 = false, int NSW = NS, bool HALVES = false>
 __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     constexpr bool SKEW = NSW > NS;
     static_assert(NSW == NS || NSW == NS + 1, "weight ring");
@@ -621,13 +623,15 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     const int n_tiles = p.tiles_m * p.tiles_n, tail_units = p.tail_tiles * p.tail_splits, dp_tiles = n_tiles - p.tail_tiles;
     int tile, split = 0, tail_idx = 0;
     bool tail = false;
-    if (EPI == EPI_SLAB) {
+    if (HALVES) {   // tiles_m counts 256-row tiles
+        tile = dp_tiles + remap_xcd(blockIdx.x, 2 * p.tail_tiles) / 2;
+    } else if (EPI == EPI_SLAB) {
         tile = remap_xcd(blockIdx.x % n_tiles, n_tiles);
         split = blockIdx.x / n_tiles;
     } else {
         // the tail units come first in the grid: their short k ranges and slab stores are over before the
         // last whole tiles finish
-        tail = (int)blockIdx.x < tail_units;
+        tail = !HALVES && (int)blockIdx.x < tail_units;
         if (tail) {
             const int u = remap_xcd(blockIdx.x, tail_units);   // runs of one split, consecutive tiles, per XCD
             split = u / p.tail_tiles;
@@ -640,6 +644,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     int tile_m, tile_n;
     tile_coords(tile, p.tiles_m, p.tiles_n, tile_m, tile_n);
     tile_n += p.tile_n0;
+    if (HALVES) {
+        tile_m = 2 * tile_m + remap_xcd(blockIdx.x, 2 * p.tail_tiles) % 2;
+        if (tile_m * BM >= p.T) return;   // the whole workgroup
+    }
 
     // ---- per-lane source offsets: wave load j of this wave fills LDS rows (NW j + wave) * RPI .. ;
     // lane l owns row l / CPR of those and slot l % CPR, which holds the row's chunk slot ^ swz(row).
@@ -706,7 +714,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     using frag_t = std::conditional_t<F8, i32x8_t, bf16x8_t>;
-    constexpr bool FIXED = BM * BN >= 6 * 4096 && !(EPI == EPI_SWIGLU && BM == 128);   // issue order: see below
+    constexpr bool FIXED = HALVES || (BM * BN >= 6 * 4096 && !(EPI == EPI_SWIGLU && BM == 128));   // issue order: see below
     constexpr bool QUARTERS = F8 && FIXED;
     frag_t wf[QUARTERS ? 1 : 2][TN], af[QUARTERS ? 1 : 2][TM];
     typedef const i32x4_t __attribute__((address_space(3))) * lds_chunk;
@@ -858,6 +866,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // (8-bit operands on 256 x 256 with eight waves, two per SIMD, hide the loads' latency without the skewed ring, but a wave's 64 x 128
     // then reads 96 KB of fragments per k step of 1024 cycles beside the 32 KB that land, all the LDS delivers; four waves read
     // 64 KB.  13B layer at T = 3875 on codes: eight waves 1257 us, with the skewed ring too; four 1231, skewed 1194.)
+    static_assert(!HALVES || (!F8 && NSW == NS), "halves of 16-bit tiles");
     static_assert(F8 || !FIXED || 2 * NF <= NM, "a fragment read behind every other MFMA");
     static_assert(TN % 2 == 0 && TM % 2 == 0, "halves");
     static_assert(!SKEW || FIXED, "the skewed ring's weights are issued in the fixed order only");
@@ -956,6 +965,18 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     const std::integral_constant<int, 0> even;
     const std::integral_constant<int, 1> odd;
     const std::true_type yes;
+    f32x4_t total[HALVES ? TN : 1][HALVES ? TM : 1];
+    // behind iteration kt (HALVES): at the end of the first k range, which lies in the steady state, its sums step aside
+    auto range_end = [&](int kt) __attribute__((always_inline)) {
+        if (!HALVES || kt + 1 != p.k_per_split) return;
+#pragma unroll
+        for (int tn = 0; tn < (HALVES ? TN : 0); ++tn)
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) {
+                total[tn][tm] = f32x4_t{0.f, 0.f, 0.f, 0.f} + acc[tn][tm];
+                acc[tn][tm] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            }
+    };
     int kt = 0;
     if (nk > 0) {
         iteration(0, even, false, false, NS < nk, NSW < nk);
@@ -967,7 +988,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             iteration(kt + 1, even, yes, yes, yes, yes);
         }
     } else {
-        for (; kt < nk - NSW; ++kt) iteration(kt, even, yes, yes, yes, yes);
+        for (; kt < nk - NSW; ++kt) {
+            iteration(kt, even, yes, yes, yes, yes);
+            range_end(kt);
+        }
     }
     while (kt < nk) {
         iteration(kt, std::integral_constant<int, F8 ? 1 : 0>{}, kt - 1 + NS < nk, kt - 1 + NSW < nk, kt + NS < nk, kt + NSW < nk);
@@ -977,6 +1001,12 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             iteration(kt, even, kt - 1 + NS < nk, kt - 1 + NSW < nk, kt + NS < nk, kt + NSW < nk);
             ++kt;
         }
+    }
+    if constexpr (HALVES) {
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = total[tn][tm] + acc[tn][tm];
     }
     if (EPI != EPI_SLAB && tail) {
         // Partial tile -> this split's slab (accumulator tile (tn, tm) of thread tid is the 16 bytes at
@@ -1577,6 +1607,32 @@ bool small_applies(const GemmArgs& p, int epi, int head_dim = 0) {
 // split, the first cols1 columns of tiles run as cand1 and the others as cand2 (cols1 = 0: all as cand).
 struct Plan { int cand, tail_tiles, splits, cols1 = 0, cand1 = 0, cand2 = 0; };
 
+// 256 x 256 tiles whose incomplete last round is cut into two k ranges: the whole tiles, then the tail as twice as many tiles of 128 rows,
+// each over both ranges with the sums of either in registers of its own (HALVES).  As many workgroups with as much to multiply, and
+// the finish kernel's sums bit for bit, without 256 KB of partial sums to memory and back per range, nor its launch.  (On codes the
+// second set of sums does not fit beside the fragments.)
+// 13B at T = 7963, tiles + finish / tiles + halves, us: q/k/v 902 + 23 / 840 + 71, W_o 338 + 30 / 271 + 77, gate/up 1513 + 17 / 1454 + 67,
+// W_down 765 + 21 / 611 + 175; W_down at T = 1409, all of it tail, 153 + 20 / 172.
+template <int EPI, int D>
+hipError_t launch_halves(const GemmArgs& base, hipStream_t s) {
+    GemmArgs p = base;
+    p.tail_splits = 0;   // the first launch ends with the whole tiles
+    const int whole = p.tiles_m * p.tiles_n - p.tail_tiles;
+    constexpr int NSW = weight_stages(256, 256, 2), smem = (2 * 256 + NSW * 256) * 128, half_smem = 3 * (128 + 256) * 128;
+    auto* const tiles = &gemm_dma_kernel<256, 256, EPI, D, 64, 2, false, false, NSW>;
+    auto* const halves = &gemm_dma_kernel<128, 256, EPI, D, 64, 3, false, false, 3, true>;
+    static std::once_flag once, once_halves;
+    static hipError_t st = hipSuccess, st_halves = hipSuccess;
+    if (hipError_t e = allow_smem_once(once, st, tiles, smem)) return e;
+    if (hipError_t e = allow_smem_once(once_halves, st_halves, halves, half_smem)) return e;
+    if (whole > 0) {
+        tiles<<<dim3(whole), dim3(64 * WGM * WGN), smem, s>>>(p);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    halves<<<dim3(2 * p.tail_tiles), dim3(64 * WGM * WGN), half_smem, s>>>(p);
+    return hipGetLastError();
+}
+
 template <int BM, int BN, int EPI, int D = 0>
 hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Plan{0, 0, 1}, int col0 = 0, int cols = 0) {
     GemmArgs p = base;
@@ -1605,6 +1661,9 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
         p.k_per_split = (nk + plan.splits - 1) / plan.splits;
         p.tail_splits = (nk + p.k_per_split - 1) / p.k_per_split;   // no empty split
         p.tail_tiles = std::min(plan.tail_tiles, tiles);
+        if constexpr (BM == 256 && BN == 256) {
+            if (p.tail_splits == 2 && nk >= 16 && !p.f8) return launch_halves<EPI, D>(p, s);
+        }
         p.tail_buf = p.accum;
         if ((int64_t)p.tail_tiles * p.tail_splits * BM * BN > kTailFloats)
             return hipErrorInvalidValue;   // a plan that does not fit the scratch: choose_cut never makes one
