@@ -217,7 +217,7 @@ __device__ __forceinline__ void load_code_scales(const GemmArgs& p, int tile_n, 
 // 16 tm + lane % 16 (of 32 tm_base on).  A workgroup has one wave per SIMD, so the epilogue lasts as long as its instructions take to
 // issue: there is no pass through the LDS, a row of tiles has one scalar base address and the distances of its accesses are constants,
 // and tiles that end inside the matrix (FULL) test nothing per access.  Every access covers runs of 64 bytes (see frag_row16); what a
-// row of tiles reads besides the sums is fetched one row ahead.  Cycles of a 256 x 256 tile of bf16 outputs: 13600 through the LDS, 8600
+// row of tiles reads besides the sums is fetched rows ahead.  Cycles of a 256 x 256 tile of bf16 outputs: 13600 through the LDS, 8600
 // here, which is what an XCD's 32 CUs, all writing at once, get through to memory (490 bytes a cycle).  8192 x 28672 x 5120 with the k
 // loop's fewer instructions (k_step) 1820 -> 1675 us; layer steps, with 16 x 16 products: 13B at T = 7963 4248 -> 3973, 70B at T = 2304
 // 3163 -> 2919.  (Workgroups that stay and load their next tile's first stages beside the epilogue gained nothing on this: the next
@@ -228,6 +228,10 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
     constexpr int FEAT = BN / WGN;
     static_assert(TN == FEAT / 16, "the wave's features");
     const int l16 = lane & 15, gq = lane >> 4;
+    // Rows whose operands are held: what a row waits for are its own loads, and, accesses completing in order, the stores issued before
+    // them; with all rows (W_o: 16 registers each) or three ahead the stores flow:
+    // W_o of the 13B layer at T = 7963 271 -> 262 us, at 1409 75.8 -> 71.5 (one row ahead before); the others as they were.
+    constexpr int R = EPI == EPI_RES_BF16_OUT_F32 ? TM : (TM < 4 ? TM : 4);
     auto quad = [&](int tn, int tm) __attribute__((always_inline)) {
         f32x4_t v = acc[tn][tm];
         asm volatile("" : "+v"(v));   // copied here: left to itself the compiler moves all sums to the other register file first, and spills
@@ -254,30 +258,32 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
     if constexpr (EPI == EPI_RES_BF16_OUT_F32) {
         const int n0 = tile_n * BN + wn * FEAT;
         auto ok = [&](int tn) { return FULL || n0 + 4 * gq + 16 * tn < p.N; };
-        uint2 res[2][TN];
+        uint2 res[R][TN];
         const bool add = p.residual != nullptr;   // no residual given: plain fp32 output
         auto fetch = [&](int tm) __attribute__((always_inline)) {
             const char* base = static_cast<const char*>(p.residual) + ((int64_t)min(t0 + 16 * tm, p.T - 1) * p.N + n0) * 2;
             const uint32_t off = row_off(tm, (int64_t)p.N * 2) + 8 * gq;
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
-                res[tm & 1][tn] = make_uint2(0, 0);
-                if (add && ok(tn)) res[tm & 1][tn] = *reinterpret_cast<const uint2*>(base + off + 32 * tn);
+                res[tm % R][tn] = make_uint2(0, 0);
+                if (add && ok(tn)) res[tm % R][tn] = *reinterpret_cast<const uint2*>(base + off + 32 * tn);
             }
         };
-        fetch(0);
+#pragma unroll
+        for (int tm = 0; tm < R - 1; ++tm) fetch(tm);
+        if constexpr (R == 1) fetch(0);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             if (!FULL && t0 + 16 * tm >= p.T) break;   // padding: nothing of this row of tiles (or the ones behind it) is stored
             __builtin_amdgcn_sched_barrier(0);   // row after row: every register is taken by sums still to be stored
-            if (tm + 1 < TM) fetch(tm + 1);
+            if (R > 1 && tm + R - 1 < TM) fetch(tm + R - 1);
             char* base = static_cast<char*>(p.out) + ((int64_t)(t0 + 16 * tm) * p.N + n0) * 4;
             const uint32_t off = row_off(tm, (int64_t)p.N * 4) + 16 * gq;
             if (!FULL && t0 + 16 * tm + l16 >= p.T) continue;
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
                 const float4 v = quad(tn, tm);
-                const uint2 r = res[tm & 1][tn];
+                const uint2 r = res[tm % R][tn];
                 if (ok(tn))
                     *reinterpret_cast<float4*>(base + off + 64 * tn) =
                         plus(v, sc[SC ? tn : 0], make_float4(bf16_lo(r.x), bf16_hi(r.x), bf16_lo(r.y), bf16_hi(r.y)));
@@ -286,24 +292,26 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
     } else if constexpr (EPI == EPI_QKV_ROPE) {
         constexpr int HEADS = FEAT / D, GH = D / 64, TH = D / 16;   // heads of the wave, 8-feature groups of half a head, tiles of a head
         const int head0 = (tile_n * BN + wn * FEAT) / D, kv_dim = p.n_kv * D;
-        float4 cs[2][GH][4];
-        int slot[2];
+        float4 cs[R][GH][4];
+        int slot[R];
         auto fetch = [&](int tm) __attribute__((always_inline)) {
             const int first = min(t0 + 16 * tm, p.T - 1);
-            slot[tm & 1] = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(p.tok_slot + first) + row_off(tm, 4));
+            slot[tm % R] = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(p.tok_slot + first) + row_off(tm, 4));
             const char* base = reinterpret_cast<const char*>(p.rope_cs + (int64_t)first * (D / 2));
             const uint32_t off = row_off(tm, D * 4) + 64 * gq;
 #pragma unroll
             for (int u = 0; u < GH; ++u)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) cs[tm & 1][u][c] = *reinterpret_cast<const float4*>(base + off + 256 * u + 16 * c);
+                for (int c = 0; c < 4; ++c) cs[tm % R][u][c] = *reinterpret_cast<const float4*>(base + off + 256 * u + 16 * c);
         };
-        fetch(0);
+#pragma unroll
+        for (int tm = 0; tm < R - 1; ++tm) fetch(tm);
+        if constexpr (R == 1) fetch(0);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             if (!FULL && t0 + 16 * tm >= p.T) break;
             __builtin_amdgcn_sched_barrier(0);
-            if (tm + 1 < TM) fetch(tm + 1);
+            if (R > 1 && tm + R - 1 < TM) fetch(tm + R - 1);
             if (!FULL && t0 + 16 * tm + l16 >= p.T) continue;
 #pragma unroll
             for (int hh = 0; hh < HEADS; ++hh) {
@@ -326,12 +334,12 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
 #pragma unroll
                         for (int h = 0; h < 2; ++h) {
                             const float4 a = lo[u][h], b = hi[u][h];
-                            rotate4(a, b, cs[tm & 1][u][2 * h], cs[tm & 1][u][2 * h + 1], lo[u][h], hi[u][h]);
+                            rotate4(a, b, cs[tm % R][u][2 * h], cs[tm % R][u][2 * h + 1], lo[u][h], hi[u][h]);
                         }
                 }
                 if (p.kv_fp8 && !is_q) {   // quantised cache: one byte per element, quantised from fp32
                     uint8_t* dst = reinterpret_cast<uint8_t*>(is_k ? p.k_pages : p.v_pages) + (head - p.n_q - (is_k ? 0 : p.n_kv)) * D +
-                                   (int64_t)slot[tm & 1] * kv_dim + 8 * gq;
+                                   (int64_t)slot[tm % R] * kv_dim + 8 * gq;
                     const float s = is_k ? p.k_inv : p.v_inv;
 #pragma unroll
                     for (int u = 0; u < GH; ++u) {
@@ -340,7 +348,7 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
                     }
                 } else {
                     uint16_t* dst = is_q ? static_cast<uint16_t*>(p.out) + (int64_t)(t0 + 16 * tm + l16) * (p.n_q * D) + head * D
-                                         : (is_k ? p.k_pages : p.v_pages) + (head - p.n_q - (is_k ? 0 : p.n_kv)) * D + (int64_t)slot[tm & 1] * kv_dim;
+                                         : (is_k ? p.k_pages : p.v_pages) + (head - p.n_q - (is_k ? 0 : p.n_kv)) * D + (int64_t)slot[tm % R] * kv_dim;
                     dst += 8 * gq;
 #pragma unroll
                     for (int u = 0; u < GH; ++u) {
@@ -359,7 +367,7 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
         auto ok = [&](int u, int h) { return FULL || n0 + 8 * gq + 32 * u + 4 * h < cols; };
         const bool codes = SC && SWI && p.out_f8;   // the down projection reads codes (n_half is a multiple of 8)
         const int esize = codes ? 1 : 2;
-        float4 res[2][EPI == EPI_RES_F32_OUT_BF16 ? GROUPS : 1][2];
+        float4 res[R][EPI == EPI_RES_F32_OUT_BF16 ? GROUPS : 1][2];
         auto fetch = [&](int tm) __attribute__((always_inline)) {
             if constexpr (EPI == EPI_RES_F32_OUT_BF16) {
                 const char* base = static_cast<const char*>(p.residual) + ((int64_t)min(t0 + 16 * tm, p.T - 1) * p.N + n0) * 4;
@@ -368,15 +376,17 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
                 for (int u = 0; u < GROUPS; ++u)
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
-                        if (ok(u, h)) res[tm & 1][u][h] = *reinterpret_cast<const float4*>(base + off + 128 * u + 16 * h);
+                        if (ok(u, h)) res[tm % R][u][h] = *reinterpret_cast<const float4*>(base + off + 128 * u + 16 * h);
             }
         };
-        fetch(0);
+#pragma unroll
+        for (int tm = 0; tm < R - 1; ++tm) fetch(tm);
+        if constexpr (R == 1) fetch(0);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             if (!FULL && t0 + 16 * tm >= p.T) break;
             __builtin_amdgcn_sched_barrier(0);
-            if (tm + 1 < TM) fetch(tm + 1);
+            if (R > 1 && tm + R - 1 < TM) fetch(tm + R - 1);
             char* base = static_cast<char*>(p.out) + ((int64_t)(t0 + 16 * tm) * cols + n0) * esize;
             const uint32_t off = row_off(tm, (int64_t)cols * esize) + 8 * gq * esize;
             if (!FULL && t0 + 16 * tm + l16 >= p.T) continue;
@@ -387,7 +397,7 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
                 for (int h = 0; h < 2; ++h) {
                     v[h] = quad(2 * u + h, tm);
                     if constexpr (EPI == EPI_RES_F32_OUT_BF16)
-                        v[h] = plus(v[h], sc[SC ? 2 * u + h : 0], res[tm & 1][u][h]);
+                        v[h] = plus(v[h], sc[SC ? 2 * u + h : 0], res[tm % R][u][h]);
                     else if constexpr (SC)
                         v[h] = scaled(v[h], sc[2 * u + h]);
                     if constexpr (SWI) {
