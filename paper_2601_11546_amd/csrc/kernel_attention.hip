@@ -174,13 +174,14 @@ template <int D>
 __device__ __forceinline__ int vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
 
 // 64 lanes x 16 bytes from per-lane global addresses to 1 KB of LDS starting at lds_addr.
+// (s_nop: between the scalar write of m0 and a load that reads it the hardware wants one instruction, and inline assembly gets none by itself.)
 __device__ __forceinline__ void dma16_ptr(const void* gptr, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_addr) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_addr) : "memory");
 }
 // The same with the non-temporal hint, for keys and values that one wave reads once (decode rows): a streaming
 // read of 256-byte head rows reaches 7.2 TB/s with it against 6.4 TB/s without.
 __device__ __forceinline__ void dma16_ptr_nt(const void* gptr, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gptr), "s"(lds_addr) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gptr), "s"(lds_addr) : "memory");
 }
 
 typedef short short4_t __attribute__((ext_vector_type(4)));

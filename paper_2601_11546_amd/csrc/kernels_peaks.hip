@@ -8,7 +8,7 @@ namespace relserve {
 
 namespace {
 
-// 16 independent accumulators per wave (the register blocking of the 256 x 256 GEMM tile), one wave per SIMD.
+// 16 independent accumulators per wave (256 registers, as many as the sums of the 256 x 256 GEMM tile), one wave per SIMD.
 __global__ void __launch_bounds__(256) mfma_issue_kernel(float* sink, int iters, uint32_t seed) {
     f32x16_t acc[16];
 #pragma unroll
@@ -103,9 +103,9 @@ __global__ void __launch_bounds__(256) stream_lds_kernel(const u32x4_t* src, int
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             if (NT)
-                asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(p + j * 64), "s"(lds0 + j * 1024) : "memory");
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(p + j * 64), "s"(lds0 + j * 1024) : "memory");
             else
-                asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p + j * 64), "s"(lds0 + j * 1024) : "memory");
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p + j * 64), "s"(lds0 + j * 1024) : "memory");
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
