@@ -8,14 +8,14 @@
 //
 // Workgroup = a grid of 2 x 2 waves over a BM (tokens) x BN (features) tile, BK = 64.
 // Main kernel (gemm_dma_kernel, K % 64 == 0): tiles go global -> LDS directly, XOR-swizzled 16-byte
-// chunks, two or three stages, one barrier per k iteration, every k step issued in a fixed order that
+// chunks, two to six stages, one barrier per k iteration, every k step issued in a fixed order that
 // slots the refill loads and the next fragment reads between the MFMAs.  Fallback kernel
 // (gemm_bf16_kernel): global -> registers -> LDS with zero-filled tails for any K % 8 == 0.
 // Workgroup ids are remapped so that each of the 8 XCDs (own L2 each) walks a contiguous run of
 // tiles, inside it token tiles fastest within panels of GROUP_M token tiles.
-// Launch plans: tile shape by a cost model; the incomplete last round of tiles may split k over
+// Launch plans: tile shape by a cost model, or two shapes side by side; the incomplete last round of tiles may split k over
 // workgroups; batches of at most 256 tokens, and narrow outputs at a few hundred, split k everywhere.
-// Every split writes partial tiles to fp32 slabs that a second kernel sums and finishes.
+// Every split but the two ranges of launch_halves writes partial tiles to fp32 slabs that a second kernel sums and finishes.
 #include <algorithm>
 #include <atomic>
 #include <mutex>
@@ -587,12 +587,11 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
         asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds_addr), "i"(at) : "memory", "scc");
 }
 
-// BKD = k extent of one LDS stage (64 or 32), NS = stages in the ring (NS - 1 are in flight).
+// BKD = k extent of one LDS stage, NS = stages in the ring (NS - 1 are in flight).
 // WNT: the weights are loaded with the non-temporal hint (launches in which no other workgroup reads them again).
 // F8: both operands hold 8-bit codes.  Nothing changes in how bytes travel (K counts pairs of codes, a stage row is
-// still 128 bytes); a k step covers 32 bytes of every row instead of 16, as one 32x32x64 MFMA whose operand is the
-// two adjacent 16-byte chunks (2 ks' + g) * 2, + 1 of the row for k half g (both operands alike, so which codes
-// meet which is fixed), and the epilogue applies the scales.
+// still 128 bytes); a stage is one k step of 16 x 16 x 128 MFMAs, whose operand is the two adjacent 16-byte chunks
+// 2 g, 2 g + 1 of the row for k quarter g (both operands alike, so which codes meet which is fixed), and the epilogue applies the scales.
 // NSW = stages of the weights' ring: NS, or NS + 1 ("skewed").  Loads of one wave complete in order, so a hand-over of the
 // skewed ring issues the activations of stage kt + NS first and the weights of stage kt + NS + 1 behind them: what the next
 // hand-over waits for are the activations, and the weights just issued stay in flight for another iteration.
@@ -662,13 +661,14 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // ---- per-lane source offsets: wave load j of this wave fills LDS rows (NW j + wave) * RPI .. ;
     // lane l owns row l / CPR of those and slot l % CPR, which holds the row's chunk slot ^ swz(row).
     // The LDS has 64 four-byte banks and serves a 16-byte-per-lane read 16 lanes at a time, so the
-    // 16 consecutive rows those lanes read must cover all 64 banks once: swz = (row >> 1) & 7 for
-    // 128-byte rows (row parity picks the bank half), (row >> 2) & 3 for 64-byte rows.
+    // 16 consecutive rows those lanes read must cover all 64 banks once: swz = (row >> 1) & 7 (row
+    // parity picks the bank half).
     // Rows past the end of a matrix re-read its last row: their products are never stored.
     const uint32_t lrow = lane / CPR;
     const uint32_t row_lo = (uint32_t)(wave * RPI) + lrow;   // LDS row modulo NW * RPI (>= 32): all the swizzle needs
-    const uint32_t chunk = (lane % CPR) ^ (BKD == 64 ? ((row_lo >> 1) & 7) : ((row_lo >> 2) & 3));
-    // (16 x 16 results of permuted features read rows 0-3, 8-11, 16-19 and 24-27 of 32, four further on, or so)
+    const uint32_t chunk = (lane % CPR) ^ ((row_lo >> 1) & 7);
+    // (the weights of permuted results, paired16, are read in rows 0-3, 8-11, 16-19 and 24-27 of 32, or four further on: a swizzle of
+    // their own gives those sixteen the same)
     constexpr bool PERM = paired16(EPI);
     auto perm_swz = [](int row) { return ((row >> 1) & 1) | ((row >> 2) & 6); };
     const uint32_t w_chunk = PERM ? (lane % CPR) ^ perm_swz(row_lo) : chunk;
@@ -698,7 +698,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
 
     // ---- LDS -> MFMA operands: this lane's address of the first fragment of a k step inside stage 0; the other fragments lie at
     // constant distances, which the read instruction holds.
-    const int swz = BKD == 64 ? ((fr >> 1) & 7) : ((fr >> 2) & 3);
+    const int swz = (fr >> 1) & 7;
     constexpr int w_wave = EPI == EPI_SWIGLU ? BN / (2 * WGN) : BN / WGN;   // first row of the wave's features (SwiGLU: in either half)
     uint32_t a_lane[KSTEPS], w_lane[KSTEPS];
 #pragma unroll
@@ -791,7 +791,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     };
     // A flag that is either a run-time bool or std::true_type: the steady-state iterations pass the latter, so their
     // loads sit in straight-line code (a branch and its scalar set-up around each load cost more issue slots than
-    // the load itself, and a wave has seven slots between two MFMAs).
+    // the load itself, and a wave has three slots between two MFMAs).
     auto on = [](auto flag) {
         if constexpr (std::is_same_v<decltype(flag), std::true_type>) return true;
         else return flag;
@@ -801,9 +801,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     // step's fragment reads that falls between MFMA i and i + 1.  A 16 x 16 MFMA lasts 16 cycles, in which a wave issues three
     // other instructions: a read or a load goes behind each, never both, a read is one instruction (its address a sum made once a
     // step) and a load two: 93 instructions beside the 128 MFMAs of an iteration, where 136 left 2450 cycles for 2048 of MFMAs, now 2280.  A CU's address unit takes one
-    // 1 KB load per ~16 cycles and a 32 x 32 MFMA lasts 32, so the refill loads of a stage (LOADS per wave,
-    // four waves) are spread over SPREAD quarters of the iteration (a k step of 32 x 32 MFMAs is one, of
-    // 16 x 16 two); issued back to back they would hold up the MFMAs behind them.  The MFMAs sit on ONE control path on purpose: at a join the compiler would make
+    // 1 KB load per ~16 cycles, the time of one MFMA, so the refill loads of a stage (LOADS per wave,
+    // four waves) are spread over SPREAD quarters of the iteration (a 16-bit k step is two); issued back
+    // to back they would hold up the MFMAs behind them.  The MFMAs sit on ONE control path on purpose: at a join the compiler would make
     // them wait for the newest reads.
     constexpr int STEPS = 2, NMS = NM * KSTEPS / STEPS;                        // steps of an iteration, NMS products each
     constexpr int PARTS = 4, SPREAD = 3, SUB = PARTS / STEPS, NMP = NMS / SUB;   // parts of an iteration; the last before the next hand-over stays free: landing time
