@@ -1622,7 +1622,9 @@ struct Plan { int cand, tail_tiles, splits, cols1 = 0, cand1 = 0, cand2 = 0; };
 // the finish kernel's sums bit for bit, without 256 KB of partial sums to memory and back per range, nor its launch.  (On codes the
 // second set of sums does not fit beside the fragments.)
 // 13B at T = 7963, tiles + finish / tiles + halves, us: q/k/v 902 + 23 / 840 + 71, W_o 338 + 30 / 271 + 77, gate/up 1513 + 17 / 1454 + 67,
-// W_down 765 + 21 / 611 + 175; W_down at T = 1409, all of it tail, 153 + 20 / 172.
+// W_down 765 + 21 / 611 + 175; W_down at T = 1409, all of it tail, 153 + 20 / 172.  Tiles of 128 rows load more per product, which grows
+// with k while the finish does not: even at 13824, and W_down of the 32B shape (k of 27648) at T = 1246 349 in halves, 320 with the finish.
+constexpr int kHalvesMaxK = 16384;
 template <int EPI, int D>
 hipError_t launch_halves(const GemmArgs& base, hipStream_t s) {
     GemmArgs p = base;
@@ -1672,7 +1674,7 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
         p.tail_splits = (nk + p.k_per_split - 1) / p.k_per_split;   // no empty split
         p.tail_tiles = std::min(plan.tail_tiles, tiles);
         if constexpr (BM == 256 && BN == 256) {
-            if (p.tail_splits == 2 && nk >= 16 && !p.f8) return launch_halves<EPI, D>(p, s);
+            if (p.tail_splits == 2 && nk >= 16 && p.K <= kHalvesMaxK && !p.f8) return launch_halves<EPI, D>(p, s);
         }
         p.tail_buf = p.accum;
         if ((int64_t)p.tail_tiles * p.tail_splits * BM * BN > kTailFloats)
