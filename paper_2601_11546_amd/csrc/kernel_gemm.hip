@@ -4,7 +4,7 @@
 // Both operands are K-contiguous, which is the natural MFMA operand layout: a lane's 8
 // consecutive k values are one 16-byte load.  The weight rows take the MFMA row index and
 // the tokens the column index, so that an accumulator quad holds 4 consecutive output
-// features of one token (one 8/16-byte store).
+// features of one token (one 8/16-byte store; where rows of fp32 are written it is the other way round, see frag_row16).
 //
 // Workgroup = a grid of 2 x 2 waves over a BM (tokens) x BN (features) tile, BK = 64.
 // Main kernel (gemm_dma_kernel, K % 64 == 0): tiles go global -> LDS directly, XOR-swizzled 16-byte
@@ -188,35 +188,57 @@ __device__ __forceinline__ void store_unit(const GemmArgs& p, int t, int n_lo, i
 
 constexpr int WGM = 2, WGN = 2;   // grid of waves over a tile
 
-// Which feature of a wave's range MFMA row i (= 4 (lane / 16) + r of the result) of weight fragment tn stands for, and of the
-// results.  fp32 rows leave as they come: a lane has 4 consecutive features, the four lanes of a token 64 consecutive bytes.
-// Where bf16 or codes are written (PAIRED16) two fragments share 32 features so that a lane has 8 consecutive ones: 64 bytes again.
-// The permutation costs nothing: it is which rows of the weights in the LDS a lane reads.
-constexpr bool paired16(int epi) { return epi != EPI_RES_BF16_OUT_F32 && epi != EPI_SLAB; }
+// Which features of a wave's range a weight fragment holds, and how results lie in the lanes.
+// Where bf16 or codes are written the weights are the first operand of the products: a lane's results are those of one token, and two
+// fragments share 32 features so that it has 8 consecutive ones, the four lanes of a token 64 consecutive bytes.
+// Where rows of fp32 are written (ROWS32: the slabs, W_o) the tokens are the first operand (the same products, the same bits): register r
+// of a lane is token 4 (lane / 16) + r, and four fragments share 64 features, fragment c the features 4 i + c, so that a lane has four
+// consecutive ones and the 16 lanes of a token 256 consecutive bytes, lane behind lane; the residual's bf16 are 128 such bytes.  An
+// access in which neighbouring lanes hold pieces of different rows is a request to the L2 for every piece of 16 bytes: with the weights
+// first here too W_o of 8192 x 2048 codes took 57.2 us at T = 2100, now 48.5, of 5120 x 2560 16-bit values 54.8, now 51.3, and a step of a
+// quarter of the 70B layer, whose projections all write slabs, at T = 256 210 us, now 202 (on codes 171, 164).
+// Neither permutation costs anything: it is which rows of the weights in the LDS a lane reads, and which of eight rows a load puts where.
+constexpr bool rows32(int epi) { return epi == EPI_RES_BF16_OUT_F32 || epi == EPI_SLAB; }
+// row of the weights in the LDS that lane i of a fragment reads, beside the fragment's first one
 template <int EPI>
-__device__ __forceinline__ int frag_row16(int i) { return paired16(EPI) ? 8 * (i >> 2) + (i & 3) : i; }
+__device__ __forceinline__ int frag_row16(int i) { return rows32(EPI) ? 8 * (i >> 1) + (i & 1) : 8 * (i >> 2) + (i & 3); }
 template <int EPI>
-constexpr int frag_base16(int tn) { return paired16(EPI) ? 32 * (tn >> 1) + 4 * (tn & 1) : 16 * tn; }
+constexpr int frag_base16(int tn) { return rows32(EPI) ? 64 * (tn >> 2) + 2 * (tn & 3) : 32 * (tn >> 1) + 4 * (tn & 1); }
+// feature that LDS row `row` holds (ROWS32: 8 a + 2 c + b holds 8 a + 4 b + c, rows of both parities for the 16 lanes of a read)
+template <int EPI>
+__device__ __forceinline__ int lds_feature(int row) { return rows32(EPI) ? (row & ~7) + ((row >> 1) & 3) + 4 * (row & 1) : row; }
+// quads of factors a wave's sums of products of codes need (one for the features a lane writes together)
+constexpr int scale_quads(int epi, int tn) { return rows32(epi) ? tn / 4 : tn; }
 
-// The factors a_scale * w_scale[feature] of a wave's sums of products of codes, fragment by fragment; loaded ahead of the k loop.
-template <int BN, int EPI, int D, int TN>
-__device__ __forceinline__ void load_code_scales(const GemmArgs& p, int tile_n, int wn, int lane, float4 (&sc)[TN]) {
+// The weights' factors w_scale[feature] of a wave's sums of products of codes; loaded ahead of the k loop.
+template <int BN, int EPI, int D, int NQ>
+__device__ __forceinline__ void load_code_scales(const GemmArgs& p, int tile_n, int wn, int lane, float4 (&sc)[NQ]) {
     constexpr bool SWI = EPI == EPI_SWIGLU;
-    constexpr int FEAT = BN / WGN;
-    const int gq = lane >> 4, cols = SWI ? p.n_half : p.N;
-    const int n0 = (SWI ? tile_n * (BN / 2) + wn * (FEAT / 2) : tile_n * BN + wn * FEAT) + (paired16(EPI) ? 8 : 4) * gq;
+    constexpr int FEAT = BN / WGN, TN = FEAT / 16;
+    static_assert(NQ == scale_quads(EPI, TN), "one quad for the features written together");
+    if constexpr (rows32(EPI)) {
+        const int n0 = tile_n * BN + wn * FEAT + 4 * (lane & 15);
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn) {
+        for (int u = 0; u < NQ; ++u) {
+            sc[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (n0 + 64 * u < p.N) sc[u] = *reinterpret_cast<const float4*>(p.w_scale + n0 + 64 * u);
+        }
+        return;
+    }
+    const int gq = lane >> 4, cols = SWI ? p.n_half : p.N;
+    const int n0 = (SWI ? tile_n * (BN / 2) + wn * (FEAT / 2) : tile_n * BN + wn * FEAT) + 8 * gq;
+#pragma unroll
+    for (int tn = 0; tn < NQ; ++tn) {
         const int n = n0 + frag_base16<EPI>(SWI ? tn % (TN / 2) : tn);
         sc[tn] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (n < cols) sc[tn] = *reinterpret_cast<const float4*>(p.w_scale + (SWI && tn >= TN / 2 ? p.n_half : 0) + n);
     }
 }
 
-// Epilogue of the 16 x 16 kernels, straight from the accumulators: acc[tn][tm] holds fragment tn's features of token
-// 16 tm + lane % 16 (of 32 tm_base on).  A workgroup has one wave per SIMD, so the epilogue lasts as long as its instructions take to
+// Epilogue of the 16 x 16 kernels, straight from the accumulators: acc[tn][tm] holds fragment tn's features of tokens
+// 16 tm .. + 15 (of 32 tm_base on; see frag_row16).  A workgroup has one wave per SIMD, so the epilogue lasts as long as its instructions take to
 // issue: there is no pass through the LDS, a row of tiles has one scalar base address and the distances of its accesses are constants,
-// and tiles that end inside the matrix (FULL) test nothing per access.  Every access covers runs of 64 bytes (see frag_row16); what a
+// and tiles that end inside the matrix (FULL) test nothing per access.  Every access covers runs of 64 bytes (256 of fp32); what a
 // row of tiles reads besides the sums is fetched rows ahead.  Cycles of a 256 x 256 tile of bf16 outputs: 13600 through the LDS, 8600
 // here, which is what an XCD's 32 CUs, all writing at once, get through to memory (490 bytes a cycle).  8192 x 28672 x 5120 with the k
 // loop's fewer instructions (k_step) 1820 -> 1675 us; layer steps, with 16 x 16 products: 13B at T = 7963 4248 -> 3973, 70B at T = 2304
@@ -224,14 +246,15 @@ __device__ __forceinline__ void load_code_scales(const GemmArgs& p, int tile_n, 
 // tile's first waits then include the stores.)
 template <int BM, int BN, int EPI, int D, bool SC, bool FULL, int TN, int TM>
 __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM], const GemmArgs& p, int tile_n, int t0, int wn, int lane,
-                                                     const float4 (&sc)[SC ? TN : 1]) {
+                                                     const float4 (&sc)[SC ? scale_quads(EPI, TN) : 1]) {
     constexpr int FEAT = BN / WGN;
     static_assert(TN == FEAT / 16, "the wave's features");
     const int l16 = lane & 15, gq = lane >> 4;
     // Rows whose operands are held: what a row waits for are its own loads, and, accesses completing in order, the stores issued before
-    // them; with all rows (W_o: 16 registers each) or three ahead the stores flow:
-    // W_o of the 13B layer at T = 7963 271 -> 262 us, at 1409 75.8 -> 71.5 (one row ahead before); the others as they were.
-    constexpr int R = EPI == EPI_RES_BF16_OUT_F32 ? TM : (TM < 4 ? TM : 4);
+    // them; with three ahead, of W_o half of a tile's rows (16 registers each), the stores flow.  W_o with all rows loaded first / half /
+    // one row ahead: 192 rows, 8192 x 2048 codes at T = 1150 27.6 / 25.9 / 27.0 us, 5120 x 2560 at 1900 30.3 / 28.1 / 29.6; 128 rows, at
+    // 1150 23.0 / 22.2 / 22.4; 256 rows 0 - 1 % apart.
+    constexpr int R = EPI == EPI_RES_BF16_OUT_F32 ? TM / 2 + 1 : (TM < 4 ? TM : 4);
     auto quad = [&](int tn, int tm) __attribute__((always_inline)) {
         f32x4_t v = acc[tn][tm];
         asm volatile("" : "+v"(v));   // copied here: left to itself the compiler moves all sums to the other register file first, and spills
@@ -255,38 +278,54 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
     auto row_off = [&](int tm, int64_t pitch) __attribute__((always_inline)) -> uint32_t {   // bytes from row t0 + 16 tm
         return (uint32_t)(FULL ? l16 : min(l16, max(p.T - 1 - t0 - 16 * tm, 0))) * (uint32_t)pitch;
     };
-    if constexpr (EPI == EPI_RES_BF16_OUT_F32) {
+    if constexpr (rows32(EPI)) {
+        constexpr int U = TN / 4;   // groups of 64 features
+        constexpr bool RES = EPI == EPI_RES_BF16_OUT_F32;
         const int n0 = tile_n * BN + wn * FEAT;
-        auto ok = [&](int tn) { return FULL || n0 + 4 * gq + 16 * tn < p.N; };
-        uint2 res[R][TN];
-        const bool add = p.residual != nullptr;   // no residual given: plain fp32 output
+        auto ok = [&](int u) { return FULL || n0 + 4 * l16 + 64 * u < p.N; };
+        const bool add = RES && p.residual != nullptr;   // no residual given: plain fp32 output
+        uint2 res[RES ? R : 1][4][U];
         auto fetch = [&](int tm) __attribute__((always_inline)) {
-            const char* base = static_cast<const char*>(p.residual) + ((int64_t)min(t0 + 16 * tm, p.T - 1) * p.N + n0) * 2;
-            const uint32_t off = row_off(tm, (int64_t)p.N * 2) + 8 * gq;
+            if constexpr (RES) {
+                const int first = min(t0 + 16 * tm, p.T - 1);
+                const char* base = static_cast<const char*>(p.residual) + ((int64_t)first * p.N + n0) * 2;
 #pragma unroll
-            for (int tn = 0; tn < TN; ++tn) {
-                res[tm % R][tn] = make_uint2(0, 0);
-                if (add && ok(tn)) res[tm % R][tn] = *reinterpret_cast<const uint2*>(base + off + 32 * tn);
+                for (int r = 0; r < 4; ++r) {
+                    const uint32_t off = (uint32_t)(FULL ? 4 * gq + r : min(4 * gq + r, p.T - 1 - first)) * (uint32_t)p.N * 2 + 8 * l16;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        res[tm % R][r][u] = make_uint2(0, 0);
+                        if (add && ok(u)) res[tm % R][r][u] = *reinterpret_cast<const uint2*>(base + off + 128 * u);
+                    }
+                }
             }
         };
 #pragma unroll
         for (int tm = 0; tm < R - 1; ++tm) fetch(tm);
         if constexpr (R == 1) fetch(0);
+        const uint32_t off = (uint32_t)(4 * gq) * (uint32_t)p.N * 4 + 16 * l16;
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             if (!FULL && t0 + 16 * tm >= p.T) break;   // padding: nothing of this row of tiles (or the ones behind it) is stored
             __builtin_amdgcn_sched_barrier(0);   // row after row: every register is taken by sums still to be stored
             if (R > 1 && tm + R - 1 < TM) fetch(tm + R - 1);
             char* base = static_cast<char*>(p.out) + ((int64_t)(t0 + 16 * tm) * p.N + n0) * 4;
-            const uint32_t off = row_off(tm, (int64_t)p.N * 4) + 16 * gq;
-            if (!FULL && t0 + 16 * tm + l16 >= p.T) continue;
+            float4 q[TN];   // (whole quads: with their elements copied one by one the compiler again moves all sums first)
 #pragma unroll
-            for (int tn = 0; tn < TN; ++tn) {
-                const float4 v = quad(tn, tm);
-                const uint2 r = res[tm % R][tn];
-                if (ok(tn))
-                    *reinterpret_cast<float4*>(base + off + 64 * tn) =
-                        plus(v, sc[SC ? tn : 0], make_float4(bf16_lo(r.x), bf16_hi(r.x), bf16_lo(r.y), bf16_hi(r.y)));
+            for (int tn = 0; tn < TN; ++tn) q[tn] = quad(tn, tm);
+            auto elem = [](const float4& v, int r) { return r == 0 ? v.x : r == 1 ? v.y : r == 2 ? v.z : v.w; };
+#pragma unroll
+            for (int r = 0; r < 4; ++r, base += (int64_t)p.N * 4) {
+                if (!FULL && t0 + 16 * tm + 4 * gq + r >= p.T) continue;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float4 o = make_float4(elem(q[4 * u], r), elem(q[4 * u + 1], r), elem(q[4 * u + 2], r), elem(q[4 * u + 3], r));
+                    if constexpr (RES) {
+                        const uint2 x = res[tm % R][r][u];
+                        o = plus(o, sc[SC ? u : 0], make_float4(bf16_lo(x.x), bf16_hi(x.x), bf16_lo(x.y), bf16_hi(x.y)));
+                    }
+                    if (ok(u)) *reinterpret_cast<float4*>(base + off + 256 * u) = o;
+                }
             }
         }
     } else if constexpr (EPI == EPI_QKV_ROPE) {
@@ -424,14 +463,15 @@ __device__ __forceinline__ void gemm_epilogue16_rows(const f32x4_t (&acc)[TN][TM
 
 template <int BM, int BN, int EPI, int D, bool SC, int TN, int TM>
 __device__ __forceinline__ void gemm_epilogue16(const f32x4_t (&acc)[TN][TM], const GemmArgs& p, int tile_m, int tile_n, int wm, int wn,
-                                                int lane, int tm_base, const float4 (&w_scales)[SC ? TN : 1] = {}) {
-    float4 sc[SC ? TN : 1];
+                                                int lane, int tm_base, const float4 (&w_scales)[SC ? scale_quads(EPI, TN) : 1] = {}) {
+    constexpr int NQ = SC ? scale_quads(EPI, TN) : 1;
+    float4 sc[NQ];
 #pragma unroll
-    for (int i = 0; i < (SC ? TN : 0); ++i)
+    for (int i = 0; i < (SC ? NQ : 0); ++i)
         sc[i] = make_float4(w_scales[i].x * p.a_scale, w_scales[i].y * p.a_scale, w_scales[i].z * p.a_scale, w_scales[i].w * p.a_scale);
     const int t0 = tile_m * BM + 32 * tm_base + wm * (BM / WGM);
     const int cols = EPI == EPI_SWIGLU ? p.n_half : p.N, last = (tile_n + 1) * (EPI == EPI_SWIGLU ? BN / 2 : BN);
-    const bool aligned = EPI == EPI_QKV_ROPE || EPI == EPI_RES_BF16_OUT_F32 || (cols % 8 == 0 && reinterpret_cast<uintptr_t>(p.out) % 16 == 0);
+    const bool aligned = EPI == EPI_QKV_ROPE || rows32(EPI) || (cols % 8 == 0 && reinterpret_cast<uintptr_t>(p.out) % 16 == 0);
     if (t0 + 16 * TM <= p.T && last <= cols && aligned)
         gemm_epilogue16_rows<BM, BN, EPI, D, SC, true>(acc, p, tile_n, t0, wn, lane, sc);
     else if (t0 < p.T)
@@ -476,12 +516,14 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs p) {
             ok = gi < p.n_half;
             n = lr < HALF ? gi : p.n_half + gi;
         } else {
-            n = tile_n * BN + lr;
+            n = tile_n * BN + lds_feature<EPI>(lr);
             ok = n < p.N;
         }
         w_off[i] = ok ? n * K + c8 : -1;
     }
-    const int st_off = lrow * 128 + (((tid & 7) ^ (lrow & 7)) << 4);  // swizzled LDS store offset
+    // swizzled LDS store offsets: by row & 7, the weights of ROWS32 by the row's group of 8 (what the 16 lanes of a read differ in)
+    auto w_swz = [](int row) { return rows32(EPI) ? (row >> 3) & 7 : row & 7; };
+    const int st_off = lrow * 128 + (((tid & 7) ^ (lrow & 7)) << 4);
 
     uint4 a_reg[A_IT], w_reg[W_IT];
     auto load_global = [&](int k0) {
@@ -501,10 +543,13 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs p) {
 #pragma unroll
         for (int i = 0; i < A_IT; ++i) *reinterpret_cast<uint4*>(sa + i * 32 * 128 + st_off) = a_reg[i];
 #pragma unroll
-        for (int i = 0; i < W_IT; ++i) *reinterpret_cast<uint4*>(sw + i * 32 * 128 + st_off) = w_reg[i];
+        for (int i = 0; i < W_IT; ++i) {
+            const int lr = lrow + 32 * i;
+            *reinterpret_cast<uint4*>(sw + lr * 128 + (((tid & 7) ^ w_swz(lr)) << 4)) = w_reg[i];
+        }
     };
 
-    // ---- LDS -> MFMA operands: rows l16 of the wave's tokens, frag_row16 of its features; both swizzled by row & 7
+    // ---- LDS -> MFMA operands: rows l16 of the wave's tokens, frag_row16 of its features
     const int a_row = wm * (BM / 2) + l16, w_lane = frag_row16<EPI>(l16);
     int w_row[TN];
 #pragma unroll
@@ -533,14 +578,15 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs p) {
             bf16x8_t wf[TN], af[TM];
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
-                wf[tn] = as_bf16x8(*reinterpret_cast<const uint4*>(sw + w_row[tn] * 128 + (((4 * ks + g) ^ (w_row[tn] & 7)) << 4)));
+                wf[tn] = as_bf16x8(*reinterpret_cast<const uint4*>(sw + w_row[tn] * 128 + (((4 * ks + g) ^ w_swz(w_row[tn])) << 4)));
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm)
                 af[tm] = as_bf16x8(*reinterpret_cast<const uint4*>(sa + (a_row + 16 * tm) * 128 + (((4 * ks + g) ^ (a_row & 7)) << 4)));
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-                for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = mfma_16x16x32(wf[tn], af[tm], acc[tn][tm]);
+                for (int tm = 0; tm < TM; ++tm)
+                    acc[tn][tm] = rows32(EPI) ? mfma_16x16x32(af[tm], wf[tn], acc[tn][tm]) : mfma_16x16x32(wf[tn], af[tm], acc[tn][tm]);
         }
         if (more) store_lds((kt + 1) & 1);
         __syncthreads();
@@ -667,11 +713,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     const uint32_t lrow = lane / CPR;
     const uint32_t row_lo = (uint32_t)(wave * RPI) + lrow;   // LDS row modulo NW * RPI (>= 32): all the swizzle needs
     const uint32_t chunk = (lane % CPR) ^ ((row_lo >> 1) & 7);
-    // (the weights of permuted results, paired16, are read in rows 0-3, 8-11, 16-19 and 24-27 of 32, or four further on: a swizzle of
-    // their own gives those sixteen the same)
-    constexpr bool PERM = paired16(EPI);
-    auto perm_swz = [](int row) { return ((row >> 1) & 1) | ((row >> 2) & 6); };
-    const uint32_t w_chunk = PERM ? (lane % CPR) ^ perm_swz(row_lo) : chunk;
+    // (the weights are read in rows 0-3, 8-11, 16-19 and 24-27 of 32, or four further on; for fp32 rows in 0, 1, 8, 9, 16, 17 .. of 64:
+    // swizzles of their own give those sixteen the same)
+    auto w_swz = [](int row) { return rows32(EPI) ? (row >> 3) & 7 : ((row >> 1) & 1) | ((row >> 2) & 6); };
     uint32_t a_voff[A_IT], w_voff[W_IT];
     // row-major: row n starts at n * K; packed: block n / 256 holds, k slice after k slice, 256 rows of 128 bytes
     const uint32_t w_shift = p.w_packed ? 8 : 0, w_block = (uint32_t)K * (p.w_packed ? 512u : 2u), w_mask = p.w_packed ? 255 : 0;
@@ -689,9 +733,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             const int gi = min(tile_n * HALF + (lr % HALF), p.n_half - 1);
             n = NW * j * RPI < HALF ? gi : p.n_half + gi;
         } else {
-            n = min(tile_n * BN + lr, p.N - 1);
+            n = min(tile_n * BN + lds_feature<EPI>(lr), p.N - 1);
         }
-        w_voff[j] = (n >> w_shift) * w_block + (n & w_mask) * 128u + w_chunk * 16;
+        w_voff[j] = (n >> w_shift) * w_block + (n & w_mask) * 128u + ((lane % CPR) ^ w_swz(lr)) * 16;
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
     const int w_stage = p.w_packed ? 32768 : 128;   // bytes from one k slice of the weights to the next
@@ -706,11 +750,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         const int c = F8 ? 2 * g : 4 * ks + g;   // the lane's (first) chunk of a row
         const uint32_t at = lds0 + fr * ROWB + ((c ^ swz) << 4);
         a_lane[ks] = at + wm * (BM / WGM) * ROWB;
-        w_lane[ks] = at + W_LDS + wn * w_wave * ROWB;
-        if constexpr (PERM) {
-            const int row = frag_row16<EPI>(fr);
-            w_lane[ks] = lds0 + W_LDS + (wn * w_wave + row) * ROWB + ((c ^ perm_swz(row)) << 4);
-        }
+        const int row = frag_row16<EPI>(fr);
+        w_lane[ks] = lds0 + W_LDS + (wn * w_wave + row) * ROWB + ((c ^ w_swz(row)) << 4);
     }
     auto a_dist = [](int tm) { return 16 * tm * ROWB; };
     auto w_dist = [](int tn) {
@@ -758,9 +799,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     auto mfma_one = [&](int buf, int i) __attribute__((always_inline)) {   // i-th of the TN * TM products of a k step
         const int tn = i / TM, tm = i % TM;
         if constexpr (F8)
-            acc[tn][tm] = mfma_16x16x128_f8(wf[buf][tn], af[buf][tm], acc[tn][tm]);
+            acc[tn][tm] = rows32(EPI) ? mfma_16x16x128_f8(af[buf][tm], wf[buf][tn], acc[tn][tm]) : mfma_16x16x128_f8(wf[buf][tn], af[buf][tm], acc[tn][tm]);
         else
-            acc[tn][tm] = mfma_16x16x32(wf[buf][tn], af[buf][tm], acc[tn][tm]);
+            acc[tn][tm] = rows32(EPI) ? mfma_16x16x32(af[buf][tm], wf[buf][tn], acc[tn][tm]) : mfma_16x16x32(wf[buf][tn], af[buf][tm], acc[tn][tm]);
     };
     // Source of the refill in progress (set at a hand-over): the k slice's first byte in both operands and the
     // freed stages' LDS addresses, so that a load costs its own two instructions plus one scalar add.
@@ -942,7 +983,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         cur = nxt;
     };
     constexpr bool SC = F8 && EPI != EPI_SLAB;
-    float4 w_scales[SC ? TN : 1];
+    float4 w_scales[SC ? scale_quads(EPI, TN) : 1];
     if constexpr (SC) load_code_scales<BN, EPI, D>(p, tile_n, wn, lane, w_scales);
     // fill both rings, wait for stage 0 only
 #pragma unroll
@@ -1034,8 +1075,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     }
     if constexpr (EPI == EPI_SLAB) {   // split-K partial sums -> this split's slab: plain rows of fp32
         p.out = p.accum + (int64_t)split * p.T * p.N;
-        p.residual = nullptr;
-        gemm_epilogue16<BM, BN, EPI_RES_BF16_OUT_F32, 0, false>(acc, p, tile_m, tile_n, wm, wn, lane, 0);
+        gemm_epilogue16<BM, BN, EPI, 0, false>(acc, p, tile_m, tile_n, wm, wn, lane, 0);
     } else {
         gemm_epilogue16<BM, BN, EPI, D, F8>(acc, p, tile_m, tile_n, wm, wn, lane, 0, w_scales);
     }
@@ -1059,7 +1099,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_tail_finish_kernel(GemmAr
     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
         for (int h = 0; h < H; ++h) acc[tn][h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    float4 w_scales[SC ? TN : 1];
+    float4 w_scales[SC ? scale_quads(EPI, TN) : 1];
     if constexpr (SC) load_code_scales<BN, EPI, D>(p, tile_n, wn, lane, w_scales);
     for (int q = 0; q < p.tail_splits; ++q) {
         const f32x4_t* src = reinterpret_cast<const f32x4_t*>(p.tail_buf) + ((size_t)q * p.tail_tiles + tail_idx) * AREA4 + tid;

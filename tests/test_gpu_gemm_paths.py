@@ -153,6 +153,60 @@ def test_rows_that_end_or_begin_inside_a_group_of_8(rs, N, shift):
             assert (buf[:shift] == 7).all() and (buf[shift + T * N:] == 7).all(), (epi, tile)
 
 
+@pytest.mark.parametrize("w8a8", [False, True], ids=["bf16", "codes"])
+@pytest.mark.parametrize("T", [1, 63, 259])
+@pytest.mark.parametrize("N", [4, 60, 68, 132, 512, 516])
+def test_fp32_rows_that_end_inside_a_group_of_64(rs, N, T, w8a8):
+    """Rows of fp32 are stored 64 features at a time by 16 lanes, four tokens by four: rows of features that end inside a group and
+    tokens that end inside four, on every tile shape and on the kernel for k of no multiple of 64.  Exact sums, as above; nothing behind
+    the last row is touched."""
+    g = torch.Generator(device="cuda").manual_seed(N + T)
+    res = torch.randint(-8, 9, (T, N), generator=g, device="cuda").bfloat16()
+    for K in (128, 384) if w8a8 else (64, 72, 320):
+        if w8a8:
+            codes = lambda *s: torch.tensor([0, 0x38, 0x40], dtype=torch.uint8, device="cuda")[torch.randint(0, 3, s, generator=g, device="cuda")]
+            value = lambda c: c.view(torch.float8_e4m3fn).double().cpu()
+            a, w = codes(T, K), codes(N, K)
+            sw = 2.0 ** torch.randint(-3, 4, (N,), generator=g, device="cuda").float()
+            sums = ((value(a) @ value(w).T) * (0.5 * sw.double().cpu())).float()
+            run = lambda r, out: rs.relserve_linear_w8a8(a, w, sw, 0.5, 1, r, out)
+        else:
+            a = torch.randint(-4, 5, (T, K), generator=g, device="cuda").bfloat16()
+            w = (torch.randint(-4, 5, (N, K), generator=g, device="cuda").float() / 64).bfloat16()
+            sums = (a.double().cpu() @ w.double().cpu().T).float()
+            run = lambda r, out: rs.relserve_linear(a, w, 1, r, out)
+        for r, want in ((None, sums), (res, sums + res.float().cpu())):
+            for tile in (-1, 0, 1, 2, 3, 4):
+                buf = torch.full((T * N + 64,), 7.0, dtype=torch.float32, device="cuda")
+                rs.relserve_debug_force_gemm_plan(tile, 0)
+                try:
+                    run(r, buf[:T * N].view(T, N))
+                    torch.cuda.synchronize()
+                finally:
+                    rs.relserve_debug_force_gemm_plan(-1, 0)
+                assert torch.equal(buf[:T * N].view(T, N).cpu(), want), (K, tile)
+                assert (buf[T * N:] == 7).all(), (K, tile)
+
+
+@pytest.mark.parametrize("T", [5, 64, 67, 128, 140, 192, 250, 256, 300])
+def test_slabs_of_rows_that_end_inside_a_group_of_64(rs, oracle, T):
+    """Split projections onto 520 features (W_o of k = 512, W_down of k = 704) beside unsplit ones of k = 520, on one row of tiles of
+    every height and on two."""
+    shape = W.LayerShape(520, 4, 2, 128, 704, 16, 1e-5, 10000.0)
+    b = W.build_batch(shape, [T - 4] + [1] * 4, [T - 4] + [5] * 4, seed=T)
+    wl = W.Workload("ragged_rows", shape, b, T)
+    weights, x = wl.weights(), W.make_activations(b.T, shape.hidden, T)
+    kp, vp = W.make_cache(shape, b.num_pages, T)
+    layer = rs.relserve_layer_create(shape)
+    pb = rs.relserve_batch_prepare(layer, b)
+    ws = torch.full((rs.relserve_workspace_bytes(layer, b.T),), 0xff, dtype=torch.uint8, device="cuda")
+    xd = dev_bf16(x)
+    y = torch.empty_like(xd)
+    rs.relserve_layer_step(layer, pb, {k: dev_bf16(v) for k, v in weights.items()}, xd, y, dev_bf16(kp), dev_bf16(vp), ws)
+    torch.cuda.synchronize()
+    assert_close(host_f32(y), oracle.layer_step(shape, b, weights, x, kp, vp).y_f32, f"step T={T}")     # the whole step's bar
+
+
 @pytest.mark.parametrize("T", [257, 482, 1308])
 @pytest.mark.parametrize("hidden", [192, 256, 448, 512])
 def test_short_k_takes_whole_tiles_at_mid_size(rs, T, hidden):
