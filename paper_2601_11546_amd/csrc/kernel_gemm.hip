@@ -766,7 +766,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     using frag_t = std::conditional_t<F8, i32x8_t, bf16x8_t>;
     constexpr bool FIXED = HALVES || (BM * BN >= 6 * 4096 && !(EPI == EPI_SWIGLU && BM == 128));   // issue order: see below
-    constexpr bool QUARTERS = F8 && FIXED;
+    constexpr bool QUARTERS = F8 && (FIXED || NS == 2);
+    constexpr bool EARLY = !FIXED && NS == 2;   // the refill goes out at once: see below
     frag_t wf[QUARTERS ? 1 : 2][TN], af[QUARTERS ? 1 : 2][TM];
     typedef const i32x4_t __attribute__((address_space(3))) * lds_chunk;
     auto read_frag = [&](uint32_t at, int dist) __attribute__((always_inline)) -> frag_t {
@@ -854,9 +855,12 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         // of the loads) go out at once, the activations (L2 hits, quick to land) trail over two more parts
         constexpr int cut[5] = {0, 8, 13, 16, 16};
         const int part = step * SUB + i / NMP, ip = i % NMP, pc = part < SPREAD ? part : SPREAD;
-        // (skewed: the activations at once, the weights over all the parts that remain)
-        const int d_lo = SKEW ? (part == 0 ? 0 : A_IT + (part - 1) * W_IT / (PARTS - 1)) : cut[pc] * LOADS / 16;
-        const int d_n = (SKEW ? A_IT + part * W_IT / (PARTS - 1) : cut[pc + 1] * LOADS / 16) - d_lo;
+        // (skewed: the activations at once, the weights over all the parts that remain.  EARLY: a small tile with two stages waits at the
+        // next hand-over for what it issues at this one, and its products are over long before: everything in the first part.  Spread
+        // over all products, codes with both steps' fragments in registers / this: 5120 x 13824, T = 520 77.4 / 64.0 us, 264 62.1 / 56.5;
+        // SwiGLU 2816 x 1024 at 2500 13.0 / 12.4)
+        const int d_lo = SKEW ? (part == 0 ? 0 : A_IT + (part - 1) * W_IT / (PARTS - 1)) : EARLY ? (part == 0 ? 0 : LOADS) : cut[pc] * LOADS / 16;
+        const int d_n = (SKEW ? A_IT + part * W_IT / (PARTS - 1) : EARLY ? LOADS : cut[pc + 1] * LOADS / 16) - d_lo;
         const int d0 = d_lo + ip * d_n / NMP, d1 = SKEW || part < SPREAD ? d_lo + (ip + 1) * d_n / NMP : d0;   // the slot's loads
         auto wanted = [&](int d) __attribute__((always_inline)) { return SKEW && d >= A_IT ? on(refill_w) : on(refill_a); };
         if (d0 < d1 && wanted(d0)) issue_to(d0);
@@ -879,7 +883,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
         }
     };
     // 8-bit operands on 16 x 16 x 128 products: a stage is one k step, and two buffers of its fragments (256 registers on a 256 x 256
-    // tile) do not fit beside the sums (small tiles do keep two).  The wave's products go quarter by quarter instead, weights' halves lo and hi against tokens'
+    // tile) do not fit beside the sums (small tiles on deep rings do keep two: 1 % of a step of 24 rows).  The wave's products go quarter by quarter instead, weights' halves lo and hi against tokens'
     // halves h and h' = 1 - h: (lo, h), (lo, h'), (hi, h'), (hi, h), and behind each quarter's products come the four fragments or so
     // that the next one adds, into registers whose last reader is over: tokens h' , weights hi, the next stage's lo and, where tokens h'
     // were, the next stage's tokens h'; so the next stage begins with h'.  Every fragment is read once, at an even rate, and the
@@ -960,6 +964,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
             k_step(LB, nxt, 0, 0, next_a, next_w);
         } else {
             const Source src = source(nxt, 0);
+            // (16-bit EARLY tiles: within eight products, 128 cycles.  5120 x 13824, T = 520 124.0 -> 122.2 us; 64-row tiles as they were)
+            constexpr int AT = EARLY ? 8 : NM;
+            static_assert(!F8 || !EARLY, "codes with two stages go quarter by quarter");
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
@@ -967,7 +974,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
                 __builtin_amdgcn_sched_barrier(0);
                 if (on(next_a)) {   // (never skewed)
 #pragma unroll
-                    for (int d = i * LOADS / NM; d < (i + 1) * LOADS / NM; ++d) issue_one(d);
+                    for (int d = i * LOADS / AT; d < min((i + 1) * LOADS / AT, LOADS); ++d) issue_one(d);
                 }
                 if constexpr (F8) {   // the next hand-over waits for these: at once
 #pragma unroll
