@@ -1672,6 +1672,7 @@ struct Plan { int cand, tail_tiles, splits, cols1 = 0, cand1 = 0, cand2 = 0; };
 // W_down 765 + 21 / 611 + 175; W_down at T = 1409, all of it tail, 153 + 20 / 172.  Tiles of 128 rows load more per product, which grows
 // with k while the finish does not: even at 13824, and W_down of the 32B shape (k of 27648) at T = 1246 349 in halves, 320 with the finish.
 constexpr int kHalvesMaxK = 16384;
+bool in_halves(int tail_splits, int K, bool f8) { return tail_splits == 2 && K >= 1024 && K <= kHalvesMaxK && !f8; }
 template <int EPI, int D>
 hipError_t launch_halves(const GemmArgs& base, hipStream_t s) {
     GemmArgs p = base;
@@ -1721,7 +1722,7 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
         p.tail_splits = (nk + p.k_per_split - 1) / p.k_per_split;   // no empty split
         p.tail_tiles = std::min(plan.tail_tiles, tiles);
         if constexpr (BM == 256 && BN == 256) {
-            if (p.tail_splits == 2 && nk >= 16 && p.K <= kHalvesMaxK && !p.f8) return launch_halves<EPI, D>(p, s);
+            if (in_halves(p.tail_splits, p.K, p.f8)) return launch_halves<EPI, D>(p, s);
         }
         p.tail_buf = p.accum;
         if ((int64_t)p.tail_tiles * p.tail_splits * BM * BN > kTailFloats)
@@ -1924,7 +1925,10 @@ void gemm_force_plan(int cand, int splits) {
 
 GemmPlan gemm_plan(int32_t T, int64_t features, int32_t K, bool qkv, bool swiglu, bool scratch) {
     const Plan p = plan_for(T, features, K, qkv, scratch, swiglu);
-    return GemmPlan{kTiles[p.cand].bm, kTiles[p.cand].bn, p.tail_tiles, p.splits};
+    GemmPlan g{kTiles[p.cand].bm, kTiles[p.cand].bn, p.tail_tiles, p.splits, p.cols1, 0, 0, false};
+    if (p.cols1 > 0) g.rows1 = kTiles[p.cand1].bm, g.rows2 = kTiles[p.cand2].bm;
+    g.halves = p.cand == 0 && p.tail_tiles > 0 && in_halves(p.splits, K, false);
+    return g;
 }
 
 int64_t gemm_scratch_floats(int64_t T, int64_t n_max) {

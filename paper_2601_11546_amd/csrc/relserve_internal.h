@@ -154,7 +154,9 @@ int64_t gemm_scratch_floats(int64_t T, int64_t n_max);
 void gemm_force_plan(int cand, int splits);   // test hook, see relserve_debug_force_gemm_plan
 // How a projection of more tokens than SKINNY_MAX_T is tiled (host arithmetic alone): tiles of rows tokens x cols features,
 // of which the last tail_tiles split their k range `splits` ways.  K counts 2-byte units, so half of it for 8-bit codes.
-struct GemmPlan { int32_t rows, cols, tail_tiles, splits; };
+// Where nothing is split and cols1 > 0 it is two launches: the first cols1 columns of tiles on rows1 tokens each, the others on rows2
+// (256 features both; rows x cols is the shape one launch would take).  halves: the split tiles run as halves (launch_halves).
+struct GemmPlan { int32_t rows, cols, tail_tiles, splits, cols1, rows1, rows2; bool halves; };
 GemmPlan gemm_plan(int32_t T, int64_t features, int32_t K, bool qkv, bool swiglu, bool scratch);
 // The RMSNorm that reads a projection's output rows next (epilogues 1 and 2).  Where the projection ends in a kernel that
 // adds up k ranges, that kernel runs the norm too and sets `done`; otherwise the caller launches it.

@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from paper_2601_11546_amd import workloads as W
+from tests import host_program
 from tests.gpu_harness import assert_close, dev_bf16, host_f32
 
 pytestmark = pytest.mark.gpu
@@ -266,6 +267,71 @@ def test_columns_of_two_tile_shapes_give_the_same_bits(rs, T, epi, N, w8a8):
             rs.relserve_debug_force_gemm_plan(-1, 0)
         outs.append(out)
     assert torch.isfinite(outs[1]).all() and torch.equal(outs[0], outs[1])
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    exe = host_program.build(tmp_path_factory.mktemp("launches"), "gemm_launches")
+    return lambda *row: host_program.run(exe, "%d %d %d %d %d %d\n" % row)[0]
+
+
+def _one_shape_or_two(rs, launches, row, run, outs):
+    """outs: what run() writes; on the automatic choice, which has to be two launches, and on one shape of 256 x 256."""
+    assert launches(*row)[4] > 0, "the size is meant to run as two launches"
+    got = []
+    for tile in (-1, 0):
+        for o in outs:
+            o.fill_(float("nan"))
+        rs.relserve_debug_force_gemm_plan(tile, 0)
+        try:
+            run()
+            torch.cuda.synchronize()
+        finally:
+            rs.relserve_debug_force_gemm_plan(-1, 0)
+        got.append([o.clone() for o in outs])
+    for two, one in zip(*got):
+        assert torch.isfinite(one).all() and torch.equal(two, one)
+
+
+@pytest.mark.parametrize("w8a8", [False, True], ids=["bf16", "codes"])
+@pytest.mark.parametrize("T, epi, N", [(1409, 0, 11012), (3300, 0, 5524), (1409, 1, 11012), (1500, 1, 11012), (1409, 2, 11012),
+                                       (806, 3, 27664), (2000, 3, 13840)])
+def test_two_launches_write_every_column_once(rs, launches, T, epi, N, w8a8):
+    """Sizes that do run as two launches (the plan is asked), with tokens and features that end inside a tile: the bits of one shape."""
+    K = 5120 if w8a8 else 2560
+    g = torch.Generator(device="cuda").manual_seed(T + N)
+    res = None if epi in (0, 3) else torch.randn(T, N, generator=g, device="cuda", dtype=torch.bfloat16 if epi == 1 else torch.float32)
+    out = torch.empty((T, N // 2 if epi == 3 else N), dtype=torch.float32 if epi == 1 else torch.bfloat16, device="cuda")
+    if w8a8:
+        codes = lambda *s: (torch.randn(s, generator=g, device="cuda") * 60).to(torch.float8_e4m3fn).view(torch.uint8)
+        a, w, sw = codes(T, K), codes(N, K), torch.rand(N, generator=g, device="cuda") * 1e-4
+        run = lambda: rs.relserve_linear_w8a8(a, w, sw, 0.03, epi, res, out)
+    else:
+        a = torch.randn(T, K, generator=g, device="cuda").bfloat16()
+        w = (torch.randn(N, K, generator=g, device="cuda") * 0.02).bfloat16()
+        run = lambda: rs.relserve_linear(a, w, epi, res, out)
+    _one_shape_or_two(rs, launches, (T, N, 2560, 0, int(epi == 3), 0), run, [out])
+
+
+@pytest.mark.parametrize("n_q, n_kv, d", [(75, 5, 128), (150, 10, 64)])
+def test_two_launches_of_the_qkv_projection(rs, launches, n_q, n_kv, d):
+    """The same where the epilogue rotates and appends: queries, keys and values, the last tile half a column."""
+    T, K = 1409, 2560
+    shape = W.LayerShape(K, n_q, n_kv, d, 704, 16, 1e-5, 10000.0)
+    g = torch.Generator(device="cuda").manual_seed(d)
+    b = W.build_batch(shape, [T - 9] + [1] * 9, [T - 9] + [40] * 9, seed=3)
+    layer = rs.relserve_layer_create(shape)
+    pb = rs.relserve_batch_prepare(layer, b)
+    h = torch.randn(T, K, generator=g, device="cuda").bfloat16()
+    w = (torch.randn(shape.qkv_dim, K, generator=g, device="cuda") * 0.02).bfloat16()
+    q = torch.empty(T, n_q * d, dtype=torch.bfloat16, device="cuda")
+    kd, vd = (torch.zeros(b.num_pages, 16, n_kv, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+
+    def run():   # slots that no token of the batch takes keep what they hold
+        kd.zero_()
+        vd.zero_()
+        rs.relserve_qkv_rope_append(layer, pb, h, w, q, kd, vd)
+    _one_shape_or_two(rs, launches, (T, shape.qkv_dim, K, 1, 0, 0), run, [q, kd, vd])
 
 
 def test_iteration_of_640_tokens_keeps_its_sums_whole(rs):
