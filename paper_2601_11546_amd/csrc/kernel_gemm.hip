@@ -1668,11 +1668,16 @@ struct Plan { int cand, tail_tiles, splits, cols1 = 0, cand1 = 0, cand2 = 0; };
 // each over both ranges with the sums of either in registers of its own (HALVES).  As many workgroups with as much to multiply, and
 // the finish kernel's sums bit for bit, without 256 KB of partial sums to memory and back per range, nor its launch.  (On codes the
 // second set of sums does not fit beside the fragments.)
-// 13B at T = 7963, tiles + finish / tiles + halves, us: q/k/v 902 + 23 / 840 + 71, W_o 338 + 30 / 271 + 77, gate/up 1513 + 17 / 1454 + 67,
-// W_down 765 + 21 / 611 + 175; W_down at T = 1409, all of it tail, 153 + 20 / 172.  Tiles of 128 rows load more per product, which grows
-// with k while the finish does not: even at 13824, and W_down of the 32B shape (k of 27648) at T = 1246 349 in halves, 320 with the finish.
-constexpr int kHalvesMaxK = 16384;
-bool in_halves(int tail_splits, int K, bool f8) { return tail_splits == 2 && K >= 1024 && K <= kHalvesMaxK && !f8; }
+// The line: tiles of 128 rows load more per product, which grows with k while what is saved does not, and run as a launch behind the whole
+// tiles instead of beside them.  Finish / halves, 154 projections of eight layers at 408 .. 8950 tokens: k of 4096 .. 8192 beside whole tiles
+// 1.016 on average (0.98 .. 1.06; W_o of the 13B layer at T = 8061 341 / 324 us, q/k/v of the 70B layer at 5394 692 / 678), k of 13824 and
+// 14336 0.98 (0.92 .. 1.03; W_down of the 13B layer at 7553 768 / 782).  Without whole tiles the ranges of the other way run alone on the chip, at a higher clock the
+// fewer they are, so there it pays where the halves nearly fill it: k of 8192, 120 tiles 1.035 (q/k/v of the 70B layer at 667 118 / 112), 96 .. 112 tiles 0.98
+// (0.93 .. 1.05); of 13824, 120 tiles 0.98.
+constexpr int kHalvesMaxK = 8192, kHalvesAloneTiles = 116;
+bool in_halves(int64_t tiles, int64_t tail_tiles, int tail_splits, int K, bool f8) {
+    return tail_splits == 2 && K >= 1024 && K <= kHalvesMaxK && !f8 && (tiles > tail_tiles || tail_tiles >= kHalvesAloneTiles);
+}
 template <int EPI, int D>
 hipError_t launch_halves(const GemmArgs& base, hipStream_t s) {
     GemmArgs p = base;
@@ -1722,7 +1727,7 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
         p.tail_splits = (nk + p.k_per_split - 1) / p.k_per_split;   // no empty split
         p.tail_tiles = std::min(plan.tail_tiles, tiles);
         if constexpr (BM == 256 && BN == 256) {
-            if (in_halves(p.tail_splits, p.K, p.f8)) return launch_halves<EPI, D>(p, s);
+            if (in_halves(tiles, p.tail_tiles, p.tail_splits, p.K, p.f8)) return launch_halves<EPI, D>(p, s);
         }
         p.tail_buf = p.accum;
         if ((int64_t)p.tail_tiles * p.tail_splits * BM * BN > kTailFloats)
@@ -1927,7 +1932,7 @@ GemmPlan gemm_plan(int32_t T, int64_t features, int32_t K, bool qkv, bool swiglu
     const Plan p = plan_for(T, features, K, qkv, scratch, swiglu);
     GemmPlan g{kTiles[p.cand].bm, kTiles[p.cand].bn, p.tail_tiles, p.splits, p.cols1, 0, 0, false};
     if (p.cols1 > 0) g.rows1 = kTiles[p.cand1].bm, g.rows2 = kTiles[p.cand2].bm;
-    g.halves = p.cand == 0 && p.tail_tiles > 0 && in_halves(p.splits, K, false);
+    g.halves = p.cand == 0 && p.tail_tiles > 0 && in_halves(tile_count(kTiles[0], T, features), p.tail_tiles, p.splits, K, false);
     return g;
 }
 

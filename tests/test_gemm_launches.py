@@ -23,8 +23,11 @@ def test_columns_of_two_shapes(launches, row, want):
 
 
 @pytest.mark.parametrize("row, halves", [
-    ((8061, 5120, 5120, 0, 0, 1), 1), ((667, 10240, 8192, 1, 0, 1), 1),
-    ((3388, 5120, 27648, 0, 0, 1), 0), ((4500, 11012, 2560, 0, 0, 0), 0),   # long k; nothing is cut without scratch
+    ((8061, 5120, 5120, 0, 0, 1), 1), ((6918, 8192, 7168, 0, 0, 1), 1), ((3870, 10240, 8192, 1, 0, 1), 1),   # beside whole tiles
+    ((7553, 5120, 13824, 0, 0, 1), 0), ((5648, 4096, 14336, 0, 0, 1), 0),                                      # long k
+    ((667, 10240, 8192, 1, 0, 1), 1), ((2854, 2560, 8192, 1, 0, 1), 1),                                        # alone on the chip, and filling it
+    ((2406, 2560, 8192, 1, 0, 1), 0), ((2258, 3072, 8192, 0, 0, 1), 0), ((1407, 5120, 13824, 0, 0, 1), 0),     # alone, and not, or of long k
+    ((8061, 5120, 5120, 0, 0, 0), 0),                                                                          # nothing is cut without scratch
 ])
 def test_tails_in_halves(launches, row, halves):
     assert launches(*row)[7] == halves

@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2601_11546_amd import duration_model
 from paper_2601_11546_amd import workloads as W
 from tests import host_program
 from tests.gpu_harness import assert_close, dev_bf16, host_f32
@@ -332,6 +333,46 @@ def test_two_launches_of_the_qkv_projection(rs, launches, n_q, n_kv, d):
         vd.zero_()
         rs.relserve_qkv_rope_append(layer, pb, h, w, q, kd, vd)
     _one_shape_or_two(rs, launches, (T, shape.qkv_dim, K, 1, 0, 0), run, [q, kd, vd])
+
+
+@pytest.mark.parametrize("T, shape, w8a8", [
+    # tiles of 256 and of 192 rows are all tail (13 x 9 and 17 or 18 x 9), two ranges each; k of 36, 32 and 17 slices, of 35, 16 and 18
+    (3132, W.LayerShape(2304, 16, 1, 128, 1088, 16, 1e-5, 10000.0), False), (3272, W.LayerShape(2304, 16, 1, 128, 1088, 16, 1e-5, 10000.0), False),
+    (3132, W.LayerShape(2304, 32, 2, 64, 1088, 16, 1e-5, 10000.0), False), (3272, W.LayerShape(2240, 8, 8, 128, 1152, 16, 1e-5, 10000.0), False),
+    # tails of two tiles beside 256 whole ones (gate/up); W_down of k = 16448
+    (300, W.LayerShape(1024, 8, 8, 128, 16448, 16, 1e-5, 10000.0), False),
+    (3132, W.LayerShape(2304, 16, 1, 128, 1152, 16, 1e-5, 10000.0), True), (300, W.LayerShape(2048, 16, 4, 128, 2176, 16, 1e-5, 10000.0), True),
+])
+def test_two_k_ranges_on_either_tile_give_the_same_bits(rs, T, shape, w8a8):
+    """256-row tiles of two k ranges, as halves (16-bit, where the rule says so) or through slabs and their finish kernel, against slabs and
+    finish of 192-row tiles: the same ranges, the same order of additions.  The last 256 rows hold 60, 200 or 44: halves with and without a lower one."""
+    b = W.build_batch(shape, [100] * (T // 100) + ([T % 100] if T % 100 else []), [100] * (T // 100) + ([T % 100] if T % 100 else []), seed=T)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    randn = lambda *s, std=0.05: torch.empty(*s, dtype=torch.float32, device="cuda").normal_(0, std, generator=g).bfloat16()
+    H, I = shape.hidden, shape.mlp_dim
+    wd = {"w_in_norm": randn(H, std=1.0), "w_qkv": randn(shape.qkv_dim, H), "w_o": randn(H, shape.q_dim), "w_post_norm": randn(H, std=1.0),
+          "w_gate_up": randn(2 * I, H), "w_down": randn(H, I)}
+    step = rs.relserve_layer_step
+    if w8a8:
+        wd, step = duration_model.quantise_layer_on_device(torch, wd), rs.relserve_layer_step_w8a8
+    x = randn(b.T, H, std=1.0)
+    pool = (b.num_pages, shape.page_size, shape.n_kv_heads, shape.head_dim)
+    layer = rs.relserve_layer_create(shape)
+    pb = rs.relserve_batch_prepare(layer, b)
+    ws = torch.empty(rs.relserve_workspace_bytes(layer, b.T), dtype=torch.uint8, device="cuda")
+    outs = []
+    for tile in (0, 1):
+        y, k, v = torch.empty_like(x), torch.zeros(pool, dtype=torch.bfloat16, device="cuda"), torch.zeros(pool, dtype=torch.bfloat16, device="cuda")
+        rs.relserve_debug_force_gemm_plan(tile, 2)
+        try:
+            step(layer, pb, wd, x, y, k, v, ws)
+            torch.cuda.synchronize()
+        finally:
+            rs.relserve_debug_force_gemm_plan(-1, 0)
+        outs.append((y, k, v))
+    assert torch.isfinite(outs[0][0]).all()
+    for name, got, want in zip("ykv", *outs):
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16)), name
 
 
 def test_iteration_of_640_tokens_keeps_its_sums_whole(rs):
