@@ -1764,10 +1764,12 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
 // refit of them for 16-bit operands changed a next token in 129 (four 13B layers, 128 decode rows and a 512-token chunk).
 //
 // 2. The shape of whole tiles: any gives the same bits, so where nothing is split the fastest one runs (whole_tile).  For the
-// SwiGLU projection of a k (in 2-byte units) below SWIGLU_FIT_K that is the shape the cut's own model names: 1.2 (16-bit) and 2.6 %
-// (8-bit) off the fastest one on average at hidden sizes of 256 .. 3072 (profiles/gemm_whole_tiles.txt).
+// SwiGLU projection of a k (in 2-byte units) below swiglu_fit_k that is the shape the cut's own model names.  Distance from the fastest of the five
+// shapes, on average, with that shape / with whole_tile's (profiles/gemm_whole_tiles.txt, ten layer shapes at 19 token counts): more than 256
+// tokens, k from 2560 on 1.3 / 0.1 % (16-bit), 0.9 / 0.4 (codes), below 0.4 / 3.1 and 0.4 / 3.6; at most 256 tokens (without scratch, as
+// relserve_linear runs them), k from 5120 on 3.7 / 0.8, 2560 .. 4096 0.9 / 3.5, below 0.0 / 1.4.
 struct TileCand { int bm, bn, wg_per_cu; float eff_cut, eff, eff_swiglu; bool qkv; };   // qkv: usable by the fused q/k/v epilogue (128 features per wave)
-constexpr int SWIGLU_FIT_K = 2560;
+constexpr int swiglu_fit_k(int T) { return T > SKINNY_MAX_T ? 2560 : 5120; }
 constexpr TileCand kTiles[] = {
     // eff: fitted to the times of every whole tile shape, forced, of the other projections that split nothing, five layer shapes
     // at 18 token counts of 264 .. 4200, 16-bit and 8-bit.  Distance of the choice from the fastest shape, on average: 0.03 % in
@@ -1894,8 +1896,8 @@ Plan plan_for(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, boo
     Plan plan;
     if (forced_plan(T, n_eff, K, need_bn256, allow_tail, &plan)) return plan;
     plan = choose_cut(T, n_eff, K, need_bn256, allow_tail);
-    if (plan.tail_tiles == 0 && !(swiglu && K < SWIGLU_FIT_K)) plan.cand = whole_tile(T, n_eff, K, need_bn256, swiglu);
-    if (plan.tail_tiles == 0 && K >= SWIGLU_FIT_K && K % 64 == 0) two_shapes(T, n_eff, K, swiglu, &plan);
+    if (plan.tail_tiles == 0 && !(swiglu && K < swiglu_fit_k(T))) plan.cand = whole_tile(T, n_eff, K, need_bn256, swiglu);
+    if (plan.tail_tiles == 0 && K >= 2560 && K % 64 == 0) two_shapes(T, n_eff, K, swiglu, &plan);
     return plan;
 }
 

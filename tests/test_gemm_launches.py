@@ -31,3 +31,12 @@ def test_columns_of_two_shapes(launches, row, want):
 ])
 def test_tails_in_halves(launches, row, halves):
     assert launches(*row)[7] == halves
+
+
+@pytest.mark.parametrize("row, tile", [
+    # SwiGLU of at most 256 tokens without scratch, where the shapes' times lie clearly apart (profiles/gemm_whole_tiles.txt)
+    ((100, 27648, 2560, 0, 1, 0), (64, 128)), ((130, 14336, 4096, 0, 1, 0), (64, 128)), ((200, 16384, 3072, 0, 1, 0), (64, 128)),
+    ((130, 27648, 5120, 0, 1, 0), (128, 256)), ((256, 27648, 5120, 0, 1, 0), (128, 256)), ((264, 27648, 5120, 0, 1, 0), (192, 256)),
+])
+def test_whole_tiles_of_few_rows(launches, row, tile):
+    assert launches(*row)[:2] == tile
