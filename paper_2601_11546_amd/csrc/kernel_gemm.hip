@@ -1850,8 +1850,9 @@ int whole_tile(int T, int64_t n_eff, int K, bool need_bn256, bool swiglu) {
 // full rounds of each 256-feature shape: as many columns as they hold, the rest on another; taken where the model that
 // whole_tile uses sees a gain of kTwoShapesGain beyond kSecondLaunchSec.  One launch / two, us, measured in turn: gate/up of the 32B layer on
 // codes at T = 806 219 / 197, of its 16-bit half 217 / 190, 70B at 577 503 / 466, 13B at 1409 315 / 303; q/k/v of the 13B layer at 2500
-// on codes 163 / 154, W_o at 3875 162 / 152; of 100 sizes of five layer shapes, 3.3 % on average.  (Below a modelled gain of 4 % the
-// second launch lost 1 - 3 % as often as it won them.)
+// on codes 163 / 154, W_o at 3875 162 / 152; of 58 sizes of ten layer
+// shapes that take it at k (in 2-byte units) of 2560 and more 5.3 % on average and no loss beyond 0.1 %, of 70 at k of 768 .. 2304 4.7 % and
+// one loss of 2.6.  (Below a modelled gain of 4 % the second launch lost 1 - 3 % as often as it won them.)
 constexpr double kSecondLaunchSec = 6e-6, kTwoShapesGain = 0.04;
 void two_shapes(int T, int64_t n_eff, int K, bool swiglu, Plan* plan) {
     const int cols = (int)((n_eff + 255) / 256);
@@ -1897,7 +1898,7 @@ Plan plan_for(int T, int64_t n_eff, int K, bool need_bn256, bool allow_tail, boo
     if (forced_plan(T, n_eff, K, need_bn256, allow_tail, &plan)) return plan;
     plan = choose_cut(T, n_eff, K, need_bn256, allow_tail);
     if (plan.tail_tiles == 0 && !(swiglu && K < swiglu_fit_k(T))) plan.cand = whole_tile(T, n_eff, K, need_bn256, swiglu);
-    if (plan.tail_tiles == 0 && K >= 2560 && K % 64 == 0) two_shapes(T, n_eff, K, swiglu, &plan);
+    if (plan.tail_tiles == 0 && K % 64 == 0) two_shapes(T, n_eff, K, swiglu, &plan);   // (the kernel for other k knows no columns)
     return plan;
 }
 

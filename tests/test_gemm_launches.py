@@ -16,6 +16,7 @@ def launches(tmp_path_factory):
     ((1409, 11012, 2560, 0, 0, 0), (32, 192, 128)), ((1500, 11012, 2560, 0, 0, 0), (32, 192, 128)), ((3300, 5524, 2560, 0, 0, 0), (14, 192, 128)),
     ((806, 27664, 2560, 0, 1, 0), (51, 192, 256)), ((2000, 13840, 2560, 0, 1, 0), (32, 256, 192)),
     ((1409, 10880, 2560, 1, 0, 0), (32, 192, 128)), ((640, 27648, 5120, 0, 1, 1), (64, 192, 128)),
+    ((4447, 11264, 2048, 0, 1, 0), (32, 192, 256)), ((4235, 12288, 1152, 0, 1, 0), (15, 256, 192)),   # short k
     ((385, 11012, 2560, 0, 0, 0), (0, 0, 0)), ((8192, 8192, 8192, 0, 0, 0), (0, 0, 0)), ((1409, 11012, 2568, 0, 0, 0), (0, 0, 0)),
 ])
 def test_columns_of_two_shapes(launches, row, want):
