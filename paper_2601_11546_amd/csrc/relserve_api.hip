@@ -1,7 +1,6 @@
 // Host boundary of the layer-step library: validation, descriptor expansion, upload,
 // workspace carving and kernel sequencing.  No arithmetic of the method lives here.
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -191,18 +190,19 @@ int32_t check_pair(const relserve_layer* L, const relserve_batch* b, const void*
 // 45 - 75 us of an iteration that prepares and destroys a batch (24 rows, four 13B layers: 820), with the GPU idle.
 // A blob comes here only if all work on its batch went to the default stream, where an event recorded as the batch is destroyed
 // stands behind it; it is handed out again when that event has passed, so neither side waits.  (Streams of the caller may be gone
-// by then; their batches take hipFree.)  At most kSpareBlobs of at most kSpareBlobBytes each; freed when the last layer handle goes.
+// by then; their batches take hipFree.)  At most kSpareBlobs of at most kSpareBlobBytes each, and none without a layer handle: freed when
+// the last one goes, and a batch that outlives it keeps nothing.
 struct SpareBlob { void* blob; size_t bytes; int device; hipEvent_t idle; };
 constexpr size_t kSpareBlobs = 8, kSpareBlobBytes = (size_t)4 << 20;
 struct SpareBlobs {
     std::mutex m;
     std::vector<SpareBlob> blobs;   // oldest first
+    int layers = 0;                 // handles alive
 };
 SpareBlobs& spare_blobs() {
     static SpareBlobs* s = new SpareBlobs;   // never destroyed: no call into the runtime at the process's end
     return *s;
 }
-std::atomic<int> g_layers{0};
 
 hipError_t free_blob(const SpareBlob& s) {
     if (s.idle) (void)hipEventDestroy(s.idle);
@@ -238,6 +238,7 @@ bool give_spare_blob(SpareBlob& s) {
     {
         SpareBlobs& sp = spare_blobs();
         std::lock_guard<std::mutex> lock(sp.m);
+        if (sp.layers == 0) return false;
         if (sp.blobs.size() >= kSpareBlobs) {
             oldest = sp.blobs.front();
             sp.blobs.erase(sp.blobs.begin());
@@ -256,6 +257,18 @@ void free_spare_blobs() {
         all.swap(sp.blobs);
     }
     for (const SpareBlob& s : all) (void)free_blob(s);
+}
+
+// +1: a handle more; -1: one less.
+void count_layer(int by) {
+    SpareBlobs& sp = spare_blobs();
+    bool last;
+    {
+        std::lock_guard<std::mutex> lock(sp.m);
+        sp.layers += by;
+        last = sp.layers == 0;
+    }
+    if (last) free_spare_blobs();
 }
 
 }  // namespace
@@ -689,7 +702,7 @@ int32_t relserve_layer_create(const relserve_layer_config* cfg, relserve_layer**
     L->inv_freq.resize(half);
     for (int i = 0; i < half; ++i)
         L->inv_freq[i] = (float)std::pow((double)cfg->rope_base, -2.0 * i / (double)cfg->head_dim);
-    ++g_layers;
+    count_layer(1);
     *out = L;
     return RELSERVE_OK;
 }
@@ -702,7 +715,7 @@ int32_t relserve_layer_destroy(relserve_layer* L) {
     }
     for (hipEvent_t e : L->event_pool) (void)hipEventDestroy(e);
     delete L;
-    if (--g_layers == 0) free_spare_blobs();
+    count_layer(-1);
     return RELSERVE_OK;
 }
 
