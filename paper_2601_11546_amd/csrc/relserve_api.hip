@@ -193,33 +193,37 @@ int32_t check_pair(const relserve_layer* L, const relserve_batch* b, const void*
 // by then; their batches take hipFree.)  At most kSpareBlobs of at most kSpareBlobBytes each, and none without a layer handle: freed when
 // the last one goes, and a batch that outlives it keeps nothing.
 struct SpareBlob { void* blob; size_t bytes; int device; hipEvent_t idle; };
-constexpr size_t kSpareBlobs = 8, kSpareBlobBytes = (size_t)4 << 20;
-struct SpareBlobs {
+constexpr int kSpareBlobs = 8;
+constexpr size_t kSpareBlobBytes = (size_t)4 << 20;
+struct SpareBlobs {   // in place, so that keeping one allocates nothing; nothing to run at the process's end
     std::mutex m;
-    std::vector<SpareBlob> blobs;   // oldest first
+    SpareBlob blobs[kSpareBlobs];   // oldest first
+    int n = 0;
     int layers = 0;                 // handles alive
 };
-SpareBlobs& spare_blobs() {
-    static SpareBlobs* s = new SpareBlobs;   // never destroyed: no call into the runtime at the process's end
-    return *s;
-}
+SpareBlobs g_spare;
 
 hipError_t free_blob(const SpareBlob& s) {
     if (s.idle) (void)hipEventDestroy(s.idle);
     return s.blob ? hipFree(s.blob) : hipSuccess;
 }
 
+// The i-th leaves the list (g_spare.m is held).
+SpareBlob pull_spare_blob(int i) {
+    const SpareBlob s = g_spare.blobs[i];
+    for (--g_spare.n; i < g_spare.n; ++i) g_spare.blobs[i] = g_spare.blobs[i + 1];
+    return s;
+}
+
 bool take_spare_blob(size_t bytes, int device, SpareBlob* out) {
-    SpareBlobs& sp = spare_blobs();
-    std::lock_guard<std::mutex> lock(sp.m);
-    for (size_t i = 0; i < sp.blobs.size(); ++i) {
-        if (sp.blobs[i].device != device || sp.blobs[i].bytes < bytes) continue;
-        if (hipEventQuery(sp.blobs[i].idle) != hipSuccess) {
+    std::lock_guard<std::mutex> lock(g_spare.m);
+    for (int i = 0; i < g_spare.n; ++i) {
+        if (g_spare.blobs[i].device != device || g_spare.blobs[i].bytes < bytes) continue;
+        if (hipEventQuery(g_spare.blobs[i].idle) != hipSuccess) {
             (void)hipGetLastError();   // not ready
             continue;
         }
-        *out = sp.blobs[i];
-        sp.blobs.erase(sp.blobs.begin() + (std::ptrdiff_t)i);
+        *out = pull_spare_blob(i);
         return true;
     }
     return false;
@@ -236,37 +240,34 @@ bool give_spare_blob(SpareBlob& s) {
     }
     SpareBlob oldest{};
     {
-        SpareBlobs& sp = spare_blobs();
-        std::lock_guard<std::mutex> lock(sp.m);
-        if (sp.layers == 0) return false;
-        if (sp.blobs.size() >= kSpareBlobs) {
-            oldest = sp.blobs.front();
-            sp.blobs.erase(sp.blobs.begin());
-        }
-        sp.blobs.push_back(s);
+        std::lock_guard<std::mutex> lock(g_spare.m);
+        if (g_spare.layers == 0) return false;
+        if (g_spare.n == kSpareBlobs) oldest = pull_spare_blob(0);
+        g_spare.blobs[g_spare.n++] = s;
     }
     (void)free_blob(oldest);
     return true;
 }
 
 void free_spare_blobs() {
-    std::vector<SpareBlob> all;
+    SpareBlob all[kSpareBlobs];
+    int n;
     {
-        SpareBlobs& sp = spare_blobs();
-        std::lock_guard<std::mutex> lock(sp.m);
-        all.swap(sp.blobs);
+        std::lock_guard<std::mutex> lock(g_spare.m);
+        n = g_spare.n;
+        std::copy(g_spare.blobs, g_spare.blobs + n, all);
+        g_spare.n = 0;
     }
-    for (const SpareBlob& s : all) (void)free_blob(s);
+    for (int i = 0; i < n; ++i) (void)free_blob(all[i]);
 }
 
 // +1: a handle more; -1: one less.
 void count_layer(int by) {
-    SpareBlobs& sp = spare_blobs();
     bool last;
     {
-        std::lock_guard<std::mutex> lock(sp.m);
-        sp.layers += by;
-        last = sp.layers == 0;
+        std::lock_guard<std::mutex> lock(g_spare.m);
+        g_spare.layers += by;
+        last = g_spare.layers == 0;
     }
     if (last) free_spare_blobs();
 }

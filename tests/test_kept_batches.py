@@ -26,7 +26,7 @@ def exe(tmp_path_factory):
 
 
 @pytest.mark.parametrize("case", ["reuse", "other_stream_behind_default", "default_behind_other_stream", "bounded", "batch_outlives_the_layers",
-                                  "threads"])
+                                  "destroy_allocates_nothing", "threads"])
 def test_kept_allocations(exe, case):
     r = subprocess.run([exe, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "ok" in r.stdout, r.stdout[-500:] + r.stderr[-500:]
