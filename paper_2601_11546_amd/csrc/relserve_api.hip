@@ -203,9 +203,16 @@ struct SpareBlobs {   // in place, so that keeping one allocates nothing; nothin
 };
 SpareBlobs g_spare;
 
+// Frees a batch's allocation, or one that was kept: also where some stream is being captured.  hipFree ends a capture in global mode on any
+// thread of the process (measured, as are the calls beside it), and the one that frees need not know of it -- another thread's, or a
+// collector's that runs while a program captures; nothing here becomes part of a graph.
 hipError_t free_blob(const SpareBlob& s) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     if (s.idle) (void)hipEventDestroy(s.idle);
-    return s.blob ? hipFree(s.blob) : hipSuccess;
+    const hipError_t e = s.blob ? hipFree(s.blob) : hipSuccess;
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return e;
 }
 
 // The i-th leaves the list (g_spare.m is held).

@@ -155,3 +155,57 @@ def test_batches_destroyed_behind_their_work(rs, other_stream):
     torch.cuda.synchronize()
     for i, y in got:
         assert torch.equal(y, want[i]), i
+
+
+def _tiny_steps(rs, n):
+    """n prepared-elsewhere batches of one size class and other contents: (layer, weights, [(batch, x, k, v, what its step gives)])."""
+    shape = W.TINY_GQA
+    g = torch.Generator(device="cuda").manual_seed(5)
+    randn = lambda *s, std=0.05: torch.empty(*s, dtype=torch.float32, device="cuda").normal_(0, std, generator=g).bfloat16()
+    H, I = shape.hidden, shape.mlp_dim
+    wd = {"w_in_norm": randn(H, std=1.0), "w_qkv": randn(shape.qkv_dim, H), "w_o": randn(H, shape.q_dim), "w_post_norm": randn(H, std=1.0),
+          "w_gate_up": randn(2 * I, H), "w_down": randn(H, I)}
+    layer = rs.relserve_layer_create(shape)
+    cases = []
+    for i in range(n):
+        b = W.build_batch(shape, [60 - 4 * i] + [1] * (4 * i + 6), [60 - 4 * i] + [9 + i] * (4 * i + 6), seed=40 + i)
+        pool = (b.num_pages, shape.page_size, shape.n_kv_heads, shape.head_dim)
+        x, k, v = randn(b.T, H, std=1.0), randn(*pool, std=1.0), randn(*pool, std=1.0)
+        y = torch.empty_like(x)
+        pb = rs.relserve_batch_prepare(layer, b)
+        rs.relserve_layer_step(layer, pb, wd, x, y, k, v, torch.empty(rs.relserve_workspace_bytes(layer, b.T), dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        pb.close()
+        cases.append((b, x, k, v, y))
+    return layer, wd, cases
+
+
+def test_handles_destroyed_inside_a_capture(rs):
+    """A program that captures may let go of old handles meanwhile: the capture goes on, and its graph gives the eager results."""
+    layer, wd, cases = _tiny_steps(rs, 3)
+    b, x, k, v, want = cases[0]
+    keep = rs.relserve_batch_prepare(layer, b)
+    ws = torch.empty(rs.relserve_workspace_bytes(layer, b.T), dtype=torch.uint8, device="cuda")
+    ws2 = torch.empty(rs.relserve_workspace_bytes(layer, cases[1][0].T), dtype=torch.uint8, device="cuda")
+    y = torch.empty_like(x)
+    side = torch.cuda.Stream()
+    old_layer = rs.relserve_layer_create(W.TINY_GQA)
+    old = [rs.relserve_batch_prepare(old_layer, cases[1][0]), rs.relserve_batch_prepare(old_layer, cases[2][0], stream=side)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        old[0].close()
+        rs.relserve_layer_step(layer, keep, wd, x, y, k, v, ws)
+        old[1].close()
+        old_layer.close()
+    for _ in range(3):
+        y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
+        again = rs.relserve_batch_prepare(layer, cases[1][0])   # takes what was kept
+        y2 = torch.empty_like(cases[1][1])
+        rs.relserve_layer_step(layer, again, wd, cases[1][1], y2, cases[1][2], cases[1][3], ws2)
+        torch.cuda.synchronize()
+        assert torch.equal(y2, cases[1][4])
+        again.close()

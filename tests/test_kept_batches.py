@@ -1,5 +1,5 @@
 """The device allocations that destroyed batches leave for later ones (CPU): relserve_api.hip linked with a HIP runtime of the test's own
-(tests/host/kept_batches.cpp), in which streams run when the test says so and memory is counted."""
+(tests/host/kept_batches.cpp), in which streams run when the test says so, captures refuse what they refuse, and memory is counted."""
 import os
 import subprocess
 
@@ -26,7 +26,7 @@ def exe(tmp_path_factory):
 
 
 @pytest.mark.parametrize("case", ["reuse", "other_stream_behind_default", "default_behind_other_stream", "bounded", "batch_outlives_the_layers",
-                                  "destroy_allocates_nothing", "threads"])
+                                  "destroy_allocates_nothing", "inside_a_capture", "threads"])
 def test_kept_allocations(exe, case):
     r = subprocess.run([exe, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "ok" in r.stdout, r.stdout[-500:] + r.stderr[-500:]
