@@ -180,6 +180,31 @@ def _tiny_steps(rs, n):
     return layer, wd, cases
 
 
+@pytest.mark.parametrize("first", ["default", "other"])
+def test_allocation_of_a_batch_whose_work_is_outstanding(rs, first):
+    """A batch's step waits behind long work on one stream, the batch is destroyed, and another stream prepares and steps the next one,
+    whose tables differ: neither sees the other's."""
+    layer, wd, cases = _tiny_steps(rs, 6)
+    other = torch.cuda.Stream()
+    streams = [torch.cuda.default_stream(), other] if first == "default" else [other, torch.cuda.default_stream()]
+    got = []
+    torch.cuda.synchronize()
+    for i in range(0, 6, 2):
+        for s, (b, x, k, v, _) in zip(streams, cases[i:i + 2]):
+            with torch.cuda.stream(s):
+                y = torch.full_like(x, float("nan"))
+                ws = torch.empty(rs.relserve_workspace_bytes(layer, b.T), dtype=torch.uint8, device="cuda")
+                pb = rs.relserve_batch_prepare(layer, b, stream=s)
+                if s is streams[0]:
+                    torch.cuda._sleep(20_000_000)   # some ms; prepare itself waits for its stream
+                rs.relserve_layer_step(layer, pb, wd, x, y, k, v, ws, stream=s)
+                pb.close()
+                got.append((y, ws))
+    torch.cuda.synchronize()
+    for (y, _), case in zip(got, cases):
+        assert torch.equal(y, case[4])
+
+
 def test_handles_destroyed_inside_a_capture(rs):
     """A program that captures may let go of old handles meanwhile: the capture goes on, and its graph gives the eager results."""
     layer, wd, cases = _tiny_steps(rs, 3)
