@@ -445,8 +445,8 @@ int32_t relserve_prefill_candidate(const int32_t* utok, int32_t n, int64_t token
                                    int64_t* tokens_taken);
 
 /* ---- peak probes: what this GPU sustains, reported by bench.py beside the published peaks ----
- * relserve_peak_probe_mfma enqueues 256 workgroups of 4 waves that each issue iters x 16 independent
- * 32x32x16 bf16 MFMAs on random operands (no memory traffic) and writes the flop count of the launch to
+ * relserve_peak_probe_mfma enqueues 256 workgroups of 4 waves that each issue iters x 32 independent
+ * 16x16x32 bf16 MFMAs on random operands (no memory traffic) and writes the flop count of the launch to
  * *flops (host).  relserve_peak_probe_stream enqueues one read of `bytes` bytes of device memory at src
  * (16-byte aligned).  sink: device memory, at least 16 bytes, never written in practice.  The caller
  * times the launches on `stream`. */

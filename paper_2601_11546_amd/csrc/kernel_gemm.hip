@@ -92,7 +92,7 @@ enum { EPI_BF16 = 0, EPI_RES_BF16_OUT_F32 = 1, EPI_RES_F32_OUT_BF16 = 2, EPI_SWI
 // Products are 16 x 16 x 32 (on 8-bit codes 16 x 16 x 128).  A chain of them gives the same bits as the chain of twice as many
 // 32 x 32 x 16 (measured, k of 32 .. 5120; on codes as 32 x 32 x 64 but for last bits where the codes span their whole range, equally
 // far from 64 bits), but a 16 x 16 result passes through the accumulators half as often per product, and the chip is power-limited in
-// these kernels: all CUs on register operands alone reach 2.07 PFLOP/s against 1.83 (4.42 against 4.06).  T = 7963, 13B: clock 1.70 -> 2.0
+// these kernels: all CUs on register operands alone reach 1.93 PFLOP/s against 1.71 (4.10 against 3.78; profiles/mfma_rates.txt).  T = 7963, 13B: clock 1.70 -> 2.0
 // GHz, gate/up 1632 -> 1579 us, W_down 813 -> 776, q/k/v 941 -> 910, the layer 4207 -> 4088.
 
 __device__ __forceinline__ int remap_xcd(int bid, int num) {

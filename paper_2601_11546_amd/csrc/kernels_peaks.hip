@@ -1,5 +1,5 @@
 // Probes of what this GPU sustains, for reporting beside the published peaks: a wave-level issue loop of
-// independent 32x32x16 bf16 MFMAs on random operands (no memory traffic), and a streaming read of a large
+// independent 16x16x32 bf16 MFMAs on random operands (no memory traffic), and a streaming read of a large
 // buffer (16-byte non-temporal loads, 32 KB per workgroup in flight).  They share nothing with the layer kernels.
 #include "device_utils.h"
 #include "relserve_internal.h"
@@ -8,31 +8,44 @@ namespace relserve {
 
 namespace {
 
-// 16 independent accumulators per wave (256 registers, as many as the sums of the 256 x 256 GEMM tile), one wave per SIMD.
+// The products of a wave of the 256 x 256 GEMM tile, 8 x 8 on operands and sums in registers (64 + 256), one wave per SIMD; an
+// iteration is half of them.  32 x 32 x 16 products on as many registers issue at 0.89 of this rate: a result passes through the
+// accumulators twice as often, and the chip is power-limited here (profiles/mfma_rates.txt).
 __global__ void __launch_bounds__(256) mfma_issue_kernel(float* sink, int iters, uint32_t seed) {
-    f32x16_t acc[16];
+    constexpr int TN = 8, TM = 8;
+    f32x4_t acc[TN][TM];
+    bf16x8_t w[TN], a[TM];
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
+    for (int i = 0; i < TN; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
-    bf16x8_t a, b;
+        for (int j = 0; j < TM; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     uint32_t h = (threadIdx.x * 2654435761u) ^ (blockIdx.x * 40503u) ^ seed;
+    auto fill = [&](bf16x8_t& o) __attribute__((always_inline)) {   // operands uniform in [-1, 1]: switching activity of real data
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {   // operands uniform in [-1, 1]: switching activity of real data
-        h = h * 1664525u + 1013904223u;
-        a[e] = (__bf16)(((int)(h >> 8) % 2001 - 1000) * 0.001f);
-        h = h * 1664525u + 1013904223u;
-        b[e] = (__bf16)(((int)(h >> 8) % 2001 - 1000) * 0.001f);
-    }
-    for (int it = 0; it < iters; ++it) {
+        for (int e = 0; e < 8; ++e) {
+            h = h * 1664525u + 1013904223u;
+            o[e] = (__bf16)(((int)(h >> 8) % 2001 - 1000) * 0.001f);
+        }
+    };
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = mfma_32x32x16(a, b, acc[i]);
-    }
+    for (int i = 0; i < TN; ++i) fill(w[i]);
+#pragma unroll
+    for (int j = 0; j < TM; ++j) fill(a[j]);
+    auto rows = [&](int first, int n) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = first; i < first + n; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[i][j] = mfma_16x16x32(w[i], a[j], acc[i][j]);
+    };
+    for (int it = 0; it + 2 <= iters; it += 2) rows(0, TN);
+    if (iters % 2) rows(0, TN / 2);
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
+    for (int i = 0; i < TN; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s += acc[i][r];
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s += acc[i][j][r];
     if (s == 12345.678f) sink[0] = s;   // keeps the loop alive, never true in practice
 }
 

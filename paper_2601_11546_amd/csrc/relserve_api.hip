@@ -1277,7 +1277,7 @@ int32_t relserve_peak_probe_mfma(void* sink, int32_t iters, double* flops, void*
     drop_stale_hip_error();
     if (!sink || !flops) return RELSERVE_ERR_NULL_POINTER;
     if (iters <= 0) return RELSERVE_ERR_BAD_ARGUMENT;
-    *flops = 256.0 * 4.0 * iters * 16.0 * 32768.0;
+    *flops = 256.0 * 4.0 * iters * 32.0 * 16384.0;
     return launch_peak_mfma(static_cast<float*>(sink), iters, static_cast<hipStream_t>(stream)) == hipSuccess
                ? RELSERVE_OK
                : RELSERVE_ERR_HIP;
