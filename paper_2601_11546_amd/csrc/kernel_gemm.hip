@@ -127,10 +127,10 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
     tile_n = in_group / gsz;
 }
 
-// Writes a unit of 4 consecutive features n_lo .. of token t (lo), or a pair of such quads that the epilogue combines: gate and up,
-// or the two halves of a rotated head (its columns n_lo - head D .. and D / 2 further).  oa, ob: what the unit reads besides the sums
-// (a quad of the residual; the angles); slot: the token's place in the cache.
-template <int EPI, int D, bool SC>
+// The small kernel's stores: a unit of 4 consecutive features n_lo .. of token t (lo), or a pair of such quads that the epilogue combines:
+// gate and up, or the two halves of a rotated head (its columns n_lo - head D .. and D / 2 further).  oa, ob: what the unit reads besides
+// the sums (a quad of the residual; the angles); slot: the token's place in the cache.
+template <int EPI, int D>
 __device__ __forceinline__ void store_unit(const GemmArgs& p, int t, int n_lo, int head, const float4& lo, const float4& hi, const float4& oa,
                                            const float4& ob, int slot_) {
     constexpr int DH = D > 0 ? D : 64;
@@ -166,12 +166,7 @@ __device__ __forceinline__ void store_unit(const GemmArgs& p, int t, int n_lo, i
     } else if constexpr (EPI == EPI_SWIGLU) {
         const float o0 = silu_mul(lo.x, hi.x), o1 = silu_mul(lo.y, hi.y), o2 = silu_mul(lo.z, hi.z), o3 = silu_mul(lo.w, hi.w);
         const int64_t o = (int64_t)t * p.n_half + n_lo;
-        if (SC && p.out_f8) {   // the down projection reads codes
-            const float s = p.out_inv;
-            *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(p.out) + o) = pack_fp8x4(o0 * s, o1 * s, o2 * s, o3 * s);
-        } else {
-            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + o) = make_uint2(pack_bf16x2(o0, o1), pack_bf16x2(o2, o3));
-        }
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + o) = make_uint2(pack_bf16x2(o0, o1), pack_bf16x2(o2, o3));
     } else {
         const int64_t o = (int64_t)t * p.N + n_lo;
         if constexpr (EPI == EPI_RES_BF16_OUT_F32) {
@@ -686,7 +681,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     } else {
         // the tail units come first in the grid: their short k ranges and slab stores are over before the
         // last whole tiles finish
-        tail = !HALVES && (int)blockIdx.x < tail_units;
+        tail = (int)blockIdx.x < tail_units;
         if (tail) {
             const int u = remap_xcd(blockIdx.x, tail_units);   // runs of one split, consecutive tiles, per XCD
             split = u / p.tail_tiles;
@@ -841,8 +836,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(GemmArgs p) {
     constexpr int NM = TN * TM, NF = TN + TM;
     // One k step, issued in a fixed order: MFMA i, then the share of the refill loads and of the next
     // step's fragment reads that falls between MFMA i and i + 1.  A 16 x 16 MFMA lasts 16 cycles, in which a wave issues three
-    // other instructions: a read or a load goes behind each, never both, a read is one instruction (its address a sum made once a
-    // step) and a load two: 93 instructions beside the 128 MFMAs of an iteration, where 136 left 2450 cycles for 2048 of MFMAs, now 2280.  A CU's address unit takes one
+    // other instructions: a read or a load goes behind each (both behind one of an iteration's), a read is one instruction (its address a sum
+    // made once a step) and a load two: 93 instructions beside the 128 MFMAs of an iteration, where 136 left 2450 cycles for 2048 of MFMAs, now 2280.  A CU's address unit takes one
     // 1 KB load per ~16 cycles, the time of one MFMA, so the refill loads of a stage (LOADS per wave,
     // four waves) are spread over SPREAD quarters of the iteration (a 16-bit k step is two); issued back
     // to back they would hold up the MFMAs behind them.  The MFMAs sit on ONE control path on purpose: at a join the compiler would make
@@ -1466,7 +1461,7 @@ __global__ void __launch_bounds__(64) gemm_small_kernel(GemmArgs p) {
         if (f >= rows[0]) break;   // rows are a multiple of 4 (of 8 in pairs)
         const float4 lo = make_float4(acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]);
         const float4 hi = make_float4(acc[NT - 1][4 * q], acc[NT - 1][4 * q + 1], acc[NT - 1][4 * q + 2], acc[NT - 1][4 * q + 3]);
-        store_unit<EPI, D, false>(p, t, n0[0] + f, head, lo, hi, oa[q], ob[q], slot);
+        store_unit<EPI, D>(p, t, n0[0] + f, head, lo, hi, oa[q], ob[q], slot);
     }
 }
 
