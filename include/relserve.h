@@ -19,8 +19,10 @@
  *   - "host" pointers are read during the call and not kept; "device" pointers
  *     are HIP device memory owned by the caller and must stay valid until the
  *     stream work that uses them has finished.
- *   - the library owns only the opaque handles it returns (and the device
- *     copy of the batch descriptor inside a relserve_batch).
+ *   - the library owns only the opaque handles it returns, the device copy of
+ *     the batch descriptor inside a relserve_batch, and, while a layer handle
+ *     lives, up to eight such copies (of at most 4 MB each) that destroyed
+ *     batches have left for the next ones.
  *   - stream arguments are hipStream_t passed as void*; all GPU work is
  *     enqueued there asynchronously, no call synchronises except
  *     relserve_batch_prepare (one blocking descriptor upload) and the
@@ -146,7 +148,8 @@ const char* relserve_strerror(int32_t status);
 /* Checks a layer shape.  Host only. */
 int32_t relserve_config_validate(const relserve_layer_config* cfg);
 
-/* Creates / destroys a layer-shape handle.  Host only, touches no device. */
+/* Creates / destroys a layer-shape handle.  Host only, but that the last handle's end frees the device copies that
+ * destroyed batches have left (which waits for the device). */
 int32_t relserve_layer_create(const relserve_layer_config* cfg, relserve_layer** out);
 int32_t relserve_layer_destroy(relserve_layer* layer);
 
@@ -165,6 +168,9 @@ int32_t relserve_batch_slots(const relserve_layer_config* cfg, const relserve_ba
  * upload has finished. */
 int32_t relserve_batch_prepare(const relserve_layer* layer, const relserve_batch_desc* desc,
                                void* stream, relserve_batch** out);
+/* Work that reads the batch may still be outstanding.  A batch prepared and used on the default stream only leaves its device copy
+ * for a later one, which takes it when that work is over, and the call does not wait; another's is freed, which waits for the device.
+ * Neither ends a stream capture in progress. */
 int32_t relserve_batch_destroy(relserve_batch* batch);
 int32_t relserve_batch_get_info(const relserve_batch* batch, relserve_batch_info* out);
 
