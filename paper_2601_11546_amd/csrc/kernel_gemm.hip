@@ -188,9 +188,10 @@ constexpr int WGM = 2, WGN = 2;   // grid of waves over a tile
 // fragments share 32 features so that it has 8 consecutive ones, the four lanes of a token 64 consecutive bytes.
 // Where rows of fp32 are written (ROWS32: the slabs, W_o) the tokens are the first operand (the same products, the same bits): register r
 // of a lane is token 4 (lane / 16) + r, and four fragments share 64 features, fragment c the features 4 i + c, so that a lane has four
-// consecutive ones and the 16 lanes of a token 256 consecutive bytes, lane behind lane; the residual's bf16 are 128 such bytes.  An
-// access in which neighbouring lanes hold pieces of different rows is a request to the L2 for every piece of 16 bytes: with the weights
-// first here too W_o of 8192 x 2048 codes took 57.2 us at T = 2100, now 48.5, of 5120 x 2560 16-bit values 54.8, now 51.3, and a step of a
+// consecutive ones and the 16 lanes of a token 256 consecutive bytes, lane behind lane; the residual's bf16 are 128 such bytes.  With
+// the weights first here too neighbouring lanes of an access hold pieces of different rows, and the CU's address unit is busy longer (a slab launch of
+// 256 x 128 tiles of codes 9.7 million cycles, now 8.3; the L2 sees the same requests of 64 bytes either way, profiles/gemm_epilogue_l2_requests.txt):
+// W_o of 8192 x 2048 codes took 57.2 us at T = 2100, now 48.5, of 5120 x 2560 16-bit values 54.8, now 51.3, and a step of a
 // quarter of the 70B layer, whose projections all write slabs, at T = 256 210 us, now 202 (on codes 171, 164).
 // Neither permutation costs anything: it is which rows of the weights in the LDS a lane reads, and which of eight rows a load puts where.
 constexpr bool rows32(int epi) { return epi == EPI_RES_BF16_OUT_F32 || epi == EPI_SLAB; }
@@ -1761,8 +1762,8 @@ hipError_t launch_cfg(const GemmArgs& base, hipStream_t s, const Plan& plan = Pl
 // 2. The shape of whole tiles: any gives the same bits, so where nothing is split the fastest one runs (whole_tile).  For the
 // SwiGLU projection of a k (in 2-byte units) below swiglu_fit_k that is the shape the cut's own model names.  Distance from the fastest of the five
 // shapes, on average, with that shape / with whole_tile's (profiles/gemm_whole_tiles.txt, ten layer shapes at 19 token counts): more than 256
-// tokens, k from 2560 on 1.3 / 0.1 % (16-bit), 0.9 / 0.4 (codes), below 0.4 / 3.1 and 0.4 / 3.6; at most 256 tokens (without scratch, as
-// relserve_linear runs them), k from 5120 on 3.7 / 0.8, 2560 .. 4096 0.9 / 3.5, below 0.0 / 1.4.
+// tokens, k from 2560 on 1.4 / 0.1 % (16-bit), 0.9 / 0.4 (codes), below 0.2 / 3.1 and 0.4 / 3.6; at most 256 tokens (without scratch, as
+// relserve_linear runs them), k from 5120 on 4.1 / 0.9, 2560 .. 4096 0.8 / 3.8, below 0.0 / 1.4.
 struct TileCand { int bm, bn, wg_per_cu; float eff_cut, eff, eff_swiglu; bool qkv; };   // qkv: usable by the fused q/k/v epilogue (128 features per wave)
 constexpr int swiglu_fit_k(int T) { return T > SKINNY_MAX_T ? 2560 : 5120; }
 constexpr TileCand kTiles[] = {
@@ -1772,10 +1773,9 @@ constexpr TileCand kTiles[] = {
     // 1.1 % (16 and 11 %).  W_o of the 13B layer at T = 1152 86 -> 74 us; 8-bit q/k/v of the 32B one at T = 806 59 -> 43.
     // With the third stage of weights 192 x 256 gained most (0.88 before): measured again at 17 token counts, 0.0 % off the fastest in
     // 16 bits (0.13 % with 0.88) and 0.4 % in 8; q/k/v of the 70B layer at T = 2304 322 (128 x 256) -> 308 us, 7168 x 8192 at 2700 289 -> 280.
-    // With 16 x 16 products all of it was measured once more, 18 token counts of 264 .. 4500 and five layer shapes: the same
-    // choices, 0.00 % off the fastest.  eff_swiglu: the SwiGLU projection of those shapes, whose 128 x 256 tile has the compiler's
-    // order and lags: 0.00 % off in 16 bits and 0.08 % in 8, where the cut's shapes were 0.4 and 0.9 % off (the small ones have fallen
-    // behind: 806 tokens of the 32B layer on codes 258 us on 128 x 128, 221 on 256 x 256; 16-bit 32B half 227, 198).
+    // With 16 x 16 products all of it was measured once more (profiles/gemm_whole_tiles.txt): 0.00 % off the fastest in 16 bits and 0.3 % on
+    // codes at hidden sizes of 5120 and more, 0.1 and 1.4 % at 256 .. 3072.  eff_swiglu: the SwiGLU projection, whose 128 x 256 tile has the
+    // compiler's order and lags: 0.00 and 0.5 %.
     {256, 256, 1, 1.00f, 1.00f, 1.00f, true}, {192, 256, 1, 0.92f, 0.98f, 0.96f, true}, {128, 256, 1, 0.68f, 0.90f, 0.75f, true},
     {128, 128, 2, 0.76f, 0.50f, 0.45f, false}, {64, 128, 3, 0.60f, 0.40f, 0.40f, false}};
 constexpr int kTileCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
@@ -1845,9 +1845,9 @@ int whole_tile(int T, int64_t n_eff, int K, bool need_bn256, bool swiglu) {
 // full rounds of each 256-feature shape: as many columns as they hold, the rest on another; taken where the model that
 // whole_tile uses sees a gain of kTwoShapesGain beyond kSecondLaunchSec.  One launch / two, us, measured in turn: gate/up of the 32B layer on
 // codes at T = 806 219 / 197, of its 16-bit half 217 / 190, 70B at 577 503 / 466, 13B at 1409 315 / 303; q/k/v of the 13B layer at 2500
-// on codes 163 / 154, W_o at 3875 162 / 152; of 58 sizes of ten layer
-// shapes that take it at k (in 2-byte units) of 2560 and more 5.3 % on average and no loss beyond 0.1 %, of 70 at k of 768 .. 2304 4.7 % and
-// one loss of 2.6.  (Below a modelled gain of 4 % the second launch lost 1 - 3 % as often as it won them.)
+// on codes 163 / 154, W_o at 3875 162 / 152; of 65 sizes of ten layer shapes that take it 5.7 % on average (-0.8 .. 13.5;
+// profiles/gemm_whole_tiles.txt), of 70 more at k (in 2-byte units) of 768 .. 2304 4.7 % and one loss of 2.6.  (Below a modelled gain of
+// 4 % the second launch lost 1 - 3 % as often as it won them.)
 constexpr double kSecondLaunchSec = 6e-6, kTwoShapesGain = 0.04;
 void two_shapes(int T, int64_t n_eff, int K, bool swiglu, Plan* plan) {
     const int cols = (int)((n_eff + 255) / 256);
